@@ -1,8 +1,10 @@
-"""ctypes binding of libprism.so (argument marshalling only).
+"""Binding of libprism.so (argument marshalling only).
 
 Function names mirror the C ABI in ``include/prism.h``.  Tensors are torch
 tensors used purely as device memory; the stream is torch's current stream.
-If the library has not been built the loader raises: there is no fallback.
+Plans and queries go through ctypes; the layer calls, which a model makes once
+per layer, go through the small C++ module ``_prism_torch`` (csrc/prism_torch.cpp).
+If either has not been built the loader raises: there is no fallback.
 """
 from __future__ import annotations
 
@@ -14,7 +16,9 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("PRISM_LIB") or os.path.join(_HERE, "libprism.so")
+BINDING_PATH = os.path.join(_HERE, "_prism_torch.so")
 _lib = None
+_fast = None                                     # the C++ module of the layer calls
 
 PRISM_OK = 0
 ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE_TOO_SMALL, ERR_HIP, ERR_NO_MEMORY, ERR_TABLE = -1, -2, -3, -4, -5, -6
@@ -62,12 +66,13 @@ class PlanInfo(ctypes.Structure):
 
 def load():
     """Load libprism.so; raise if it is missing (build it with build.py)."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError(f"{LIB_PATH} is not built: run `python -m paper_2605_08581_amd.build` "
-                           "(there is no CPU or PyTorch fallback)")
+    for path in (LIB_PATH, BINDING_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is not built: run `python -m paper_2605_08581_amd.build` "
+                               "(there is no CPU or PyTorch fallback)")
     # PyTorch supplies the device memory and streams, so the library must use
     # the HIP runtime PyTorch ships (same SONAME): make sure that copy is the
     # one already in the process before libprism.so resolves its dependency.
@@ -111,8 +116,10 @@ def load():
     lib.prism_plan_profile_read.restype = ctypes.c_int
     lib.prism_plan_profile_read.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double),
                                             ctypes.POINTER(ctypes.c_double), i32p]
-    _ = i32p
-    _lib = lib
+    from . import _prism_torch as fast
+    fast.bind_api(*(ctypes.cast(f, vp).value for f in (lib.prism_kv_append, lib.prism_prefix_attention,
+                                                       lib.prism_prefix_prefill, lib.prism_prefix_prefill_static)))
+    _lib, _fast = lib, fast
     return lib
 
 
@@ -214,10 +221,16 @@ class Plan:
         if rc != PRISM_OK:
             self._h = ctypes.c_void_p()
             raise PrismError(rc, "prism_plan_create")
+        row_kv = shape.num_kv_heads * shape.head_dim
+        self._call = _fast.make_call(self._h.value, self._total_suffix * shape.num_q_heads * shape.head_dim,
+                                     self._total_suffix * row_kv, shape.num_pages * shape.page_size * row_kv,
+                                     shape.batch * shape.max_blocks_per_req, self.prism_plan_workspace_bytes())
 
     def close(self):
         h = getattr(self, "_h", None)
         if h is not None and h.value and ctypes is not None:
+            if getattr(self, "_call", None) is not None:
+                _fast.close_call(self._call)
             self._lib.prism_plan_destroy(h)
             self._h.value = None
 
@@ -236,7 +249,11 @@ class Plan:
     def prism_plan_forget_workspace(self):
         self._lib.prism_plan_forget_workspace(self._h)
 
-    def _check_call(self, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, workspace):
+    def _refused(self, rc, where, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, workspace):
+        """Raise for a call that did not return PRISM_OK.  rc > 0: a tensor is not what the
+        plan was made for (device, dtype, contiguity, element count); say which."""
+        if rc < 0:
+            raise PrismError(rc, where)
         sh, n = self.shape, self._total_suffix
         row_q, row_kv = sh.num_q_heads * sh.head_dim, sh.num_kv_heads * sh.head_dim
         if q is not False:
@@ -250,42 +267,30 @@ class Plan:
         _check("k_pool", k_pool, "bf16", pool)
         _check("v_pool", v_pool, "bf16", pool)
         _check("block_table", block_table, "i32", sh.batch * sh.max_blocks_per_req)
+        raise TypeError(f"{where}: not a torch tensor")
 
     def prism_kv_append(self, k_suffix, v_suffix, k_pool, v_pool, block_table):
-        self._check_call(False, k_suffix, v_suffix, k_pool, v_pool, block_table, None, None)
-        rc = self._lib.prism_kv_append(self._h, _ptr(k_suffix), _ptr(v_suffix), _ptr(k_pool),
-                                       _ptr(v_pool), _ptr(block_table), _stream())
-        if rc != PRISM_OK:
-            raise PrismError(rc, "prism_kv_append")
+        rc = _fast.kv_append(self._call, k_suffix, v_suffix, k_pool, v_pool, block_table)
+        if rc:
+            self._refused(rc, "prism_kv_append", False, k_suffix, v_suffix, k_pool, v_pool, block_table, None, None)
 
+    # A workspace that is missing or too small is reported by the library itself.
     def prism_prefix_attention(self, q, k_pool, v_pool, block_table, out, workspace=None):
-        if workspace is not None and workspace.numel() >= self.prism_plan_workspace_bytes():
-            self._check_call(q, False, False, k_pool, v_pool, block_table, out, workspace)   # size errors come from the library
-        nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-        rc = self._lib.prism_prefix_attention(self._h, _ptr(q), _ptr(k_pool), _ptr(v_pool),
-                                              _ptr(block_table), _ptr(out), _ptr(workspace),
-                                              nbytes, _stream())
-        if rc != PRISM_OK:
-            raise PrismError(rc, "prism_prefix_attention")
+        rc = _fast.prefix_attention(self._call, q, k_pool, v_pool, block_table, out, workspace)
+        if rc:
+            self._refused(rc, "prism_prefix_attention", q, False, False, k_pool, v_pool, block_table, out, workspace)
 
     def prism_prefix_prefill(self, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out,
                              workspace=None):
-        if workspace is not None and workspace.numel() >= self.prism_plan_workspace_bytes():
-            self._check_call(q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, workspace)
-        nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-        rc = self._lib.prism_prefix_prefill(self._h, _ptr(q), _ptr(k_suffix), _ptr(v_suffix),
-                                            _ptr(k_pool), _ptr(v_pool), _ptr(block_table),
-                                            _ptr(out), _ptr(workspace), nbytes, _stream())
-        if rc != PRISM_OK:
-            raise PrismError(rc, "prism_prefix_prefill")
+        rc = _fast.prefix_prefill(self._call, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, workspace)
+        if rc:
+            self._refused(rc, "prism_prefix_prefill", q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, workspace)
 
     def prism_prefix_prefill_static(self, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out):
-        self._check_call(q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, None)
-        rc = self._lib.prism_prefix_prefill_static(self._h, _ptr(q), _ptr(k_suffix), _ptr(v_suffix),
-                                                   _ptr(k_pool), _ptr(v_pool), _ptr(block_table),
-                                                   _ptr(out), _stream())
-        if rc != PRISM_OK:
-            raise PrismError(rc, "prism_prefix_prefill_static")
+        rc = _fast.prefix_prefill_static(self._call, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out)
+        if rc:
+            self._refused(rc, "prism_prefix_prefill_static", q, k_suffix, v_suffix, k_pool, v_pool, block_table, out,
+                          None)
 
     def prism_plan_profile_enable(self, on: bool):
         self._lib.prism_plan_profile_enable(self._h, int(on))
