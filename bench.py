@@ -23,7 +23,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
-KERNEL_SOURCES = ("prism_kernels.hip", "prism_attn64.hip", "prism_device.h", "prism_acc.h")
+KERNEL_SOURCES = ("prism_kernels.hip", "prism_attn64.hip", "prism_stream.hip", "prism_device.h", "prism_acc.h")
 
 
 def kernel_source_sha():
@@ -66,6 +66,12 @@ def roofline_of(acc, attn_ms):
              "frac": achieved / PEAK_HBM_GBS}
     r.update({"kernel_ms": attn_ms, "t_mfma_ms": t_mfma * 1e3, "t_hbm_unique_ms": t_hbm * 1e3})
     return r
+
+
+def kernel_name(info):
+    if info.rows_per_wave == info.tile_rows:      # one wave holds all rows of the workgroup
+        return "stream_attn_kernel"
+    return "prefill_attn_kernel" if info.rows_per_wave == 32 else "prefill_attn64_kernel"
 
 
 class Wave:
@@ -343,9 +349,9 @@ def main():
     roof = roofline_of(acc, attn_ms)
     roof["traffic"] = traffic
     roof.update({
-        "kernel": "prefill_attn_kernel" if info.rows_per_wave == 32 else "prefill_attn64_kernel",
+        "kernel": kernel_name(info),
         "t_hbm_per_request_ms": acc["bytes_per_request"] / (PEAK_HBM_GBS * 1e9) * 1e3,
-        "append_ms": append_ms, "append_gbs": acc["append_bytes"] / max(append_ms, 1e-9) / 1e6,
+        "append_ms": append_ms, "append_gbs": acc["append_bytes"] / append_ms / 1e6 if append_ms > 0 else None,
         "reduce_ms": reduce_ms,
         "kernels_ms_sum": attn_ms + append_ms + reduce_ms,
         "step_over_kernels": timing["ms_per_step"] / max(attn_ms + append_ms + reduce_ms, 1e-9),

@@ -94,20 +94,25 @@ typedef struct prism_plan_options {
    * read only during plan creation.  Requests whose tables start with the same
    * page share a cached prefix (exact-prefix reuse, Eq. 3); the planner then
    * runs their workgroups next to each other on one die so that the shared
-   * pages are fetched from HBM once.  NULL = no placement hint.                */
+   * pages are fetched from HBM once.  It also shows that no request's cached
+   * prefix lies in pages this very wave appends to; prism_prefix_prefill may
+   * then append inside the attention kernel instead of before it, so the copy
+   * must match the device table of the calls.  NULL = no placement hint, and
+   * always two kernels.                                                        */
   const int32_t *block_table_host;
 } prism_plan_options_t;
 
 typedef struct prism_plan prism_plan_t;
 
 typedef struct prism_plan_info {
-  int32_t tile_rows;           /* query rows per workgroup                             */
+  int32_t tile_rows;           /* query rows per workgroup (16, 32 or 64: few rows per
+                                  kv head, the kernel whose waves split the keys)      */
   int32_t tile_keys;           /* keys per inner iteration                             */
   int32_t num_items;           /* attention workgroups per call                        */
   int32_t num_split_items;     /* of those, how many write fp32 partials               */
-  int32_t num_reduce_groups;   /* (request, kv head, row tile) groups merged afterwards*/
+  int32_t num_reduce_groups;   /* (request, kv head, row tile) groups merged from parts*/
   int32_t total_suffix;        /* sum_S                                                */
-  int32_t rows_per_wave;       /* query rows per wavefront: 32 or 64                   */
+  int32_t rows_per_wave;       /* query rows per wavefront                             */
   int32_t reserved[1];
   int64_t flops;               /* 4*d*Hq*sum_r(S_r*P_r + S_r(S_r+1)/2): unmasked pairs */
   int64_t kv_bytes_per_request;/* K and V bytes of every request's whole sequence      */
@@ -176,8 +181,8 @@ int prism_prefix_attention(const prism_plan_t *plan, const void *q, const void *
                            void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /*
- * The whole layer call: prism_kv_append followed, in stream order, by
- * prism_prefix_attention.  Cached prefix pages are only read; shared prefix
+ * The whole layer call: results as of prism_kv_append followed, in stream order,
+ * by prism_prefix_attention (one kernel where the plan allows it).  Cached prefix pages are only read; shared prefix
  * pages may appear in many rows of block_table.
  */
 int prism_prefix_prefill(const prism_plan_t *plan, const void *q, const void *k_suffix,
@@ -218,7 +223,8 @@ int prism_validate(const prism_shape_t *shape, const int32_t *prefix_len_host,
  * append call brackets its kernels with HIP events on the call's stream.
  * prism_plan_profile_read synchronises those events and returns, summed since
  * the last read, the milliseconds spent in the append, attention and reduce
- * kernels and the number of attention launches; it then resets the sums.
+ * kernels and the number of attention launches; it then resets the sums.  Work
+ * that the attention kernel does itself (appending, merging) counts as its time.
  */
 int prism_plan_profile_enable(prism_plan_t *plan, int enable);
 int prism_plan_profile_read(prism_plan_t *plan, double *append_ms, double *attention_ms,

@@ -191,26 +191,31 @@ struct Timed {
   }
 };
 
-LaunchParams make_params(const prism_plan *p, const void *q, const void *k_pool, const void *v_pool,
-                         const int32_t *bt, void *out, unsigned char *lists_dev) {
+// k_new, v_new: the packed suffix rows when the attention kernel is to append
+// them itself, else null.
+LaunchParams make_params(const prism_plan *p, const void *q, const void *k_new, const void *v_new, void *k_pool,
+                         void *v_pool, const int32_t *bt, void *out, unsigned char *lists_dev) {
   LaunchParams lp{};
-  lp.q = q;
-  lp.k_pool = k_pool;
-  lp.v_pool = v_pool;
-  lp.block_table = bt;
-  lp.out = out;
-  lp.items = (const AttnItem *)lists_dev;
-  lp.groups = (const ReduceGroup *)(lists_dev + p->items_bytes);
-  lp.partials = (float *)(lists_dev + p->lists_bytes);
+  AttnArgs &a = lp.args;
+  a.q = q;
+  a.k_pool = k_pool;
+  a.v_pool = v_pool;
+  a.k_new = k_new;
+  a.v_new = v_new;
+  a.block_table = bt;
+  a.out = out;
+  a.items = (const AttnItem *)lists_dev;
+  a.groups = (ReduceGroup *)(lists_dev + p->items_bytes);
+  a.partials = (float *)(lists_dev + p->lists_bytes);
+  a.Hq = p->shape.num_q_heads;
+  a.Hkv = p->shape.num_kv_heads;
+  a.max_blocks = p->shape.max_blocks_per_req;
+  a.scale_log2e = p->scale_log2e;
   lp.num_items = (int)p->sch.items.size();
   lp.num_groups = (int)p->sch.groups.size();
   lp.tile_rows = p->sch.tile_rows;
   lp.rows_per_wave = p->sch.rows_per_wave;
-  lp.Hq = p->shape.num_q_heads;
-  lp.Hkv = p->shape.num_kv_heads;
   lp.d = p->shape.head_dim;
-  lp.max_blocks = p->shape.max_blocks_per_req;
-  lp.scale_log2e = p->scale_log2e;
   return lp;
 }
 
@@ -227,6 +232,10 @@ int do_append(const prism_plan *plan, const void *k_suffix, const void *v_suffix
   return PRISM_OK;
 }
 
+// Which of the attention kernels merge split partials, and append, themselves.
+bool merges_itself(const prism_plan *p) { return p->sch.stream; }
+bool appends_itself(const prism_plan *p) { return p->sch.stream; }
+
 // One asynchronous copy of the work lists into the first bytes of dst.
 int upload_lists(const prism_plan *plan, void *dst, void *stream) {
   if (plan->lists_bytes == 0) return PRISM_OK;
@@ -242,21 +251,33 @@ int upload_lists(const prism_plan *plan, void *dst, void *stream) {
   return PRISM_OK;
 }
 
-int do_attention(const prism_plan *plan, const void *q, const void *k_pool, const void *v_pool,
-                 const int32_t *bt, void *out, unsigned char *lists_dev, void *stream) {
+int do_attention(const prism_plan *plan, const void *q, const void *k_new, const void *v_new, void *k_pool,
+                 void *v_pool, const int32_t *bt, void *out, unsigned char *lists_dev, void *stream) {
   if (plan->sch.items.empty()) return PRISM_OK;
-  LaunchParams lp = make_params(plan, q, k_pool, v_pool, bt, out, lists_dev);
+  LaunchParams lp = make_params(plan, q, k_new, v_new, k_pool, v_pool, bt, out, lists_dev);
   {
     Timed t(plan, stream, 1);
-    int e = launch_attention(lp, stream);
+    int e = plan->sch.stream           ? launch_stream(lp, stream)
+            : lp.rows_per_wave == 64 ? launch_attention64(lp, stream)
+                                     : launch_attention(lp, stream);
     if (e != 0) return hip_fail((hipError_t)e, "prefill attention launch");
   }
-  if (lp.num_groups > 0) {
+  if (lp.num_groups > 0 && !merges_itself(plan)) {
     Timed t(plan, stream, 2);
     int e = launch_reduce(lp, stream);
     if (e != 0) return hip_fail((hipError_t)e, "split reduce launch");
   }
   return PRISM_OK;
+}
+
+// Append, then attention; in one kernel where the plan allows it.
+int do_prefill(const prism_plan *plan, const void *q, const void *k_suffix, const void *v_suffix, void *k_pool,
+               void *v_pool, const int32_t *bt, void *out, unsigned char *lists_dev, void *stream) {
+  if (plan->sch.fused_append && appends_itself(plan))
+    return do_attention(plan, q, k_suffix, v_suffix, k_pool, v_pool, bt, out, lists_dev, stream);
+  int rc = do_append(plan, k_suffix, v_suffix, k_pool, v_pool, bt, stream);
+  if (rc != PRISM_OK) return rc;
+  return do_attention(plan, q, nullptr, nullptr, k_pool, v_pool, bt, out, lists_dev, stream);
 }
 
 void fill_info(const Schedule &sch, prism_plan_info_t *out) {
@@ -460,7 +481,8 @@ int prism_prefix_attention(const prism_plan_t *plan, const void *q, const void *
   if (rc != PRISM_OK) return rc;
   rc = ensure_lists(plan, workspace, hip_stream);
   if (rc != PRISM_OK) return rc;
-  return do_attention(plan, q, k_pool, v_pool, block_table_dev, out, (unsigned char *)workspace, hip_stream);
+  return do_attention(plan, q, nullptr, nullptr, (void *)k_pool, (void *)v_pool, block_table_dev, out,
+                      (unsigned char *)workspace, hip_stream);
 }
 
 int prism_prefix_prefill(const prism_plan_t *plan, const void *q, const void *k_suffix,
@@ -476,9 +498,8 @@ int prism_prefix_prefill(const prism_plan_t *plan, const void *q, const void *k_
   if (rc != PRISM_OK) return rc;
   rc = ensure_lists(plan, workspace, hip_stream);
   if (rc != PRISM_OK) return rc;
-  rc = do_append(plan, k_suffix, v_suffix, k_pool, v_pool, block_table_dev, hip_stream);
-  if (rc != PRISM_OK) return rc;
-  return do_attention(plan, q, k_pool, v_pool, block_table_dev, out, (unsigned char *)workspace, hip_stream);
+  return do_prefill(plan, q, k_suffix, v_suffix, k_pool, v_pool, block_table_dev, out, (unsigned char *)workspace,
+                    hip_stream);
 }
 
 int prism_prefix_prefill_static(const prism_plan_t *plan, const void *q, const void *k_suffix,
@@ -519,9 +540,7 @@ int prism_prefix_prefill_static(const prism_plan_t *plan, const void *q, const v
       return rc;
     }
   }
-  rc = do_append(plan, k_suffix, v_suffix, k_pool, v_pool, block_table_dev, hip_stream);
-  if (rc != PRISM_OK) return rc;
-  return do_attention(plan, q, k_pool, v_pool, block_table_dev, out, scratch, hip_stream);
+  return do_prefill(plan, q, k_suffix, v_suffix, k_pool, v_pool, block_table_dev, out, scratch, hip_stream);
 }
 
 int prism_validate(const prism_shape_t *shape, const int32_t *prefix_len_host,

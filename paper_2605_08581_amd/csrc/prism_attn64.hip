@@ -598,8 +598,8 @@ __global__ __launch_bounds__(NW * 64, 1) void prefill_attn64_kernel(
           *reinterpret_cast<float4 *>(po + 32 * db + 8 * g4 + 4 * hh) = o4;
         }
       if (hh == 0) {
-        slot[(size_t)BM * D + lr] = m_run[rb];
-        slot[(size_t)BM * D + BM + lr] = l_tot;
+        slot[(size_t)BM * D + 2 * lr] = m_run[rb];
+        slot[(size_t)BM * D + 2 * lr + 1] = l_tot;
       }
     }
   }
@@ -613,9 +613,9 @@ static int launch_attn64_t(const LaunchParams &p, hipStream_t st) {
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (attr != hipSuccess) return (int)attr;
   return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st,
-                       (const __bf16 *)p.q, (const __bf16 *)p.k_pool, (const __bf16 *)p.v_pool,
-                       p.block_table, (__bf16 *)p.out, p.partials, p.items, p.Hq, p.Hkv, p.max_blocks,
-                       p.scale_log2e);
+                       (const __bf16 *)p.args.q, (const __bf16 *)p.args.k_pool, (const __bf16 *)p.args.v_pool,
+                       p.args.block_table, (__bf16 *)p.args.out, p.args.partials, p.args.items, p.args.Hq, p.args.Hkv,
+                       p.args.max_blocks, p.args.scale_log2e);
 }
 
 // 128 rows: two waves, two workgroups per compute unit, K ring of 3 and V ring

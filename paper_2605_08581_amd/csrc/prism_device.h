@@ -80,6 +80,201 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 
+// 16 bytes per lane into registers, by inline assembly: for loads that stay in
+// flight beside the LDS copies.  The value is there after a wait_vmem that
+// covers it; pass it through an empty asm("+v") after that wait, and use it
+// nowhere before.
+__device__ __forceinline__ void load16_uncounted(bf16x8 &dst, const void *src) {
+  __asm__ volatile("global_load_dwordx4 %0, %1, off" : "=v"(dst) : "v"(src) : "memory");
+}
+// Wait until at most N vector memory operations of this wave are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vmem() {
+  static_assert(N <= 63, "vmcnt is a 6-bit counter");
+  __asm__ volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds_reads() { __asm__ volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+
+// Read-only data at a wave-uniform address, by scalar loads.  Work items and
+// block-table entries go this way: as vector loads they would queue behind the
+// LDS copies, and waiting for one would wait for every copy before it.
+template <class T>
+using ConstantPtr = const T __attribute__((address_space(4))) *;
+template <class T>
+__device__ __forceinline__ ConstantPtr<T> constant_ptr(const T *p) {
+  return (ConstantPtr<T>)(uintptr_t)p;
+}
+__device__ __forceinline__ AttnItem load_item(const AttnItem *items, int i) {
+  ConstantPtr<int32_t> w = constant_ptr((const int32_t *)(items + i));
+  AttnItem it;
+  it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.kv_begin = w[3]; it.kv_end = w[4];
+  it.part_slot = w[5]; it.prefix = w[6]; it.suffix = w[7]; it.q_off = w[8]; it.group = w[9];
+  return it;
+}
+
+// ---- where the rows of one (page, kv head) block come from ------------------
+// Cached positions lie in the pool.  When the call appends as well (k_new set),
+// positions of the new tokens are read from the packed suffix arrays, so that
+// attention does not depend on the append having happened; the page where the
+// cached prefix ends inside takes rows from both.  Descriptors end after the
+// last valid row: rows past the end of the sequence arrive as zeros.
+struct PageRows {
+  i32x4 k, v;            // the block's (first) source
+  i32x4 k_old, v_old;    // pool block of a page with rows from both sources
+  uint32_t stride;       // bytes from row to row of k, v
+  int cached_rows;       // 16: all from the pool; 0: all new; else rows below it come from k_old, v_old
+};
+struct PageSource {
+  const AttnArgs &p;
+  const int P, T, row_bytes, q_off, kv_head;
+  __device__ __forceinline__ PageSource(const AttnArgs &args, const AttnItem &it, int row)
+      : p(args), P(it.prefix), T(it.prefix + it.suffix), row_bytes(row), q_off(it.q_off), kv_head(it.kv_head) {}
+  __device__ __forceinline__ PageRows rows(int blk, int32_t page) const {
+    const int pos0 = blk * kPage;
+    int valid = T - pos0;
+    if (valid > kPage) valid = kPage;
+    const int64_t block = ((int64_t)page * p.Hkv + kv_head) * (kPage * row_bytes);
+    const unsigned char *kb = (const unsigned char *)p.k_pool + block, *vb = (const unsigned char *)p.v_pool + block;
+    PageRows r;
+    r.cached_rows = kPage;
+    r.stride = (uint32_t)row_bytes;
+    if (p.k_new) {
+      r.cached_rows = P - pos0;
+      if (r.cached_rows > kPage) r.cached_rows = kPage;
+      if (r.cached_rows < 0) r.cached_rows = 0;
+    }
+    if (r.cached_rows == kPage) {
+      r.k = block_resource(kb, (uint32_t)(valid * row_bytes));
+      r.v = block_resource(vb, (uint32_t)(valid * row_bytes));
+      r.k_old = r.k;
+      r.v_old = r.v;
+      return r;
+    }
+    r.stride = (uint32_t)(p.Hkv * row_bytes);
+    const int tok = pos0 > P ? pos0 - P : 0;
+    const int64_t first = ((int64_t)(q_off + tok) * p.Hkv + kv_head) * row_bytes;
+    const uint32_t bytes = (uint32_t)(valid - r.cached_rows - 1) * r.stride + (uint32_t)row_bytes;
+    r.k = block_resource((const unsigned char *)p.k_new + first, bytes);
+    r.v = block_resource((const unsigned char *)p.v_new + first, bytes);
+    r.k_old = block_resource(kb, (uint32_t)(r.cached_rows * row_bytes));
+    r.v_old = block_resource(vb, (uint32_t)(r.cached_rows * row_bytes));
+    return r;
+  }
+};
+
+// Append by the attention workgroups: the workgroup of a row tile and key range
+// writes the K/V rows of the tokens whose first packed row lies in its tile and
+// whose position lies in its range - every new row exactly once per kv head.
+template <int D, int NT>
+__device__ __forceinline__ void append_item_rows(const AttnArgs &p, const AttnItem &it, int G, int tile_rows, int tid) {
+  constexpr int CH = D / 8;
+  int lo = (it.row0 + G - 1) / G, hi = (it.row0 + tile_rows + G - 1) / G;
+  if (lo < it.kv_begin - it.prefix) lo = it.kv_begin - it.prefix;
+  if (hi > it.suffix) hi = it.suffix;
+  if (hi > it.kv_end - it.prefix) hi = it.kv_end - it.prefix;
+  const int32_t *bt = p.block_table + (int64_t)it.req * p.max_blocks;
+  const u32x4 *ks = (const u32x4 *)p.k_new, *vs = (const u32x4 *)p.v_new;
+  u32x4 *kd = (u32x4 *)p.k_pool, *vd = (u32x4 *)p.v_pool;
+#pragma unroll 4
+  for (int c = tid; c < (hi - lo) * CH; c += NT) {
+    const int tok = lo + c / CH, ch = c % CH, pos = it.prefix + tok;
+    const int64_t src = ((int64_t)(it.q_off + tok) * p.Hkv + it.kv_head) * CH + ch;
+    const int64_t dst = (((int64_t)bt[pos / kPage] * p.Hkv + it.kv_head) * kPage + pos % kPage) * CH + ch;
+    kd[dst] = ks[src];
+    vd[dst] = vs[src];
+  }
+}
+
+// ---- split-KV partials between workgroups -----------------------------------
+// Slot layout: fp32 O[tile_rows][D], then (m, l) per row.  Written and read with
+// device-scope accesses: they go through to memory that every die sees, so the
+// only ordering needed is "my stores are done" before the arrival is counted.
+__device__ __forceinline__ void store_shared(float *dst, float a, float b) {
+  const uint64_t v = (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32);
+  __hip_atomic_store(reinterpret_cast<uint64_t *>(dst), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_shared(const float *src) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t *>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
+template <int D>
+__device__ __forceinline__ void store_out_row(const AttnArgs &p, int q_off, int kv_head, int G, int row, int c4,
+                                              const __attribute__((ext_vector_type(4))) float &acc, float scale) {
+  __bf16 *op = (__bf16 *)p.out + ((int64_t)(q_off + row / G) * p.Hq + kv_head * G + row % G) * D + c4;
+  bf16x4 o4;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o4[r] = (__bf16)(acc[r] * scale);
+  *reinterpret_cast<bf16x4 *>(op) = o4;
+}
+
+// Counts this workgroup's partial as written; true in the workgroup that is the
+// last of its group (which leaves the counter at zero for the next call).
+__device__ __forceinline__ bool last_of_group(const AttnArgs &p, int group, int tid, int *flag) {
+  wait_vmem<0>();                                // this wave's partials have been acknowledged
+  __syncthreads();                               // every wave's have
+  if (tid == 0) {
+    int32_t *arrived = &p.groups[group].arrived;
+    const int32_t n = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = n + 1 == p.groups[group].nsplit;
+    if (last) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last;
+  }
+  __syncthreads();
+  return *flag != 0;
+}
+
+// out = sum_s e^{(m_s-m)c} O_s / sum_s e^{(m_s-m)c} l_s with m = max_s m_s (the
+// associative log-sum-exp combine of softmax partials) for the rows of one
+// group.  A thread owns four dims of a row.  Bound by the latency of reads that
+// miss every cache, so the partials are taken eight at a time, all their reads
+// in flight together.
+template <int D>
+__device__ __forceinline__ void merge_group(const AttnArgs &p, int group, int G, int tile_rows, int tid, int first_row,
+                                            int row_step) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_;
+  constexpr int TPR = D / 4, BATCH = 8;
+  const ReduceGroup g = p.groups[group];
+  const size_t slot_f = (size_t)tile_rows * (D + 2);
+  const float *base = p.partials + (size_t)g.first_slot * slot_f;
+  int n = g.suffix * G - g.row0;
+  if (n > tile_rows) n = tile_rows;
+  const int c4 = (tid % TPR) * 4;
+  for (int row = first_row + tid / TPR; row < n; row += row_step) {
+    const float *ml = base + (size_t)tile_rows * D + 2 * row, *po = base + (size_t)row * D + c4;
+    float m = -INFINITY, l = 0.f;
+    f32x4_ acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < g.nsplit; s0 += BATCH) {
+      float2 a[BATCH], x[BATCH], y[BATCH];
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {
+        const int s = s0 + i < g.nsplit ? s0 + i : g.nsplit - 1;
+        a[i] = load_shared(ml + s * slot_f);
+        x[i] = load_shared(po + s * slot_f);
+        y[i] = load_shared(po + s * slot_f + 2);
+      }
+      float m_new = m;
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) m_new = fmaxf(m_new, a[i].x);
+      const float keep = fast_exp2((m - m_new) * p.scale_log2e);
+      m = m_new;
+      l *= keep;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] *= keep;
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {
+        const float w = s0 + i < g.nsplit ? fast_exp2((a[i].x - m) * p.scale_log2e) : 0.f;
+        l += w * a[i].y;
+        acc[0] += w * x[i].x;
+        acc[1] += w * x[i].y;
+        acc[2] += w * y[i].x;
+        acc[3] += w * y[i].y;
+      }
+    }
+    store_out_row<D>(p, g.q_off, g.kv_head, G, g.row0 + row, c4, acc, 1.0f / l);
+  }
+}
+
 // O^T += V^T P^T.  With 64 rows per wave the O^T accumulators (128 registers at
 // d = 128) live in accumulation registers for the whole kernel while the score
 // tiles, which the vector ALU works on, stay in ordinary registers; the

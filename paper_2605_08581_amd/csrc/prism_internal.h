@@ -10,6 +10,7 @@ namespace prism {
 
 constexpr int kPage = 16;          // tokens per KV page
 constexpr int kTileKeys = 64;      // keys per inner iteration of the attention kernel
+constexpr int kStreamRows = 64;    // most packed rows per (request, kv head) of the key-splitting kernel
 constexpr int kNumCU = 256;        // MI355X compute units
 constexpr int kNumXCD = 8;         // accelerator complex dies, each with its own L2
 
@@ -26,7 +27,8 @@ struct AttnItem {
   int32_t prefix;      // P_r
   int32_t suffix;      // S_r
   int32_t q_off;       // token offset of the request in the packed q/out arrays
-  int32_t pad[7];
+  int32_t group;       // part_slot >= 0: the ReduceGroup that merges it
+  int32_t pad[6];
 };
 static_assert(sizeof(AttnItem) == 64, "AttnItem is 64 bytes");
 
@@ -39,7 +41,7 @@ struct ReduceGroup {
   int32_t first_slot;
   int32_t suffix;
   int32_t q_off;
-  int32_t pad;
+  int32_t arrived;     // partials written so far; zero between calls
 };
 static_assert(sizeof(ReduceGroup) == 32, "ReduceGroup is 32 bytes");
 
@@ -60,6 +62,8 @@ struct KernelTimes;    // defined in prism_api.cpp
 struct Schedule {
   int tile_rows = 128;
   int rows_per_wave = 32;
+  bool stream = false;         // few rows per kv head: the kernel whose waves split the keys
+  bool fused_append = false;   // attention may read new tokens from the packed arrays and append them itself
   std::vector<AttnItem> items;
   std::vector<ReduceGroup> groups;
   std::vector<int32_t> q_off;   // per request: first row in the packed q / k_suffix / v_suffix arrays
@@ -71,7 +75,7 @@ struct Schedule {
   int64_t total_suffix = 0;
 };
 
-// Bytes of one partial slot: fp32 O[tile_rows][d] then m[tile_rows], l[tile_rows].
+// Bytes of one partial slot: fp32 O[tile_rows][d], then the pair (m, l) per row.
 inline size_t partial_slot_bytes(int tile_rows, int d) {
   return (size_t)tile_rows * (size_t)(d + 2) * sizeof(float);
 }
@@ -83,25 +87,32 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 int validate_table(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,
                    const int32_t *table);
 
-// Kernel launchers (prism_kernels.hip).  Return hipError_t as int.
-struct LaunchParams {
+// What every attention kernel reads, passed by value.
+struct AttnArgs {
   const void *q;
-  const void *k_pool;
-  const void *v_pool;
+  void *k_pool, *v_pool;         // bf16; written only when k_new is set
+  const void *k_new, *v_new;     // packed suffix rows to append, or null: the pools hold them already
   const int32_t *block_table;
   void *out;
   float *partials;
   const AttnItem *items;
-  const ReduceGroup *groups;
+  ReduceGroup *groups;
+  int Hq, Hkv, max_blocks;
+  float scale_log2e;
+};
+
+// Kernel launchers.  Return hipError_t as int.
+struct LaunchParams {
+  AttnArgs args;
   int num_items;
   int num_groups;
   int tile_rows;
   int rows_per_wave;
-  int Hq, Hkv, d, max_blocks;
-  float scale_log2e;
+  int d;
 };
-int launch_attention(const LaunchParams &p, void *stream);
+int launch_attention(const LaunchParams &p, void *stream);     // 32 rows per wave (prism_kernels.hip)
 int launch_attention64(const LaunchParams &p, void *stream);   // 64 rows per wave (prism_attn64.hip)
+int launch_stream(const LaunchParams &p, void *stream);        // waves split the keys (prism_stream.hip)
 int launch_reduce(const LaunchParams &p, void *stream);
 int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_pool,
                   const int32_t *block_table, const AppendChunk &chunk, int max_suffix, int Hkv, int d,

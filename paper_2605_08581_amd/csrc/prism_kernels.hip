@@ -641,8 +641,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
           *reinterpret_cast<float4 *>(po + 32 * db + 8 * g4 + 4 * hh) = o4;
         }
       if (hh == 0) {
-        slot[(size_t)BM * D + lr] = m_run[rb];
-        slot[(size_t)BM * D + BM + lr] = l_tot;
+        slot[(size_t)BM * D + 2 * lr] = m_run[rb];
+        slot[(size_t)BM * D + 2 * lr + 1] = l_tot;
       }
     }
   }
@@ -670,14 +670,14 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(
   float m = -INFINITY;
   for (int s = 0; s < g.nsplit; ++s) {
     const float *slot = partials + (size_t)(g.first_slot + s) * slot_f;
-    m = fmaxf(m, slot[(size_t)tile_rows * D + lr]);
+    m = fmaxf(m, slot[(size_t)tile_rows * D + 2 * lr]);
   }
   float l = 0.f;
   float4 acc = {0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < g.nsplit; ++s) {
     const float *slot = partials + (size_t)(g.first_slot + s) * slot_f;
-    const float ms = slot[(size_t)tile_rows * D + lr];
-    const float ls = slot[(size_t)tile_rows * D + tile_rows + lr];
+    const float ms = slot[(size_t)tile_rows * D + 2 * lr];
+    const float ls = slot[(size_t)tile_rows * D + 2 * lr + 1];
     const float w = fast_exp2((ms - m) * scale_log2e);
     const float4 o = *reinterpret_cast<const float4 *>(slot + (size_t)lr * D + c4);
     l += w * ls;
@@ -705,9 +705,9 @@ static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (attr != hipSuccess) return (int)attr;
   return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st,
-                       (const __bf16 *)p.q, (const __bf16 *)p.k_pool, (const __bf16 *)p.v_pool,
-                       p.block_table, (__bf16 *)p.out, p.partials, p.items, p.Hq, p.Hkv, p.max_blocks,
-                       p.scale_log2e);
+                       (const __bf16 *)p.args.q, (const __bf16 *)p.args.k_pool, (const __bf16 *)p.args.v_pool,
+                       p.args.block_table, (__bf16 *)p.args.out, p.args.partials, p.args.items, p.args.Hq, p.args.Hkv,
+                       p.args.max_blocks, p.args.scale_log2e);
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot
@@ -717,7 +717,6 @@ static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
 int launch_attention(const LaunchParams &p, void *stream) {
   if (p.num_items == 0) return 0;
   hipStream_t st = (hipStream_t)stream;
-  if (p.rows_per_wave == 64) return launch_attention64(p, stream);
   if (p.d == 128) {
     if (p.tile_rows == 64) return launch_attn_t<128, 1, 2, 2, 2>(p, st);
     if (p.tile_rows == 128) return launch_attn_t<128, 1, 4, 2, 2>(p, st);
@@ -733,12 +732,14 @@ int launch_reduce(const LaunchParams &p, void *stream) {
   hipStream_t st = (hipStream_t)stream;
   if (p.d == 128) {
     dim3 grid((unsigned)p.num_groups, (unsigned)((p.tile_rows + 7) / 8));
-    return launch_kernel(split_reduce_kernel<128>, grid, dim3(256), 0, st, (const float *)p.partials,
-                         (__bf16 *)p.out, p.groups, p.tile_rows, p.Hq, p.Hkv, p.scale_log2e);
+    return launch_kernel(split_reduce_kernel<128>, grid, dim3(256), 0, st, (const float *)p.args.partials,
+                         (__bf16 *)p.args.out, (const ReduceGroup *)p.args.groups, p.tile_rows, p.args.Hq, p.args.Hkv,
+                         p.args.scale_log2e);
   } else {
     dim3 grid((unsigned)p.num_groups, (unsigned)((p.tile_rows + 15) / 16));
-    return launch_kernel(split_reduce_kernel<64>, grid, dim3(256), 0, st, (const float *)p.partials,
-                         (__bf16 *)p.out, p.groups, p.tile_rows, p.Hq, p.Hkv, p.scale_log2e);
+    return launch_kernel(split_reduce_kernel<64>, grid, dim3(256), 0, st, (const float *)p.args.partials,
+                         (__bf16 *)p.args.out, (const ReduceGroup *)p.args.groups, p.tile_rows, p.args.Hq, p.args.Hkv,
+                         p.args.scale_log2e);
   }
 }
 

@@ -39,12 +39,34 @@ struct RowTile {
   int64_t cluster_cost;   // all key tiles of the (cluster, kv head) set
 };
 
+// Whether some request's cached prefix lies in pages that the same wave appends
+// to (pages published to later requests of the wave before they are written).
+// Attention then has to run after the whole append.
+bool reads_pages_of_this_wave(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,
+                              const int32_t *table) {
+  std::vector<int32_t> writer(s.num_pages, -1);    // request that appends to the page, -2: several
+  for (int pass = 0; pass < 2; ++pass)
+    for (int r = 0; r < s.batch; ++r) {
+      if (suffix[r] == 0) continue;
+      const int32_t *row = table + (size_t)r * s.max_blocks_per_req;
+      const int whole = prefix[r] / kPage, last = (prefix[r] + suffix[r] - 1) / kPage;
+      for (int b = pass == 0 ? whole : 0; b <= (pass == 0 ? last : whole); ++b) {
+        if (row[b] < 0 || row[b] >= s.num_pages) return true;
+        int32_t &w = writer[row[b]];
+        if (pass == 0) w = w == -1 || w == r ? r : -2;
+        else if (b < whole ? w != -1 : w != r) return true;
+      }
+    }
+  return false;
+}
+
 }  // namespace
 
 int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,
                    const prism_plan_options_t &opt, Schedule *out) {
   int rc = check_shape(s);
   if (rc != PRISM_OK) return rc;
+  const int G = s.num_q_heads / s.num_kv_heads;
   int tile_rows = opt.tile_rows ? opt.tile_rows : 128;
   if (tile_rows != 64 && tile_rows != 128 && tile_rows != 256) return PRISM_ERR_UNSUPPORTED;
   const int rows_per_wave = opt.rows_per_wave ? opt.rows_per_wave : 32;
@@ -52,14 +74,12 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   if (rows_per_wave == 64 && tile_rows == 64) return PRISM_ERR_UNSUPPORTED;
   if (opt.split_kv < 0 || opt.min_split_keys < 0 || opt.min_split_keys % kTileKeys != 0)
     return PRISM_ERR_UNSUPPORTED;
-  const int G = s.num_q_heads / s.num_kv_heads;
   const int d = s.head_dim;
 
   Schedule sch;
-  sch.tile_rows = tile_rows;
-  sch.rows_per_wave = rows_per_wave;
   std::vector<int32_t> q_off(s.batch);
   int64_t total = 0;
+  int64_t most_rows = 0;       // packed rows of the largest request, per kv head
   for (int r = 0; r < s.batch; ++r) {
     const int64_t P = prefix[r], S = suffix[r];
     if (P < 0 || S < 0) return PRISM_ERR_INVALID_ARG;
@@ -69,9 +89,23 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     q_off[r] = (int32_t)total;
     total += S;
     sch.flops += 4LL * d * s.num_q_heads * (S * P + S * (S + 1) / 2);
-    if (S > 0) sch.kv_bytes += 2LL * 2 * d * s.num_kv_heads * (P + S);
+    if (S > 0) {
+      sch.kv_bytes += 2LL * 2 * d * s.num_kv_heads * (P + S);
+      most_rows = std::max(most_rows, S * G);
+    }
   }
   sch.total_suffix = total;
+
+  // Up to 64 packed rows per (request, kv head) - decode steps, short suffixes -
+  // a wave's work is bound by bytes or latency, not by the matrix cores: the
+  // kernel whose waves split the keys then keeps every wave busy.  Above that
+  // the row tiles of the prefill kernel are full enough.
+  const bool stream = !opt.tile_rows && !opt.rows_per_wave && most_rows <= kStreamRows;
+  if (stream) tile_rows = most_rows <= 16 ? 16 : most_rows <= 32 ? 32 : 64;
+  sch.stream = stream;
+  sch.tile_rows = tile_rows;
+  sch.rows_per_wave = stream ? tile_rows : rows_per_wave;
+  sch.fused_append = opt.block_table_host && !reads_pages_of_this_wave(s, prefix, suffix, opt.block_table_host);
 
   sch.q_off = q_off;
 
@@ -111,9 +145,52 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 
   // Split-KV: aim for a few workgroups per compute unit; never cut below
   // min_split_keys.
-  const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 1024) / kTileKeys);
-  const int64_t target_items = 3LL * kNumCU;
+  const int default_min = stream ? 256 : 1024;
+  const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : default_min) / kTileKeys);
+  const int64_t target_items = (stream ? 2LL : 3LL) * kNumCU;
   int chunk = (int)std::max<int64_t>(min_chunk, (total_cost + target_items - 1) / target_items);
+  // The key-splitting kernel fills the chip with one workgroup per CU (two at
+  // d = 64: LDS), so it is cut to fit whole rounds of that many: for each number
+  // of rounds the smallest chunk whose workgroups fit, and of those the one with
+  // the least (rounds x chunk length).  Each round costs about kRoundTiles more
+  // for starting and merging, and a range only kSlackTiles longer than the chunk
+  // stays whole: a merge costs about 4 us, what a workgroup needs for 8 tiles.
+  // (16 requests x 300..4100 keys, 8 kv heads: 34.2 us with 1.8 uneven rounds,
+  // 31.5 us with one.)
+  constexpr int kMaxRounds = 8, kRoundTiles = 8, kSlackTiles = 4;
+  bool fit = false;
+  if (stream && opt.split_kv == 0) {
+    const int64_t slots = (d == 64 ? 2 : 1) * kNumCU;
+    auto pieces = [&](int cost, int c) { return std::max(1, (cost - kSlackTiles + c - 1) / c); };
+    int64_t best = INT64_MAX;
+    int longest = min_chunk;
+    std::vector<int> costs;
+    for (int r = 0; r < s.batch; ++r)
+      if (suffix[r] > 0) {
+        costs.push_back((prefix[r] + suffix[r] + kTileKeys - 1) / kTileKeys);
+        longest = std::max(longest, costs.back());
+      }
+    auto items_at = [&](int c) {
+      int64_t n = 0;
+      for (int cost : costs) n += pieces(cost, c);
+      return n * s.num_kv_heads;
+    };
+    for (int k = 1; k <= kMaxRounds; ++k) {
+      if (items_at(longest) > k * slots) continue;
+      int lo = min_chunk, hi = longest;
+      while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        if (items_at(mid) <= k * slots) hi = mid;
+        else lo = mid + 1;
+      }
+      const int64_t time = (int64_t)k * (lo + kRoundTiles);
+      if (time < best) {
+        best = time;
+        chunk = lo;
+        fit = true;
+      }
+    }
+  }
 
   // Heaviest (cluster, kv head) set first; inside a set the requests, and
   // inside a request the row tiles, stay adjacent so that they run at the same
@@ -156,6 +233,8 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       int nsplit = 1;
       if (opt.split_kv > 1) {
         nsplit = std::min(opt.split_kv, t.cost);
+      } else if (fit) {
+        nsplit = std::max(1, (t.cost - kSlackTiles + chunk - 1) / chunk);
       } else if (opt.split_kv == 0 && t.cost >= 2 * chunk) {
         nsplit = (t.cost + chunk - 1) / chunk;
       }
@@ -183,6 +262,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       g.first_slot = next_slot;
       g.suffix = suffix[t.req];
       g.q_off = q_off[t.req];
+      it.group = (int32_t)sch.groups.size();
       sch.groups.push_back(g);
       for (int c = 0; c < nsplit; ++c) {
         it.kv_begin = c * per * kTileKeys;

@@ -1,0 +1,351 @@
+// Attention for few query rows per (request, kv head): decode steps and short
+// suffixes.  At most 64 packed rows share every K/V byte, so the work is below
+// 64 flop per byte and the kernel is bound by how many bytes it keeps in flight
+// from HBM, or, for small waves, by latency.
+//
+// One workgroup serves one (request, kv head, key range).  Its four waves split
+// the KEYS, not the rows: wave w takes the 32-key tiles w, w+4, ... for all rows.
+// No K/V byte is shared between waves, so each wave streams into LDS rings of
+// its own with direct-to-LDS copies and waits for its own copies only; there is
+// no barrier until the waves' partial results meet at the end.  Two tiles per
+// wave are in flight or in use, 128 KB per CU at d = 128: about 100 KB on the
+// way, which covers the HBM latency.  (Measured beside it at d = 128: two waves
+// with four tiles each 7 % slower on 64 x 4096 keys, one wave with three or four
+// tiles 4 %; two waves with two tiles, two workgroups per CU, equal there and
+// 4 % slower on small batches.)
+//
+// With the row tile of the prefill kernel (128 rows, four waves sharing one
+// tile) the same work left three of four waves without rows, took two barriers
+// per tile and ran a chain of 64-key steps per workgroup.  16 requests x 300 to
+// 4100 keys, 32/8 heads, d = 128 (143 MB): three launches 49 us, now one of
+// 31.5 us = 4.5 TB/s; 64 x 4096 keys, 40 heads (4.37 GB): 771 -> 753 us =
+// 5.8 TB/s, where a plain streaming read reaches 6.5.
+//
+// Products are taken transposed as in the prefill kernel, with the 16x16x32
+// MFMA because rows come in blocks of 16:
+//   S^T = K Q^T    A = K rows from LDS, B = Q rows in registers
+//   O^T = V^T P^T  A = V read transposed from LDS, B = P^T from the S^T registers
+// In the 16x16 accumulator layout lane l holds column l%16 (a query row) and
+// rows 4*(l/16) + r, r = 0..3 (keys for S^T, head dims for O^T).  The 32 keys of
+// the second product are numbered 8*(l/16) + j: j < 4 is key 4*(l/16)+j of the
+// first 16 keys, j >= 4 is key 4*(l/16)+j-4 of the second 16, which is where the
+// S^T accumulators already hold them.
+#include "prism_device.h"
+
+namespace prism {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+template <int D, int RB>
+struct StreamShape {
+  static constexpr int NW = 4;                              // waves per workgroup
+  static constexpr int NS = 2;                              // tiles per wave in flight or in use
+  static constexpr int kTile = 32;                          // keys per wave and step: two pages
+  static constexpr int kTileBytes = 2 * kTile * D * 2;      // K then V
+  static constexpr int kRows = 16 * RB;
+  static constexpr int kRowPitch = D + 4;                   // floats; keeps 16 rows off one bank
+  static constexpr size_t kRingBytes = (size_t)NW * NS * kTileBytes;
+  static constexpr size_t kMergeBytes = (size_t)NW * kRows * (kRowPitch + 2) * sizeof(float);
+  static constexpr size_t kLdsBytes = (kRingBytes > kMergeBytes ? kRingBytes : kMergeBytes) + 16;
+};
+
+// largest / sum over the four 16-lane groups that hold one query row
+__device__ __forceinline__ float max_across_groups(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_across_halves(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+}
+__device__ __forceinline__ float sum_across_groups(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return sum_across_halves(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+}
+
+template <int D, int RB>
+__global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
+  using Shape = StreamShape<D, RB>;
+  constexpr int NW = Shape::NW, NS = Shape::NS;
+  constexpr int NT = NW * 64;
+  constexpr int CPR = D / 8;                     // 16-byte chunks per key row
+  constexpr int ROW = D * 2;                     // bytes per key row
+  constexpr int UPP = kPage * ROW / 1024;        // 1 KB copies per (page, head) block
+  constexpr int KPU = 1024 / ROW;                // keys per copy
+  constexpr int KK = D / 32;                     // MFMA k-steps over the head dim
+  constexpr int DB = D / 16;                     // 16-wide head-dim blocks of O^T
+  constexpr int TK = Shape::kTile;
+  constexpr int COPIES = 2 * 2 * UPP;            // copies per tile: two pages of K and of V
+  static_assert((NS - 1) * COPIES <= 63, "pending copies must fit the vmcnt counter");
+
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+
+  const AttnItem it = load_item(p.items, blockIdx.x);
+  if (it.req < 0) return;                        // idle padding entry
+  const int G = p.Hq / p.Hkv;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, g4 = lane >> 4;
+  const int P = it.prefix, S = it.suffix, T = P + S;
+  const int rows = S * G;                        // <= 16*RB: the planner's rule for this kernel
+  const ConstantPtr<int32_t> bt = constant_ptr(p.block_table + (int64_t)it.req * p.max_blocks);
+
+  // ---- Q fragments: lane holds row c16, dims 32kk+8*g4..+7.  Loaded by inline
+  // assembly, like the copies: the compiler cannot count copies that it does not
+  // see and would otherwise drain them all before the first use of Q.
+  bf16x8 qf[RB][KK];
+  int limit[RB];                                 // last visible key of the lane's row
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = rb * 16 + c16;
+    const bool valid = row < rows;
+    const int tok = valid ? row / G : 0, g = valid ? row % G : 0;
+    limit[rb] = valid ? P + tok : -1;
+    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * p.Hq + it.kv_head * G + g) * D + 8 * g4;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) load16_uncounted(qf[rb][kk], qp + 32 * kk);   // row 0 stands in for rows past the end
+  }
+
+  // ---- paged copies of this wave's tiles
+  const uint32_t lds_base = lds_address(lds) + (uint32_t)(wave * NS * Shape::kTileBytes);
+  const PageSource src(p, it, ROW);
+  uint32_t lane_chunk[UPP];                      // swizzled 16-byte chunk this lane fetches
+#pragma unroll
+  for (int i = 0; i < UPP; ++i)
+    lane_chunk[i] = (uint32_t)(((lane % CPR) ^ swz<D>(i * KPU + lane / CPR)) << 4);
+  const int lane_row = lane / CPR;
+  struct PageIds {
+    int32_t p[2];
+  };
+  const int last_blk = (T - 1) / kPage;          // keys past the end are masked; any finite page will do for them
+  auto pages_of = [&](int key0) -> PageIds {
+    const int blk = key0 / kPage;
+    return PageIds{{bt[blk < last_blk ? blk : last_blk], bt[blk + 1 < last_blk ? blk + 1 : last_blk]}};
+  };
+  auto copy_tile = [&](int key0, const PageIds &pages, int slot) {
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg) {
+      const int blk = key0 / kPage + pg;
+      const PageRows a = src.rows(blk < last_blk ? blk : last_blk, pages.p[pg]);
+      const uint32_t dst = lds_base + (uint32_t)(slot * Shape::kTileBytes + pg * kPage * ROW);
+      if (a.cached_rows == 0 || a.cached_rows == kPage) {
+#pragma unroll
+        for (int i = 0; i < UPP; ++i) {
+          const uint32_t off = (uint32_t)(i * KPU + lane_row) * a.stride + lane_chunk[i];
+          copy16_to_lds(a.k, off, dst + (uint32_t)(i * 1024));
+          copy16_to_lds(a.v, off, dst + (uint32_t)(TK * ROW + i * 1024));
+        }
+      } else {                                   // the page where the cached prefix ends: its rows come from both
+#pragma unroll
+        for (int i = 0; i < UPP; ++i) {
+          const int row = i * KPU + lane_row;
+          const uint32_t off = (uint32_t)row * ROW + lane_chunk[i];
+          if (row < a.cached_rows) {
+            copy16_to_lds(a.k_old, off, dst + (uint32_t)(i * 1024));
+            copy16_to_lds(a.v_old, off, dst + (uint32_t)(TK * ROW + i * 1024));
+          } else {
+            const uint32_t off_new = (uint32_t)(row - a.cached_rows) * a.stride + lane_chunk[i];
+            copy16_to_lds(a.k, off_new, dst + (uint32_t)(i * 1024));
+            copy16_to_lds(a.v, off_new, dst + (uint32_t)(TK * ROW + i * 1024));
+          }
+        }
+      }
+    }
+  };
+
+  const int n_tiles = (it.kv_end - it.kv_begin + TK - 1) / TK;
+  const int mine = n_tiles > wave ? (n_tiles - wave + NW - 1) / NW : 0;
+  auto key0_of = [&](int t) { return it.kv_begin + (wave + t * NW) * TK; };
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    if (t < mine) copy_tile(key0_of(t), pages_of(key0_of(t)), t);
+  if (mine >= NS) wait_vmem<NS * COPIES <= 63 ? NS * COPIES : 63>();   // Q was requested before any copy
+  else wait_vmem<0>();
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) __asm__ volatile("" : "+v"(qf[rb][kk]));
+
+  // per-lane LDS addresses of the fragment reads, relative to a tile slot
+  typedef __attribute__((address_space(3))) const bf16x8 *lds_b128_ptr;
+  typedef __attribute__((address_space(3))) s16x4 *lds_tr_ptr;
+  uint32_t k_lane[KK], v_lane[DB];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) k_lane[kk] = lds_base + (uint32_t)lds_off<D>(c16, 4 * kk + g4);
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+    v_lane[db] = lds_base + (uint32_t)(TK * ROW + lds_off<D>(4 * g4 + (c16 >> 2), 2 * db + ((c16 & 3) >> 1)) +
+                                       ((c16 & 1) << 3));
+
+  f32x4 oacc[DB][RB];
+  float m_run[RB], l_run[RB], bound[RB];
+  const float slack = kRescaleThreshold / p.scale_log2e;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    m_run[rb] = bound[rb] = -1e30f;
+    l_run[rb] = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  for (int t = 0; t < mine; ++t) {
+    const int ring = t % NS;
+    const uint32_t slot = (uint32_t)(ring * Shape::kTileBytes);
+    const PageIds ahead = pages_of(t + NS < mine ? key0_of(t + NS) : it.kv_begin);
+    if (t + NS <= mine) wait_vmem<(NS - 1) * COPIES>();   // only later tiles' copies may still be on their way
+    else wait_vmem<0>();
+    f32x4 s[2][RB];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) s[kb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 a = *(lds_b128_ptr)(uintptr_t)(k_lane[kk] + slot + (uint32_t)(kb * kPage * ROW));
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          s[kb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[rb][kk], s[kb][rb], 0, 0, 0);
+      }
+    }
+    const int key0 = key0_of(t);
+    if (key0 + TK - 1 > P) {                     // some row may not see all of these keys
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (key0 + kb * 16 + 4 * g4 + r > limit[rb]) s[kb][rb][r] = -INFINITY;
+    }
+    // lazy running maximum, as in the prefill kernel
+    float mx[RB];
+    bool grow = false;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      mx[rb] = s[0][rb][0];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx[rb] = fmaxf(mx[rb], s[kb][rb][r]);
+      grow |= mx[rb] > bound[rb];
+    }
+    if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const float m_new = fmaxf(m_run[rb], max_across_groups(mx[rb]));
+        const float alpha = fast_exp2((m_run[rb] - m_new) * p.scale_log2e);
+        bound[rb] = m_new + slack;
+        m_run[rb] = m_new;
+        l_run[rb] *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) oacc[db][rb][r] *= alpha;
+      }
+    }
+    bf16x8 pf[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const float mc = m_run[rb] * p.scale_log2e;
+      float sum = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float e = fast_exp2(fmaf(s[kb][rb][r], p.scale_log2e, -mc));
+          sum += e;
+          pf[rb][4 * kb + r] = (__bf16)e;
+        }
+      l_run[rb] += sum;
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      union {
+        s16x4 h[2];
+        bf16x8 v;
+      } a;
+      a.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(uintptr_t)(v_lane[db] + slot));
+      a.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(uintptr_t)(v_lane[db] + slot + (uint32_t)(kPage * ROW)));
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) oacc[db][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, pf[rb], oacc[db][rb], 0, 0, 0);
+    }
+    if (t + NS < mine) {
+      wait_lds_reads();                          // the slot is free once this wave's reads of it are done
+      copy_tile(key0_of(t + NS), ahead, ring);
+    }
+  }
+
+  // ---- the new tokens' rows go to their pages (this workgroup's key range only)
+  if (p.k_new) append_item_rows<D, NT>(p, it, G, Shape::kRows, tid);
+
+  // ---- the waves' partial results meet in LDS
+  wait_vmem<0>();
+  __syncthreads();                               // every ring is idle from here on
+  float *part = reinterpret_cast<float *>(lds);
+  float *ml = part + (size_t)NW * Shape::kRows * Shape::kRowPitch;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int slot_row = wave * Shape::kRows + rb * 16 + c16;
+    const float l_tot = sum_across_groups(l_run[rb]);
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      *reinterpret_cast<f32x4 *>(part + (size_t)slot_row * Shape::kRowPitch + 16 * db + 4 * g4) = oacc[db][rb];
+    if (g4 == 0) {
+      ml[2 * slot_row] = m_run[rb];
+      ml[2 * slot_row + 1] = l_tot;
+    }
+  }
+  __syncthreads();
+  constexpr int TPR = D / 4;                     // threads per row, four dims each
+  float *slot_out = it.part_slot >= 0 ? p.partials + (size_t)it.part_slot * Shape::kRows * (D + 2) : nullptr;
+  for (int c = tid; c < rows * TPR; c += NT) {
+    const int row = c / TPR, c4 = (c % TPR) * 4;
+    float m = ml[2 * row];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, ml[2 * (w * Shape::kRows + row)]);
+    float l = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int sr = w * Shape::kRows + row;
+      const float e = fast_exp2((ml[2 * sr] - m) * p.scale_log2e);
+      const f32x4 o = *reinterpret_cast<const f32x4 *>(part + (size_t)sr * Shape::kRowPitch + c4);
+      l += e * ml[2 * sr + 1];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] += e * o[r];
+    }
+    if (!slot_out) {
+      store_out_row<D>(p, it.q_off, it.kv_head, G, row, c4, acc, 1.0f / l);
+    } else {
+      store_shared(slot_out + (size_t)row * D + c4, acc[0], acc[1]);
+      store_shared(slot_out + (size_t)row * D + c4 + 2, acc[2], acc[3]);
+      if (c4 == 0) store_shared(slot_out + (size_t)Shape::kRows * D + 2 * row, m, l);
+    }
+  }
+  if (slot_out) {
+    int *flag = reinterpret_cast<int *>(lds + Shape::kLdsBytes - 16);
+    if (last_of_group(p, it.group, tid, flag)) merge_group<D>(p, it.group, G, Shape::kRows, tid, 0, NT / TPR);
+  }
+}
+
+template <int D, int RB>
+static int launch_stream_t(const LaunchParams &p, hipStream_t st) {
+  constexpr size_t lds_bytes = StreamShape<D, RB>::kLdsBytes;
+  auto kernel = stream_attn_kernel<D, RB>;
+  static const hipError_t attr = hipFuncSetAttribute(
+      (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  if (attr != hipSuccess) return (int)attr;
+  return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(StreamShape<D, RB>::NW * 64), lds_bytes, st, p.args);
+}
+
+template <int D>
+static int launch_stream_d(const LaunchParams &p, hipStream_t st) {
+  if (p.tile_rows == 16) return launch_stream_t<D, 1>(p, st);
+  if (p.tile_rows == 32) return launch_stream_t<D, 2>(p, st);
+  return launch_stream_t<D, 4>(p, st);
+}
+
+int launch_stream(const LaunchParams &p, void *stream) {
+  if (p.num_items == 0) return 0;
+  hipStream_t st = (hipStream_t)stream;
+  return p.d == 128 ? launch_stream_d<128>(p, st) : launch_stream_d<64>(p, st);
+}
+
+}  // namespace prism

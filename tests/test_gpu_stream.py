@@ -1,0 +1,93 @@
+"""GPU parity of the kernel for few rows per kv head (its waves split the keys):
+row blocks of 16, both head dims, prefixes that end inside a page (rows of one
+page come from the pool and from the packed arrays), split keys with the merge
+by the last workgroup, and the append done by the attention workgroups."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_08581_amd import binding as B
+from paper_2605_08581_amd import workload as W
+
+from gpu_util import check_close, full_parity, widen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group,suffix", [(1, [1, 15, 16]), (4, [1, 4, 3]), (1, [17, 32, 1]), (8, [2, 4, 1]),
+                                          (1, [33, 64, 63]), (5, [12, 7, 1])],
+                         ids=["16", "g4x16", "32", "g8x32", "64", "g5x60"])
+def test_row_blocks_and_page_edges(oracle_lib, group, suffix, d):
+    """Up to 16, 32 and 64 rows; cached lengths 0, inside a page, on a page edge,
+    around the 32-key tile and far past it; sequences of a single key."""
+    prefix = [0, 37, 1500] if suffix[0] > 1 else [1000, 16, 31]
+    b = W.make_custom_batch("stream", W.Geometry(2 * group, 2, d), prefix + [0], suffix + [1], seed=61)
+    info = full_parity(oracle_lib, b)
+    assert info.tile_rows in (16, 32, 64)
+    full_parity(oracle_lib, b, split_kv=3)
+
+
+@pytest.mark.parametrize("geom", [W.Geometry(8, 8, 128), W.Geometry(32, 8, 128), W.Geometry(8, 1, 64)],
+                         ids=["mha128", "gqa128", "mqa64"])
+def test_wave_larger_than_the_chip(oracle_lib, geom):
+    """Enough workgroups for two waves each, ragged lengths, split by the planner; two calls in a
+    row on one workspace (the arrival counters must be back at zero)."""
+    rng = np.random.default_rng(3)
+    n = 48
+    b = W.make_custom_batch("many", geom, rng.integers(1, 1800, n).tolist(), [1] * n, seed=62)
+    t = W.make_tensors(b, "cuda")
+    host = {k: W.bf16_bits(v) for k, v in t.items()}
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table)
+    ws = torch.empty(plan.prism_plan_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    bt = torch.from_numpy(b.block_table).cuda()
+    kp, vp = oracle_lib.kv_append(host["k_suffix"], host["v_suffix"], host["k_pool"], host["v_pool"],
+                                  b.block_table, b.prefix_len, b.suffix_len)
+    ref = oracle_lib.attention(host["q"], kp, vp, b.block_table, b.prefix_len, b.suffix_len, b.softmax_scale)
+    for _ in range(2):
+        out = torch.full_like(t["q"], float("nan"))
+        plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"], bt, out, ws)
+        torch.cuda.synchronize()
+        check_close(widen(W.bf16_bits(out)), ref, b.name)
+    plan.close()
+    assert np.array_equal(W.bf16_bits(t["k_pool"]), kp) and np.array_equal(W.bf16_bits(t["v_pool"]), vp)
+
+
+@pytest.mark.parametrize("suffix", [[20, 20], [150, 40]], ids=["stream", "tile"])
+@pytest.mark.parametrize("hint", [True, False], ids=["table", "no-table"])
+def test_prefix_pages_written_by_the_same_wave(oracle_lib, suffix, hint):
+    """The second request's cached prefix is what the first one appends in this
+    very call: attention must then see the appended rows."""
+    geom = W.Geometry(2, 2, 128)
+    b = W.make_custom_batch("in-wave", geom, [32, 48], suffix, seed=63)
+    table = b.block_table.copy()
+    table[1, :3] = table[0, :3]                    # positions 32..47 of request 0 are new tokens
+    t = W.make_tensors(b, "cuda")
+    host = {k: W.bf16_bits(v) for k, v in t.items()}
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=table if hint else None)
+    ws = torch.empty(plan.prism_plan_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    out = torch.full_like(t["q"], float("nan"))
+    plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"],
+                              torch.from_numpy(table).cuda(), out, ws)
+    torch.cuda.synchronize()
+    plan.close()
+    kp, vp = oracle_lib.kv_append(host["k_suffix"], host["v_suffix"], host["k_pool"], host["v_pool"],
+                                  table, b.prefix_len, b.suffix_len)
+    assert np.array_equal(W.bf16_bits(t["k_pool"]), kp) and np.array_equal(W.bf16_bits(t["v_pool"]), vp)
+    ref = oracle_lib.attention(host["q"], kp, vp, table, b.prefix_len, b.suffix_len, b.softmax_scale)
+    check_close(widen(W.bf16_bits(out)), ref, b.name)
+
+
+def test_slots_past_the_sequence_hold_nan(oracle_lib):
+    """Unused slots of the last page must not reach the products, whether the
+    new rows come from the packed arrays or from the pool."""
+    b = W.make_custom_batch("nan", W.Geometry(4, 4, 128), [32, 5], [21, 2], seed=64)
+
+    def mutate(t):
+        for r in range(b.batch):
+            T = int(b.prefix_len[r] + b.suffix_len[r])
+            pg = int(b.block_table[r, (T - 1) // 16])
+            t["k_pool"][pg, :, T % 16:, :] = float("nan")
+            t["v_pool"][pg, :, T % 16:, :] = float("inf")
+    full_parity(oracle_lib, b, mutate=mutate)
+    full_parity(oracle_lib, b, mutate=mutate, entry="separate")
