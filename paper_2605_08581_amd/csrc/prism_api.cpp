@@ -234,7 +234,7 @@ int do_append(const prism_plan *plan, const void *k_suffix, const void *v_suffix
 
 // Which of the attention kernels merge split partials, and append, themselves.
 bool merges_itself(const prism_plan *p) { return p->sch.stream; }
-bool appends_itself(const prism_plan *p) { return p->sch.stream; }
+bool appends_itself(const prism_plan *p) { return p->sch.stream || p->sch.rows_per_wave == 32; }
 
 // One asynchronous copy of the work lists into the first bytes of dst.
 int upload_lists(const prism_plan *plan, void *dst, void *stream) {

@@ -112,78 +112,47 @@ __device__ __forceinline__ AttnItem load_item(const AttnItem *items, int i) {
   return it;
 }
 
+// All of a group but its arrival counter.
+__device__ __forceinline__ ReduceGroup load_group(const ReduceGroup *groups, int i) {
+  ConstantPtr<int32_t> w = constant_ptr((const int32_t *)(groups + i));
+  ReduceGroup g;
+  g.req = w[0]; g.kv_head = w[1]; g.row0 = w[2]; g.nsplit = w[3]; g.first_slot = w[4]; g.suffix = w[5]; g.q_off = w[6];
+  g.arrived = 0;
+  return g;
+}
+
 // ---- where the rows of one (page, kv head) block come from ------------------
 // Cached positions lie in the pool.  When the call appends as well (k_new set),
 // positions of the new tokens are read from the packed suffix arrays, so that
 // attention does not depend on the append having happened; the page where the
-// cached prefix ends inside takes rows from both.  Descriptors end after the
-// last valid row: rows past the end of the sequence arrive as zeros.
-struct PageRows {
-  i32x4 k, v;            // the block's (first) source
-  i32x4 k_old, v_old;    // pool block of a page with rows from both sources
-  uint32_t stride;       // bytes from row to row of k, v
-  int cached_rows;       // 16: all from the pool; 0: all new; else rows below it come from k_old, v_old
-};
+// cached prefix ends inside takes rows from both.  Descriptors of new rows end
+// after the request's last row: rows past the sequence arrive as zeros.
 struct PageSource {
   const AttnArgs &p;
-  const int P, T, row_bytes, q_off, kv_head;
+  const int P, S, row_bytes, q_off, kv_head;
+  const int first_new;                           // positions from here on are packed rows
+  const uint32_t new_stride;                     // bytes from one packed row of the head to the next
   __device__ __forceinline__ PageSource(const AttnArgs &args, const AttnItem &it, int row)
-      : p(args), P(it.prefix), T(it.prefix + it.suffix), row_bytes(row), q_off(it.q_off), kv_head(it.kv_head) {}
-  __device__ __forceinline__ PageRows rows(int blk, int32_t page) const {
-    const int pos0 = blk * kPage;
-    int valid = T - pos0;
-    if (valid > kPage) valid = kPage;
-    const int64_t block = ((int64_t)page * p.Hkv + kv_head) * (kPage * row_bytes);
-    const unsigned char *kb = (const unsigned char *)p.k_pool + block, *vb = (const unsigned char *)p.v_pool + block;
-    PageRows r;
-    r.cached_rows = kPage;
-    r.stride = (uint32_t)row_bytes;
-    if (p.k_new) {
-      r.cached_rows = P - pos0;
-      if (r.cached_rows > kPage) r.cached_rows = kPage;
-      if (r.cached_rows < 0) r.cached_rows = 0;
-    }
-    if (r.cached_rows == kPage) {
-      r.k = block_resource(kb, (uint32_t)(valid * row_bytes));
-      r.v = block_resource(vb, (uint32_t)(valid * row_bytes));
-      r.k_old = r.k;
-      r.v_old = r.v;
-      return r;
-    }
-    r.stride = (uint32_t)(p.Hkv * row_bytes);
-    const int tok = pos0 > P ? pos0 - P : 0;
+      : p(args), P(it.prefix), S(it.suffix), row_bytes(row), q_off(it.q_off), kv_head(it.kv_head),
+        first_new(args.k_new ? it.prefix : 0x7fffffff), new_stride((uint32_t)(args.Hkv * row)) {}
+  // byte offset of the (page, kv head) block in a pool
+  __device__ __forceinline__ int64_t block_of(int32_t page) const {
+    return ((int64_t)page * p.Hkv + kv_head) * (kPage * row_bytes);
+  }
+  // the first `rows` rows of a pool block, K (which = 0) or V (1)
+  __device__ __forceinline__ i32x4 old_rows(int which, int32_t page, int rows = kPage) const {
+    return block_resource((const unsigned char *)(which ? p.v_pool : p.k_pool) + block_of(page),
+                          (uint32_t)(rows * row_bytes));
+  }
+  // up to `rows` packed rows from token tok on (clamped into the request's own rows)
+  __device__ __forceinline__ i32x4 new_rows(int which, int tok, int rows = kPage) const {
+    if (tok < 0) tok = 0;
+    if (rows > S - tok) rows = S - tok;
     const int64_t first = ((int64_t)(q_off + tok) * p.Hkv + kv_head) * row_bytes;
-    const uint32_t bytes = (uint32_t)(valid - r.cached_rows - 1) * r.stride + (uint32_t)row_bytes;
-    r.k = block_resource((const unsigned char *)p.k_new + first, bytes);
-    r.v = block_resource((const unsigned char *)p.v_new + first, bytes);
-    r.k_old = block_resource(kb, (uint32_t)(r.cached_rows * row_bytes));
-    r.v_old = block_resource(vb, (uint32_t)(r.cached_rows * row_bytes));
-    return r;
+    return block_resource((const unsigned char *)(which ? p.v_new : p.k_new) + first,
+                          (uint32_t)(rows - 1) * new_stride + (uint32_t)row_bytes);
   }
 };
-
-// Append by the attention workgroups: the workgroup of a row tile and key range
-// writes the K/V rows of the tokens whose first packed row lies in its tile and
-// whose position lies in its range - every new row exactly once per kv head.
-template <int D, int NT>
-__device__ __forceinline__ void append_item_rows(const AttnArgs &p, const AttnItem &it, int G, int tile_rows, int tid) {
-  constexpr int CH = D / 8;
-  int lo = (it.row0 + G - 1) / G, hi = (it.row0 + tile_rows + G - 1) / G;
-  if (lo < it.kv_begin - it.prefix) lo = it.kv_begin - it.prefix;
-  if (hi > it.suffix) hi = it.suffix;
-  if (hi > it.kv_end - it.prefix) hi = it.kv_end - it.prefix;
-  const int32_t *bt = p.block_table + (int64_t)it.req * p.max_blocks;
-  const u32x4 *ks = (const u32x4 *)p.k_new, *vs = (const u32x4 *)p.v_new;
-  u32x4 *kd = (u32x4 *)p.k_pool, *vd = (u32x4 *)p.v_pool;
-#pragma unroll 4
-  for (int c = tid; c < (hi - lo) * CH; c += NT) {
-    const int tok = lo + c / CH, ch = c % CH, pos = it.prefix + tok;
-    const int64_t src = ((int64_t)(it.q_off + tok) * p.Hkv + it.kv_head) * CH + ch;
-    const int64_t dst = (((int64_t)bt[pos / kPage] * p.Hkv + it.kv_head) * kPage + pos % kPage) * CH + ch;
-    kd[dst] = ks[src];
-    vd[dst] = vs[src];
-  }
-}
 
 // ---- split-KV partials between workgroups -----------------------------------
 // Slot layout: fp32 O[tile_rows][D], then (m, l) per row.  Written and read with
@@ -226,52 +195,74 @@ __device__ __forceinline__ bool last_of_group(const AttnArgs &p, int group, int 
 
 // out = sum_s e^{(m_s-m)c} O_s / sum_s e^{(m_s-m)c} l_s with m = max_s m_s (the
 // associative log-sum-exp combine of softmax partials) for the rows of one
-// group.  A thread owns four dims of a row.  Bound by the latency of reads that
-// miss every cache, so the partials are taken eight at a time, all their reads
-// in flight together.
-template <int D>
-__device__ __forceinline__ void merge_group(const AttnArgs &p, int group, int G, int tile_rows, int tid, int first_row,
-                                            int row_step) {
+// group from row `begin` up to row `end` of the tile, by a workgroup of
+// `threads`.  A thread owns four dims of R rows.  Bound by the latency of reads
+// that miss the caches, so R x BATCH partials have all their reads in flight
+// together.  SHARED: the partials were written by this very launch.
+template <bool SHARED>
+__device__ __forceinline__ float2 load_part(const float *src) {
+  if constexpr (SHARED) return load_shared(src);
+  else return *reinterpret_cast<const float2 *>(src);
+}
+template <int D, int R, int BATCH, bool SHARED>
+__device__ __forceinline__ void merge_group(const AttnArgs &p, int group, int G, int tile_rows, int tid, int threads,
+                                            int begin, int end) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_;
-  constexpr int TPR = D / 4, BATCH = 8;
-  const ReduceGroup g = p.groups[group];
+  constexpr int TPR = D / 4;
+  const ReduceGroup g = load_group(p.groups, group);
   const size_t slot_f = (size_t)tile_rows * (D + 2);
   const float *base = p.partials + (size_t)g.first_slot * slot_f;
   int n = g.suffix * G - g.row0;
   if (n > tile_rows) n = tile_rows;
-  const int c4 = (tid % TPR) * 4;
-  for (int row = first_row + tid / TPR; row < n; row += row_step) {
-    const float *ml = base + (size_t)tile_rows * D + 2 * row, *po = base + (size_t)row * D + c4;
-    float m = -INFINITY, l = 0.f;
-    f32x4_ acc = {0.f, 0.f, 0.f, 0.f};
+  if (n > end) n = end;
+  const int c4 = (tid % TPR) * 4, step = threads / TPR;
+  for (int row0 = begin + tid / TPR; row0 < n; row0 += R * step) {
+    float m[R], l[R];
+    f32x4_ acc[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      m[k] = -INFINITY;
+      l[k] = 0.f;
+      acc[k] = f32x4_{0.f, 0.f, 0.f, 0.f};
+    }
     for (int s0 = 0; s0 < g.nsplit; s0 += BATCH) {
-      float2 a[BATCH], x[BATCH], y[BATCH];
+      float2 a[R][BATCH], x[R][BATCH], y[R][BATCH];
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i) {
-        const int s = s0 + i < g.nsplit ? s0 + i : g.nsplit - 1;
-        a[i] = load_shared(ml + s * slot_f);
-        x[i] = load_shared(po + s * slot_f);
-        y[i] = load_shared(po + s * slot_f + 2);
+      for (int k = 0; k < R; ++k) {
+        const int row = row0 + k * step < n ? row0 + k * step : n - 1;
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {
+          const float *slot = base + (s0 + i < g.nsplit ? s0 + i : g.nsplit - 1) * slot_f;
+          a[k][i] = load_part<SHARED>(slot + (size_t)tile_rows * D + 2 * row);
+          x[k][i] = load_part<SHARED>(slot + (size_t)row * D + c4);
+          y[k][i] = load_part<SHARED>(slot + (size_t)row * D + c4 + 2);
+        }
       }
-      float m_new = m;
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i) m_new = fmaxf(m_new, a[i].x);
-      const float keep = fast_exp2((m - m_new) * p.scale_log2e);
-      m = m_new;
-      l *= keep;
+      for (int k = 0; k < R; ++k) {
+        float m_new = m[k];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r] *= keep;
+        for (int i = 0; i < BATCH; ++i) m_new = fmaxf(m_new, a[k][i].x);
+        const float keep = fast_exp2((m[k] - m_new) * p.scale_log2e);
+        m[k] = m_new;
+        l[k] *= keep;
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i) {
-        const float w = s0 + i < g.nsplit ? fast_exp2((a[i].x - m) * p.scale_log2e) : 0.f;
-        l += w * a[i].y;
-        acc[0] += w * x[i].x;
-        acc[1] += w * x[i].y;
-        acc[2] += w * y[i].x;
-        acc[3] += w * y[i].y;
+        for (int r = 0; r < 4; ++r) acc[k][r] *= keep;
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {
+          const float w = s0 + i < g.nsplit ? fast_exp2((a[k][i].x - m_new) * p.scale_log2e) : 0.f;
+          l[k] += w * a[k][i].y;
+          acc[k][0] += w * x[k][i].x;
+          acc[k][1] += w * x[k][i].y;
+          acc[k][2] += w * y[k][i].x;
+          acc[k][3] += w * y[k][i].y;
+        }
       }
     }
-    store_out_row<D>(p, g.q_off, g.kv_head, G, g.row0 + row, c4, acc, 1.0f / l);
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+      if (row0 + k * step < n)
+        store_out_row<D>(p, g.q_off, g.kv_head, G, g.row0 + row0 + k * step, c4, acc[k], 1.0f / l[k]);
   }
 }
 

@@ -90,15 +90,12 @@ int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_po
 // --------------------------------------------------------------------------
 
 template <int D, int RB, int NW, int WPE, int NS>
-__global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
-    const __bf16 *__restrict__ q, const __bf16 *__restrict__ k_pool,
-    const __bf16 *__restrict__ v_pool, const int32_t *__restrict__ block_table,
-    __bf16 *__restrict__ out, float *__restrict__ partials, const AttnItem *__restrict__ items,
-    int Hq, int Hkv, int max_blocks, float scale_log2e) {
+__global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnArgs p) {
   constexpr int BN = kTileKeys;
   constexpr int NT = NW * 64;
   constexpr int BM = NW * 32 * RB;
   constexpr int CPR = D / 8;                     // 16-byte chunks per key row
+  constexpr int ROW = D * 2;                     // bytes per key row
   constexpr int TILE_BYTES = BN * D * 2;
   constexpr int UNITS = TILE_BYTES / 1024;       // wave-wide 1 KB copies per tile (K or V)
   constexpr int KPU = 1024 / (D * 2);            // keys per copy
@@ -115,11 +112,13 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   static_assert(NS >= 2, "each ring needs the slot in use and one being filled");
   // byte offsets of the ring slots that hold tile t
-  auto k_slot = [&](int t) -> uint32_t { return (uint32_t)(t % NS) * TILE_BYTES; };
-  auto v_slot = [&](int t) -> uint32_t { return (uint32_t)(NS + t % NS) * TILE_BYTES; };
+  auto k_slot = [&](int t) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(t % NS) * TILE_BYTES; };
+  auto v_slot = [&](int t) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(NS + t % NS) * TILE_BYTES; };
 
-  const AttnItem it = items[blockIdx.x];
+  const AttnItem it = load_item(p.items, blockIdx.x);
   if (it.req < 0) return;                        // idle padding entry
+  const int Hq = p.Hq, Hkv = p.Hkv;
+  const float scale_log2e = p.scale_log2e;
   const int G = Hq / Hkv;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   const int rows_total = S * G;
   const int T = P + S;
   const int nblk = (T + kPage - 1) / kPage;
-  const int32_t *bt = block_table + (int64_t)it.req * max_blocks;
+  const ConstantPtr<int32_t> bt = constant_ptr(p.block_table + (int64_t)it.req * p.max_blocks);
 
   // ---- Q fragments (B operand of S^T): lane holds row l32, dims 16kk+8hh..+7
   const int wrow0 = it.row0 + wave * (32 * RB);
@@ -143,7 +142,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     const int tok = valid ? row / G : 0;
     const int g = valid ? row % G : 0;
     limit[rb] = valid ? P + tok : -1;
-    const __bf16 *qp = q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G + g) * D + 8 * hh;
+    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G + g) * D + 8 * hh;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       bf16x8 v = {};
@@ -190,48 +189,105 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   // (page, head) block as long as possible so a wave needs few page ids.
   // Lane l fills LDS slot (row l/CPR, chunk l%CPR) of the unit and therefore
   // fetches chunk (l%CPR) ^ swz(row).
-  const int64_t head_off = (int64_t)it.kv_head * (kPage * D * 2);
-  const int64_t page_stride = (int64_t)Hkv * (kPage * D * 2);
-  uint32_t lane_src[UPW];                         // byte offset inside the (page, head) block
+  const PageSource src(p, it, ROW);
+  const int wave_blk = (wave * UPW) / UPP;        // first page of a tile this wave copies from
+  constexpr int NL = UPW < UPP ? UPW : UPP;       // copies repeat with the page
+  uint32_t lane_old[NL], lane_new[NL];            // byte offset of the lane's chunk: pool block / packed rows
+  auto lane_row = [&](int i) __attribute__((always_inline)) -> int {             // the page's row that copy i of this lane fetches
+    return (((UPW < UPP ? wave * UPW : 0) + i % NL) * KPU + lane / CPR) % kPage;
+  };
 #pragma unroll
-  for (int i = 0; i < UPW; ++i) {
-    const int key = (wave * UPW + i) * KPU + lane / CPR;   // key inside the tile
-    lane_src[i] = (uint32_t)((key % kPage) * (D * 2) + (((lane % CPR) ^ swz<D>(key)) << 4));
+  for (int i = 0; i < NL; ++i) {
+    const uint32_t chunk = (uint32_t)(((lane % CPR) ^ swz<D>(lane_row(i))) << 4);
+    lane_old[i] = (uint32_t)(lane_row(i) * ROW) + chunk;
+    lane_new[i] = (uint32_t)lane_row(i) * src.new_stride + chunk;
   }
   const uint32_t lds_base = lds_address(lds);
-  const int wave_blk = (wave * UPW) / UPP;        // first page of a tile this wave copies from
   struct PageIds {
     int32_t p[PPW];
   };
-  auto pages_of = [&](int t) -> PageIds {         // page ids of tile t for this wave
+  auto blk_of = [&](int t, int j) __attribute__((always_inline)) -> int {        // page j of tile t that this wave copies, inside the sequence
+    const int blk = (kv_begin + t * BN) / kPage + wave_blk + j;
+    return blk > nblk - 1 ? nblk - 1 : blk;
+  };
+  auto pages_of = [&](int t) __attribute__((always_inline)) -> PageIds {         // its page ids
     PageIds r;
 #pragma unroll
-    for (int j = 0; j < PPW; ++j) {
-      int blk = (kv_begin + t * BN) / kPage + wave_blk + j;
-      if (blk > nblk - 1) blk = nblk - 1;         // never read a table entry past the sequence
-      r.p[j] = bt[blk];
-    }
+    for (int j = 0; j < PPW; ++j) r.p[j] = bt[blk_of(t, j)];
     return r;
   };
-  auto copy_rows = [&](const void *pool, int which, int slot, const PageIds &pg) {
+  // This wave's share of tile t into a ring slot, wherever its rows come from.
+  auto copy_rows = [&](int which, int slot, int t, const PageIds &pg) __attribute__((always_inline)) {
+    static_for<0, PPW>([&](auto jt) __attribute__((always_inline)) {
+      constexpr int j = decltype(jt)::value;
+      const int blk = blk_of(t, j), pos0 = blk * kPage;
+      const uint32_t to = lds_base + (uint32_t)((which * NS + slot) * TILE_BYTES + (wave * UPW + j * NL) * 1024);
+      if (pos0 + kPage <= src.first_new) {
+        const i32x4 rows = src.old_rows(which, pg.p[j]);
 #pragma unroll
-    for (int i = 0; i < UPW; ++i) {
-      const int u = wave * UPW + i;
-      const unsigned char *blk =                                      // wave-uniform
-          (const unsigned char *)pool + (int64_t)pg.p[i / UPP] * page_stride + head_off;
-      copy16_to_lds(block_resource(blk, kPage * D * 2), lane_src[i],
-                    lds_base + (uint32_t)((which * NS + slot) * TILE_BYTES + u * 1024));
-    }
+        for (int l = 0; l < NL; ++l) copy16_to_lds(rows, lane_old[l], to + (uint32_t)(l * 1024));
+      } else if (pos0 >= src.first_new) {
+        const i32x4 rows = src.new_rows(which, pos0 - P);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) copy16_to_lds(rows, lane_new[l], to + (uint32_t)(l * 1024));
+      } else {                                     // the page where the cached prefix ends: rows from both
+        const int cached = P - pos0;
+        const i32x4 rows_old = src.old_rows(which, pg.p[j]), rows_new = src.new_rows(which, 0, kPage - cached);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          if (lane_row(l) < cached) copy16_to_lds(rows_old, lane_old[l], to + (uint32_t)(l * 1024));
+          else copy16_to_lds(rows_new, lane_new[l] - (uint32_t)cached * src.new_stride, to + (uint32_t)(l * 1024));
+        }
+      }
+    });
+  };
+
+  // ---- append: new rows are written to their pages straight from the ring
+  // slots they were copied into.  The workgroup owns the tokens whose first
+  // packed row lies in its row tile and whose position lies in its key range -
+  // every new row once per kv head - and they all lie in the tiles of the last
+  // loop below, each wave writing the rows it copied.  (As a copy of its own at
+  // the end of the workgroup, global to global, the same bytes cost 0.35 ms of
+  // 3.6 ms on 92 765 new tokens x 40 heads: its load latency is not covered.)
+  int own_lo = 0x7fffffff, own_hi = 0x7fffffff;   // positions
+  if (p.k_new) {
+    own_lo = P + (it.row0 + G - 1) / G;
+    own_hi = P + (it.row0 + BM + G - 1) / G;
+    if (own_hi > T) own_hi = T;
+    if (own_hi > kv_end) own_hi = kv_end;
+  }
+  auto write_rows = [&](int which, uint32_t slot_off, int t) __attribute__((always_inline)) {
+    static_for<0, PPW>([&](auto jt) __attribute__((always_inline)) {
+      constexpr int j = decltype(jt)::value;
+      const int pos0 = kv_begin + t * BN + (wave_blk + j) * kPage;
+      if (pos0 + kPage <= own_lo || pos0 >= own_hi) return;
+      unsigned char *block = (unsigned char *)(which ? p.v_pool : p.k_pool) + src.block_of(bt[pos0 / kPage]);
+      u32x4 data[NL];
+#pragma unroll
+      for (int l = 0; l < NL; ++l)
+        data[l] = *(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)(
+            lds_base + slot_off + (uint32_t)((wave * UPW + j * NL + l) * 1024 + lane * 16));
+#pragma unroll
+      for (int l = 0; l < NL; ++l)
+        if (pos0 + lane_row(l) >= own_lo && pos0 + lane_row(l) < own_hi)
+          *reinterpret_cast<u32x4 *>(block + lane_old[l]) = data[l];
+    });
+  };
+  auto append_tile = [&](int t) __attribute__((always_inline)) {   // K and V of tile t are in their slots
+    if (kv_begin + (t + 1) * BN <= own_lo) return;
+    write_rows(0, k_slot(t), t);
+    write_rows(1, v_slot(t), t);
+    wait_lds_reads();                             // before K of a later tile is copied over it
   };
 
   PageIds pg_v, pg_k;                             // page ids of tiles t+NS-1 and t+NS
-  // copy i (0 .. UPW-1) of this wave's share of a tile, as one instruction
-  auto copy_one = [&](const void *pool, int which, int slot, const PageIds &pg, auto it_) __attribute__((always_inline)) {
-    constexpr int i = decltype(it_)::value;
-    const int u = wave * UPW + i;
-    const unsigned char *blk = (const unsigned char *)pool + (int64_t)pg.p[i / UPP] * page_stride + head_off;
-    copy16_to_lds(block_resource(blk, kPage * D * 2), lane_src[i],
-                  lds_base + (uint32_t)((which * NS + slot) * TILE_BYTES + u * 1024));
+  // Copy i (0 .. UPW-1) of this wave's share of a tile whose pages are all
+  // cached, or all new: one instruction, its descriptor from scalar registers.
+  auto copy_one = [&](int which, int slot, int t, const PageIds &pg, auto new_tag, auto it_) __attribute__((always_inline)) {
+    constexpr int i = decltype(it_)::value, j = i / UPP;
+    const uint32_t to = lds_base + (uint32_t)((which * NS + slot) * TILE_BYTES + (wave * UPW + i) * 1024);
+    if constexpr (decltype(new_tag)::value) copy16_to_lds(src.new_rows(which, blk_of(t, j) * kPage - P), lane_new[i % NL], to);
+    else copy16_to_lds(src.old_rows(which, pg.p[j]), lane_old[i % NL], to);
   };
   const int i16 = lane & 15;
   const int grp = (lane >> 4) & 1;
@@ -255,13 +311,13 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   }
   // K fragment i (0 .. KB*KK-1) of the tile in K ring slot at byte offset
   // slot_off: rows kb*32+l32, dims 16kk+8hh..+7
-  auto k_frag = [&](uint32_t slot_off, int i) -> bf16x8 {
+  auto k_frag = [&](uint32_t slot_off, int i) __attribute__((always_inline)) -> bf16x8 {
     return *(lds_b128_ptr)(uintptr_t)(k_lane[i % KK] + slot_off + (uint32_t)((i / KK) * 32 * D * 2));
   };
   // V^T fragment j (0 .. KS*DB-1): head dims 32db+l32, keys of k-step ks.
   // Transposing read: within 16 lanes, lane i supplies the address of 4 head
   // dims 4*(i%4).. of key (i/4); it receives 4 keys of head dim i.
-  auto v_frag = [&](uint32_t slot_off, int j) -> bf16x8 {
+  auto v_frag = [&](uint32_t slot_off, int j) __attribute__((always_inline)) -> bf16x8 {
     const int ks = j / DB, db = j % DB;
     const uint32_t step_off = slot_off + (uint32_t)(ks * 16 * D * 2);
     union {
@@ -272,7 +328,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     a.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(uintptr_t)(v_lane[db][1] + step_off));
     return a.v;
   };
-  auto mask_tile = [&](f32x16 (&sx)[KB][RB], int key0) {
+  auto mask_tile = [&](f32x16 (&sx)[KB][RB], int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -288,7 +344,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   // Only when some score of the wave exceeds its bound do the two lanes of a
   // row exchange maxima, raise the running maximum and rescale what has been
   // accumulated.
-  auto raise_max = [&](const f32x16 (&sx)[KB][RB]) {
+  auto raise_max = [&](const f32x16 (&sx)[KB][RB]) __attribute__((always_inline)) {
     float mx[RB];
     bool grow = false;
 #pragma unroll
@@ -318,7 +374,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     }
   };
   // P^T fragment of k-step ks from the scores (exp2, row sums, bf16 rounding)
-  auto p_frag = [&](const f32x16 (&sx)[KB][RB], int ks, int rb, float mc) -> bf16x8 {
+  auto p_frag = [&](const f32x16 (&sx)[KB][RB], int ks, int rb, float mc) __attribute__((always_inline)) -> bf16x8 {
     bf16x8 pf;
     float sum = 0.f;
 #pragma unroll
@@ -333,7 +389,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
 
   // Scores of one tile, not overlapped with anything (first tile, and tiles
   // that need the causal mask).
-  auto plain_scores = [&](f32x16 (&sx)[KB][RB], uint32_t k_lds, int key0, bool masked) {
+  auto plain_scores = [&](f32x16 (&sx)[KB][RB], uint32_t k_lds, int key0, bool masked) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -352,7 +408,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   };
   // Softmax and O^T update of the current tile, nothing overlapped (tiles on
   // the causal diagonal and the last tile).
-  auto tail_step = [&](f32x16 (&sc)[KB][RB], uint32_t v_cur) {
+  auto tail_step = [&](f32x16 (&sc)[KB][RB], uint32_t v_cur) __attribute__((always_inline)) {
     float mc[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) mc[rb] = m_run[rb] * scale_log2e;
@@ -387,8 +443,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   constexpr int LA = 3;                           // fragment reads run this many fragments ahead
   constexpr int NCH = (NQK + NPV) * RB;           // chunks (= MFMAs) per step
   constexpr int CSPAN = (NQK + (KS - 1) * DB) * RB;   // chunks over which the exponentials spread
-  auto step = [&](f32x16 (&sc)[KB][RB], f32x16 (&sn)[KB][RB], uint32_t k_next, uint32_t v_cur,
-                  int next_key0, auto mask_tag, auto vslot_tag, auto kslot_tag) __attribute__((always_inline)) {
+  auto step = [&](f32x16 (&sc)[KB][RB], f32x16 (&sn)[KB][RB], uint32_t k_next, uint32_t v_cur, int t,
+                  auto mask_tag, auto vslot_tag, auto kslot_tag, auto new_tag) __attribute__((always_inline)) {
     constexpr int VSLOT = decltype(vslot_tag)::value, KSLOT = decltype(kslot_tag)::value;
     constexpr int NC = 2 * UPW;
     constexpr int STRIDE = 2 * NC <= NCH ? 2 : 1;   // every other chunk from the start of the step
@@ -406,7 +462,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) sn[kb][rb][r] = 0.f;
-    auto fetch = [&](int i) {                     // fragment i of the chain: K first, then V^T
+    auto fetch = [&](int i) __attribute__((always_inline)) {                     // fragment i of the chain: K first, then V^T
       if (i < NQK) frag[i % (LA + 1)] = k_frag(k_next, i);
       else if (i < NQK + NPV) frag[i % (LA + 1)] = v_frag(v_cur, i - NQK);
     };
@@ -422,7 +478,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     // the tolerance.
     constexpr int NX = NEL * RB;
     auto home = [](int x) { return 1 + (x * (CSPAN - 2)) / NX; };
-    auto softmax_slice = [&](int c) {
+    auto softmax_slice = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
       for (int x = 0; x < NX; ++x) {
         const int ks = x / (8 * RB), rb = (x / 8) % RB, e8 = x % 8;
@@ -445,8 +501,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
       static_for<0, NC>([&](auto kt) __attribute__((always_inline)) {
         constexpr int k = decltype(kt)::value;
         if (c == k * STRIDE + STRIDE - 1) {
-          if constexpr (k < UPW) copy_one(v_pool, 1, VSLOT, pg_v, std::integral_constant<int, k>{});
-          else copy_one(k_pool, 0, KSLOT, pg_k, std::integral_constant<int, k - UPW>{});
+          if constexpr (k < UPW) copy_one(1, VSLOT, t + NS - 1, pg_v, new_tag, std::integral_constant<int, k>{});
+          else copy_one(0, KSLOT, t + NS, pg_k, new_tag, std::integral_constant<int, k - UPW>{});
         }
       });
     };
@@ -470,7 +526,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     });
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) l_run[rb] += sum_even[rb] + sum_odd[rb];
-    if (decltype(mask_tag)::value) mask_tile(sn, next_key0);   // the next tile touches the diagonal
+    if (decltype(mask_tag)::value) mask_tile(sn, kv_begin + (t + 1) * BN);   // the next tile touches the diagonal
     raise_max(sn);
   };
 
@@ -485,13 +541,13 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   // free slot and are never used: that keeps the pending count uniform.
   constexpr int PENDING_OK = 2 * (NS - 2) * UPW;
   static_assert((2 * NS - 2) * UPW <= 63, "pending copies must fit the vmcnt counter");
-  auto wait_pending = [&](auto n_tag) {
+  auto wait_pending = [&](auto n_tag) __attribute__((always_inline)) {
     constexpr int n = decltype(n_tag)::value;
     __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));   // vmcnt(n) only
   };
   const bool wave_live = my_nt > 0;
   f32x16 s_a[KB][RB], s_b[KB][RB];
-  if (nt > 0) copy_rows(k_pool, 0, 0, pages_of(0));
+  if (nt > 0) copy_rows(0, 0, 0, pages_of(0));
   if constexpr (NS > 2) {
     // With rings deeper than two slots copies stay in flight across
     // iterations.  The compiler cannot count them (they are inline assembly),
@@ -507,15 +563,15 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   }
   if (nt > 0) {
     PageIds pg = pages_of(0);
-    copy_rows(v_pool, 1, 0, pg);
+    copy_rows(1, 0, 0, pg);
     pg = pages_of(1);
 #pragma unroll
     for (int j = 1; j < NS - 1; ++j) {
-      copy_rows(k_pool, 0, j, pg);
-      copy_rows(v_pool, 1, j, pg);
+      copy_rows(0, j, j, pg);
+      copy_rows(1, j, j, pg);
       pg = pages_of(j + 1);
     }
-    copy_rows(k_pool, 0, NS - 1, pg);
+    copy_rows(0, NS - 1, NS - 1, pg);
     pg_v = pg;
     pg_k = pages_of(NS);
     wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
@@ -524,13 +580,13 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   }
   // j is the tile index modulo NS, known at compile time in the fast loop so
   // that every LDS address there is a register plus an immediate.
-  auto issue_copies = [&](int v_ring_slot, int k_ring_slot, int t) {
-    copy_rows(v_pool, 1, v_ring_slot, pg_v);
-    copy_rows(k_pool, 0, k_ring_slot, pg_k);
+  auto issue_copies = [&](int v_ring_slot, int k_ring_slot, int t) __attribute__((always_inline)) {
+    copy_rows(1, v_ring_slot, t + NS - 1, pg_v);
+    copy_rows(0, k_ring_slot, t + NS, pg_k);
     pg_v = pg_k;
     pg_k = pages_of(t + NS + 1);
   };
-  auto arrive = [&]() {
+  auto arrive = [&]() __attribute__((always_inline)) {
     wait_pending(std::integral_constant<int, PENDING_OK>{});   // this wave's part has landed
     __syncthreads();                              // everyone's has; the previous iteration is over
   };
@@ -545,45 +601,68 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     if (n_fast > nt - 1) n_fast = nt - 1;
     if (n_fast < 0) n_fast = 0;
   }
-  auto fast_iteration = [&](int t, auto j_tag) __attribute__((always_inline)) {
-    constexpr int j = decltype(j_tag)::value;
+  // How an iteration gets its copies: all pages cached, all new, or whichever
+  // they are.  The first two are single instructions between the chunks of the
+  // step; the last, for the few iterations around the end of the cached prefix,
+  // is a burst before it.
+  enum { kOld, kNew, kAny };
+  auto fast_iteration = [&](int t, auto j_tag, auto from_tag) __attribute__((always_inline)) {
+    constexpr int j = decltype(j_tag)::value, FROM = decltype(from_tag)::value;
     static_assert(NS % 2 == 0, "score buffers alternate with the tile parity");
     constexpr uint32_t k_next = (uint32_t)((j + 1) % NS) * TILE_BYTES;
     constexpr uint32_t v_cur = (uint32_t)(NS + j) * TILE_BYTES;
+    constexpr int VSLOT = (j + NS - 1) % NS, KSLOT = j;
     arrive();
-    if (wave_live) {
-      // the step issues this iteration's copies itself, between its chunks
-      using VSlot = std::integral_constant<int, (j + NS - 1) % NS>;
-      using KSlot = std::integral_constant<int, j>;
-      if (j % 2 == 0) step(s_a, s_b, k_next, v_cur, 0, std::false_type{}, VSlot{}, KSlot{});
-      else step(s_b, s_a, k_next, v_cur, 0, std::false_type{}, VSlot{}, KSlot{});
+    if constexpr (FROM == kAny) issue_copies(VSLOT, KSLOT, t);
+    using VSlot = std::integral_constant<int, FROM == kAny ? -1 : VSLOT>;
+    using KSlot = std::integral_constant<int, FROM == kAny ? -1 : KSLOT>;
+    using New = std::integral_constant<bool, FROM == kNew>;
+    if (j % 2 == 0) step(s_a, s_b, k_next, v_cur, t, std::false_type{}, VSlot{}, KSlot{}, New{});
+    else step(s_b, s_a, k_next, v_cur, t, std::false_type{}, VSlot{}, KSlot{}, New{});
+    if constexpr (FROM == kOld) {
       pg_v = pg_k;
       pg_k = pages_of(t + NS + 1);
-    } else {
-      issue_copies((j + NS - 1) % NS, j, t);      // a wave with no rows left only copies
     }
   };
   static_assert(NS == 2 || NS == 4, "the loop is unrolled for rings of 2 or 4 slots");
   int t = 0;
-  for (; t + NS <= n_fast; t += NS) {
-    fast_iteration(t, std::integral_constant<int, 0>{});
-    fast_iteration(t + 1, std::integral_constant<int, 1>{});
-    if (NS > 2) {
-      fast_iteration(t + 2, std::integral_constant<int, 2 % NS>{});
-      fast_iteration(t + 3, std::integral_constant<int, 3 % NS>{});
+  auto fast_loop = [&](int end, auto from_tag) __attribute__((always_inline)) {
+    for (; t + NS <= end; t += NS) {
+      fast_iteration(t, std::integral_constant<int, 0>{}, from_tag);
+      fast_iteration(t + 1, std::integral_constant<int, 1>{}, from_tag);
+      if (NS > 2) {
+        fast_iteration(t + 2, std::integral_constant<int, 2 % NS>{}, from_tag);
+        fast_iteration(t + 3, std::integral_constant<int, 3 % NS>{}, from_tag);
+      }
     }
-  }
-  // The tiles up to the causal diagonal (and a few left over from the loop
-  // above): the same overlapped step with the causal mask applied to the new
-  // scores, ring slots chosen at run time, scores handed back in s_a.  (A wave
-  // whose rows end early computes fully masked tiles until the workgroup's key
-  // range ends - at most two - and they add exact zeros.)
-  for (; t + 1 < nt; ++t) {
-    arrive();
-    issue_copies((t + NS - 1) % NS, t % NS, t);
-    if (wave_live) {
-      step(s_a, s_b, k_slot(t + 1), v_slot(t), kv_begin + (t + 1) * BN, std::true_type{},
-           std::integral_constant<int, -1>{}, std::integral_constant<int, -1>{});
+  };
+  if (!wave_live) {                               // a wave without rows only copies
+    for (; t + 1 < nt; ++t) {
+      arrive();
+      append_tile(t);
+      issue_copies((t + NS - 1) % NS, t % NS, t);
+    }
+  } else {
+    // Tiles below all_old hold cached keys only, tiles from all_new on new keys
+    // only (when the pools hold everything already, every tile counts as cached).
+    const int all_old = p.k_new ? (P > kv_begin ? (P - kv_begin) / BN : 0) : nt + 2 * NS;
+    const int all_new = p.k_new ? (P > kv_begin ? (P - kv_begin + BN - 1) / BN : 0) : nt + 2 * NS;
+    // an iteration copies V of tile t+NS-1 and K of tile t+NS
+    fast_loop(all_old - NS < n_fast ? all_old - NS : n_fast, std::integral_constant<int, kOld>{});
+    const int mixed_end = all_new;                // = (first iteration that copies new keys only) + NS-1
+    fast_loop(mixed_end < n_fast ? mixed_end : n_fast, std::integral_constant<int, kAny>{});
+    fast_loop(n_fast, std::integral_constant<int, kNew>{});
+    // The tiles up to the causal diagonal (and a few left over from the loops
+    // above): the same overlapped step with the causal mask applied to the new
+    // scores, ring slots chosen at run time, scores handed back in s_a.  (A wave
+    // whose rows end early computes fully masked tiles until the workgroup's key
+    // range ends - at most two - and they add exact zeros.)
+    for (; t + 1 < nt; ++t) {
+      arrive();
+      append_tile(t);
+      issue_copies((t + NS - 1) % NS, t % NS, t);
+      step(s_a, s_b, k_slot(t + 1), v_slot(t), t, std::true_type{}, std::integral_constant<int, -1>{},
+           std::integral_constant<int, -1>{}, std::false_type{});
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -593,7 +672,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
   if (nt > 0) {                                   // the last tile: softmax and PV only
     const uint32_t v_cur = v_slot(t);
     arrive();
-    if (kv_begin + nt * BN > T) {
+    append_tile(t);
+    if (!p.k_new && kv_begin + nt * BN > T) {
       // Slots past the end of the sequence hold whatever the pool held: clear
       // those V rows so that 0 * garbage cannot poison the products.
       for (int c = tid; c < BN * CPR; c += NT)
@@ -615,7 +695,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
     if (it.part_slot < 0) {
       const float inv = 1.0f / l_tot;
       const int tok = row / G, g = row % G;
-      __bf16 *op = out + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G + g) * D;
+      __bf16 *op = (__bf16 *)p.out + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G + g) * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -626,7 +706,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
           *reinterpret_cast<bf16x4 *>(op + 32 * db + 8 * g4 + 4 * hh) = o4;
         }
     } else {
-      float *slot = partials + (size_t)it.part_slot * ((size_t)BM * (D + 2));
+      float *slot = p.partials + (size_t)it.part_slot * ((size_t)BM * (D + 2));
       const int lr = row - it.row0;
       float *po = slot + (size_t)lr * D;
 #pragma unroll
@@ -640,61 +720,25 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(
           o4.w = oacc[db][rb][4 * g4 + 3];
           *reinterpret_cast<float4 *>(po + 32 * db + 8 * g4 + 4 * hh) = o4;
         }
-      if (hh == 0) {
-        slot[(size_t)BM * D + 2 * lr] = m_run[rb];
-        slot[(size_t)BM * D + 2 * lr + 1] = l_tot;
-      }
+      if (hh == 0) *reinterpret_cast<float2 *>(slot + (size_t)BM * D + 2 * lr) = make_float2(m_run[rb], l_tot);
     }
   }
 }
 
 // --------------------------------------------------------------------------
-// Split-KV merge: out = sum_s e^{(m_s-m)c} O_s / sum_s e^{(m_s-m)c} l_s with
-// m = max_s m_s (the associative log-sum-exp combine of softmax partials).
-// One workgroup of D/4 x ROWS threads merges ROWS rows; a thread owns 4 dims.
+// Split-KV merge for the row tiles of the prefill kernels (64 rows and more;
+// the key-splitting kernel merges its few rows itself).  A merge inside the
+// attention kernel was 40 us slower on 8 requests x 16k-32k keys: partials of
+// 64 KB have to be written through to memory, and one workgroup then reads
+// hundreds of KB while its CU half idles.  Here a thread takes four dims of two
+// rows, up to four partials of each in flight at once.
 // --------------------------------------------------------------------------
+constexpr int kReduceRows = 2;                    // rows per thread
 template <int D>
-__global__ __launch_bounds__(256) void split_reduce_kernel(
-    const float *__restrict__ partials, __bf16 *__restrict__ out,
-    const ReduceGroup *__restrict__ groups, int tile_rows, int Hq, int Hkv, float scale_log2e) {
-  constexpr int TPR = D / 4;                      // threads per row
-  constexpr int ROWS = 256 / TPR;
-  const ReduceGroup g = groups[blockIdx.x];
-  const int G = Hq / Hkv;
-  const int rows_total = g.suffix * G;
-  const int lr = blockIdx.y * ROWS + threadIdx.x / TPR;
-  const int c4 = (threadIdx.x % TPR) * 4;
-  const int row = g.row0 + lr;
-  if (lr >= tile_rows || row >= rows_total) return;
-  const size_t slot_f = (size_t)tile_rows * (D + 2);
-  float m = -INFINITY;
-  for (int s = 0; s < g.nsplit; ++s) {
-    const float *slot = partials + (size_t)(g.first_slot + s) * slot_f;
-    m = fmaxf(m, slot[(size_t)tile_rows * D + 2 * lr]);
-  }
-  float l = 0.f;
-  float4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < g.nsplit; ++s) {
-    const float *slot = partials + (size_t)(g.first_slot + s) * slot_f;
-    const float ms = slot[(size_t)tile_rows * D + 2 * lr];
-    const float ls = slot[(size_t)tile_rows * D + 2 * lr + 1];
-    const float w = fast_exp2((ms - m) * scale_log2e);
-    const float4 o = *reinterpret_cast<const float4 *>(slot + (size_t)lr * D + c4);
-    l += w * ls;
-    acc.x += w * o.x;
-    acc.y += w * o.y;
-    acc.z += w * o.z;
-    acc.w += w * o.w;
-  }
-  const float inv = 1.0f / l;
-  const int tok = row / G, gi = row % G;
-  __bf16 *op = out + ((int64_t)(g.q_off + tok) * Hq + g.kv_head * G + gi) * D + c4;
-  bf16x4 o4;
-  o4[0] = (__bf16)(acc.x * inv);
-  o4[1] = (__bf16)(acc.y * inv);
-  o4[2] = (__bf16)(acc.z * inv);
-  o4[3] = (__bf16)(acc.w * inv);
-  *reinterpret_cast<bf16x4 *>(op) = o4;
+__global__ __launch_bounds__(256) void split_reduce_kernel(const AttnArgs p, int tile_rows) {
+  constexpr int ROWS = 256 / (D / 4) * kReduceRows;
+  merge_group<D, kReduceRows, 4, false>(p, blockIdx.x, p.Hq / p.Hkv, tile_rows, threadIdx.x, 256, blockIdx.y * ROWS,
+                                        (blockIdx.y + 1) * ROWS);
 }
 
 template <int D, int RB, int NW, int WPE, int NS>
@@ -704,10 +748,7 @@ static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute(
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (attr != hipSuccess) return (int)attr;
-  return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st,
-                       (const __bf16 *)p.args.q, (const __bf16 *)p.args.k_pool, (const __bf16 *)p.args.v_pool,
-                       p.args.block_table, (__bf16 *)p.args.out, p.args.partials, p.args.items, p.args.Hq, p.args.Hkv,
-                       p.args.max_blocks, p.args.scale_log2e);
+  return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st, p.args);
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot
@@ -729,18 +770,10 @@ int launch_attention(const LaunchParams &p, void *stream) {
 
 int launch_reduce(const LaunchParams &p, void *stream) {
   if (p.num_groups == 0) return 0;
-  hipStream_t st = (hipStream_t)stream;
-  if (p.d == 128) {
-    dim3 grid((unsigned)p.num_groups, (unsigned)((p.tile_rows + 7) / 8));
-    return launch_kernel(split_reduce_kernel<128>, grid, dim3(256), 0, st, (const float *)p.args.partials,
-                         (__bf16 *)p.args.out, (const ReduceGroup *)p.args.groups, p.tile_rows, p.args.Hq, p.args.Hkv,
-                         p.args.scale_log2e);
-  } else {
-    dim3 grid((unsigned)p.num_groups, (unsigned)((p.tile_rows + 15) / 16));
-    return launch_kernel(split_reduce_kernel<64>, grid, dim3(256), 0, st, (const float *)p.args.partials,
-                         (__bf16 *)p.args.out, (const ReduceGroup *)p.args.groups, p.tile_rows, p.args.Hq, p.args.Hkv,
-                         p.args.scale_log2e);
-  }
+  const int rows = 256 / (p.d / 4) * kReduceRows;
+  const dim3 grid((unsigned)p.num_groups, (unsigned)((p.tile_rows + rows - 1) / rows));
+  return launch_kernel(p.d == 128 ? split_reduce_kernel<128> : split_reduce_kernel<64>, grid, dim3(256), 0,
+                       (hipStream_t)stream, p.args, p.tile_rows);
 }
 
 // --------------------------------------------------------------------------

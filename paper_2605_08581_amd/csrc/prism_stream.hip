@@ -123,28 +123,63 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
 #pragma unroll
     for (int pg = 0; pg < 2; ++pg) {
       const int blk = key0 / kPage + pg;
-      const PageRows a = src.rows(blk < last_blk ? blk : last_blk, pages.p[pg]);
+      const int pos0 = (blk < last_blk ? blk : last_blk) * kPage;
       const uint32_t dst = lds_base + (uint32_t)(slot * Shape::kTileBytes + pg * kPage * ROW);
-      if (a.cached_rows == 0 || a.cached_rows == kPage) {
+      const int cached = src.first_new - pos0;   // rows of the page that come from the pool
+      if (cached >= kPage) {
+        const int valid = T - pos0 < kPage ? T - pos0 : kPage;   // the last page may hold anything past the sequence
+        const i32x4 rk = src.old_rows(0, pages.p[pg], valid), rv = src.old_rows(1, pages.p[pg], valid);
 #pragma unroll
         for (int i = 0; i < UPP; ++i) {
-          const uint32_t off = (uint32_t)(i * KPU + lane_row) * a.stride + lane_chunk[i];
-          copy16_to_lds(a.k, off, dst + (uint32_t)(i * 1024));
-          copy16_to_lds(a.v, off, dst + (uint32_t)(TK * ROW + i * 1024));
+          const uint32_t off = (uint32_t)((i * KPU + lane_row) * ROW) + lane_chunk[i];
+          copy16_to_lds(rk, off, dst + (uint32_t)(i * 1024));
+          copy16_to_lds(rv, off, dst + (uint32_t)(TK * ROW + i * 1024));
+        }
+      } else if (cached <= 0) {
+        const i32x4 rk = src.new_rows(0, pos0 - P), rv = src.new_rows(1, pos0 - P);
+#pragma unroll
+        for (int i = 0; i < UPP; ++i) {
+          const uint32_t off = (uint32_t)(i * KPU + lane_row) * src.new_stride + lane_chunk[i];
+          copy16_to_lds(rk, off, dst + (uint32_t)(i * 1024));
+          copy16_to_lds(rv, off, dst + (uint32_t)(TK * ROW + i * 1024));
         }
       } else {                                   // the page where the cached prefix ends: its rows come from both
+        const i32x4 ok = src.old_rows(0, pages.p[pg]), ov = src.old_rows(1, pages.p[pg]);
+        const i32x4 nk = src.new_rows(0, 0, kPage - cached), nv = src.new_rows(1, 0, kPage - cached);
 #pragma unroll
         for (int i = 0; i < UPP; ++i) {
           const int row = i * KPU + lane_row;
-          const uint32_t off = (uint32_t)row * ROW + lane_chunk[i];
-          if (row < a.cached_rows) {
-            copy16_to_lds(a.k_old, off, dst + (uint32_t)(i * 1024));
-            copy16_to_lds(a.v_old, off, dst + (uint32_t)(TK * ROW + i * 1024));
+          if (row < cached) {
+            const uint32_t off = (uint32_t)(row * ROW) + lane_chunk[i];
+            copy16_to_lds(ok, off, dst + (uint32_t)(i * 1024));
+            copy16_to_lds(ov, off, dst + (uint32_t)(TK * ROW + i * 1024));
           } else {
-            const uint32_t off_new = (uint32_t)(row - a.cached_rows) * a.stride + lane_chunk[i];
-            copy16_to_lds(a.k, off_new, dst + (uint32_t)(i * 1024));
-            copy16_to_lds(a.v, off_new, dst + (uint32_t)(TK * ROW + i * 1024));
+            const uint32_t off = (uint32_t)(row - cached) * src.new_stride + lane_chunk[i];
+            copy16_to_lds(nk, off, dst + (uint32_t)(i * 1024));
+            copy16_to_lds(nv, off, dst + (uint32_t)(TK * ROW + i * 1024));
           }
+        }
+      }
+    }
+  };
+
+  // The new rows of a tile, from its ring slot to their pages: every position
+  // belongs to one tile of one workgroup per kv head.
+  auto append_tile = [&](int key0, uint32_t slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg) {
+      const int pos0 = key0 + pg * kPage;
+      if (pos0 + kPage <= P || pos0 >= T) continue;
+      const int64_t block = src.block_of(bt[pos0 / kPage]);
+#pragma unroll
+      for (int kv = 0; kv < 2; ++kv) {
+        unsigned char *dst = (unsigned char *)(kv ? p.v_pool : p.k_pool) + block;
+#pragma unroll
+        for (int i = 0; i < UPP; ++i) {
+          const int row = i * KPU + lane_row;
+          const u32x4 data = *(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)(
+              lds_base + slot + (uint32_t)(kv * TK * ROW + pg * kPage * ROW + i * 1024 + lane * 16));
+          if (pos0 + row >= P && pos0 + row < T) *reinterpret_cast<u32x4 *>(dst + row * ROW + lane_chunk[i]) = data;
         }
       }
     }
@@ -191,6 +226,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
     const PageIds ahead = pages_of(t + NS < mine ? key0_of(t + NS) : it.kv_begin);
     if (t + NS <= mine) wait_vmem<(NS - 1) * COPIES>();   // only later tiles' copies may still be on their way
     else wait_vmem<0>();
+    if (p.k_new && key0_of(t) + TK > P) append_tile(key0_of(t), slot);
     f32x4 s[2][RB];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
@@ -272,9 +308,6 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
     }
   }
 
-  // ---- the new tokens' rows go to their pages (this workgroup's key range only)
-  if (p.k_new) append_item_rows<D, NT>(p, it, G, Shape::kRows, tid);
-
   // ---- the waves' partial results meet in LDS
   wait_vmem<0>();
   __syncthreads();                               // every ring is idle from here on
@@ -321,7 +354,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   }
   if (slot_out) {
     int *flag = reinterpret_cast<int *>(lds + Shape::kLdsBytes - 16);
-    if (last_of_group(p, it.group, tid, flag)) merge_group<D>(p, it.group, G, Shape::kRows, tid, 0, NT / TPR);
+    if (last_of_group(p, it.group, tid, flag)) merge_group<D, 1, 8, true>(p, it.group, G, Shape::kRows, tid, NT, 0, Shape::kRows);
   }
 }
 
