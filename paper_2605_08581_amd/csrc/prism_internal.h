@@ -10,7 +10,7 @@ namespace prism {
 
 constexpr int kPage = 16;          // tokens per KV page
 constexpr int kTileKeys = 64;      // keys per inner iteration of the attention kernel
-constexpr int kStreamRows = 64;    // most packed rows per (request, kv head) of the key-splitting kernel
+constexpr int kStreamRows = 32;    // most packed rows per (request, kv head) of the key-splitting kernel
 constexpr int kNumCU = 256;        // MI355X compute units
 constexpr int kNumXCD = 8;         // accelerator complex dies, each with its own L2
 

@@ -537,8 +537,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // finished with, and ends with the scores of tile t+1.  Copies are issued in
   // the fixed order K0 V0 K1 V1 ... and complete in that order, so "K of t+1
   // and V of t have landed" is "at most 2(NS-2) tile copies still pending".
-  // Copies past the end of the key range read the (clamped) last page into a
-  // free slot and are never used: that keeps the pending count uniform.
+  // A deep ring counts on that order to the end, so its copies past the key
+  // range read the (clamped) last page into a free slot, never to be used.  With
+  // two slots every wait is for everything outstanding, and such copies, which
+  // the last tiles would then have to wait for, are left out.
   constexpr int PENDING_OK = 2 * (NS - 2) * UPW;
   static_assert((2 * NS - 2) * UPW <= 63, "pending copies must fit the vmcnt counter");
   auto wait_pending = [&](auto n_tag) __attribute__((always_inline)) {
@@ -565,24 +567,26 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     PageIds pg = pages_of(0);
     copy_rows(1, 0, 0, pg);
     pg = pages_of(1);
+    const bool second = NS > 2 || nt > 1;
 #pragma unroll
     for (int j = 1; j < NS - 1; ++j) {
       copy_rows(0, j, j, pg);
       copy_rows(1, j, j, pg);
       pg = pages_of(j + 1);
     }
-    copy_rows(0, NS - 1, NS - 1, pg);
+    if (second) copy_rows(0, NS - 1, NS - 1, pg);
     pg_v = pg;
     pg_k = pages_of(NS);
-    wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
+    if (second) wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
+    else wait_pending(std::integral_constant<int, 0>{});
     __syncthreads();
     if (wave_live) plain_scores(s_a, k_slot(0), kv_begin, kv_begin + BN - 1 > lo_limit);
   }
   // j is the tile index modulo NS, known at compile time in the fast loop so
   // that every LDS address there is a register plus an immediate.
   auto issue_copies = [&](int v_ring_slot, int k_ring_slot, int t) __attribute__((always_inline)) {
-    copy_rows(1, v_ring_slot, t + NS - 1, pg_v);
-    copy_rows(0, k_ring_slot, t + NS, pg_k);
+    if (NS > 2 || t + NS - 1 < nt) copy_rows(1, v_ring_slot, t + NS - 1, pg_v);
+    if (NS > 2 || t + NS < nt) copy_rows(0, k_ring_slot, t + NS, pg_k);
     pg_v = pg_k;
     pg_k = pages_of(t + NS + 1);
   };
@@ -598,7 +602,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   {
     const int blk_limit = P + it.row0 / G;        // last key visible to the workgroup's first row
     if (blk_limit >= kv_begin + 2 * BN - 1) n_fast = (blk_limit + 1 - kv_begin) / BN - 1;
-    if (n_fast > nt - 1) n_fast = nt - 1;
+    const int most = NS > 2 ? nt - 1 : nt - NS;   // their copies end inside the key range
+    if (n_fast > most) n_fast = most;
     if (n_fast < 0) n_fast = 0;
   }
   // How an iteration gets its copies: all pages cached, all new, or whichever

@@ -39,6 +39,103 @@ struct RowTile {
   int64_t cluster_cost;   // all key tiles of the (cluster, kv head) set
 };
 
+// How the key range of a row tile is cut: into pieces of about `chunk` key tiles,
+// a range that exceeds it by no more than `slack` staying whole.
+struct SplitRule {
+  int chunk = 0, slack = 0;                        // chunk 0: never cut
+  int pieces(int cost) const {
+    return chunk ? std::max(1, std::min(cost, (cost - slack + chunk - 1) / chunk)) : 1;
+  }
+};
+
+// Time, in key tiles, until `slots` workers have done all pieces, longest first.
+int64_t makespan(const std::vector<int> &costs, int heads, const SplitRule &rule, int slots) {
+  std::vector<std::pair<int, int64_t>> pieces;     // length, how many
+  int64_t total = 0;
+  for (int c : costs) {
+    const int n = rule.pieces(c), len = (c + n - 1) / n;
+    pieces.push_back({len, (int64_t)n * heads});
+    total += (int64_t)n * heads * len;
+  }
+  std::sort(pieces.rbegin(), pieces.rend());
+  std::vector<int64_t> at(total / slots + 2 * (int64_t)pieces[0].first + 2, 0);   // workers by load so far
+  at[0] = slots;
+  int64_t low = 0, high = 0;
+  for (auto &p : pieces)
+    while (p.second > 0) {
+      while (at[low] == 0) ++low;
+      const int64_t k = std::min(at[low], p.second);
+      at[low] -= k;
+      at[low + p.first] += k;
+      p.second -= k;
+      high = std::max(high, low + p.first);
+    }
+  return high;
+}
+
+// The smallest chunk >= min_chunk whose pieces number at most `items`.
+SplitRule fit(const std::vector<int> &costs, int heads, int min_chunk, int slack, int64_t items) {
+  int lo = min_chunk, hi = std::max(min_chunk, costs[0]);
+  while (lo < hi) {
+    const SplitRule mid{(lo + hi) / 2, slack};
+    int64_t n = 0;
+    for (int c : costs) n += mid.pieces(c);
+    if (n * heads <= items) hi = mid.chunk;
+    else lo = mid.chunk + 1;
+  }
+  return SplitRule{lo, slack};
+}
+
+SplitRule choose_split(const std::vector<int> &costs, int heads, int min_chunk, bool stream, int d) {
+  int64_t total = 0;
+  for (int c : costs) total += c;
+  total *= heads;
+  const int64_t n = (int64_t)costs.size() * heads;
+  if (stream) {
+    // One workgroup per CU (two at d = 64: LDS) and bound by bytes: cut to fill
+    // the chip once, and not at all when it is full anyway - then only ranges
+    // far above a CU's share.  A merge costs about 4 us, a workgroup's time for
+    // 8 key tiles alone.  16 requests x 300..4100 keys x 8 heads: uncut 45.9 us,
+    // 2 pieces each 35.6, 4 pieces 33.7, cut to 256 items 31.5; 320 ranges of
+    // 1000..4000 keys: uncut 72.6 us, cut to two rounds 77.9.
+    const int64_t slots = (d == 64 ? 2 : 1) * kNumCU;
+    if (n <= slots) return fit(costs, heads, min_chunk, 4, slots);
+    const int chunk = (int)std::max<int64_t>(min_chunk, total / slots);
+    return SplitRule{chunk, chunk};
+  }
+  // The prefill kernel takes about 1.1 us per key tile alone on a CU and 1.9 us
+  // beside a second workgroup; cutting costs another launch (5 us) and 0.02 us
+  // of partials per piece.  Waves that fill the chip several times are left
+  // alone but for extreme ranges; for the others the least estimate decides.
+  // (148 rows x 1040 keys x 8 heads: 16 workgroups 20.0 us, 64 of them 14.8;
+  // 3 requests of 100..300 rows x 1000..3300 keys, 8/2 heads: 31.4 -> 21.2 us.)
+  if (n > 4 * kNumCU) {
+    const int chunk = (int)std::max<int64_t>(min_chunk, (total + 3 * kNumCU - 1) / (3 * kNumCU));
+    return SplitRule{chunk, chunk};
+  }
+  auto estimate = [&](const SplitRule &r) {
+    int64_t cut = 0;
+    int longest = 0;
+    for (int c : costs) {
+      const int k = r.pieces(c);
+      longest = std::max(longest, (c + k - 1) / k);
+      if (k > 1) cut += (int64_t)k * heads;
+    }
+    return std::max(1.1 * longest, 0.95 * (double)makespan(costs, heads, r, kNumCU)) + (cut ? 5.0 + 0.02 * cut : 0.0);
+  };
+  SplitRule best;
+  double best_time = estimate(best);
+  for (int64_t items : {1, 2, 3, 4}) {
+    const SplitRule r = fit(costs, heads, min_chunk, 6, items * kNumCU);
+    const double t = estimate(r);
+    if (t < best_time) {
+      best_time = t;
+      best = r;
+    }
+  }
+  return best;
+}
+
 // Whether some request's cached prefix lies in pages that the same wave appends
 // to (pages published to later requests of the wave before they are written).
 // Attention then has to run after the whole append.
@@ -96,12 +193,13 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   }
   sch.total_suffix = total;
 
-  // Up to 64 packed rows per (request, kv head) - decode steps, short suffixes -
+  // Up to 32 packed rows per (request, kv head) - decode steps, short suffixes -
   // a wave's work is bound by bytes or latency, not by the matrix cores: the
-  // kernel whose waves split the keys then keeps every wave busy.  Above that
-  // the row tiles of the prefill kernel are full enough.
+  // kernel whose waves split the keys then keeps every wave busy.  With 33..64
+  // rows the prefill kernel is ahead (40 heads x 160 ranges of up to 300 keys:
+  // 11.2 us against 13.3; 17..32 rows: 9.9 against 9.0).
   const bool stream = !opt.tile_rows && !opt.rows_per_wave && most_rows <= kStreamRows;
-  if (stream) tile_rows = most_rows <= 16 ? 16 : most_rows <= 32 ? 32 : 64;
+  if (stream) tile_rows = most_rows <= 16 ? 16 : 32;
   sch.stream = stream;
   sch.tile_rows = tile_rows;
   sch.rows_per_wave = stream ? tile_rows : rows_per_wave;
@@ -125,7 +223,6 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 
   // Row tiles of every (request, kv head).
   std::vector<RowTile> tiles;
-  int64_t total_cost = 0;
   for (int r = 0; r < s.batch; ++r) {
     const int P = prefix[r], S = suffix[r];
     if (S == 0) continue;
@@ -138,59 +235,19 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
         const int cost = (kv_len + kTileKeys - 1) / kTileKeys;
         const int gmax = (P + S + kTileKeys - 1) / kTileKeys;
         tiles.push_back(RowTile{r, h, t * tile_rows, kv_len, cost, gmax, cluster[r], 0});
-        total_cost += cost;
       }
     }
   }
 
-  // Split-KV: aim for a few workgroups per compute unit; never cut below
-  // min_split_keys.
-  const int default_min = stream ? 256 : 1024;
-  const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : default_min) / kTileKeys);
-  const int64_t target_items = (stream ? 2LL : 3LL) * kNumCU;
-  int chunk = (int)std::max<int64_t>(min_chunk, (total_cost + target_items - 1) / target_items);
-  // The key-splitting kernel fills the chip with one workgroup per CU (two at
-  // d = 64: LDS), so it is cut to fit whole rounds of that many: for each number
-  // of rounds the smallest chunk whose workgroups fit, and of those the one with
-  // the least (rounds x chunk length).  Each round costs about kRoundTiles more
-  // for starting and merging, and a range only kSlackTiles longer than the chunk
-  // stays whole: a merge costs about 4 us, what a workgroup needs for 8 tiles.
-  // (16 requests x 300..4100 keys, 8 kv heads: 34.2 us with 1.8 uneven rounds,
-  // 31.5 us with one.)
-  constexpr int kMaxRounds = 8, kRoundTiles = 8, kSlackTiles = 4;
-  bool fit = false;
-  if (stream && opt.split_kv == 0) {
-    const int64_t slots = (d == 64 ? 2 : 1) * kNumCU;
-    auto pieces = [&](int cost, int c) { return std::max(1, (cost - kSlackTiles + c - 1) / c); };
-    int64_t best = INT64_MAX;
-    int longest = min_chunk;
-    std::vector<int> costs;
-    for (int r = 0; r < s.batch; ++r)
-      if (suffix[r] > 0) {
-        costs.push_back((prefix[r] + suffix[r] + kTileKeys - 1) / kTileKeys);
-        longest = std::max(longest, costs.back());
-      }
-    auto items_at = [&](int c) {
-      int64_t n = 0;
-      for (int cost : costs) n += pieces(cost, c);
-      return n * s.num_kv_heads;
-    };
-    for (int k = 1; k <= kMaxRounds; ++k) {
-      if (items_at(longest) > k * slots) continue;
-      int lo = min_chunk, hi = longest;
-      while (lo < hi) {
-        const int mid = (lo + hi) / 2;
-        if (items_at(mid) <= k * slots) hi = mid;
-        else lo = mid + 1;
-      }
-      const int64_t time = (int64_t)k * (lo + kRoundTiles);
-      if (time < best) {
-        best = time;
-        chunk = lo;
-        fit = true;
-      }
-    }
-  }
+  // Split-KV: never below min_split_keys.
+  std::vector<int> costs;      // key tiles of each row tile of one kv head, descending
+  for (const RowTile &t : tiles)
+    if (t.kv_head == 0) costs.push_back(t.cost);
+  std::sort(costs.rbegin(), costs.rend());
+  const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
+  const SplitRule rule = opt.split_kv == 0 && !costs.empty()
+                             ? choose_split(costs, s.num_kv_heads, min_chunk, stream, d)
+                             : SplitRule{};
 
   // Heaviest (cluster, kv head) set first; inside a set the requests, and
   // inside a request the row tiles, stay adjacent so that they run at the same
@@ -231,13 +288,8 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     for (; i < j; ++i) {
       const RowTile &t = tiles[i];
       int nsplit = 1;
-      if (opt.split_kv > 1) {
-        nsplit = std::min(opt.split_kv, t.cost);
-      } else if (fit) {
-        nsplit = std::max(1, (t.cost - kSlackTiles + chunk - 1) / chunk);
-      } else if (opt.split_kv == 0 && t.cost >= 2 * chunk) {
-        nsplit = (t.cost + chunk - 1) / chunk;
-      }
+      if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, t.cost);
+      else if (opt.split_kv == 0) nsplit = rule.pieces(t.cost);
       AttnItem it{};
       it.req = t.req;
       it.kv_head = t.kv_head;

@@ -1,6 +1,6 @@
 // Attention for few query rows per (request, kv head): decode steps and short
-// suffixes.  At most 64 packed rows share every K/V byte, so the work is below
-// 64 flop per byte and the kernel is bound by how many bytes it keeps in flight
+// suffixes.  At most 32 packed rows share every K/V byte, so the work is below
+// 32 flop per byte and the kernel is bound by how many bytes it keeps in flight
 // from HBM, or, for small waves, by latency.
 //
 // One workgroup serves one (request, kv head, key range).  Its four waves split
@@ -370,9 +370,7 @@ static int launch_stream_t(const LaunchParams &p, hipStream_t st) {
 
 template <int D>
 static int launch_stream_d(const LaunchParams &p, hipStream_t st) {
-  if (p.tile_rows == 16) return launch_stream_t<D, 1>(p, st);
-  if (p.tile_rows == 32) return launch_stream_t<D, 2>(p, st);
-  return launch_stream_t<D, 4>(p, st);
+  return p.tile_rows == 16 ? launch_stream_t<D, 1>(p, st) : launch_stream_t<D, 2>(p, st);
 }
 
 int launch_stream(const LaunchParams &p, void *stream) {

@@ -19,12 +19,13 @@ pytestmark = pytest.mark.gpu
                                           (1, [33, 64, 63]), (5, [12, 7, 1])],
                          ids=["16", "g4x16", "32", "g8x32", "64", "g5x60"])
 def test_row_blocks_and_page_edges(oracle_lib, group, suffix, d):
-    """Up to 16, 32 and 64 rows; cached lengths 0, inside a page, on a page edge,
+    """Up to 16 and 32 rows, and 33 to 64 (the prefill kernel again); cached lengths 0, inside a page, on a page edge,
     around the 32-key tile and far past it; sequences of a single key."""
     prefix = [0, 37, 1500] if suffix[0] > 1 else [1000, 16, 31]
     b = W.make_custom_batch("stream", W.Geometry(2 * group, 2, d), prefix + [0], suffix + [1], seed=61)
     info = full_parity(oracle_lib, b)
-    assert info.tile_rows in (16, 32, 64)
+    rows = max(suffix) * group
+    assert info.tile_rows == (16 if rows <= 16 else 32 if rows <= 32 else 128)
     full_parity(oracle_lib, b, split_kv=3)
 
 
