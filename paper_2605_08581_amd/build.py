@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libprism.so")
-BINDING = os.path.join(HERE, "_prism_torch.so")
+BINDING = os.path.join(HERE, "_prism_torch.so")     # Python entry of the layer calls, against PyTorch's headers
+SCHED_BINDING = os.path.join(HERE, "_prism_sched.so")  # Python entry of the control plane's per-request calls
 SOURCES = ["prism_plan.cpp", "prism_api.cpp", "prism_sched.cpp", "prism_kernels.hip", "prism_attn64.hip", "prism_stream.hip"]
 # packed fp32 VALU ops stay off: the kernels are written as ordinary float code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-mllvm", "-amdgpu-mfma-vgpr-form",
@@ -51,29 +52,32 @@ def emit_assembly(src: str, out_dir: str) -> str:
     return out
 
 
-def _build_binding() -> str:
-    """The Python entry of the layer calls (host code only, against PyTorch's own headers)."""
-    import torch
-    base = os.path.dirname(torch.__file__)
-    lib = os.path.join(base, "lib")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-deprecated-declarations",
-           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(base, "include"), "-isystem", "/opt/rocm/include",
-           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "prism_torch.cpp"), "-o", BINDING,
-           "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+def _build_module(src: str, out: str, flags: list, libs: list) -> None:
+    """A Python extension module of host code only."""
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *flags, "-I", os.path.join(ROOT, "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, src), "-o", out, *libs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError("g++ failed on prism_torch.cpp:\n" + r.stderr)
-    return BINDING
+        raise RuntimeError(f"g++ failed on {src}:\n" + r.stderr)
+
+
+def _build_bindings() -> None:
+    import torch
+    base = os.path.dirname(torch.__file__)
+    _build_module("prism_pysched.cpp", SCHED_BINDING, [], [])
+    _build_module("prism_torch.cpp", BINDING,
+                  ["-Wno-deprecated-declarations", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+                   f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                   "-isystem", os.path.join(base, "include"), "-isystem", "/opt/rocm/include"],
+                  ["-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"])
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libprism.so and the Python entry; always recompiles."""
+    """Compile every source, link libprism.so and the Python entries; always recompiles."""
     with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
-        binding = ex.submit(_build_binding)
+        bindings = ex.submit(_build_bindings)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
-        binding.result()
+        bindings.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

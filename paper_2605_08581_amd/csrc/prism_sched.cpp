@@ -9,9 +9,7 @@
 #include <cmath>
 #include <cstring>
 #include <deque>
-#include <map>
 #include <new>
-#include <queue>
 #include <unordered_map>
 #include <unordered_set>
 #include <vector>
@@ -39,32 +37,57 @@ inline uint64_t hash_ids(const int32_t *v, size_t n) {
 
 namespace {
 
+// Segment ids are arbitrary; everything below counts and compares by a dense
+// index given at first sight, so that a round works on flat arrays.
+// Indexes given back are used again, so the arrays stay as long as the most
+// segments that were in use at once.
+struct SegmentIndex {
+  std::unordered_map<int32_t, int32_t> of;   // segment -> dense index
+  std::vector<int32_t> id;                   // dense index -> segment
+  std::vector<int32_t> unused;               // dense indexes given back
+  int32_t add(int32_t segment) {
+    auto ins = of.emplace(segment, (int32_t)id.size());
+    if (!ins.second) return ins.first->second;
+    if (unused.empty()) {
+      id.push_back(segment);
+    } else {
+      ins.first->second = unused.back();
+      unused.pop_back();
+      id[ins.first->second] = segment;
+    }
+    return ins.first->second;
+  }
+  void give_back(int32_t d) {
+    of.erase(id[d]);
+    unused.push_back(d);
+  }
+};
+
 struct QReq {
   int64_t id;
   double arrival;
-  std::vector<int32_t> skel, seg_tokens;
+  std::vector<int32_t> skel, seg_tokens;     // skel: dense indexes
+  // Distinct segments of the skeleton, ascending by segment id: the counters of
+  // Sec. 3.2 count requests, so a segment listed twice still counts once.
+  std::vector<int32_t> distinct;
   std::vector<uint8_t> reorderable;
   int32_t system_tokens, suffix_tokens;
 };
-
-struct Counter {
-  int32_t g = 0, a = 0, n = 0;
-};
-
-// Distinct segments of a skeleton: the counters of Sec. 3.2 count requests, so a
-// segment that a request lists twice still counts once.
-inline void distinct_segments(const std::vector<int32_t> &skel, std::vector<int32_t> &out) {
-  out.assign(skel.begin(), skel.end());
-  std::sort(out.begin(), out.end());
-  out.erase(std::unique(out.begin(), out.end()), out.end());
-}
 
 }  // namespace
 
 struct prism_qas {
   prism_qas_options_t opt;
+  SegmentIndex seg;
+  std::vector<int32_t> by_id;                // dense indexes in use, ascending by segment id
+  bool by_id_stale = false;
+  // per dense index: requests pending (g) and active (a) that list the segment,
+  // kept up to date by submit, round and complete; the rest is scratch of a round
+  std::vector<int32_t> g, a, n, nb;
+  std::vector<double> p0;
+  std::vector<uint8_t> seen;
   std::deque<QReq> pending;
-  std::unordered_map<int64_t, std::vector<int32_t>> active;  // id -> distinct segments
+  std::unordered_map<int64_t, std::vector<int32_t>> active;  // id -> distinct segments (dense)
   std::unordered_set<int64_t> known;                         // pending or active ids
   std::vector<prism_qas_hint_t> hints;
   std::vector<prism_qas_segment_t> segments;
@@ -106,7 +129,16 @@ extern "C" int prism_qas_submit(prism_qas_t *q, int64_t request, double arrival,
   QReq r;
   r.id = request;
   r.arrival = arrival;
-  r.skel.assign(skeleton, skeleton + m);
+  r.skel.resize(m);
+  for (int i = 0; i < m; ++i) r.skel[i] = q->seg.add(skeleton[i]);
+  const std::vector<int32_t> &id = q->seg.id;
+  q->g.resize(id.size());
+  q->a.resize(id.size());
+  r.distinct = r.skel;
+  std::sort(r.distinct.begin(), r.distinct.end(), [&](int32_t x, int32_t y) { return id[x] < id[y]; });
+  r.distinct.erase(std::unique(r.distinct.begin(), r.distinct.end()), r.distinct.end());
+  for (int32_t d : r.distinct)
+    if (q->g[d]++ == 0 && q->a[d] == 0) q->by_id_stale = true;
   r.seg_tokens.assign(segment_tokens, segment_tokens + m);
   if (reorderable) r.reorderable.assign(reorderable, reorderable + m);
   else r.reorderable.assign(m, 1);
@@ -120,6 +152,11 @@ extern "C" int prism_qas_complete(prism_qas_t *q, int64_t request) {
   if (!q) return PRISM_ERR_INVALID_ARG;
   auto it = q->active.find(request);
   if (it == q->active.end()) return PRISM_ERR_INVALID_ARG;
+  for (int32_t d : it->second)
+    if (--q->a[d] == 0 && q->g[d] == 0) {
+      q->seg.give_back(d);
+      q->by_id_stale = true;
+    }
   q->active.erase(it);
   q->known.erase(request);
   return PRISM_OK;
@@ -136,36 +173,41 @@ extern "C" int prism_qas_round(prism_qas_t *q) {
   q->priorities.clear();
   const int np = (int)q->pending.size();
 
-  // Counters over the frozen queue and the active set (Sec. 3.2).
-  std::unordered_map<int32_t, Counter> cnt;
-  std::vector<std::vector<int32_t>> distinct(np);
-  for (int i = 0; i < np; ++i) {
-    distinct_segments(q->pending[i].skel, distinct[i]);
-    for (int32_t r : distinct[i]) cnt[r].g++;
+  // The counters g and a over the frozen queue and the active set (Sec. 3.2) are
+  // up to date; P_t(r; empty batch) of Eq. 9 follows from them once per round.
+  const std::vector<int32_t> &id = q->seg.id;
+  const size_t ns = id.size();
+  q->n.assign(ns, 0);
+  q->nb.assign(ns, 0);
+  q->seen.assign(ns, 0);
+  q->p0.resize(ns);
+  for (size_t d = 0; d < ns; ++d) q->p0[d] = o.w_global * q->g[d] + o.w_active * q->a[d];
+  if (q->by_id_stale) {
+    q->by_id.clear();
+    for (size_t d = 0; d < ns; ++d)
+      if (q->g[d] || q->a[d]) q->by_id.push_back((int32_t)d);
+    std::sort(q->by_id.begin(), q->by_id.end(), [&](int32_t x, int32_t y) { return id[x] < id[y]; });
+    q->by_id_stale = false;
   }
-  for (auto &kv : q->active)
-    for (int32_t r : kv.second) cnt[r].a++;
-  auto p0 = [&](int32_t r) -> double {  // P_t(r; empty batch), Eq. 9
-    auto it = cnt.find(r);
-    if (it == cnt.end()) return 0.0;
-    return o.w_global * it->second.g + o.w_active * it->second.a;
-  };
   // "higher priority first", equal priorities by segment id so that every
   // request serializes the same hot segments in the same order
-  auto before = [&](int32_t r1, int32_t r2) {
-    double a = p0(r1), b = p0(r2);
-    return a != b ? a > b : r1 < r2;
-  };
+  const double *p0 = q->p0.data();
+  auto before = [&](int32_t r1, int32_t r2) { return p0[r1] != p0[r2] ? p0[r1] > p0[r2] : id[r1] < id[r2]; };
 
-  std::vector<std::vector<int32_t>> star(np), star_len(np);  // Pi*_i and its segment lengths
+  std::vector<int32_t> star, star_len;                        // Pi*_i and its segment lengths, requests back to back
+  std::vector<size_t> star_at(np + 1, 0);
+  for (int i = 0; i < np; ++i) star_at[i + 1] = star_at[i] + q->pending[i].skel.size();
+  star.resize(star_at[np]);
+  star_len.resize(star_at[np]);
   std::vector<int> selected(np, 0);                           // 0 no, 1 hot, 2 cold
   std::vector<int> bucket_of(np, 0), rank_of(np, 0);
   struct Bucket {
-    std::vector<int32_t> sig;
+    std::vector<int32_t> sig;                                 // segment ids
     uint64_t hash;
     std::vector<int> members;
     double score = 0;
     int order = 0;
+    int next = -1;                                            // bucket of the same hash
   };
   std::vector<Bucket> buckets;
   std::vector<int> dispatch;  // indices into pending, dispatch order
@@ -173,72 +215,81 @@ extern "C" int prism_qas_round(prism_qas_t *q) {
                                                        : o.dispatch_budget - o.cold_quota;
 
   if (o.mode == PRISM_QAS_MODE_FIFO) {
-    for (int i = 0; i < np; ++i) { star[i] = q->pending[i].skel; star_len[i] = q->pending[i].seg_tokens; }
+    for (int i = 0; i < np; ++i) {
+      std::copy(q->pending[i].skel.begin(), q->pending[i].skel.end(), star.begin() + star_at[i]);
+      std::copy(q->pending[i].seg_tokens.begin(), q->pending[i].seg_tokens.end(), star_len.begin() + star_at[i]);
+    }
     for (int i = 0; i < np && (int)dispatch.size() < o.dispatch_budget; ++i) { selected[i] = 2; dispatch.push_back(i); }
   } else {
-    std::map<std::vector<int32_t>, int> index;  // signature -> bucket, exact (no hash collisions)
+    std::unordered_map<uint64_t, int> index;  // hash of the signature -> its first bucket; signatures are compared
+    std::vector<int> slots, movable, order, perm, pos;
+    std::vector<char> is_best;
+    std::vector<int32_t> sig;
     for (int i = 0; i < np; ++i) {
       const QReq &rq = q->pending[i];
       const int m = (int)rq.skel.size();
+      int32_t *st = star.data() + star_at[i];
       // Front alignment: the f_front best reorderable segments take the first
       // reorderable positions, best first; the other reorderable segments keep
       // their relative order in the positions that are left; pinned segments
       // do not move.
-      std::vector<int> slots, movable;
-      for (int j = 0; j < m; ++j) if (rq.reorderable[j]) { slots.push_back(j); movable.push_back(j); }
-      std::vector<int> best = movable;
-      std::stable_sort(best.begin(), best.end(), [&](int x, int y) { return before(rq.skel[x], rq.skel[y]); });
-      if ((int)best.size() > o.front_width) best.resize(o.front_width);
-      std::vector<char> is_best(m, 0);
-      for (int j : best) is_best[j] = 1;
-      std::vector<int> order = best;
+      slots.clear();
+      for (int j = 0; j < m; ++j) if (rq.reorderable[j]) slots.push_back(j);
+      movable = slots;
+      order = movable;
+      std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return before(rq.skel[x], rq.skel[y]); });
+      if ((int)order.size() > o.front_width) order.resize(o.front_width);
+      is_best.assign(m, 0);
+      for (int j : order) is_best[j] = 1;
       for (int j : movable) if (!is_best[j]) order.push_back(j);
-      std::vector<int> perm(m);
+      perm.resize(m);
       for (int j = 0; j < m; ++j) perm[j] = j;
       for (size_t s = 0; s < slots.size(); ++s) perm[slots[s]] = order[s];
-      star[i].resize(m); star_len[i].resize(m);
-      for (int j = 0; j < m; ++j) { star[i][j] = rq.skel[perm[j]]; star_len[i][j] = rq.seg_tokens[perm[j]]; }
+      for (int j = 0; j < m; ++j) { st[j] = rq.skel[perm[j]]; star_len[star_at[i] + j] = rq.seg_tokens[perm[j]]; }
 
       // Order-sensitive signature (Eq. 10): the kappa best segments of Pi*, written
       // in the order in which Pi* serializes them.
-      std::vector<int> pos(m);
+      pos.resize(m);
       for (int j = 0; j < m; ++j) pos[j] = j;
-      std::stable_sort(pos.begin(), pos.end(), [&](int x, int y) {
-        if (star[i][x] == star[i][y]) return false;
-        return before(star[i][x], star[i][y]);
-      });
+      std::stable_sort(pos.begin(), pos.end(), [&](int x, int y) { return st[x] != st[y] && before(st[x], st[y]); });
       if ((int)pos.size() > o.signature_size) pos.resize(o.signature_size);
       std::sort(pos.begin(), pos.end());
-      std::vector<int32_t> sig;
-      for (int j : pos) sig.push_back(star[i][j]);
-      auto ins = index.emplace(sig, (int)buckets.size());
-      if (ins.second) {
-        Bucket b;
-        b.sig = sig;
-        b.hash = hash_ids(sig.data(), sig.size());
-        buckets.push_back(std::move(b));
+      sig.clear();
+      for (int j : pos) sig.push_back(id[st[j]]);
+      const uint64_t hash = hash_ids(sig.data(), sig.size());
+      auto ins = index.emplace(hash, (int)buckets.size());
+      int bi = ins.second ? -1 : ins.first->second;
+      while (bi >= 0 && buckets[bi].sig != sig) bi = buckets[bi].next;
+      if (bi < 0) {
+        bi = (int)buckets.size();
+        buckets.emplace_back();
+        buckets[bi].sig = sig;
+        buckets[bi].hash = hash;
+        if (!ins.second) {
+          buckets[bi].next = buckets[ins.first->second].next;
+          buckets[ins.first->second].next = bi;
+        }
       }
-      Bucket &b = buckets[ins.first->second];
-      bucket_of[i] = ins.first->second;
+      Bucket &b = buckets[bi];
+      bucket_of[i] = bi;
       rank_of[i] = (int)b.members.size();
       b.members.push_back(i);
     }
     // Candidate hot-lane batch, its next counter and the bucket score (Eq. 11-12).
+    std::vector<int32_t> support;
     for (Bucket &b : buckets) {
-      std::unordered_map<int32_t, int32_t> nb;
-      std::vector<int32_t> support;
-      for (size_t k = 0; k < b.members.size(); ++k) {
-        for (int32_t r : distinct[b.members[k]]) {
-          support.push_back(r);
-          if ((int)k < hot_slots) nb[r]++;
+      support.clear();
+      for (size_t k = 0; k < b.members.size(); ++k)
+        for (int32_t r : q->pending[b.members[k]].distinct) {
+          if (!q->seen[r]) { q->seen[r] = 1; support.push_back(r); }
+          if ((int)k < hot_slots) q->nb[r]++;
         }
-      }
-      std::sort(support.begin(), support.end());
-      support.erase(std::unique(support.begin(), support.end()), support.end());
+      std::sort(support.begin(), support.end(), [&](int32_t x, int32_t y) { return id[x] < id[y]; });
       double sum = 0;
       for (int32_t r : support) {
-        auto it = nb.find(r);
-        sum += p0(r) + o.w_next * (it == nb.end() ? 0 : it->second);
+        sum += p0[r] + o.w_next * q->nb[r];
+        q->nb[r] = 0;
+        q->seen[r] = 0;
       }
       double util = sum / (double)std::max<size_t>(1, support.size());
       b.score = o.alpha_size * (double)b.members.size() + o.beta_util * util;
@@ -268,24 +319,16 @@ extern "C" int prism_qas_round(prism_qas_t *q) {
 
   // Dispatch-batch next counter and priority P^_t (Sec. 3.3).
   for (int i : dispatch)
-    for (int32_t r : distinct[i]) cnt[r].n++;
-  auto p_hat = [&](int32_t r) {
-    auto it = cnt.find(r);
-    if (it == cnt.end()) return 0.0;
-    return o.w_global * it->second.g + o.w_active * it->second.a + o.w_next * it->second.n;
-  };
-  std::vector<int32_t> seg_ids;
-  seg_ids.reserve(cnt.size());
-  for (auto &kv : cnt) seg_ids.push_back(kv.first);
-  std::sort(seg_ids.begin(), seg_ids.end());
-  for (int32_t r : seg_ids) {
-    const Counter &c = cnt[r];
+    for (int32_t r : q->pending[i].distinct) q->n[r]++;
+  auto p_hat = [&](int32_t r) { return o.w_global * q->g[r] + o.w_active * q->a[r] + o.w_next * q->n[r]; };
+  for (int32_t r : q->by_id) {
     prism_qas_priority_t e;
-    e.segment = r; e.g = c.g; e.a = c.a; e.n = c.n; e.priority = p_hat(r);
+    e.segment = id[r]; e.g = q->g[r]; e.a = q->a[r]; e.n = q->n[r]; e.priority = p_hat(r);
     q->priorities.push_back(e);
   }
 
-  // Hints, then the move from the pending buffer into the active set.
+  // Hints (with the counters of the round), then the move from the pending
+  // buffer into the active set.
   for (int i : dispatch) {
     const QReq &rq = q->pending[i];
     prism_qas_hint_t h;
@@ -293,26 +336,30 @@ extern "C" int prism_qas_round(prism_qas_t *q) {
     h.request = rq.id;
     h.arrival = rq.arrival;
     h.lane = selected[i] == 1 ? 0 : 1;
-    h.num_segments = (int32_t)star[i].size();
+    h.num_segments = (int32_t)rq.skel.size();
     h.first = (int32_t)q->segments.size();
     if (o.mode == PRISM_QAS_MODE_QAS) {
       const Bucket &b = buckets[bucket_of[i]];
       h.bucket = b.hash; h.bucket_order = b.order; h.rank = rank_of[i]; h.bucket_score = b.score;
     }
     int32_t off = rq.system_tokens;
-    for (size_t j = 0; j < star[i].size(); ++j) {
+    for (size_t j = star_at[i]; j < star_at[i + 1]; ++j) {
       prism_qas_segment_t s;
       std::memset(&s, 0, sizeof s);
-      off += star_len[i][j];
-      s.segment = star[i][j];
+      off += star_len[j];
+      const int32_t r = star[j];
+      s.segment = id[r];
       s.end_offset = off;
-      const Counter &c = cnt[s.segment];
-      s.g = c.g; s.a = c.a; s.n = c.n;
-      s.priority = p_hat(s.segment);
+      s.g = q->g[r]; s.a = q->a[r]; s.n = q->n[r];
+      s.priority = p_hat(r);
       q->segments.push_back(s);
     }
     q->hints.push_back(h);
-    q->active.emplace(rq.id, distinct[i]);
+  }
+  for (int i : dispatch) {
+    QReq &rq = q->pending[i];
+    for (int32_t r : rq.distinct) { q->g[r]--; q->a[r]++; }
+    q->active.emplace(rq.id, std::move(rq.distinct));
   }
   std::deque<QReq> rest;
   for (int i = 0; i < np; ++i)
@@ -373,13 +420,14 @@ struct Node {
   int32_t parent = -1;
   std::vector<int32_t> tok;    // whole pages of tokens on the edge into this node
   std::vector<int32_t> pages;  // their page ids
-  std::unordered_multimap<uint64_t, int32_t> child;  // hash of first page -> node
+  uint64_t hash = 0;           // of (parent, first page): its place among all nodes
+  int32_t children = 0;
   int32_t ref = 0;
   int32_t kind = PRISM_SPAN_NONE, segment = -1, end_offset = 0;
   int32_t snap_g = 0, snap_a = 0, snap_n = 0;
   uint32_t hits = 0, gen = 0;
   double last = 0;
-  bool attached = false, is_protected = false;
+  bool attached = false, is_protected = false, mark = false;
   bool pending = false;  // published at admission: its KV is written by the wave now forming
 };
 
@@ -395,6 +443,53 @@ struct DReq {
 struct Prio {
   double p = 0;
   int32_t g = 0, a = 0, n = 0;
+  uint32_t round = 0;          // the table it came with
+};
+
+// All nodes by (parent, first page), open addressing with linear probing.
+struct ChildTable {
+  std::vector<int32_t> slot = std::vector<int32_t>(64, -1);   // node, or -1
+  size_t used = 0;
+  size_t home(uint64_t hash) const { return (size_t)hash & (slot.size() - 1); }
+  template <class HashOf>
+  void insert(uint64_t hash, int32_t node, HashOf hash_of) {
+    if (2 * (used + 1) > slot.size()) {
+      std::vector<int32_t> old(2 * slot.size(), -1);
+      old.swap(slot);
+      for (int32_t u : old)
+        if (u >= 0) place(hash_of(u), u);
+    }
+    place(hash, node);
+    ++used;
+  }
+  template <class HashOf>
+  void erase(uint64_t hash, int32_t node, HashOf hash_of) {
+    const size_t mask = slot.size() - 1;
+    size_t i = home(hash);
+    while (slot[i] != node) i = (i + 1) & mask;
+    // close the gap: move up every later entry of the run that may stand here
+    for (size_t j = (i + 1) & mask; slot[j] >= 0; j = (j + 1) & mask) {
+      const size_t h = home(hash_of(slot[j]));
+      if (((j - h) & mask) >= ((j - i) & mask)) { slot[i] = slot[j]; i = j; }
+    }
+    slot[i] = -1;
+    --used;
+  }
+  template <class Same>
+  int32_t find(uint64_t hash, Same same) const {
+    const size_t mask = slot.size() - 1;
+    for (size_t i = home(hash); slot[i] >= 0; i = (i + 1) & mask)
+      if (same(slot[i])) return slot[i];
+    return -1;
+  }
+
+ private:
+  void place(uint64_t hash, int32_t node) {
+    const size_t mask = slot.size() - 1;
+    size_t i = home(hash);
+    while (slot[i] >= 0) i = (i + 1) & mask;
+    slot[i] = node;
+  }
 };
 
 }  // namespace
@@ -406,31 +501,41 @@ struct prism_dart {
   std::vector<int32_t> free_nodes;
   std::vector<int32_t> free_pages;
   std::unordered_map<int64_t, DReq> reqs;
-  std::unordered_map<int32_t, Prio> prio;
-  std::priority_queue<HeapEntry, std::vector<HeapEntry>, HeapAfter> heap;
+  ChildTable table;
+  // Priorities by dense segment index; an entry counts if it came with the
+  // current round.  Beside the nodes, for scans over all of them: the segment of
+  // an attached reusable node (else -1) and its priority (else 0).
+  SegmentIndex seg;
+  std::vector<Prio> prio;
+  uint32_t round = 1;
+  std::vector<int32_t> node_seg;
+  std::vector<double> node_prio;
+  std::vector<int32_t> protected_now, cand;
+  std::vector<HeapEntry> heap;               // std heap order, smallest key first
   std::deque<int32_t> evicted;
   double now = 0;
   prism_dart_stats_t st;
 
   // ---- helpers -----------------------------------------------------------
-  uint64_t page_hash(const int32_t *t) const { return hash_ids(t, (size_t)ps); }
-
+  uint64_t child_hash(int32_t parent, const int32_t *first_page) const {
+    return mix64(hash_ids(first_page, (size_t)ps) ^ (uint64_t)(uint32_t)parent);
+  }
   int32_t find_child(int32_t u, const int32_t *first_page) const {
-    const Node &n = nodes[u];
-    auto range = n.child.equal_range(page_hash(first_page));
-    for (auto it = range.first; it != range.second; ++it)
-      if (std::memcmp(nodes[it->second].tok.data(), first_page, sizeof(int32_t) * ps) == 0) return it->second;
-    return -1;
+    const uint64_t h = child_hash(u, first_page);
+    return table.find(h, [&](int32_t c) {
+      const Node &n = nodes[c];
+      return n.hash == h && n.parent == u && std::memcmp(n.tok.data(), first_page, sizeof(int32_t) * ps) == 0;
+    });
   }
   void link(int32_t parent, int32_t c) {
     nodes[c].parent = parent;
-    nodes[parent].child.emplace(page_hash(nodes[c].tok.data()), c);
+    nodes[c].hash = child_hash(parent, nodes[c].tok.data());
+    nodes[parent].children++;
+    table.insert(nodes[c].hash, c, [&](int32_t u) { return nodes[u].hash; });
   }
   void unlink(int32_t c) {
-    Node &p = nodes[nodes[c].parent];
-    auto range = p.child.equal_range(page_hash(nodes[c].tok.data()));
-    for (auto it = range.first; it != range.second; ++it)
-      if (it->second == c) { p.child.erase(it); return; }
+    nodes[nodes[c].parent].children--;
+    table.erase(nodes[c].hash, c, [&](int32_t u) { return nodes[u].hash; });
   }
   int32_t new_node() {
     int32_t id;
@@ -440,16 +545,24 @@ struct prism_dart {
     nodes[id] = Node();
     nodes[id].gen = gen;
     nodes[id].attached = true;
+    node_seg.resize(nodes.size(), -1);
+    node_prio.resize(nodes.size(), 0.0);
+    set_segment(id, -1);
     return id;
+  }
+  // dense index of the reusable segment that node u holds, -1 for none
+  void set_segment(int32_t u, int32_t d) {
+    node_seg[u] = d;
+    node_prio[u] = d >= 0 && prio[d].round == round ? prio[d].p : 0.0;
+  }
+  int32_t segment_index(int32_t segment) {
+    const int32_t d = seg.add(segment);
+    if ((size_t)d >= prio.size()) prio.resize(d + 1);
+    return d;
   }
   bool evictable(int32_t u) const {
     const Node &n = nodes[u];
-    return u != 0 && n.attached && n.ref == 0 && n.child.empty() && n.kind != PRISM_SPAN_SYSTEM;
-  }
-  double seg_priority(const Node &n) const {
-    if (n.kind != PRISM_SPAN_REUSABLE) return 0.0;
-    auto it = prio.find(n.segment);
-    return it == prio.end() ? 0.0 : it->second.p;
+    return u != 0 && n.attached && n.ref == 0 && n.children == 0 && n.kind != PRISM_SPAN_SYSTEM;
   }
   EvictKey key_of(int32_t u) const {
     const Node &n = nodes[u];
@@ -457,20 +570,19 @@ struct prism_dart {
       case PRISM_EVICT_LRU: return {0, 0.0, n.last};
       case PRISM_EVICT_LFU: return {0, (double)n.hits, n.last};
       case PRISM_EVICT_LRU_ACTIVE: {
-        double a = 0;
-        if (n.kind == PRISM_SPAN_REUSABLE) {
-          auto it = prio.find(n.segment);
-          if (it != prio.end()) a = it->second.a;
-        }
-        return {0, a, n.last};
+        const int32_t d = node_seg[u];
+        return {0, d >= 0 && prio[d].round == round ? (double)prio[d].a : 0.0, n.last};
       }
       default: break;
     }
     if (n.kind != PRISM_SPAN_REUSABLE) return {0, 0.0, n.last};  // private suffix (or no hint)
     if (n.is_protected) return {2, 0.0, n.last};
-    return {1, seg_priority(n), n.last};
+    return {1, node_prio[u], n.last};
   }
-  void push(int32_t u) { heap.push({key_of(u), u, nodes[u].gen}); }
+  void push(int32_t u) {
+    heap.push_back({key_of(u), u, nodes[u].gen});
+    std::push_heap(heap.begin(), heap.end(), HeapAfter());
+  }
 
   void lock(int32_t u) { for (; u != 0; u = nodes[u].parent) nodes[u].ref++; }
   void unlock(int32_t u) {
@@ -495,6 +607,7 @@ struct prism_dart {
     un.end_offset = cn.end_offset - (int32_t)cn.pages.size() * ps;
     un.snap_g = cn.snap_g; un.snap_a = cn.snap_a; un.snap_n = cn.snap_n;
     un.hits = cn.hits; un.last = cn.last; un.is_protected = false; un.pending = cn.pending;
+    set_segment(u, node_seg[c]);
     link(parent, u);
     link(u, c);
     return u;
@@ -526,42 +639,44 @@ struct prism_dart {
     return cur;
   }
 
+  // The protection set: the f best reusable nodes.  Called at every eviction, so
+  // it scans one array of priorities instead of the nodes and touches only the
+  // nodes that are or were protected.
   void refresh_protection() {
     if (opt.policy != PRISM_EVICT_DART) return;
-    std::vector<int32_t> cand;
-    for (int32_t u = 1; u < (int32_t)nodes.size(); ++u) {
-      const Node &n = nodes[u];
-      if (n.attached && n.kind == PRISM_SPAN_REUSABLE && seg_priority(n) > 0) cand.push_back(u);
-    }
+    cand.clear();
+    for (int32_t u = 1; u < (int32_t)nodes.size(); ++u)
+      if (node_prio[u] > 0) cand.push_back(u);
     const size_t f = opt.protect_budget < 0 ? 0 : (size_t)opt.protect_budget;
     auto better = [&](int32_t x, int32_t y) {
-      double px = seg_priority(nodes[x]), py = seg_priority(nodes[y]);
-      if (px != py) return px > py;
+      if (node_prio[x] != node_prio[y]) return node_prio[x] > node_prio[y];
       if (nodes[x].last != nodes[y].last) return nodes[x].last > nodes[y].last;
       return x < y;
     };
     if (cand.size() > f) {
-      std::partial_sort(cand.begin(), cand.begin() + f, cand.end(), better);
+      std::nth_element(cand.begin(), cand.begin() + f, cand.end(), better);
       cand.resize(f);
     }
-    std::vector<char> keep(nodes.size(), 0);
-    for (int32_t u : cand) keep[u] = 1;
-    int32_t count = 0;
-    for (int32_t u = 1; u < (int32_t)nodes.size(); ++u) {
+    for (int32_t u : cand) nodes[u].mark = true;
+    for (int32_t u : protected_now) {
       Node &n = nodes[u];
-      if (!n.attached) continue;
-      const bool was = n.is_protected;
-      n.is_protected = keep[u] != 0;
-      count += n.is_protected;
-      // a node that lost protection now has a smaller key than the heap holds
-      if (was && !n.is_protected && evictable(u)) push(u);
+      if (!n.attached || !n.is_protected || n.mark) continue;
+      n.is_protected = false;
+      // its key is now smaller than the one the heap holds
+      if (evictable(u)) push(u);
     }
-    st.protected_nodes = count;
+    for (int32_t u : cand) {
+      nodes[u].is_protected = true;
+      nodes[u].mark = false;
+    }
+    st.protected_nodes = (int32_t)cand.size();
+    protected_now.swap(cand);
   }
 
   void collect() {
     for (int32_t u = 1; u < (int32_t)nodes.size(); ++u)
-      if (evictable(u)) push(u);
+      if (evictable(u)) heap.push_back({key_of(u), u, nodes[u].gen});
+    std::make_heap(heap.begin(), heap.end(), HeapAfter());
     st.heap_rebuilds++;
   }
 
@@ -573,8 +688,9 @@ struct prism_dart {
     while (freed < k_free_tokens) {
       if (heap.empty()) collect();
       if (heap.empty()) break;
-      HeapEntry e = heap.top();
-      heap.pop();
+      std::pop_heap(heap.begin(), heap.end(), HeapAfter());
+      const HeapEntry e = heap.back();
+      heap.pop_back();
       st.heap_pops++;
       if (e.node <= 0 || e.node >= (int32_t)nodes.size() || nodes[e.node].gen != e.gen || !evictable(e.node)) {
         st.heap_stale++;
@@ -582,7 +698,7 @@ struct prism_dart {
       }
       EvictKey cur = key_of(e.node);
       if (!(cur == e.key)) {
-        heap.push({cur, e.node, e.gen});
+        push(e.node);
         st.heap_stale++;
         continue;
       }
@@ -597,6 +713,7 @@ struct prism_dart {
       st.tree_pages -= (int32_t)n.pages.size();
       n.attached = false;
       n.gen++;
+      set_segment(e.node, -1);
       n.tok.clear(); n.tok.shrink_to_fit();
       n.pages.clear(); n.pages.shrink_to_fit();
       free_nodes.push_back(e.node);
@@ -663,9 +780,10 @@ struct prism_dart {
       n.kind = sp.kind;
       n.segment = sp.kind == PRISM_SPAN_REUSABLE ? sp.segment : -1;
       n.end_offset = (pos + k) * ps;
+      set_segment(c, n.kind == PRISM_SPAN_REUSABLE ? segment_index(n.segment) : -1);
       if (n.kind == PRISM_SPAN_REUSABLE) {
-        auto pit = prio.find(n.segment);
-        if (pit != prio.end()) { n.snap_g = pit->second.g; n.snap_a = pit->second.a; n.snap_n = pit->second.n; }
+        const Prio &p = prio[node_seg[c]];
+        if (p.round == round) { n.snap_g = p.g; n.snap_a = p.a; n.snap_n = p.n; }
       }
       n.last = now;
       cur = c;
@@ -700,6 +818,8 @@ extern "C" int prism_dart_create(const prism_dart_options_t *options, prism_dart
   t->ps = o.page_size;
   t->nodes.emplace_back();
   t->nodes[0].attached = true;
+  t->node_seg.assign(1, -1);
+  t->node_prio.assign(1, 0.0);
   t->free_pages.reserve(o.num_pages);
   for (int32_t p = o.num_pages - 1; p >= 0; --p) t->free_pages.push_back(o.first_page + p);
   std::memset(&t->st, 0, sizeof t->st);
@@ -713,14 +833,21 @@ extern "C" void prism_dart_destroy(prism_dart_t *t) { delete t; }
 extern "C" int prism_dart_set_round(prism_dart_t *t, double now, const prism_qas_priority_t *table, int32_t n) {
   if (!t || n < 0 || (n > 0 && !table)) return PRISM_ERR_INVALID_ARG;
   t->now = std::max(t->now, now);
-  t->prio.clear();
-  for (int32_t i = 0; i < n; ++i) {
-    Prio p;
-    p.p = table[i].priority; p.g = table[i].g; p.a = table[i].a; p.n = table[i].n;
-    t->prio[table[i].segment] = p;
+  t->round++;
+  if (t->seg.id.size() > 4096 + 4 * (t->nodes.size() + (size_t)n)) {   // mostly segments long gone: start over
+    t->seg = SegmentIndex();
+    t->prio.clear();
+    for (int32_t u = 1; u < (int32_t)t->nodes.size(); ++u)
+      if (t->node_seg[u] >= 0) t->node_seg[u] = t->segment_index(t->nodes[u].segment);
   }
+  for (int32_t i = 0; i < n; ++i) {
+    Prio &p = t->prio[t->segment_index(table[i].segment)];
+    p.p = table[i].priority; p.g = table[i].g; p.a = table[i].a; p.n = table[i].n;
+    p.round = t->round;
+  }
+  for (int32_t u = 1; u < (int32_t)t->nodes.size(); ++u) t->set_segment(u, t->node_seg[u]);
   // priorities may have dropped: every stored key is suspect, start the heap over
-  while (!t->heap.empty()) t->heap.pop();
+  t->heap.clear();
   t->refresh_protection();
   return PRISM_OK;
 }
@@ -857,8 +984,8 @@ extern "C" int prism_dart_dump(const prism_dart_t *t, prism_dart_node_t *out, in
       prism_dart_node_t &d = out[k];
       d.id = u; d.parent = n.parent == 0 ? -1 : n.parent;
       d.num_pages = (int32_t)n.pages.size(); d.ref = n.ref; d.kind = n.kind; d.segment = n.segment;
-      d.num_children = (int32_t)n.child.size(); d.is_protected = n.is_protected;
-      d.end_offset = n.end_offset; d.hits = n.hits; d.last = n.last; d.priority = t->seg_priority(n);
+      d.num_children = n.children; d.is_protected = n.is_protected;
+      d.end_offset = n.end_offset; d.hits = n.hits; d.last = n.last; d.priority = t->node_prio[u];
     }
     ++k;
   }
@@ -880,17 +1007,22 @@ extern "C" int prism_dart_check(const prism_dart_t *t) {
   auto claim = [&](int32_t p) { if (p < base || p >= base + np) return false; return ++owner[p - base] == 1; };
   for (int32_t p : t->free_pages) if (!claim(p)) return PRISM_ERR_TABLE;
   std::vector<int32_t> ref(t->nodes.size(), 0);
-  int32_t tree_pages = 0, private_pages = 0;
+  std::vector<int32_t> children(t->nodes.size(), 0);
+  int32_t tree_pages = 0, private_pages = 0, linked = 0;
   for (int32_t u = 1; u < (int32_t)t->nodes.size(); ++u) {
     const Node &n = t->nodes[u];
     if (!n.attached) continue;
     if (n.pages.empty() || n.tok.size() != n.pages.size() * (size_t)ps) return PRISM_ERR_TABLE;
     for (int32_t p : n.pages) if (!claim(p)) return PRISM_ERR_TABLE;
     tree_pages += (int32_t)n.pages.size();
+    ++linked;
     if (n.parent < 0 || n.parent >= (int32_t)t->nodes.size() || !t->nodes[n.parent].attached) return PRISM_ERR_TABLE;
     if (t->find_child(n.parent, n.tok.data()) != u) return PRISM_ERR_TABLE;
-    for (auto &kv : n.child) if (t->nodes[kv.second].parent != u || !t->nodes[kv.second].attached) return PRISM_ERR_TABLE;
+    children[n.parent]++;
   }
+  if (t->table.used != (size_t)linked) return PRISM_ERR_TABLE;
+  for (size_t u = 0; u < t->nodes.size(); ++u)
+    if (t->nodes[u].attached && t->nodes[u].children != children[u]) return PRISM_ERR_TABLE;
   for (auto &kv : t->reqs) {
     const DReq &r = kv.second;
     for (size_t j = 0; j < r.row.size(); ++j)

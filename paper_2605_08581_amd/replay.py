@@ -69,6 +69,7 @@ def replay(trace: T.Trace, cfg: ReplayConfig, on_wave: Optional[Callable[[WaveRe
     reqs = trace.requests
     by_id = {r.id: r for r in reqs}
     seg_len = trace.segment_tokens
+    system_end, reusable = len(trace.system), [S.SPAN_REUSABLE] * max((len(r.skeleton) for r in reqs), default=0)
     nxt, t, busy_until = 0, 0.0, 0.0
     done_heap: list = []
     ttft, wave_sizes, gpu_ms, uncached_per_wave = [], [], [], []
@@ -88,20 +89,20 @@ def replay(trace: T.Trace, cfg: ReplayConfig, on_wave: Optional[Callable[[WaveRe
             qas.complete(rid)
             dart.release(rid)
         c0 = time.perf_counter()
-        hints, segs, pri = qas.round()
+        ids, seg_of, end_of, first, pri = qas.round_columns()
         t_sched += time.perf_counter() - c0
-        if not hints:
+        if not ids:
             continue
         c0 = time.perf_counter()
         dart.set_round(t, pri)
         t_tree += time.perf_counter() - c0
         rec = WaveRecord(t, [], [], [], [], [], 0.0)
-        for h in hints:
-            r = by_id[h.request]
-            mine = segs[h.first:h.first + h.num_segments]
-            tokens = trace.materialize(r, [s.segment for s in mine])
-            anchors = [(len(trace.system), S.SPAN_SYSTEM, -1)]
-            anchors += [(s.end_offset, S.SPAN_REUSABLE, s.segment) for s in mine]
+        for i, rid in enumerate(ids):
+            r = by_id[rid]
+            lo, hi = first[i], first[i + 1]
+            tokens = trace.materialize(r, seg_of[lo:hi])
+            anchors = [(system_end, S.SPAN_SYSTEM, -1)]
+            anchors += zip(end_of[lo:hi], reusable[:hi - lo], seg_of[lo:hi])
             anchors.append((len(tokens), S.SPAN_PRIVATE, -1))
             while True:
                 try:
@@ -140,7 +141,7 @@ def replay(trace: T.Trace, cfg: ReplayConfig, on_wave: Optional[Callable[[WaveRe
             ttft.append(busy_until - by_id[rid].arrival)
             heapq.heappush(done_heap, (busy_until + cfg.decode_tokens * cfg.t_token, rid))
         waves += 1
-        wave_sizes.append(len(hints))
+        wave_sizes.append(len(ids))
         uncached_per_wave.append(uncached)
         total_tokens += sum(rec.prompt_tokens)
         total_hit += sum(rec.hit_tokens)

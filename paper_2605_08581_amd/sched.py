@@ -1,6 +1,8 @@
-"""ctypes binding of the host control plane in libprism.so (argument marshalling
-only): the query-aware scheduler and the demand-aware radix tree declared in
-``include/prism_sched.h``.  Nothing here touches a device."""
+"""Binding of the host control plane in libprism.so (argument marshalling only):
+the query-aware scheduler and the demand-aware radix tree declared in
+``include/prism_sched.h``.  Nothing here touches a device.  Calls made for every
+request go through the C module ``_prism_sched`` (csrc/prism_pysched.cpp), the
+others through ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -42,6 +44,9 @@ class QasSegment(ctypes.Structure):
                 ("priority", f64)]
 
 
+_HINT, _SEGMENT = np.dtype(QasHint), np.dtype(QasSegment)
+
+
 class QasPriority(ctypes.Structure):
     _fields_ = [("segment", i32), ("g", i32), ("a", i32), ("n", i32), ("priority", f64)]
 
@@ -71,10 +76,11 @@ class DartNode(ctypes.Structure):
 
 
 _ready = False
+_fast = None                                     # the C module of the per-request calls
 
 
 def _lib():
-    global _ready
+    global _ready, _fast
     lib = B.load()
     if _ready:
         return lib
@@ -108,6 +114,11 @@ def _lib():
         fn = getattr(lib, name)
         if fn.restype is not None:
             fn.restype = ctypes.c_int
+    from . import _prism_sched as fast
+    fast.bind_api(*(ctypes.cast(f, vp).value for f in (lib.prism_qas_submit, lib.prism_qas_complete,
+                                                       lib.prism_dart_set_time, lib.prism_dart_admit,
+                                                       lib.prism_dart_commit, lib.prism_dart_release)))
+    _fast = fast
     _ready = True
     return lib
 
@@ -141,16 +152,27 @@ class Qas:
             o.alpha_size, o.beta_util = score_weights
         self._h = ctypes.c_void_p()
         _check(lib.prism_qas_create(ctypes.byref(o), ctypes.byref(self._h)), "prism_qas_create")
+        self._p = self._h.value
 
     def close(self):
         if getattr(self, "_h", None) and self._h.value:
             _lib().prism_qas_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._p = 0
 
     __del__ = close
 
     def submit(self, request: int, arrival: float, skeleton: Sequence[int], segment_tokens: Sequence[int],
                reorderable: Optional[Sequence[int]] = None, system_tokens: int = 0, suffix_tokens: int = 0):
+        if reorderable is None:
+            try:
+                rc = _fast.submit(self._p, request, arrival, skeleton, segment_tokens, system_tokens, suffix_tokens)
+            except TypeError:                    # other number types, other sequences
+                rc = _fast.submit(self._p, request, float(arrival), _i32(skeleton), _i32(segment_tokens),
+                                  int(system_tokens), int(suffix_tokens))
+            if rc < 0:
+                raise B.PrismError(rc, "prism_qas_submit")
+            return
         sk, st = _i32(skeleton), _i32(segment_tokens)
         ro = None
         if reorderable is not None:
@@ -160,10 +182,17 @@ class Qas:
                                        system_tokens, suffix_tokens), "prism_qas_submit")
 
     def complete(self, request: int):
-        _check(_lib().prism_qas_complete(self._h, request), "prism_qas_complete")
+        rc = _fast.complete(self._p, request)
+        if rc < 0:
+            raise B.PrismError(rc, "prism_qas_complete")
 
     def round(self):
         """Run one round; returns (hints, segments, priorities) as ctypes arrays."""
+        hints, n, segs, ns, pri = self._round()
+        return hints[:n], segs[:ns], pri
+
+    def _round(self):
+        """The same as whole ctypes arrays and their lengths."""
         lib = _lib()
         n = _check(lib.prism_qas_round(self._h), "prism_qas_round")
         hints = (QasHint * max(n, 1))()
@@ -174,7 +203,15 @@ class Qas:
         npri = _check(lib.prism_qas_round_priorities(self._h, None, 0), "prism_qas_round_priorities")
         pri = (QasPriority * max(npri, 1))()
         lib.prism_qas_round_priorities(self._h, pri, npri)
-        return list(hints[:n]), list(segs[:ns]), (pri, npri)
+        return hints, n, segs, ns, (pri, npri)
+
+    def round_columns(self):
+        """Run one round; returns (request ids, segment ids, end offsets, first segment of each request
+        plus the total, priorities): plain lists, for callers that need no more of the hints."""
+        hints, n, segs, ns, pri = self._round()
+        h = np.frombuffer(hints, dtype=_HINT)[:n]
+        s = np.frombuffer(segs, dtype=_SEGMENT)[:ns]
+        return h["request"].tolist(), s["segment"].tolist(), s["end_offset"].tolist(), h["first"].tolist() + [ns], pri
 
     @property
     def pending(self) -> int:
@@ -196,11 +233,13 @@ class Dart:
         self.page_size = page_size
         self._h = ctypes.c_void_p()
         _check(lib.prism_dart_create(ctypes.byref(o), ctypes.byref(self._h)), "prism_dart_create")
+        self._p = self._h.value
 
     def close(self):
         if getattr(self, "_h", None) and self._h.value:
             _lib().prism_dart_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._p = 0
 
     __del__ = close
 
@@ -218,27 +257,31 @@ class Dart:
         _check(_lib().prism_dart_set_round(self._h, float(now), arr, n), "prism_dart_set_round")
 
     def set_time(self, now: float):
-        _check(_lib().prism_dart_set_time(self._h, float(now)), "prism_dart_set_time")
+        _check(_fast.set_time(self._p, now), "prism_dart_set_time")
 
     def admit(self, request: int, tokens, anchors: Sequence[Tuple[int, int, int]] = (), reserve_tokens: int = 0):
         """Returns (hit_tokens, block_row ndarray)."""
-        tok = _i32(tokens)
-        pages = (len(tok) + reserve_tokens + self.page_size - 1) // self.page_size
-        row = np.full(max(pages, 1), -1, dtype=np.int32)
-        an = (DartAnchor * max(len(anchors), 1))()
-        for i, (off, kind, seg) in enumerate(anchors):
-            an[i] = DartAnchor(off, kind, seg)
-        hit = i32(0)
-        _check(_lib().prism_dart_admit(self._h, request, _p32(tok), len(tok), an, len(anchors), reserve_tokens,
-                                       _p32(row), len(row), ctypes.byref(hit)), "prism_dart_admit")
-        return hit.value, row
+        pages = (len(tokens) + reserve_tokens + self.page_size - 1) // self.page_size
+        row = np.empty(pages if pages > 0 else 1, dtype=np.int32)
+        try:
+            hit = _fast.admit(self._p, request, tokens, anchors, reserve_tokens, row)
+        except TypeError:                        # other number types, other sequences
+            hit = _fast.admit(self._p, request, _i32(tokens), [tuple(int(x) for x in a) for a in anchors],
+                              int(reserve_tokens), row)
+        if hit < 0:
+            raise B.PrismError(hit, "prism_dart_admit")
+        return hit, row
 
     def commit(self, request: int, row: np.ndarray) -> np.ndarray:
-        _check(_lib().prism_dart_commit(self._h, request, _p32(row), len(row)), "prism_dart_commit")
+        rc = _fast.commit(self._p, request, row)
+        if rc < 0:
+            raise B.PrismError(rc, "prism_dart_commit")
         return row
 
     def release(self, request: int):
-        _check(_lib().prism_dart_release(self._h, request), "prism_dart_release")
+        rc = _fast.release(self._p, request)
+        if rc < 0:
+            raise B.PrismError(rc, "prism_dart_release")
 
     def evict(self, k_free_tokens: int) -> Tuple[int, int]:
         freed = i32(0)

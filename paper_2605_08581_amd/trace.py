@@ -44,8 +44,8 @@ class Trace:
 
     def materialize(self, req: TraceRequest, order: Sequence[int]) -> np.ndarray:
         """Serialized prompt: system prefix, the segments in the given order, suffix."""
-        parts = [self.system] + [self.passages[r] for r in order] + [req.suffix]
-        return np.concatenate(parts).astype(np.int32)
+        segments = self.passages[np.asarray(order, dtype=np.intp)].ravel()
+        return np.concatenate((self.system, segments, req.suffix)).astype(np.int32, copy=False)
 
 
 def make_trace(n_requests: int = 2048, qps: float = 60.0, seed: int = 20260508, num_passages: int = 981,
