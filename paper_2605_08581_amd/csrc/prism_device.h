@@ -80,13 +80,6 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
 
-// 16 bytes per lane into registers, by inline assembly: for loads that stay in
-// flight beside the LDS copies.  The value is there after a wait_vmem that
-// covers it; pass it through an empty asm("+v") after that wait, and use it
-// nowhere before.
-__device__ __forceinline__ void load16_uncounted(bf16x8 &dst, const void *src) {
-  __asm__ volatile("global_load_dwordx4 %0, %1, off" : "=v"(dst) : "v"(src) : "memory");
-}
 // Wait until at most N vector memory operations of this wave are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmem() {

@@ -46,7 +46,10 @@ struct StreamShape {
   static constexpr int kRowPitch = D + 4;                   // floats; keeps 16 rows off one bank
   static constexpr size_t kRingBytes = (size_t)NW * NS * kTileBytes;
   static constexpr size_t kMergeBytes = (size_t)NW * kRows * (kRowPitch + 2) * sizeof(float);
-  static constexpr size_t kLdsBytes = (kRingBytes > kMergeBytes ? kRingBytes : kMergeBytes) + 16;
+  static constexpr size_t kQBytes = (size_t)kRows * D * 2;  // every wave has a copy: no barrier before its first use
+  static constexpr size_t kLdsBytes = kRingBytes + NW * kQBytes;
+  static_assert(kMergeBytes <= kRingBytes, "the merge works in the idle rings");
+  static_assert(kLdsBytes <= 160 * 1024, "LDS of a CU");
 };
 
 // largest / sum over the four 16-lane groups that hold one query row
@@ -72,7 +75,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   constexpr int DB = D / 16;                     // 16-wide head-dim blocks of O^T
   constexpr int TK = Shape::kTile;
   constexpr int COPIES = 2 * 2 * UPP;            // copies per tile: two pages of K and of V
-  static_assert((NS - 1) * COPIES <= 63, "pending copies must fit the vmcnt counter");
+  static_assert(NS * COPIES <= 63, "pending copies must fit the vmcnt counter");
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
@@ -87,20 +90,24 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   const int rows = S * G;                        // <= 16*RB: the planner's rule for this kernel
   const ConstantPtr<int32_t> bt = constant_ptr(p.block_table + (int64_t)it.req * p.max_blocks);
 
-  // ---- Q fragments: lane holds row c16, dims 32kk+8*g4..+7.  Loaded by inline
-  // assembly, like the copies: the compiler cannot count copies that it does not
-  // see and would otherwise drain them all before the first use of Q.
-  bf16x8 qf[RB][KK];
+  // ---- Q rows into LDS, by the same copies as the keys and before them, so that
+  // waiting for Q leaves the key copies in flight (loads into registers, which the
+  // compiler waits for, would drain them: it does not see the copies).  The copy of
+  // fragment (rb, kk) fetches for each lane the 16 bytes that the lane will read
+  // back: row c16, dims 32kk+8*g4..+7.  Row 0 stands in for rows past the end.
+  const uint32_t q_lds = lds_address(lds) + (uint32_t)(Shape::kRingBytes + wave * Shape::kQBytes);
   int limit[RB];                                 // last visible key of the lane's row
+  const i32x4 q_rows = block_resource((const __bf16 *)p.q + ((int64_t)it.q_off * p.Hq + it.kv_head * G) * D,
+                                      (uint32_t)(((S - 1) * p.Hq + G) * ROW));
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = rb * 16 + c16;
     const bool valid = row < rows;
     const int tok = valid ? row / G : 0, g = valid ? row % G : 0;
     limit[rb] = valid ? P + tok : -1;
-    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * p.Hq + it.kv_head * G + g) * D + 8 * g4;
+    const uint32_t off = (uint32_t)((tok * p.Hq + g) * ROW + 16 * g4);
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) load16_uncounted(qf[rb][kk], qp + 32 * kk);   // row 0 stands in for rows past the end
+    for (int kk = 0; kk < KK; ++kk) copy16_to_lds(q_rows, off + (uint32_t)(64 * kk), q_lds + (uint32_t)((rb * KK + kk) * 1024));
   }
 
   // ---- paged copies of this wave's tiles
@@ -191,16 +198,18 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
 #pragma unroll
   for (int t = 0; t < NS; ++t)
     if (t < mine) copy_tile(key0_of(t), pages_of(key0_of(t)), t);
-  if (mine >= NS) wait_vmem<NS * COPIES <= 63 ? NS * COPIES : 63>();   // Q was requested before any copy
+  if (mine >= NS) wait_vmem<NS * COPIES>();      // Q was requested before any key
   else wait_vmem<0>();
+  typedef __attribute__((address_space(3))) const bf16x8 *lds_b128_ptr;
+  typedef __attribute__((address_space(3))) s16x4 *lds_tr_ptr;
+  bf16x8 qf[RB][KK];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) __asm__ volatile("" : "+v"(qf[rb][kk]));
+    for (int kk = 0; kk < KK; ++kk)
+      qf[rb][kk] = *(lds_b128_ptr)(uintptr_t)(q_lds + (uint32_t)((rb * KK + kk) * 1024 + lane * 16));
 
   // per-lane LDS addresses of the fragment reads, relative to a tile slot
-  typedef __attribute__((address_space(3))) const bf16x8 *lds_b128_ptr;
-  typedef __attribute__((address_space(3))) s16x4 *lds_tr_ptr;
   uint32_t k_lane[KK], v_lane[DB];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) k_lane[kk] = lds_base + (uint32_t)lds_off<D>(c16, 4 * kk + g4);
@@ -353,7 +362,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
     }
   }
   if (slot_out) {
-    int *flag = reinterpret_cast<int *>(lds + Shape::kLdsBytes - 16);
+    int *flag = reinterpret_cast<int *>(lds + Shape::kRingBytes);   // Q is no longer needed
     if (last_of_group(p, it.group, tid, flag)) merge_group<D, 1, 8, true>(p, it.group, G, Shape::kRows, tid, NT, 0, Shape::kRows);
   }
 }
