@@ -9,6 +9,8 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <exception>
+
 #include <ATen/core/Tensor.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -177,14 +179,27 @@ PyObject *prefix_prefill_static(PyObject *, PyObject *const *a, Py_ssize_t n) {
   return PyLong_FromLong(g_api.prefill_static(c->plan, q, k, v, kp, vp, (const int32_t *)bt, out, stream()));
 }
 
+// A tensor without storage of its own, or a process without a device, makes
+// torch's accessors throw; that must not leave through the interpreter's C frames.
+template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
+  } catch (const std::exception &e) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+  }
+  return nullptr;
+}
+
+#define LAYER_CALL(f) (PyCFunction)(void (*)(void))guarded<f>, METH_FASTCALL, nullptr
 PyMethodDef methods[] = {
     {"bind_api", bind_api, METH_VARARGS, nullptr},
     {"make_call", make_call, METH_VARARGS, nullptr},
     {"close_call", close_call, METH_O, nullptr},
-    {"kv_append", (PyCFunction)(void (*)(void))kv_append, METH_FASTCALL, nullptr},
-    {"prefix_attention", (PyCFunction)(void (*)(void))prefix_attention, METH_FASTCALL, nullptr},
-    {"prefix_prefill", (PyCFunction)(void (*)(void))prefix_prefill, METH_FASTCALL, nullptr},
-    {"prefix_prefill_static", (PyCFunction)(void (*)(void))prefix_prefill_static, METH_FASTCALL, nullptr},
+    {"kv_append", LAYER_CALL(kv_append)},
+    {"prefix_attention", LAYER_CALL(prefix_attention)},
+    {"prefix_prefill", LAYER_CALL(prefix_prefill)},
+    {"prefix_prefill_static", LAYER_CALL(prefix_prefill_static)},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_prism_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -195,3 +195,22 @@ def test_measure_peaks_rejects_bad_arguments(lib):
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 16, 1, ctypes.byref(m), ctypes.byref(h), None) == B.ERR_INVALID_ARG
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 1 << 30, 0, ctypes.byref(m), ctypes.byref(h), None) == B.ERR_INVALID_ARG
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 1 << 30, 1, None, ctypes.byref(h), None) == B.ERR_INVALID_ARG
+
+
+def test_layer_call_that_torch_refuses_raises():
+    """Without a device torch has no current stream: an exception in Python, and not the end of the process."""
+    import subprocess
+    import sys
+    code = """
+from paper_2605_08581_amd import binding as B, workload as W
+b = W.make_custom_batch("x", W.Geometry(2, 2, 64), [16], [5], seed=1)
+plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len)
+for call, n in ((plan.prism_prefix_attention, 5), (plan.prism_prefix_prefill, 7)):
+    try:
+        call(*[None] * n)
+    except Exception as e:
+        print("raised")
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="", CUDA_VISIBLE_DEVICES="")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=env, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.split() == ["raised"] * 2, r.stderr[-2000:]
