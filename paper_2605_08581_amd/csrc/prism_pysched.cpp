@@ -36,6 +36,18 @@ bool integer(PyObject *o, long long *v) {
   Py_DECREF(n);
   return !(*v == -1 && PyErr_Occurred());
 }
+// A request's id: any integer, of which 64 bits count (ids may be unsigned hashes).
+bool request_of(PyObject *o, long long *v) {
+  if (!PyIndex_Check(o)) {
+    PyErr_SetString(PyExc_TypeError, "an integer is needed");
+    return false;
+  }
+  PyObject *n = PyNumber_Index(o);
+  if (!n) return false;
+  *v = (long long)PyLong_AsUnsignedLongLongMask(n);
+  Py_DECREF(n);
+  return true;
+}
 bool int32_of(PyObject *o, int32_t *v) {
   long long x;
   if (!integer(o, &x)) return false;
@@ -109,7 +121,7 @@ PyObject *submit(PyObject *, PyObject *const *a, Py_ssize_t n) {
   Int32s skel, tok;
   const double arrival = PyFloat_AsDouble(a[2]);
   if (arrival == -1.0 && PyErr_Occurred()) return nullptr;
-  if (!integer(a[1], &request) || !skel.take(a[3]) || !tok.take(a[4]) || !int32_of(a[5], &system) ||
+  if (!request_of(a[1], &request) || !skel.take(a[3]) || !tok.take(a[4]) || !int32_of(a[5], &system) ||
       !int32_of(a[6], &suffix))
     return nullptr;
   if (skel.n != tok.n) {
@@ -124,13 +136,13 @@ PyObject *submit(PyObject *, PyObject *const *a, Py_ssize_t n) {
 PyObject *complete(PyObject *, PyObject *const *a, Py_ssize_t n) {
   long long request;
   if (n != 2) return wrong_count("complete");
-  if (!integer(a[1], &request)) return nullptr;
+  if (!request_of(a[1], &request)) return nullptr;
   return PyLong_FromLong(g_api.complete((prism_qas_t *)handle(a[0]), request));
 }
 PyObject *release(PyObject *, PyObject *const *a, Py_ssize_t n) {
   long long request;
   if (n != 2) return wrong_count("release");
-  if (!integer(a[1], &request)) return nullptr;
+  if (!request_of(a[1], &request)) return nullptr;
   return PyLong_FromLong(g_api.release((prism_dart_t *)handle(a[0]), request));
 }
 
@@ -148,7 +160,7 @@ PyObject *admit(PyObject *, PyObject *const *a, Py_ssize_t n) {
   long long request;
   int32_t reserve, hit = 0;
   Int32s tok, row;
-  if (!integer(a[1], &request) || !tok.take(a[2]) || !int32_of(a[4], &reserve) || !row.take(a[5], true)) return nullptr;
+  if (!request_of(a[1], &request) || !tok.take(a[2]) || !int32_of(a[4], &reserve) || !row.take(a[5], true)) return nullptr;
   if (!PyList_Check(a[3]) && !PyTuple_Check(a[3])) {
     PyErr_SetString(PyExc_TypeError, "anchors: a list or tuple is needed");
     return nullptr;
@@ -176,7 +188,7 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (n != 3) return wrong_count("commit");
   long long request;
   Int32s row;
-  if (!integer(a[1], &request) || !row.take(a[2], true)) return nullptr;
+  if (!request_of(a[1], &request) || !row.take(a[2], true)) return nullptr;
   return PyLong_FromLong(g_api.commit((prism_dart_t *)handle(a[0]), request, row.data, (int32_t)row.n));
 }
 

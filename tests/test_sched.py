@@ -536,3 +536,14 @@ def test_replay_is_deterministic_and_qas_helps():
     shared = R.replay(tr, R.ReplayConfig(policy="dart", share_in_wave=True, **base), check_every=1)
     assert shared["in_wave_hit_tokens"] > 0 and a["in_wave_hit_tokens"] == 0
     assert shared["hit_rate"] > a["hit_rate"]
+
+
+def test_request_ids_are_64_bits():
+    """Ids that are unsigned hashes pass through as their 64 bits."""
+    q = S.Qas(2)
+    q.submit(2**64 - 5, 0.0, [1], [16])
+    q.submit(2**63, 1, [1], [16], reorderable=[1])
+    assert [r % 2**64 for r in _run_round(q)["dispatch"]] == [2**64 - 5, 2**63]
+    q.complete(2**64 - 5)
+    q.complete(2**63)
+    assert q.active == 0
