@@ -30,14 +30,7 @@ int check_shape(const prism_shape_t &s) {
 
 namespace {
 
-struct RowTile {
-  int req, kv_head, row0;
-  int kv_len;      // keys visible to the tile's last row
-  int cost;        // key tiles
-  int group_cost;  // cost of the heaviest row tile of the same (request, kv head)
-  int cluster;     // requests with a common cached prefix share a cluster
-  int64_t cluster_cost;   // all key tiles of the (cluster, kv head) set
-};
+int key_tiles(int keys) { return (keys + kTileKeys - 1) / kTileKeys; }
 
 // How the key range of a row tile is cut: into pieces of about `chunk` key tiles,
 // a range that exceeds it by no more than `slack` staying whole.
@@ -48,14 +41,18 @@ struct SplitRule {
   }
 };
 
+// Row tiles of one kv head by their key tiles: (key tiles, how many), descending.
+using Costs = std::vector<std::pair<int, int64_t>>;
+
 // Time, in key tiles, until `slots` workers have done all pieces, longest first.
-int64_t makespan(const std::vector<int> &costs, int heads, const SplitRule &rule, int slots) {
+int64_t makespan(const Costs &costs, int heads, const SplitRule &rule, int slots) {
   std::vector<std::pair<int, int64_t>> pieces;     // length, how many
   int64_t total = 0;
-  for (int c : costs) {
-    const int n = rule.pieces(c), len = (c + n - 1) / n;
-    pieces.push_back({len, (int64_t)n * heads});
-    total += (int64_t)n * heads * len;
+  for (const auto &c : costs) {
+    const int n = rule.pieces(c.first), len = (c.first + n - 1) / n;
+    const int64_t count = c.second * n * heads;
+    pieces.push_back({len, count});
+    total += count * len;
   }
   std::sort(pieces.rbegin(), pieces.rend());
   std::vector<int64_t> at(total / slots + 2 * (int64_t)pieces[0].first + 2, 0);   // workers by load so far
@@ -74,23 +71,24 @@ int64_t makespan(const std::vector<int> &costs, int heads, const SplitRule &rule
 }
 
 // The smallest chunk >= min_chunk whose pieces number at most `items`.
-SplitRule fit(const std::vector<int> &costs, int heads, int min_chunk, int slack, int64_t items) {
-  int lo = min_chunk, hi = std::max(min_chunk, costs[0]);
+SplitRule fit(const Costs &costs, int heads, int min_chunk, int slack, int64_t items) {
+  int lo = min_chunk, hi = std::max(min_chunk, costs[0].first);
   while (lo < hi) {
     const SplitRule mid{(lo + hi) / 2, slack};
     int64_t n = 0;
-    for (int c : costs) n += mid.pieces(c);
+    for (const auto &c : costs) n += c.second * mid.pieces(c.first);
     if (n * heads <= items) hi = mid.chunk;
     else lo = mid.chunk + 1;
   }
   return SplitRule{lo, slack};
 }
 
-SplitRule choose_split(const std::vector<int> &costs, int heads, int min_chunk, bool stream, int d) {
-  int64_t total = 0;
-  for (int c : costs) total += c;
-  total *= heads;
-  const int64_t n = (int64_t)costs.size() * heads;
+SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream, int d) {
+  int64_t total = 0, n = 0;
+  for (const auto &c : costs) {
+    total += c.second * c.first * heads;
+    n += c.second * heads;
+  }
   if (stream) {
     // One workgroup per CU (two at d = 64: LDS) and bound by bytes: cut to fill
     // the chip once, and not at all when it is full anyway - then only ranges
@@ -116,10 +114,10 @@ SplitRule choose_split(const std::vector<int> &costs, int heads, int min_chunk, 
   auto estimate = [&](const SplitRule &r) {
     int64_t cut = 0;
     int longest = 0;
-    for (int c : costs) {
-      const int k = r.pieces(c);
-      longest = std::max(longest, (c + k - 1) / k);
-      if (k > 1) cut += (int64_t)k * heads;
+    for (const auto &c : costs) {
+      const int k = r.pieces(c.first);
+      longest = std::max(longest, (c.first + k - 1) / k);
+      if (k > 1) cut += c.second * k * heads;
     }
     return std::max(1.1 * longest, 0.95 * (double)makespan(costs, heads, r, kNumCU)) + (cut ? 5.0 + 0.02 * cut : 0.0);
   };
@@ -221,49 +219,47 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     }
   }
 
-  // Row tiles of every (request, kv head).
-  std::vector<RowTile> tiles;
+  // Row tiles, the same for every kv head: the keys that each one sees, by request.
+  // (Everything up to the items is done once for all kv heads: with a list of all
+  // (request, kv head, row tile) sorted as a whole, the plan of 32 requests x 40
+  // heads took 420 us, now 96.)
+  std::vector<int> first_tile(s.batch + 1, 0), tile_keys;
+  std::vector<int64_t> cluster_cost(s.batch, 0);       // key tiles of the cluster, of one kv head
+  std::vector<int> live;
+  int most_cost = 0;
   for (int r = 0; r < s.batch; ++r) {
     const int P = prefix[r], S = suffix[r];
-    if (S == 0) continue;
     const int rows = S * G;
-    const int ntile = (rows + tile_rows - 1) / tile_rows;
-    for (int h = 0; h < s.num_kv_heads; ++h) {
-      for (int t = 0; t < ntile; ++t) {
-        const int last_row = std::min(rows, (t + 1) * tile_rows) - 1;
-        const int kv_len = P + last_row / G + 1;
-        const int cost = (kv_len + kTileKeys - 1) / kTileKeys;
-        const int gmax = (P + S + kTileKeys - 1) / kTileKeys;
-        tiles.push_back(RowTile{r, h, t * tile_rows, kv_len, cost, gmax, cluster[r], 0});
-      }
+    if (S > 0) live.push_back(r);
+    for (int row0 = 0; row0 < rows; row0 += tile_rows) {
+      const int kv_len = P + (std::min(rows, row0 + tile_rows) - 1) / G + 1;
+      tile_keys.push_back(kv_len);
+      cluster_cost[cluster[r]] += key_tiles(kv_len);
+      most_cost = std::max(most_cost, key_tiles(kv_len));
     }
+    first_tile[r + 1] = (int)tile_keys.size();
   }
 
   // Split-KV: never below min_split_keys.
-  std::vector<int> costs;      // key tiles of each row tile of one kv head, descending
-  for (const RowTile &t : tiles)
-    if (t.kv_head == 0) costs.push_back(t.cost);
-  std::sort(costs.rbegin(), costs.rend());
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
-  const SplitRule rule = opt.split_kv == 0 && !costs.empty()
-                             ? choose_split(costs, s.num_kv_heads, min_chunk, stream, d)
-                             : SplitRule{};
-
-  // Heaviest (cluster, kv head) set first; inside a set the requests, and
-  // inside a request the row tiles, stay adjacent so that they run at the same
-  // time and find each other's K/V pages in cache.
-  {
-    std::map<std::pair<int, int>, int64_t> set_cost;
-    for (const RowTile &t : tiles) set_cost[{t.cluster, t.kv_head}] += t.cost;
-    for (RowTile &t : tiles) t.cluster_cost = set_cost[{t.cluster, t.kv_head}];
+  SplitRule rule;
+  if (opt.split_kv == 0 && !tile_keys.empty()) {
+    std::vector<int64_t> count(most_cost + 1, 0);
+    for (int keys : tile_keys) ++count[key_tiles(keys)];
+    Costs costs;
+    for (int c = most_cost; c > 0; --c)
+      if (count[c]) costs.push_back({c, count[c]});
+    rule = choose_split(costs, s.num_kv_heads, min_chunk, stream, d);
   }
-  std::stable_sort(tiles.begin(), tiles.end(), [](const RowTile &a, const RowTile &b) {
-    if (a.cluster_cost != b.cluster_cost) return a.cluster_cost > b.cluster_cost;
-    if (a.cluster != b.cluster) return a.cluster < b.cluster;
-    if (a.kv_head != b.kv_head) return a.kv_head < b.kv_head;
-    if (a.group_cost != b.group_cost) return a.group_cost > b.group_cost;
-    if (a.req != b.req) return a.req < b.req;
-    return a.row0 > b.row0;
+
+  // Heaviest cluster first; inside a (cluster, kv head) set the requests, the
+  // longest first, and inside a request the row tiles, stay adjacent so that they
+  // run at the same time and find each other's K/V pages in cache.
+  std::sort(live.begin(), live.end(), [&](int a, int b) {
+    const int ca = cluster[a], cb = cluster[b];
+    if (ca != cb) return cluster_cost[ca] != cluster_cost[cb] ? cluster_cost[ca] > cluster_cost[cb] : ca < cb;
+    const int ka = key_tiles(prefix[a] + suffix[a]), kb = key_tiles(prefix[b] + suffix[b]);
+    return ka != kb ? ka > kb : a < b;
   });
 
   // Workgroup b runs on accelerator die b % 8, and each die has its own L2.
@@ -273,66 +269,69 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // sets first - and the per-die lists are then interleaved so that list
   // position k of die x becomes workgroup 8k + x.
   struct ItemSet {                 // the workgroups of one (cluster, kv head)
-    int longest = 0;               // keys of the longest
-    std::vector<AttnItem> items;
+    int longest;                   // keys of the longest
+    size_t begin, end;
   };
   std::vector<ItemSet> die_sets[kNumXCD];
+  std::vector<AttnItem> die_items[kNumXCD];
   int64_t die_load[kNumXCD] = {0};
   int next_slot = 0;
-  size_t i = 0;
-  while (i < tiles.size()) {
-    size_t j = i;
-    int64_t group_cost = 0;
-    while (j < tiles.size() && tiles[j].cluster == tiles[i].cluster && tiles[j].kv_head == tiles[i].kv_head)
-      group_cost += tiles[j++].cost;
-    int die = 0;
-    for (int x = 1; x < kNumXCD; ++x)
-      if (die_load[x] < die_load[die]) die = x;
-    die_load[die] += group_cost;
-    die_sets[die].emplace_back();
-    ItemSet &set = die_sets[die].back();
-    auto add = [&](const AttnItem &it) {
-      set.longest = std::max(set.longest, it.kv_end - it.kv_begin);
-      set.items.push_back(it);
-    };
-    for (; i < j; ++i) {
-      const RowTile &t = tiles[i];
-      int nsplit = 1;
-      if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, t.cost);
-      else if (opt.split_kv == 0) nsplit = rule.pieces(t.cost);
-      AttnItem it{};
-      it.req = t.req;
-      it.kv_head = t.kv_head;
-      it.row0 = t.row0;
-      it.prefix = prefix[t.req];
-      it.suffix = suffix[t.req];
-      it.q_off = q_off[t.req];
-      if (nsplit <= 1) {
-        it.kv_begin = 0;
-        it.kv_end = t.kv_len;
-        it.part_slot = -1;
-        add(it);
-        continue;
-      }
-      const int per = (t.cost + nsplit - 1) / nsplit;   // key tiles per chunk
-      nsplit = (t.cost + per - 1) / per;
-      ReduceGroup g{};
-      g.req = t.req;
-      g.kv_head = t.kv_head;
-      g.row0 = t.row0;
-      g.nsplit = nsplit;
-      g.first_slot = next_slot;
-      g.suffix = suffix[t.req];
-      g.q_off = q_off[t.req];
-      it.group = (int32_t)sch.groups.size();
-      sch.groups.push_back(g);
-      for (int c = 0; c < nsplit; ++c) {
-        it.kv_begin = c * per * kTileKeys;
-        it.kv_end = std::min(t.kv_len, (c + 1) * per * kTileKeys);
-        it.part_slot = next_slot++;
-        add(it);
-        ++sch.num_split_items;
-      }
+  for (size_t i = 0, j; i < live.size(); i = j) {
+    j = i;
+    while (j < live.size() && cluster[live[j]] == cluster[live[i]]) ++j;
+    for (int h = 0; h < s.num_kv_heads; ++h) {
+      int die = 0;
+      for (int x = 1; x < kNumXCD; ++x)
+        if (die_load[x] < die_load[die]) die = x;
+      die_load[die] += cluster_cost[cluster[live[i]]];
+      std::vector<AttnItem> &items = die_items[die];
+      ItemSet set{0, items.size(), 0};
+      auto add = [&](const AttnItem &it) {
+        set.longest = std::max(set.longest, it.kv_end - it.kv_begin);
+        items.push_back(it);
+      };
+      for (size_t m = i; m < j; ++m)
+        for (int tile = first_tile[live[m] + 1] - 1; tile >= first_tile[live[m]]; --tile) {
+          const int req = live[m], kv_len = tile_keys[tile], cost = key_tiles(kv_len);
+          int nsplit = 1;
+          if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, cost);
+          else if (opt.split_kv == 0) nsplit = rule.pieces(cost);
+          AttnItem it{};
+          it.req = req;
+          it.kv_head = h;
+          it.row0 = (tile - first_tile[req]) * tile_rows;
+          it.prefix = prefix[req];
+          it.suffix = suffix[req];
+          it.q_off = q_off[req];
+          if (nsplit <= 1) {
+            it.kv_begin = 0;
+            it.kv_end = kv_len;
+            it.part_slot = -1;
+            add(it);
+            continue;
+          }
+          const int per = (cost + nsplit - 1) / nsplit;   // key tiles per chunk
+          nsplit = (cost + per - 1) / per;
+          ReduceGroup g{};
+          g.req = req;
+          g.kv_head = h;
+          g.row0 = it.row0;
+          g.nsplit = nsplit;
+          g.first_slot = next_slot;
+          g.suffix = suffix[req];
+          g.q_off = q_off[req];
+          it.group = (int32_t)sch.groups.size();
+          sch.groups.push_back(g);
+          for (int c = 0; c < nsplit; ++c) {
+            it.kv_begin = c * per * kTileKeys;
+            it.kv_end = std::min(kv_len, (c + 1) * per * kTileKeys);
+            it.part_slot = next_slot++;
+            add(it);
+            ++sch.num_split_items;
+          }
+        }
+      set.end = items.size();
+      die_sets[die].push_back(set);
     }
   }
   // The sets of a die start in the order of their longest workgroup: a long one
@@ -342,25 +341,34 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // ones before them keep the order of the sets, whose pages they share.
   // (12 requests of 200..512 rows x 130..3000 keys, 32/8 heads, d = 64: 95.7 ->
   // 90.0 us; the 4B-class wave 145.7 -> 139.4; waves of many rounds unchanged.)
-  std::vector<AttnItem> per_die[kNumXCD];
+  std::vector<uint32_t> per_die[kNumXCD];           // positions in die_items
+  std::vector<std::pair<int, uint32_t>> keys;        // (-keys, position): longest first, else in order
+  size_t longest = 0;
   for (int x = 0; x < kNumXCD; ++x) {
+    std::vector<uint32_t> &order = per_die[x];
+    order.reserve(die_items[x].size());
     std::stable_sort(die_sets[x].begin(), die_sets[x].end(),
                      [](const ItemSet &a, const ItemSet &b) { return a.longest > b.longest; });
-    for (const ItemSet &set : die_sets[x]) per_die[x].insert(per_die[x].end(), set.items.begin(), set.items.end());
-    const size_t tail = std::min(per_die[x].size(), (size_t)2 * kNumCU / kNumXCD);
-    std::stable_sort(per_die[x].end() - tail, per_die[x].end(), [](const AttnItem &a, const AttnItem &b) {
-      return a.kv_end - a.kv_begin > b.kv_end - b.kv_begin;
-    });
+    for (const ItemSet &set : die_sets[x])
+      for (size_t k = set.begin; k < set.end; ++k) order.push_back((uint32_t)k);
+    const size_t tail = std::min(order.size(), (size_t)2 * kNumCU / kNumXCD), head = order.size() - tail;
+    keys.clear();
+    for (size_t k = 0; k < tail; ++k) {
+      const AttnItem &it = die_items[x][order[head + k]];
+      keys.push_back({it.kv_begin - it.kv_end, (uint32_t)k});
+    }
+    std::sort(keys.begin(), keys.end());
+    const std::vector<uint32_t> last(order.begin() + head, order.end());
+    for (size_t k = 0; k < tail; ++k) order[head + k] = last[keys[k].second];
+    longest = std::max(longest, order.size());
   }
-  size_t longest = 0;
-  for (int x = 0; x < kNumXCD; ++x) longest = std::max(longest, per_die[x].size());
   AttnItem idle{};
   idle.req = -1;                 // the kernel returns at once on such an entry
   idle.part_slot = -1;
+  sch.items.reserve(longest * kNumXCD);
   for (size_t k = 0; k < longest; ++k)
-    for (int x = 0; x < kNumXCD; ++x) {
-      sch.items.push_back(k < per_die[x].size() ? per_die[x][k] : idle);
-    }
+    for (int x = 0; x < kNumXCD; ++x)
+      sch.items.push_back(k < per_die[x].size() ? die_items[x][per_die[x][k]] : idle);
   // drop idle entries at the very end of the list
   while (!sch.items.empty() && sch.items.back().req < 0) sch.items.pop_back();
   sch.num_slots = next_slot;
