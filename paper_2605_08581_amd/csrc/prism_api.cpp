@@ -273,7 +273,11 @@ int do_attention(const prism_plan *plan, const void *q, const void *k_new, const
 // Append, then attention; in one kernel where the plan allows it.
 int do_prefill(const prism_plan *plan, const void *q, const void *k_suffix, const void *v_suffix, void *k_pool,
                void *v_pool, const int32_t *bt, void *out, unsigned char *lists_dev, void *stream) {
-  if (plan->sch.fused_append && appends_itself(plan))
+  // The attention kernels fetch new rows 16 bytes at a time straight into LDS, which
+  // unlike loads into registers takes no address at will: rows that do not lie on
+  // 16 bytes go by the append kernel.
+  const bool aligned = (((uintptr_t)k_suffix | (uintptr_t)v_suffix) & 15) == 0;
+  if (plan->sch.fused_append && appends_itself(plan) && aligned)
     return do_attention(plan, q, k_suffix, v_suffix, k_pool, v_pool, bt, out, lists_dev, stream);
   int rc = do_append(plan, k_suffix, v_suffix, k_pool, v_pool, bt, stream);
   if (rc != PRISM_OK) return rc;

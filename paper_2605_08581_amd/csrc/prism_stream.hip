@@ -95,6 +95,8 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   // compiler waits for, would drain them: it does not see the copies).  The copy of
   // fragment (rb, kk) fetches for each lane the 16 bytes that the lane will read
   // back: row c16, dims 32kk+8*g4..+7.  Row 0 stands in for rows past the end.
+  // Q rows that do not lie on 16 bytes, which those copies do not promise to take,
+  // go through registers, element by element.
   const uint32_t q_lds = lds_address(lds) + (uint32_t)(Shape::kRingBytes + wave * Shape::kQBytes);
   int limit[RB];                                 // last visible key of the lane's row
   const i32x4 q_rows = block_resource((const __bf16 *)p.q + ((int64_t)it.q_off * p.Hq + it.kv_head * G) * D,
@@ -107,7 +109,18 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
     limit[rb] = valid ? P + tok : -1;
     const uint32_t off = (uint32_t)((tok * p.Hq + g) * ROW + 16 * g4);
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) copy16_to_lds(q_rows, off + (uint32_t)(64 * kk), q_lds + (uint32_t)((rb * KK + kk) * 1024));
+    for (int kk = 0; kk < KK; ++kk) {
+      const uint32_t dst = q_lds + (uint32_t)((rb * KK + kk) * 1024);
+      if (((uintptr_t)p.q & 15) == 0) {
+        copy16_to_lds(q_rows, off + (uint32_t)(64 * kk), dst);
+      } else {
+        const __bf16 *from = (const __bf16 *)p.q + ((int64_t)it.q_off * p.Hq + it.kv_head * G) * D + off / 2 + 32 * kk;
+        bf16x8 x;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = from[e];
+        *(__attribute__((address_space(3))) bf16x8 *)(uintptr_t)(dst + (uint32_t)(lane * 16)) = x;
+      }
+    }
   }
 
   // ---- paged copies of this wave's tiles

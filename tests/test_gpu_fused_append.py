@@ -35,3 +35,18 @@ def test_key_ranges_share_the_append(oracle_lib, split_kv, geom):
     b = W.make_custom_batch("ranges", geom, [0, 300, 1000, 77], [300, 150, 70, 400], seed=72)
     info = full_parity(oracle_lib, b, split_kv=split_kv)
     assert info.num_reduce_groups > 0
+
+
+@pytest.mark.parametrize("moved", [["q"], ["k_suffix"], ["v_suffix"], ["q", "k_suffix", "v_suffix"]], ids="-".join)
+@pytest.mark.parametrize("suffix", [[3, 1, 16], [40, 130, 7]], ids=["few-rows", "tiles"])
+def test_rows_off_the_16_byte_grid(oracle_lib, suffix, moved):
+    """Contiguous inputs that start 8 bytes past a 16-byte boundary: views into a larger buffer."""
+    def mutate(t):
+        for name in moved:
+            x = t[name]
+            buf = torch.empty(x.numel() + 4, dtype=x.dtype, device=x.device)
+            t[name] = buf[4:].view(x.shape)
+            t[name].copy_(x)
+            assert t[name].is_contiguous() and t[name].data_ptr() % 16 == 8
+    full_parity(oracle_lib, W.make_custom_batch("views", W.Geometry(4, 2, 128), [0, 37, 500], suffix, seed=73),
+                mutate=mutate)
