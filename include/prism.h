@@ -98,7 +98,8 @@ typedef struct prism_plan_options {
    * prefix lies in pages this very wave appends to; prism_prefix_prefill may
    * then append inside the attention kernel instead of before it, so the copy
    * must match the device table of the calls.  NULL = no placement hint, and
-   * always two kernels.                                                        */
+   * always two kernels; the same where k_suffix or v_suffix does not start on
+   * a 16-byte boundary.                                                        */
   const int32_t *block_table_host;
 } prism_plan_options_t;
 
