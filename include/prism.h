@@ -200,7 +200,8 @@ int prism_prefix_prefill(const prism_plan_t *plan, const void *q, const void *k_
  * image (each GPU the library runs on holds one until the process ends); the
  * call allocates nothing.  A plan whose prism_plan_workspace_bytes exceeds
  * PRISM_STATIC_SCRATCH_BYTES is refused with PRISM_ERR_WORKSPACE_TOO_SMALL
- * (prism_last_hip_error has the text).  Every call on a GPU shares that GPU's
+ * (prism_last_hip_error has the text); with automatic cuts (split_kv = 0) that
+ * happens only to work lists that do not fit even uncut.  Every call on a GPU shares that GPU's
  * array: calls must be ordered on one stream (or otherwise not overlap), also
  * across plans; the array keeps the last call's contents and nothing in it
  * needs clearing between calls.  Results are those of prism_prefix_prefill.

@@ -41,8 +41,6 @@ struct EventPair {
 constexpr size_t kMaxPendingTimings = 1 << 16;   // event pairs kept until prism_plan_profile_read
 std::atomic<uint64_t> g_plan_serial{1};
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 // Pinned host memory for the plans' work lists.  Releasing pinned memory makes
 // the runtime wait for every stream of the device, so blocks are never handed
 // back to it: a destroyed plan's block goes on a free list (by power-of-two
@@ -297,13 +295,6 @@ void fill_info(const Schedule &sch, prism_plan_info_t *out) {
   out->kv_bytes_per_request = sch.kv_bytes;
 }
 
-// Bytes of workspace: work lists (256-byte aligned parts), then partial slots.
-void layout_sizes(const Schedule &sch, size_t *items_b, size_t *lists_b, size_t *total_b) {
-  *items_b = align_up(sch.items.size() * sizeof(AttnItem), 256);
-  *lists_b = *items_b + align_up(sch.groups.size() * sizeof(ReduceGroup), 256);
-  *total_b = *lists_b + sch.workspace_bytes;
-}
-
 int check_workspace(const prism_plan *plan, const void *workspace, size_t bytes) {
   if (plan->total_bytes == 0) return PRISM_OK;
   if (!workspace) return PRISM_ERR_INVALID_ARG;
@@ -381,7 +372,9 @@ int prism_plan_create(const prism_shape_t *shape, const int32_t *prefix_len_host
   }
   p->scale_log2e = shape->softmax_scale * 1.4426950408889634f;
   p->serial = g_plan_serial.fetch_add(1);
-  layout_sizes(p->sch, &p->items_bytes, &p->lists_bytes, &p->total_bytes);
+  p->items_bytes = items_bytes(p->sch);
+  p->lists_bytes = lists_bytes(p->sch);
+  p->total_bytes = p->lists_bytes + p->sch.workspace_bytes;
   if (p->lists_bytes > 0) {
     // pinned, so that the upload is a true asynchronous copy
     void *h = g_pinned.take(p->lists_bytes, &p->host_pinned, &p->host_capacity);
@@ -415,11 +408,7 @@ int prism_plan_dry_run(const prism_shape_t *shape, const int32_t *prefix_len_hos
   }
   if (rc != PRISM_OK) return rc;
   if (info) fill_info(sch, info);
-  if (workspace_bytes) {
-    size_t items_b, lists_b, total_b;
-    layout_sizes(sch, &items_b, &lists_b, &total_b);
-    *workspace_bytes = total_b;
-  }
+  if (workspace_bytes) *workspace_bytes = lists_bytes(sch) + sch.workspace_bytes;
   if (items_out) {
     for (size_t i = 0; i < sch.items.size() && (int32_t)i < items_capacity; ++i) {
       const AttnItem &it = sch.items[i];   // idle padding entries have req = -1

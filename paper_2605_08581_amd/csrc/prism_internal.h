@@ -80,6 +80,13 @@ inline size_t partial_slot_bytes(int tile_rows, int d) {
   return (size_t)tile_rows * (size_t)(d + 2) * sizeof(float);
 }
 
+// Bytes of the work lists in front of the partial slots: items, then groups, each
+// padded to 256 bytes.
+inline size_t items_bytes(const Schedule &sch) { return (sch.items.size() * sizeof(AttnItem) + 255) / 256 * 256; }
+inline size_t lists_bytes(const Schedule &sch) {
+  return items_bytes(sch) + (sch.groups.size() * sizeof(ReduceGroup) + 255) / 256 * 256;
+}
+
 // Host planner (prism_plan.cpp).  Returns PRISM_OK or an error code.
 int check_shape(const prism_shape_t &s);
 int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,

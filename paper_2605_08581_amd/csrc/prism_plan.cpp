@@ -83,6 +83,23 @@ SplitRule fit(const Costs &costs, int heads, int min_chunk, int slack, int64_t i
   return SplitRule{lo, slack};
 }
 
+// The same rule with the smallest larger chunk that leaves at most `slots` pieces
+// of cut ranges.
+SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t slots) {
+  const bool follows = rule.slack == rule.chunk;
+  auto with = [&](int chunk) { return SplitRule{chunk, follows ? chunk : rule.slack}; };
+  int lo = rule.chunk + 1, hi = std::max(lo, costs[0].first);   // the largest cuts nothing
+  while (lo < hi) {
+    const SplitRule mid = with((lo + hi) / 2);
+    int64_t n = 0;
+    for (const auto &c : costs)
+      if (mid.pieces(c.first) > 1) n += c.second * mid.pieces(c.first);
+    if (n * heads <= slots) hi = mid.chunk;
+    else lo = mid.chunk + 1;
+  }
+  return with(lo);
+}
+
 SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream, int d) {
   int64_t total = 0, n = 0;
   for (const auto &c : costs) {
@@ -243,10 +260,10 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // Split-KV: never below min_split_keys.
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
   SplitRule rule;
+  Costs costs;
   if (opt.split_kv == 0 && !tile_keys.empty()) {
     std::vector<int64_t> count(most_cost + 1, 0);
     for (int keys : tile_keys) ++count[key_tiles(keys)];
-    Costs costs;
     for (int c = most_cost; c > 0; --c)
       if (count[c]) costs.push_back({c, count[c]});
     rule = choose_split(costs, s.num_kv_heads, min_chunk, stream, d);
@@ -262,117 +279,134 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     return ka != kb ? ka > kb : a < b;
   });
 
-  // Workgroup b runs on accelerator die b % 8, and each die has its own L2.
-  // Row tiles (and key chunks) of one (request, kv head), and of requests with
-  // a common cached prefix, read the same K/V pages, so each (cluster, kv
-  // head) set is dealt whole to one die - the least loaded so far, heaviest
-  // sets first - and the per-die lists are then interleaved so that list
-  // position k of die x becomes workgroup 8k + x.
-  struct ItemSet {                 // the workgroups of one (cluster, kv head)
-    int longest;                   // keys of the longest
-    size_t begin, end;
+  auto deal = [&](const SplitRule &rule) {
+    sch.items.clear();
+    sch.groups.clear();
+    sch.num_split_items = 0;
+    // Workgroup b runs on accelerator die b % 8, and each die has its own L2.
+    // Row tiles (and key chunks) of one (request, kv head), and of requests with
+    // a common cached prefix, read the same K/V pages, so each (cluster, kv
+    // head) set is dealt whole to one die - the least loaded so far, heaviest
+    // sets first - and the per-die lists are then interleaved so that list
+    // position k of die x becomes workgroup 8k + x.
+    struct ItemSet {                 // the workgroups of one (cluster, kv head)
+      int longest;                   // keys of the longest
+      size_t begin, end;
+    };
+    std::vector<ItemSet> die_sets[kNumXCD];
+    std::vector<AttnItem> die_items[kNumXCD];
+    int64_t die_load[kNumXCD] = {0};
+    int next_slot = 0;
+    for (size_t i = 0, j; i < live.size(); i = j) {
+      j = i;
+      while (j < live.size() && cluster[live[j]] == cluster[live[i]]) ++j;
+      for (int h = 0; h < s.num_kv_heads; ++h) {
+        int die = 0;
+        for (int x = 1; x < kNumXCD; ++x)
+          if (die_load[x] < die_load[die]) die = x;
+        die_load[die] += cluster_cost[cluster[live[i]]];
+        std::vector<AttnItem> &items = die_items[die];
+        ItemSet set{0, items.size(), 0};
+        auto add = [&](const AttnItem &it) {
+          set.longest = std::max(set.longest, it.kv_end - it.kv_begin);
+          items.push_back(it);
+        };
+        for (size_t m = i; m < j; ++m)
+          for (int tile = first_tile[live[m] + 1] - 1; tile >= first_tile[live[m]]; --tile) {
+            const int req = live[m], kv_len = tile_keys[tile], cost = key_tiles(kv_len);
+            int nsplit = 1;
+            if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, cost);
+            else if (opt.split_kv == 0) nsplit = rule.pieces(cost);
+            AttnItem it{};
+            it.req = req;
+            it.kv_head = h;
+            it.row0 = (tile - first_tile[req]) * tile_rows;
+            it.prefix = prefix[req];
+            it.suffix = suffix[req];
+            it.q_off = q_off[req];
+            if (nsplit <= 1) {
+              it.kv_begin = 0;
+              it.kv_end = kv_len;
+              it.part_slot = -1;
+              add(it);
+              continue;
+            }
+            const int per = (cost + nsplit - 1) / nsplit;   // key tiles per chunk
+            nsplit = (cost + per - 1) / per;
+            ReduceGroup g{};
+            g.req = req;
+            g.kv_head = h;
+            g.row0 = it.row0;
+            g.nsplit = nsplit;
+            g.first_slot = next_slot;
+            g.suffix = suffix[req];
+            g.q_off = q_off[req];
+            it.group = (int32_t)sch.groups.size();
+            sch.groups.push_back(g);
+            for (int c = 0; c < nsplit; ++c) {
+              it.kv_begin = c * per * kTileKeys;
+              it.kv_end = std::min(kv_len, (c + 1) * per * kTileKeys);
+              it.part_slot = next_slot++;
+              add(it);
+              ++sch.num_split_items;
+            }
+          }
+        set.end = items.size();
+        die_sets[die].push_back(set);
+      }
+    }
+    // The sets of a die start in the order of their longest workgroup: a long one
+    // that starts late runs on alone.  (In the order of total work, in which they
+    // are dealt, a request of few rows over a long prefix comes last.)  For the
+    // same reason the last two workgroups per CU go strictly longest first; the
+    // ones before them keep the order of the sets, whose pages they share.
+    // (12 requests of 200..512 rows x 130..3000 keys, 32/8 heads, d = 64: 95.7 ->
+    // 90.0 us; the 4B-class wave 145.7 -> 139.4; waves of many rounds unchanged.)
+    std::vector<uint32_t> per_die[kNumXCD];           // positions in die_items
+    std::vector<std::pair<int, uint32_t>> keys;        // (-keys, position): longest first, else in order
+    size_t longest = 0;
+    for (int x = 0; x < kNumXCD; ++x) {
+      std::vector<uint32_t> &order = per_die[x];
+      order.reserve(die_items[x].size());
+      std::stable_sort(die_sets[x].begin(), die_sets[x].end(),
+                       [](const ItemSet &a, const ItemSet &b) { return a.longest > b.longest; });
+      for (const ItemSet &set : die_sets[x])
+        for (size_t k = set.begin; k < set.end; ++k) order.push_back((uint32_t)k);
+      const size_t tail = std::min(order.size(), (size_t)2 * kNumCU / kNumXCD), head = order.size() - tail;
+      keys.clear();
+      for (size_t k = 0; k < tail; ++k) {
+        const AttnItem &it = die_items[x][order[head + k]];
+        keys.push_back({it.kv_begin - it.kv_end, (uint32_t)k});
+      }
+      std::sort(keys.begin(), keys.end());
+      const std::vector<uint32_t> last(order.begin() + head, order.end());
+      for (size_t k = 0; k < tail; ++k) order[head + k] = last[keys[k].second];
+      longest = std::max(longest, order.size());
+    }
+    AttnItem idle{};
+    idle.req = -1;                 // the kernel returns at once on such an entry
+    idle.part_slot = -1;
+    sch.items.reserve(longest * kNumXCD);
+    for (size_t k = 0; k < longest; ++k)
+      for (int x = 0; x < kNumXCD; ++x)
+        sch.items.push_back(k < per_die[x].size() ? die_items[x][per_die[x][k]] : idle);
+    // drop idle entries at the very end of the list
+    while (!sch.items.empty() && sch.items.back().req < 0) sch.items.pop_back();
+    sch.num_slots = next_slot;
+    sch.workspace_bytes = (size_t)next_slot * partial_slot_bytes(tile_rows, d);
   };
-  std::vector<ItemSet> die_sets[kNumXCD];
-  std::vector<AttnItem> die_items[kNumXCD];
-  int64_t die_load[kNumXCD] = {0};
-  int next_slot = 0;
-  for (size_t i = 0, j; i < live.size(); i = j) {
-    j = i;
-    while (j < live.size() && cluster[live[j]] == cluster[live[i]]) ++j;
-    for (int h = 0; h < s.num_kv_heads; ++h) {
-      int die = 0;
-      for (int x = 1; x < kNumXCD; ++x)
-        if (die_load[x] < die_load[die]) die = x;
-      die_load[die] += cluster_cost[cluster[live[i]]];
-      std::vector<AttnItem> &items = die_items[die];
-      ItemSet set{0, items.size(), 0};
-      auto add = [&](const AttnItem &it) {
-        set.longest = std::max(set.longest, it.kv_end - it.kv_begin);
-        items.push_back(it);
-      };
-      for (size_t m = i; m < j; ++m)
-        for (int tile = first_tile[live[m] + 1] - 1; tile >= first_tile[live[m]]; --tile) {
-          const int req = live[m], kv_len = tile_keys[tile], cost = key_tiles(kv_len);
-          int nsplit = 1;
-          if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, cost);
-          else if (opt.split_kv == 0) nsplit = rule.pieces(cost);
-          AttnItem it{};
-          it.req = req;
-          it.kv_head = h;
-          it.row0 = (tile - first_tile[req]) * tile_rows;
-          it.prefix = prefix[req];
-          it.suffix = suffix[req];
-          it.q_off = q_off[req];
-          if (nsplit <= 1) {
-            it.kv_begin = 0;
-            it.kv_end = kv_len;
-            it.part_slot = -1;
-            add(it);
-            continue;
-          }
-          const int per = (cost + nsplit - 1) / nsplit;   // key tiles per chunk
-          nsplit = (cost + per - 1) / per;
-          ReduceGroup g{};
-          g.req = req;
-          g.kv_head = h;
-          g.row0 = it.row0;
-          g.nsplit = nsplit;
-          g.first_slot = next_slot;
-          g.suffix = suffix[req];
-          g.q_off = q_off[req];
-          it.group = (int32_t)sch.groups.size();
-          sch.groups.push_back(g);
-          for (int c = 0; c < nsplit; ++c) {
-            it.kv_begin = c * per * kTileKeys;
-            it.kv_end = std::min(kv_len, (c + 1) * per * kTileKeys);
-            it.part_slot = next_slot++;
-            add(it);
-            ++sch.num_split_items;
-          }
-        }
-      set.end = items.size();
-      die_sets[die].push_back(set);
-    }
+  deal(rule);
+  // A plan of the library's own choosing fits the scratch of the entry that takes
+  // no workspace whenever its uncut form does: it is cut less until it fits.
+  // (Four rounds of 128-row pieces at d = 128, the most that the rule above
+  // chooses, are 65 MiB of partials.)
+  while (rule.chunk && sch.num_slots) {
+    const size_t lists = lists_bytes(sch);
+    if (lists + sch.workspace_bytes <= PRISM_STATIC_SCRATCH_BYTES) break;
+    const size_t room = lists < PRISM_STATIC_SCRATCH_BYTES ? PRISM_STATIC_SCRATCH_BYTES - lists : 0;
+    rule = coarser(costs, s.num_kv_heads, rule, (int64_t)(room / partial_slot_bytes(tile_rows, d)));
+    deal(rule);
   }
-  // The sets of a die start in the order of their longest workgroup: a long one
-  // that starts late runs on alone.  (In the order of total work, in which they
-  // are dealt, a request of few rows over a long prefix comes last.)  For the
-  // same reason the last two workgroups per CU go strictly longest first; the
-  // ones before them keep the order of the sets, whose pages they share.
-  // (12 requests of 200..512 rows x 130..3000 keys, 32/8 heads, d = 64: 95.7 ->
-  // 90.0 us; the 4B-class wave 145.7 -> 139.4; waves of many rounds unchanged.)
-  std::vector<uint32_t> per_die[kNumXCD];           // positions in die_items
-  std::vector<std::pair<int, uint32_t>> keys;        // (-keys, position): longest first, else in order
-  size_t longest = 0;
-  for (int x = 0; x < kNumXCD; ++x) {
-    std::vector<uint32_t> &order = per_die[x];
-    order.reserve(die_items[x].size());
-    std::stable_sort(die_sets[x].begin(), die_sets[x].end(),
-                     [](const ItemSet &a, const ItemSet &b) { return a.longest > b.longest; });
-    for (const ItemSet &set : die_sets[x])
-      for (size_t k = set.begin; k < set.end; ++k) order.push_back((uint32_t)k);
-    const size_t tail = std::min(order.size(), (size_t)2 * kNumCU / kNumXCD), head = order.size() - tail;
-    keys.clear();
-    for (size_t k = 0; k < tail; ++k) {
-      const AttnItem &it = die_items[x][order[head + k]];
-      keys.push_back({it.kv_begin - it.kv_end, (uint32_t)k});
-    }
-    std::sort(keys.begin(), keys.end());
-    const std::vector<uint32_t> last(order.begin() + head, order.end());
-    for (size_t k = 0; k < tail; ++k) order[head + k] = last[keys[k].second];
-    longest = std::max(longest, order.size());
-  }
-  AttnItem idle{};
-  idle.req = -1;                 // the kernel returns at once on such an entry
-  idle.part_slot = -1;
-  sch.items.reserve(longest * kNumXCD);
-  for (size_t k = 0; k < longest; ++k)
-    for (int x = 0; x < kNumXCD; ++x)
-      sch.items.push_back(k < per_die[x].size() ? die_items[x][per_die[x][k]] : idle);
-  // drop idle entries at the very end of the list
-  while (!sch.items.empty() && sch.items.back().req < 0) sch.items.pop_back();
-  sch.num_slots = next_slot;
-  sch.workspace_bytes = (size_t)next_slot * partial_slot_bytes(tile_rows, d);
   *out = std::move(sch);
   return PRISM_OK;
 }

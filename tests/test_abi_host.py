@@ -151,6 +151,30 @@ def test_planner_forced_and_disabled_split(lib):
     assert _check_cover(W.make_config(2), 0, 0).num_reduce_groups == 0
 
 
+SCRATCH = 64 << 20                             # PRISM_STATIC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("prefix,suffix", [([21234, 27950, 30066], [394, 200, 307]),
+                                           ([15614, 17014, 17805, 18118, 17242], [363, 252, 414, 373, 377])])
+@pytest.mark.parametrize("tile_rows", [0, 64, 256])
+def test_automatic_cuts_fit_the_static_scratch(lib, prefix, suffix, tile_rows):
+    """Waves whose pieces at four workgroups per CU would not fit it."""
+    b = W.make_custom_batch("scratch", W.Geometry(32, 8, 128), prefix, suffix, seed=1)
+    assert _check_cover(b, tile_rows, 0).num_split_items > 0
+    assert B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, tile_rows=tile_rows)[1] <= SCRATCH
+
+
+def test_automatic_cuts_of_random_waves_fit_the_static_scratch(lib):
+    rng = np.random.default_rng(7)
+    for _ in range(400):
+        n, hkv = int(rng.integers(2, 25)), int(rng.choice([1, 2, 8, 40]))
+        prefix, suffix = rng.integers(16384, 65537, n), rng.integers(33, 401, n)
+        sh = B.make_shape(hkv * int(rng.choice([1, 4])), hkv, 128, 1 << 16, n, 4200, 0.1)
+        for tile_rows, width in ((0, 0), (256, 64)):
+            ws = B.prism_plan_dry_run(sh, prefix, suffix, tile_rows=tile_rows, rows_per_wave=width)[1]
+            assert ws <= SCRATCH, (sh.num_q_heads, hkv, prefix.tolist(), suffix.tolist(), tile_rows)
+
+
 def test_placement_hint_keeps_prefix_sharers_on_one_die(lib):
     """With a host block table, requests whose tables start with the same page
     (a common cached prefix) run the same kv head on the same die."""
