@@ -96,6 +96,18 @@ struct Int32s {
   }
 };
 
+// The entry points run without the interpreter's lock: an eviction or a round
+// over a long queue lets other Python threads go on.
+struct Unlocked {
+  PyThreadState *state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <class F, class... Args>
+int call_unlocked(F *entry, Args... args) {
+  Unlocked unlocked;
+  return entry(args...);
+}
+
 PyObject *wrong_count(const char *what) {
   PyErr_Format(PyExc_TypeError, "%s: wrong number of arguments", what);
   return nullptr;
@@ -128,8 +140,8 @@ PyObject *submit(PyObject *, PyObject *const *a, Py_ssize_t n) {
     PyErr_SetString(PyExc_ValueError, "skeleton and segment_tokens must have the same length");
     return nullptr;
   }
-  return PyLong_FromLong(g_api.submit((prism_qas_t *)handle(a[0]), request, arrival, skel.data, tok.data, nullptr,
-                                      (int32_t)skel.n, system, suffix));
+  return PyLong_FromLong(call_unlocked(g_api.submit, (prism_qas_t *)handle(a[0]), request, arrival, skel.data, tok.data,
+                                       nullptr, (int32_t)skel.n, system, suffix));
 }
 
 // complete(qas, request) / release(dart, request)
@@ -137,20 +149,20 @@ PyObject *complete(PyObject *, PyObject *const *a, Py_ssize_t n) {
   long long request;
   if (n != 2) return wrong_count("complete");
   if (!request_of(a[1], &request)) return nullptr;
-  return PyLong_FromLong(g_api.complete((prism_qas_t *)handle(a[0]), request));
+  return PyLong_FromLong(call_unlocked(g_api.complete, (prism_qas_t *)handle(a[0]), request));
 }
 PyObject *release(PyObject *, PyObject *const *a, Py_ssize_t n) {
   long long request;
   if (n != 2) return wrong_count("release");
   if (!request_of(a[1], &request)) return nullptr;
-  return PyLong_FromLong(g_api.release((prism_dart_t *)handle(a[0]), request));
+  return PyLong_FromLong(call_unlocked(g_api.release, (prism_dart_t *)handle(a[0]), request));
 }
 
 PyObject *set_time(PyObject *, PyObject *const *a, Py_ssize_t n) {
   if (n != 2) return wrong_count("set_time");
   const double now = PyFloat_AsDouble(a[1]);
   if (now == -1.0 && PyErr_Occurred()) return nullptr;
-  return PyLong_FromLong(g_api.set_time((prism_dart_t *)handle(a[0]), now));
+  return PyLong_FromLong(call_unlocked(g_api.set_time, (prism_dart_t *)handle(a[0]), now));
 }
 
 // admit(dart, request, tokens, anchors, reserve_tokens, row): the hit length, or a
@@ -179,8 +191,8 @@ PyObject *admit(PyObject *, PyObject *const *a, Py_ssize_t n) {
       return nullptr;
   }
   for (Py_ssize_t i = 0; i < row.n; ++i) row.data[i] = -1;
-  const int rc = g_api.admit((prism_dart_t *)handle(a[0]), request, tok.data, (int32_t)tok.n, anchors.data(), (int32_t)m,
-                             reserve, row.data, (int32_t)row.n, &hit);
+  const int rc = call_unlocked(g_api.admit, (prism_dart_t *)handle(a[0]), request, tok.data, (int32_t)tok.n,
+                               anchors.data(), (int32_t)m, reserve, row.data, (int32_t)row.n, &hit);
   return PyLong_FromLong(rc < 0 ? rc : hit);
 }
 
@@ -189,7 +201,8 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
   long long request;
   Int32s row;
   if (!request_of(a[1], &request) || !row.take(a[2], true)) return nullptr;
-  return PyLong_FromLong(g_api.commit((prism_dart_t *)handle(a[0]), request, row.data, (int32_t)row.n));
+  return PyLong_FromLong(
+      call_unlocked(g_api.commit, (prism_dart_t *)handle(a[0]), request, row.data, (int32_t)row.n));
 }
 
 #define FAST(f) (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr

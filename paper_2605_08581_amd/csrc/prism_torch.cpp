@@ -80,6 +80,22 @@ bool raw_pointer(PyObject *o, void **ptr) {       // unchecked, for calls that t
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
+// The entry points run without the interpreter's lock: a launch waits when the
+// stream's queue is full, and other Python threads go on meanwhile.
+template <class F, class... Args>
+PyObject *call_unlocked(F *entry, Args... args) {
+  struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+  };
+  long rc;
+  {
+    Unlocked unlocked;
+    rc = entry(args...);
+  }
+  return PyLong_FromLong(rc);
+}
+
 PyObject *wrong_count(const char *what) {
   PyErr_Format(PyExc_TypeError, "%s: wrong number of arguments", what);
   return nullptr;
@@ -120,7 +136,7 @@ PyObject *kv_append(PyObject *, PyObject *const *a, Py_ssize_t n) {
       !fits(a[3], at::kBFloat16, c->pool, &kp) || !fits(a[4], at::kBFloat16, c->pool, &vp) ||
       !fits(a[5], at::kInt, c->table, &bt))
     return PyLong_FromLong(kRefused);
-  return PyLong_FromLong(g_api.append(c->plan, k, v, kp, vp, (const int32_t *)bt, stream()));
+  return call_unlocked(g_api.append, c->plan, k, v, kp, vp, (const int32_t *)bt, stream());
 }
 
 // prefix_attention(call, q, k_pool, v_pool, block_table, out, workspace)
@@ -140,7 +156,7 @@ PyObject *prefix_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
          raw_pointer(a[5], &out);
   }
   if (!ok) return PyLong_FromLong(kRefused);
-  return PyLong_FromLong(g_api.attention(c->plan, q, kp, vp, (const int32_t *)bt, out, ws, bytes, stream()));
+  return call_unlocked(g_api.attention, c->plan, q, kp, vp, (const int32_t *)bt, out, ws, bytes, stream());
 }
 
 // prefix_prefill(call, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out, workspace)
@@ -161,8 +177,7 @@ PyObject *prefix_prefill(PyObject *, PyObject *const *a, Py_ssize_t n) {
          raw_pointer(a[5], &vp) && raw_pointer(a[6], &bt) && raw_pointer(a[7], &out);
   }
   if (!ok) return PyLong_FromLong(kRefused);
-  return PyLong_FromLong(
-      g_api.prefill(c->plan, q, k, v, kp, vp, (const int32_t *)bt, out, ws, bytes, stream()));
+  return call_unlocked(g_api.prefill, c->plan, q, k, v, kp, vp, (const int32_t *)bt, out, ws, bytes, stream());
 }
 
 // prefix_prefill_static(call, q, k_suffix, v_suffix, k_pool, v_pool, block_table, out)
@@ -176,7 +191,7 @@ PyObject *prefix_prefill_static(PyObject *, PyObject *const *a, Py_ssize_t n) {
       !fits(a[5], at::kBFloat16, c->pool, &vp) || !fits(a[6], at::kInt, c->table, &bt) ||
       !fits(a[7], at::kBFloat16, c->q, &out))
     return PyLong_FromLong(kRefused);
-  return PyLong_FromLong(g_api.prefill_static(c->plan, q, k, v, kp, vp, (const int32_t *)bt, out, stream()));
+  return call_unlocked(g_api.prefill_static, c->plan, q, k, v, kp, vp, (const int32_t *)bt, out, stream());
 }
 
 // A tensor without storage of its own, or a process without a device, makes

@@ -1,0 +1,34 @@
+"""Layer calls from Python: what happens around the entry points themselves."""
+import ctypes
+import threading
+
+import pytest
+
+from paper_2605_08581_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def test_other_threads_run_during_a_layer_call():
+    """The entries are replaced by libc's usleep, which takes the plan as its microseconds: every call
+    then lasts 0.4 s, and another Python thread has to get its turns within it (one that
+    waits for the call to end gets one)."""
+    lib = B.load()
+    real = [ctypes.cast(f, ctypes.c_void_p).value for f in (lib.prism_kv_append, lib.prism_prefix_attention,
+                                                            lib.prism_prefix_prefill, lib.prism_prefix_prefill_static)]
+    fast, usleep = B._fast, ctypes.cast(ctypes.CDLL(None).usleep, ctypes.c_void_p).value
+    call = fast.make_call(400000, 0, 0, 0, 0, 0)   # no elements are needed, so None will do for every tensor
+    fast.bind_api(*[usleep] * 4)
+    try:
+        for entry, n in ((fast.kv_append, 5), (fast.prefix_attention, 6), (fast.prefix_prefill, 8),
+                         (fast.prefix_prefill_static, 7)):
+            turns, over = [], threading.Event()
+            other = threading.Thread(target=lambda: [turns.append(1) for _ in range(1000) if not over.wait(0.005)])
+            other.start()
+            status = entry(call, *[None] * n)
+            got = len(turns)
+            over.set()
+            other.join()
+            assert status == 0 and got >= 5, entry.__name__
+    finally:
+        fast.bind_api(*real)

@@ -3,6 +3,8 @@ hand-worked round, a plain-Python reference written from the paper, brute-force
 prefix matching, and the invariants of Alg. 1 / Alg. 2.  No GPU."""
 import os
 import random
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -547,3 +549,29 @@ def test_request_ids_are_64_bits():
     q.complete(2**64 - 5)
     q.complete(2**63)
     assert q.active == 0
+
+
+def test_other_threads_run_during_a_call():
+    """The entries are replaced by libc's usleep, which takes the handle as its microseconds: every
+    per-request call then lasts 0.4 s, and another Python thread has to get its turns within it
+    (one that waits for the call to end gets one)."""
+    code = """
+import ctypes, threading
+import numpy as np
+from paper_2605_08581_amd import sched as S
+S._lib()
+fast, usleep = S._fast, ctypes.cast(ctypes.CDLL(None).usleep, ctypes.c_void_p).value
+fast.bind_api(*[usleep] * 6)
+us, row = 400000, np.zeros(1, dtype=np.int32)
+for call in (lambda: fast.submit(us, 1, 0.0, [1], [16], 0, 0), lambda: fast.complete(us, 1), lambda: fast.set_time(us, 1.0),
+             lambda: fast.admit(us, 1, [1], [], 0, row), lambda: fast.commit(us, 1, row), lambda: fast.release(us, 1)):
+    turns, over = [], threading.Event()
+    other = threading.Thread(target=lambda: [turns.append(1) for _ in range(1000) if not over.wait(0.005)])
+    other.start()
+    assert call() == 0
+    print(int(len(turns) >= 5))
+    over.set()
+    other.join()
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.split() == ["1"] * 6, r.stdout + r.stderr[-2000:]
