@@ -65,7 +65,7 @@ bool workspace_of(PyObject *o, const Call *c, void **ptr, size_t *bytes, bool *o
   const at::Tensor &t = THPVariable_Unpack(o);
   *ptr = t.data_ptr();
   *bytes = (size_t)t.numel() * t.element_size();
-  if (t.numel() < c->workspace) return false;
+  if (*bytes < (size_t)c->workspace) return false;   // in bytes, as the library compares them
   *ok = t.is_cuda() && t.is_contiguous() && t.scalar_type() == at::kByte;
   return true;
 }

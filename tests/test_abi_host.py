@@ -9,6 +9,7 @@ import sys
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_08581_amd import binding as B
 from paper_2605_08581_amd import workload as W
@@ -239,6 +240,26 @@ def test_measure_peaks_rejects_bad_arguments(lib):
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 16, 1, ctypes.byref(m), ctypes.byref(h), None) == B.ERR_INVALID_ARG
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 1 << 30, 0, ctypes.byref(m), ctypes.byref(h), None) == B.ERR_INVALID_ARG
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 1 << 30, 1, None, ctypes.byref(h), None) == B.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("make", [lambda n: torch.empty(-(-n // 4), dtype=torch.float32),
+                                  lambda n: torch.empty(-(-n // 4) * 2, dtype=torch.float32)[::2],
+                                  lambda n: torch.empty(n, dtype=torch.uint8)],
+                         ids=["few-wide-elements", "strided", "host"])
+def test_workspace_of_another_kind_is_refused(lib, make):
+    """Large enough in bytes, so the library would take the pointer: the tensors, here all on the host,
+    must be checked before it sees the call."""
+    b = W.make_custom_batch("ws", W.Geometry(4, 2, 64), [32, 5], [20, 9], seed=2)
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, split_kv=2)
+    n, ws = plan.prism_plan_workspace_bytes(), make(plan.prism_plan_workspace_bytes())
+    assert n > 0 and ws.numel() * ws.element_size() >= n
+    t = W.make_tensors(b, "cpu")
+    table, out = torch.from_numpy(b.block_table), torch.empty_like(t["q"])
+    with pytest.raises(ValueError):
+        plan.prism_prefix_attention(t["q"], t["k_pool"], t["v_pool"], table, out, ws)
+    with pytest.raises(ValueError):
+        plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"], table, out, ws)
+    plan.close()
 
 
 def test_layer_call_that_torch_refuses_raises():

@@ -3,8 +3,10 @@ import ctypes
 import threading
 
 import pytest
+import torch
 
 from paper_2605_08581_amd import binding as B
+from paper_2605_08581_amd import workload as W
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +34,19 @@ def test_other_threads_run_during_a_layer_call():
             assert status == 0 and got >= 5, entry.__name__
     finally:
         fast.bind_api(*real)
+
+
+def test_workspace_of_wide_elements_is_refused():
+    """As many bytes as the plan needs, in floats."""
+    b = W.make_custom_batch("ws", W.Geometry(4, 2, 64), [32, 5], [20, 9], seed=2)
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, split_kv=2)
+    t, table = W.make_tensors(b, "cuda"), torch.from_numpy(b.block_table).cuda()
+    out = torch.zeros_like(t["q"])
+    ws = torch.empty(-(-plan.prism_plan_workspace_bytes() // 4), dtype=torch.float32, device="cuda")
+    with pytest.raises(ValueError, match="workspace"):
+        plan.prism_prefix_attention(t["q"], t["k_pool"], t["v_pool"], table, out, ws)
+    with pytest.raises(ValueError, match="workspace"):
+        plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"], table, out, ws)
+    torch.cuda.synchronize()
+    assert not out.any()
+    plan.close()
