@@ -173,6 +173,8 @@ int prism_kv_append(const prism_plan_t *plan, const void *k_suffix, const void *
 /*
  * Attention only: the pools must already hold the suffix KV (for example from
  * prism_kv_append earlier on the same stream).  Writes out[sum_S][Hq][d].
+ * k_pool and v_pool start on a 16-byte boundary, here and in both prefill calls
+ * (PRISM_ERR_INVALID_ARG otherwise).
  * workspace is DEVICE memory, 256-byte aligned, of at least
  * prism_plan_workspace_bytes (NULL only when that is 0).  Fails with
  * PRISM_ERR_UNSUPPORTED on a device that is not gfx950 with 256 compute units.

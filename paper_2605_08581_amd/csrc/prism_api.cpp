@@ -303,6 +303,14 @@ int check_workspace(const prism_plan *plan, const void *workspace, size_t bytes)
   return PRISM_OK;
 }
 
+// Every attention kernel copies pool pages 16 bytes at a time straight into LDS,
+// which promises nothing for other addresses: such pools would give wrong keys
+// without an error.
+int check_pools(const void *k_pool, const void *v_pool) {
+  if ((((uintptr_t)k_pool | (uintptr_t)v_pool) & 15) == 0) return PRISM_OK;
+  return fail_with(PRISM_ERR_INVALID_ARG, "k_pool and v_pool must start on a 16-byte boundary");
+}
+
 // Lists into the caller's workspace unless they are there already.
 int ensure_lists(const prism_plan *plan, void *workspace, void *stream) {
   if (plan->lists_bytes == 0 || plan->lists_in == workspace) return PRISM_OK;
@@ -470,6 +478,8 @@ int prism_prefix_attention(const prism_plan_t *plan, const void *q, const void *
   int rc = check_workspace(plan, workspace, workspace_bytes);
   if (rc != PRISM_OK) return rc;
   if (plan->sch.items.empty()) return PRISM_OK;
+  rc = check_pools(k_pool, v_pool);
+  if (rc != PRISM_OK) return rc;
   rc = check_device();
   if (rc != PRISM_OK) return rc;
   rc = ensure_lists(plan, workspace, hip_stream);
@@ -487,6 +497,8 @@ int prism_prefix_prefill(const prism_plan_t *plan, const void *q, const void *k_
   int rc = check_workspace(plan, workspace, workspace_bytes);
   if (rc != PRISM_OK) return rc;
   if (plan->sch.total_suffix == 0) return PRISM_OK;
+  rc = check_pools(k_pool, v_pool);
+  if (rc != PRISM_OK) return rc;
   rc = check_device();
   if (rc != PRISM_OK) return rc;
   rc = ensure_lists(plan, workspace, hip_stream);
@@ -505,7 +517,9 @@ int prism_prefix_prefill_static(const prism_plan_t *plan, const void *q, const v
                      "this plan needs more scratch than prism_prefix_prefill_static holds; "
                      "use prism_prefix_prefill with a caller workspace");
   if (plan->sch.total_suffix == 0) return PRISM_OK;
-  int rc = check_device();
+  int rc = check_pools(k_pool, v_pool);
+  if (rc != PRISM_OK) return rc;
+  rc = check_device();
   if (rc != PRISM_OK) return rc;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);

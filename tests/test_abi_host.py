@@ -242,6 +242,20 @@ def test_measure_peaks_rejects_bad_arguments(lib):
     assert lib.prism_measure_peaks(ctypes.c_void_p(4096), 1 << 30, 1, None, ctypes.byref(h), None) == B.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("k_off,v_off", [(8, 0), (0, 2), (4, 4)])
+@pytest.mark.parametrize("suffix", [[3, 1], [200, 40]], ids=["few-rows", "tiles"])
+def test_pools_off_the_16_byte_grid_are_refused(lib, suffix, k_off, v_off):
+    """Refused before anything is launched: the addresses here belong to nobody."""
+    b = W.make_custom_batch("off", W.Geometry(4, 2, 64), [32, 5], suffix, seed=2)
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len)
+    at, n = ctypes.c_void_p(1 << 20), plan.prism_plan_workspace_bytes()
+    k, v = ctypes.c_void_p((1 << 20) + k_off), ctypes.c_void_p((1 << 20) + v_off)
+    assert lib.prism_prefix_attention(plan._h, at, k, v, at, at, at, n, None) == B.ERR_INVALID_ARG
+    assert lib.prism_prefix_prefill(plan._h, at, at, at, k, v, at, at, at, n, None) == B.ERR_INVALID_ARG
+    assert lib.prism_prefix_prefill_static(plan._h, at, at, at, k, v, at, at, None) == B.ERR_INVALID_ARG
+    plan.close()
+
+
 @pytest.mark.parametrize("make", [lambda n: torch.empty(-(-n // 4), dtype=torch.float32),
                                   lambda n: torch.empty(-(-n // 4) * 2, dtype=torch.float32)[::2],
                                   lambda n: torch.empty(n, dtype=torch.uint8)],
