@@ -89,17 +89,21 @@ typedef struct prism_plan_options {
   int32_t min_split_keys;      /* auto split: smallest KV chunk, multiple of 64        */
   int32_t rows_per_wave;       /* query rows per wavefront: 32 or 64 (64 needs tile_rows
                                   128 or 256: two or four waves, one per SIMD)         */
-  int32_t reserved[4];
+  int32_t table_is_final;      /* nonzero: block_table_host is the table that every call
+                                  with this plan finds on the device, see there          */
+  int32_t reserved[3];
   /* Optional HOST copy of the block table (int32 [batch][max_blocks_per_req]),
    * read only during plan creation.  Requests whose tables start with the same
    * page share a cached prefix (exact-prefix reuse, Eq. 3); the planner then
    * runs their workgroups next to each other on one die so that the shared
-   * pages are fetched from HBM once.  It also shows that no request's cached
-   * prefix lies in pages this very wave appends to; prism_prefix_prefill may
-   * then append inside the attention kernel instead of before it, so the copy
-   * must match the device table of the calls.  NULL = no placement hint, and
-   * always two kernels; the same where k_suffix or v_suffix does not start on
-   * a 16-byte boundary.                                                        */
+   * pages are fetched from HBM once.  NULL = no placement hint.
+   * By itself the copy only places work, and results are right whatever it
+   * holds.  With table_is_final it also shows that no request's cached prefix
+   * lies in pages this very wave appends to; the prefill calls may then append
+   * inside the attention kernel instead of before it.  Results are undefined if
+   * the device table then differs from the copy in any entry a request uses.
+   * The calls take two kernels all the same where k_suffix or v_suffix does not
+   * start on a 16-byte boundary.                                               */
   const int32_t *block_table_host;
 } prism_plan_options_t;
 
@@ -114,7 +118,8 @@ typedef struct prism_plan_info {
   int32_t num_reduce_groups;   /* (request, kv head, row tile) groups merged from parts*/
   int32_t total_suffix;        /* sum_S                                                */
   int32_t rows_per_wave;       /* query rows per wavefront                             */
-  int32_t reserved[1];
+  int32_t append_in_attention; /* 1: the prefill calls append inside the attention kernel
+                                  (unless rows do not lie on 16 bytes)                 */
   int64_t flops;               /* 4*d*Hq*sum_r(S_r*P_r + S_r(S_r+1)/2): unmasked pairs */
   int64_t kv_bytes_per_request;/* K and V bytes of every request's whole sequence      */
 } prism_plan_info_t;

@@ -52,7 +52,7 @@ class Shape(ctypes.Structure):
 class PlanOptions(ctypes.Structure):
     _fields_ = [("tile_rows", ctypes.c_int32), ("split_kv", ctypes.c_int32),
                 ("min_split_keys", ctypes.c_int32), ("rows_per_wave", ctypes.c_int32),
-                ("reserved", ctypes.c_int32 * 4),
+                ("table_is_final", ctypes.c_int32), ("reserved", ctypes.c_int32 * 3),
                 ("block_table_host", ctypes.c_void_p)]
 
 
@@ -60,7 +60,7 @@ class PlanInfo(ctypes.Structure):
     _fields_ = [("tile_rows", ctypes.c_int32), ("tile_keys", ctypes.c_int32),
                 ("num_items", ctypes.c_int32), ("num_split_items", ctypes.c_int32),
                 ("num_reduce_groups", ctypes.c_int32), ("total_suffix", ctypes.c_int32),
-                ("rows_per_wave", ctypes.c_int32), ("reserved", ctypes.c_int32 * 1), ("flops", ctypes.c_int64),
+                ("rows_per_wave", ctypes.c_int32), ("append_in_attention", ctypes.c_int32), ("flops", ctypes.c_int64),
                 ("kv_bytes_per_request", ctypes.c_int64)]
 
 
@@ -172,9 +172,9 @@ def prism_validate(shape: Shape, prefix_len, suffix_len, block_table) -> int:
     return int(load().prism_validate(ctypes.byref(shape), pl.ctypes.data, sl.ctypes.data, bt.ctypes.data))
 
 
-def _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave=0):
+def _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave=0, table_is_final=True):
     """PlanOptions plus the host array it points to (keep both alive during the call)."""
-    opt = PlanOptions(tile_rows, split_kv, min_split_keys, rows_per_wave)
+    opt = PlanOptions(tile_rows, split_kv, min_split_keys, rows_per_wave, int(table_is_final))
     bt = None
     if block_table is not None:
         bt = _host_i32(block_table)
@@ -183,11 +183,12 @@ def _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave=0):
 
 
 def prism_plan_dry_run(shape: Shape, prefix_len, suffix_len, tile_rows: int = 0, split_kv: int = 0,
-                       min_split_keys: int = 0, block_table=None, rows_per_wave: int = 0):
+                       min_split_keys: int = 0, block_table=None, rows_per_wave: int = 0,
+                       table_is_final: bool = True):
     """Host-only schedule: returns (PlanInfo, workspace_bytes, items int32 [n, 8])."""
     lib = load()
     pl, sl = _host_i32(prefix_len), _host_i32(suffix_len)
-    opt, _bt = _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave)
+    opt, _bt = _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave, table_is_final)
     info, ws = PlanInfo(), ctypes.c_size_t()
     n = lib.prism_plan_dry_run(ctypes.byref(shape), pl.ctypes.data, sl.ctypes.data, ctypes.byref(opt),
                                ctypes.byref(info), ctypes.byref(ws), None, 0)
@@ -201,10 +202,14 @@ def prism_plan_dry_run(shape: Shape, prefix_len, suffix_len, tile_rows: int = 0,
 
 
 class Plan:
-    """Owns a prism_plan_t*.  Methods are the C entry points of the same name."""
+    """Owns a prism_plan_t*.  Methods are the C entry points of the same name.
+
+    ``block_table`` is the host copy of the table that the calls get on the device.  For a copy that only
+    resembles it (a plan made early, or used with other tables later) pass ``table_is_final=False``: it then
+    places work and nothing else depends on it."""
 
     def __init__(self, shape: Shape, prefix_len, suffix_len, tile_rows: int = 0, split_kv: int = 0,
-                 min_split_keys: int = 0, block_table=None, rows_per_wave: int = 0):
+                 min_split_keys: int = 0, block_table=None, rows_per_wave: int = 0, table_is_final: bool = True):
         lib = load()
         self._lib = lib
         self._h = ctypes.c_void_p()
@@ -214,7 +219,7 @@ class Plan:
             raise ValueError("prefix_len/suffix_len must have `batch` entries")
         if block_table is not None and tuple(np.shape(block_table)) != (shape.batch, shape.max_blocks_per_req):
             raise ValueError("block_table must be [batch, max_blocks_per_req]")
-        opt, _bt = _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave)
+        opt, _bt = _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave, table_is_final)
         self._total_suffix = int(sl.sum())
         rc = lib.prism_plan_create(ctypes.byref(shape), pl.ctypes.data, sl.ctypes.data,
                                    ctypes.byref(opt), ctypes.byref(self._h))

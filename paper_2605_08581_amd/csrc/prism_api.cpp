@@ -230,9 +230,8 @@ int do_append(const prism_plan *plan, const void *k_suffix, const void *v_suffix
   return PRISM_OK;
 }
 
-// Which of the attention kernels merge split partials, and append, themselves.
+// Which of the attention kernels merge split partials themselves.
 bool merges_itself(const prism_plan *p) { return p->sch.stream; }
-bool appends_itself(const prism_plan *p) { return p->sch.stream || p->sch.rows_per_wave == 32; }
 
 // One asynchronous copy of the work lists into the first bytes of dst.
 int upload_lists(const prism_plan *plan, void *dst, void *stream) {
@@ -275,7 +274,7 @@ int do_prefill(const prism_plan *plan, const void *q, const void *k_suffix, cons
   // unlike loads into registers takes no address at will: rows that do not lie on
   // 16 bytes go by the append kernel.
   const bool aligned = (((uintptr_t)k_suffix | (uintptr_t)v_suffix) & 15) == 0;
-  if (plan->sch.fused_append && appends_itself(plan) && aligned)
+  if (plan->sch.fused_append && aligned)
     return do_attention(plan, q, k_suffix, v_suffix, k_pool, v_pool, bt, out, lists_dev, stream);
   int rc = do_append(plan, k_suffix, v_suffix, k_pool, v_pool, bt, stream);
   if (rc != PRISM_OK) return rc;
@@ -291,6 +290,7 @@ void fill_info(const Schedule &sch, prism_plan_info_t *out) {
   out->num_reduce_groups = (int32_t)sch.groups.size();
   out->total_suffix = (int32_t)sch.total_suffix;
   out->rows_per_wave = sch.rows_per_wave;
+  out->append_in_attention = sch.fused_append;
   out->flops = sch.flops;
   out->kv_bytes_per_request = sch.kv_bytes;
 }

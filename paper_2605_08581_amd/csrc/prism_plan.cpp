@@ -244,7 +244,9 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   sch.stream = stream;
   sch.tile_rows = tile_rows;
   sch.rows_per_wave = stream ? tile_rows : rows_per_wave;
-  sch.fused_append = opt.block_table_host && !reads_pages_of_this_wave(s, prefix, suffix, opt.block_table_host);
+  // Both kernels that do it take 32 rows a wave at most.
+  sch.fused_append = (stream || rows_per_wave == 32) && opt.block_table_host && opt.table_is_final &&
+                     !reads_pages_of_this_wave(s, prefix, suffix, opt.block_table_host);
 
   sch.q_off = q_off;
 

@@ -196,6 +196,26 @@ def test_placement_hint_keeps_prefix_sharers_on_one_die(lib):
     assert all(len(v) == 1 for v in die.values())
 
 
+def test_append_inside_attention_needs_a_final_table(lib):
+    """A table that is only a placement hint may differ from the one on the device: nothing but the order
+    of the work follows from it.  Options that a caller has zeroed say just that."""
+    b = W.make_custom_batch("hint", W.Geometry(4, 2, 128), [32, 48], [20, 200], seed=1)
+    args = (B.shape_of(b), b.prefix_len, b.suffix_len)
+    fused = lambda **kw: B.prism_plan_dry_run(*args, **kw)[0].append_in_attention
+    assert fused(block_table=b.block_table) == 1
+    assert fused(block_table=b.block_table, table_is_final=False) == 0
+    assert fused() == 0
+    assert fused(block_table=b.block_table, rows_per_wave=64) == 0
+    table = b.block_table.copy()
+    table[1, :3] = table[0, :3]                # a cached prefix that the same wave writes
+    assert fused(block_table=table) == 0
+    opt, info = B.PlanOptions(), B.PlanInfo()
+    opt.block_table_host = b.block_table.ctypes.data
+    lib.prism_plan_dry_run(ctypes.byref(args[0]), args[1].ctypes.data, args[2].ctypes.data, ctypes.byref(opt),
+                           ctypes.byref(info), None, None, 0)
+    assert info.num_items > 0 and info.append_in_attention == 0
+
+
 def test_plan_needs_no_memory_for_pages_outside_the_wave(lib):
     """A pool of 2^30 pages: an array over it (4 GiB) does not fit the limit set here."""
     code = """

@@ -8,6 +8,8 @@ import torch
 from paper_2605_08581_amd import binding as B
 from paper_2605_08581_amd import workload as W
 
+from gpu_util import check_close, widen
+
 pytestmark = pytest.mark.gpu
 
 
@@ -50,3 +52,25 @@ def test_workspace_of_wide_elements_is_refused():
     torch.cuda.synchronize()
     assert not out.any()
     plan.close()
+
+
+@pytest.mark.parametrize("suffix", [[20, 20], [150, 40]], ids=["stream", "tile"])
+def test_a_table_that_is_only_a_hint_may_differ(oracle_lib, suffix):
+    """On the device the second request's cached prefix is what the first one appends in this very call;
+    the table that the plan was made from does not show it."""
+    b = W.make_custom_batch("hint", W.Geometry(2, 2, 128), [32, 48], suffix, seed=65)
+    table = b.block_table.copy()
+    table[1, :3] = table[0, :3]                    # positions 32..47 of request 0 are new tokens
+    t = W.make_tensors(b, "cuda")
+    host = {k: W.bf16_bits(v) for k, v in t.items()}
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table, table_is_final=False)
+    ws = torch.empty(plan.prism_plan_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    out = torch.full_like(t["q"], float("nan"))
+    plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"],
+                              torch.from_numpy(table).cuda(), out, ws)
+    torch.cuda.synchronize()
+    plan.close()
+    kp, vp = oracle_lib.kv_append(host["k_suffix"], host["v_suffix"], host["k_pool"], host["v_pool"],
+                                  table, b.prefix_len, b.suffix_len)
+    ref = oracle_lib.attention(host["q"], kp, vp, table, b.prefix_len, b.suffix_len, b.softmax_scale)
+    check_close(widen(W.bf16_bits(out)), ref, b.name)
