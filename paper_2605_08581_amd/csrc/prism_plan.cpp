@@ -33,11 +33,12 @@ namespace {
 int key_tiles(int keys) { return (keys + kTileKeys - 1) / kTileKeys; }
 
 // How the key range of a row tile is cut: into pieces of about `chunk` key tiles,
-// a range that exceeds it by no more than `slack` staying whole.
+// a range that exceeds it by no more than `slack` staying whole, and no piece
+// shorter than `least`.
 struct SplitRule {
-  int chunk = 0, slack = 0;                        // chunk 0: never cut
+  int chunk = 0, slack = 0, least = 1;             // chunk 0: never cut
   int pieces(int cost) const {
-    return chunk ? std::max(1, std::min(cost, (cost - slack + chunk - 1) / chunk)) : 1;
+    return chunk ? std::max(1, std::min(cost / least, (cost - slack + chunk - 1) / chunk)) : 1;
   }
 };
 
@@ -74,20 +75,20 @@ int64_t makespan(const Costs &costs, int heads, const SplitRule &rule, int slots
 SplitRule fit(const Costs &costs, int heads, int min_chunk, int slack, int64_t items) {
   int lo = min_chunk, hi = std::max(min_chunk, costs[0].first);
   while (lo < hi) {
-    const SplitRule mid{(lo + hi) / 2, slack};
+    const SplitRule mid{(lo + hi) / 2, slack, min_chunk};
     int64_t n = 0;
     for (const auto &c : costs) n += c.second * mid.pieces(c.first);
     if (n * heads <= items) hi = mid.chunk;
     else lo = mid.chunk + 1;
   }
-  return SplitRule{lo, slack};
+  return SplitRule{lo, slack, min_chunk};
 }
 
 // The same rule with the smallest larger chunk that leaves at most `slots` pieces
 // of cut ranges.
 SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t slots) {
   const bool follows = rule.slack == rule.chunk;
-  auto with = [&](int chunk) { return SplitRule{chunk, follows ? chunk : rule.slack}; };
+  auto with = [&](int chunk) { return SplitRule{chunk, follows ? chunk : rule.slack, rule.least}; };
   int lo = rule.chunk + 1, hi = std::max(lo, costs[0].first);   // the largest cuts nothing
   while (lo < hi) {
     const SplitRule mid = with((lo + hi) / 2);
@@ -116,7 +117,7 @@ SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream
     const int64_t slots = (d == 64 ? 2 : 1) * kNumCU;
     if (n <= slots) return fit(costs, heads, min_chunk, 4, slots);
     const int chunk = (int)std::max<int64_t>(min_chunk, total / slots);
-    return SplitRule{chunk, chunk};
+    return SplitRule{chunk, chunk, min_chunk};
   }
   // The prefill kernel takes about 1.1 us per key tile alone on a CU and 1.9 us
   // beside a second workgroup; cutting costs another launch (5 us) and 0.02 us
@@ -126,7 +127,7 @@ SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream
   // 3 requests of 100..300 rows x 1000..3300 keys, 8/2 heads: 31.4 -> 21.2 us.)
   if (n > 4 * kNumCU) {
     const int chunk = (int)std::max<int64_t>(min_chunk, (total + 3 * kNumCU - 1) / (3 * kNumCU));
-    return SplitRule{chunk, chunk};
+    return SplitRule{chunk, chunk, min_chunk};
   }
   auto estimate = [&](const SplitRule &r) {
     int64_t cut = 0;
@@ -285,7 +286,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     first_tile[r + 1] = (int)tile_keys.size();
   }
 
-  // Split-KV: never below min_split_keys.
+  // Split-KV: no piece of the automatic cuts has fewer key tiles than min_split_keys.
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
   SplitRule rule;
   Costs costs;
@@ -359,8 +360,9 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
               add(it);
               continue;
             }
-            const int per = (cost + nsplit - 1) / nsplit;   // key tiles per chunk
-            nsplit = (cost + per - 1) / per;
+            const int per = (cost + nsplit - 1) / nsplit;   // most key tiles of a piece
+            nsplit = (cost + per - 1) / per;                // pieces differ by one key tile at most
+            auto tile_of = [&](int piece) { return cost / nsplit * piece + std::min(piece, cost % nsplit); };
             ReduceGroup g{};
             g.req = req;
             g.kv_head = h;
@@ -372,8 +374,8 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
             it.group = (int32_t)sch.groups.size();
             sch.groups.push_back(g);
             for (int c = 0; c < nsplit; ++c) {
-              it.kv_begin = c * per * kTileKeys;
-              it.kv_end = std::min(kv_len, (c + 1) * per * kTileKeys);
+              it.kv_begin = tile_of(c) * kTileKeys;
+              it.kv_end = std::min(kv_len, tile_of(c + 1) * kTileKeys);
               it.part_slot = next_slot++;
               add(it);
               ++sch.num_split_items;

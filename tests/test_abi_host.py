@@ -154,6 +154,27 @@ def test_planner_forced_and_disabled_split(lib):
     assert _check_cover(W.make_config(2), 0, 0).num_reduce_groups == 0
 
 
+@pytest.mark.parametrize("d,rows", [(128, (1, 9)), (64, (1, 9)), (128, (33, 500)), (64, (33, 500))])
+@pytest.mark.parametrize("least", [0, 64, 1280])
+def test_pieces_are_even_and_not_too_short(lib, d, rows, least):
+    rng = np.random.default_rng(11)
+    cut = 0
+    for _ in range(60):
+        n = int(rng.integers(1, 9))
+        b = W.make_custom_batch("even", W.Geometry(8, 4, d), rng.integers(0, 9000, n).tolist(),
+                                rng.integers(rows[0], rows[1], n).tolist(), seed=1)
+        _check_cover(b, 0, 0, least)
+        items = B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, min_split_keys=least)[2]
+        tiles = {}
+        for req, kvh, row0, kb, ke, slot, _, _ in items[items[:, 0] >= 0].tolist():
+            if slot >= 0:
+                tiles.setdefault((req, kvh, row0), []).append((ke + 63) // 64 - kb // 64)
+        for piece in tiles.values():
+            assert min(piece) >= (least or 256) // 64 and max(piece) - min(piece) <= 1, piece
+        cut += len(tiles)
+    assert cut > 0
+
+
 SCRATCH = 64 << 20                             # PRISM_STATIC_SCRATCH_BYTES
 
 
