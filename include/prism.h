@@ -104,7 +104,7 @@ typedef struct prism_plan_options {
    * inside the attention kernel instead of before it.  Results are undefined if
    * the device table then differs from the copy in any entry a request uses.
    * The calls take two kernels all the same where k_suffix or v_suffix does not
-   * start on a 16-byte boundary.                                               */
+   * start on a 16-byte boundary, or lies in memory that out covers.            */
   const int32_t *block_table_host;
 } prism_plan_options_t;
 
@@ -120,7 +120,7 @@ typedef struct prism_plan_info {
   int32_t total_suffix;        /* sum_S                                                */
   int32_t rows_per_wave;       /* query rows per wavefront                             */
   int32_t append_in_attention; /* 1: the prefill calls append inside the attention kernel
-                                  (unless rows do not lie on 16 bytes)                 */
+                                  (with exceptions: see block_table_host)              */
   int64_t flops;               /* 4*d*Hq*sum_r(S_r*P_r + S_r(S_r+1)/2): unmasked pairs */
   int64_t kv_bytes_per_request;/* K and V bytes of every request's whole sequence      */
 } prism_plan_info_t;

@@ -274,7 +274,15 @@ int do_prefill(const prism_plan *plan, const void *q, const void *k_suffix, cons
   // unlike loads into registers takes no address at will: rows that do not lie on
   // 16 bytes go by the append kernel.
   const bool aligned = (((uintptr_t)k_suffix | (uintptr_t)v_suffix) & 15) == 0;
-  if (plan->sch.fused_append && aligned)
+  // A caller that has no further use for the rows may give their memory as out.
+  // The append kernel has then read them all before attention writes there; inside
+  // one kernel a workgroup would write over rows that another has yet to read.
+  const size_t row = (size_t)plan->sch.total_suffix * plan->shape.head_dim * 2;
+  const size_t out_bytes = row * plan->shape.num_q_heads, kv_bytes = row * plan->shape.num_kv_heads;
+  auto apart = [&](const void *rows) {
+    return (uintptr_t)rows + kv_bytes <= (uintptr_t)out || (uintptr_t)out + out_bytes <= (uintptr_t)rows;
+  };
+  if (plan->sch.fused_append && aligned && apart(k_suffix) && apart(v_suffix))
     return do_attention(plan, q, k_suffix, v_suffix, k_pool, v_pool, bt, out, lists_dev, stream);
   int rc = do_append(plan, k_suffix, v_suffix, k_pool, v_pool, bt, stream);
   if (rc != PRISM_OK) return rc;

@@ -74,3 +74,29 @@ def test_a_table_that_is_only_a_hint_may_differ(oracle_lib, suffix):
                                   table, b.prefix_len, b.suffix_len)
     ref = oracle_lib.attention(host["q"], kp, vp, table, b.prefix_len, b.suffix_len, b.softmax_scale)
     check_close(widen(W.bf16_bits(out)), ref, b.name)
+
+
+@pytest.mark.parametrize("over", ["k_suffix", "v_suffix", "k_suffix, half"])
+@pytest.mark.parametrize("suffix", [[3, 16], [700, 400]], ids=["stream", "tile"])
+def test_out_in_the_memory_of_the_new_rows(oracle_lib, suffix, over):
+    """Results are those of the append followed by attention, so out may lie where the rows to append were."""
+    b = W.make_custom_batch("reuse", W.Geometry(4, 4, 64), [64, 5], suffix, seed=66)
+    t = W.make_tensors(b, "cuda")
+    host = {k: W.bf16_bits(v) for k, v in t.items()}
+    rows, half = t[over.split(",")[0]], t["q"].numel() // 2
+    buf = torch.empty(2 * rows.numel(), dtype=rows.dtype, device="cuda")
+    mine = buf[:rows.numel()].view(rows.shape)
+    mine.copy_(rows)
+    t[over.split(",")[0]] = mine
+    out = buf[half:half + rows.numel()].view(t["q"].shape) if "half" in over else mine.view(t["q"].shape)
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table)
+    ws = torch.empty(plan.prism_plan_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"],
+                              torch.from_numpy(b.block_table).cuda(), out, ws)
+    torch.cuda.synchronize()
+    plan.close()
+    kp, vp = oracle_lib.kv_append(host["k_suffix"], host["v_suffix"], host["k_pool"], host["v_pool"],
+                                  b.block_table, b.prefix_len, b.suffix_len)
+    assert (W.bf16_bits(t["k_pool"]) == kp).all() and (W.bf16_bits(t["v_pool"]) == vp).all()
+    ref = oracle_lib.attention(host["q"], kp, vp, b.block_table, b.prefix_len, b.suffix_len, b.softmax_scale)
+    check_close(widen(W.bf16_bits(out)), ref, b.name)
