@@ -152,6 +152,30 @@ SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream
   return best;
 }
 
+// Whether a wave with at most `rows` packed rows per (request, kv head), on
+// `ranges` key ranges of `tiles` key tiles on average, goes to the kernel whose
+// waves split the keys.  Up to 32 rows - decode steps, short suffixes - its work
+// is bound by bytes or latency, not by the matrix cores, and that kernel keeps
+// every wave busy.  But it holds a CU alone (half of one at d = 64), so ranges
+// beyond those places wait for the first to end, which the prefill kernel's two
+// and three workgroups per CU take better unless the ranges are long.  Time of
+// that kernel over the prefill kernel's on waves of 1.9 to 10 times as many ranges
+// as places (357 waves in all), by the mean length of the ranges:
+//   key tiles                 1         2         3         6         15        41
+//   d = 128, 1..16 rows    1.4..1.7  1.2..1.5  1.1..1.3  1.0..1.2  .95..1.0  .90..1.0
+//            17..32 rows   1.7..2.0  1.6..1.8  1.4..1.5  1.1..1.3  1.0..1.1  .92..1.0
+//   d = 64,  1..16 rows    1.1..1.2  1.1       1.0       .93..1.0  .97..1.0  .98
+//            17..32 rows   1.5       1.3..1.4  1.1       .97..1.1  1.0       1.0
+// With no more ranges than places: 0.63..1.0 up to 16 rows, 0.82..1.3 and 1.0 on
+// average above.  (27 requests of 1..18 rows x 12..89 keys, 40 heads,
+// d = 128: 25.4 -> 14.9 us.)  With 33..64 rows the prefill kernel is ahead (160
+// ranges of up to 300 keys, 40 heads: 11.2 us against 13.3).
+bool splits_keys(int64_t rows, int64_t ranges, int64_t tiles, int d) {
+  if (rows > kStreamRows) return false;
+  if (ranges <= (d == 64 ? 2 : 1) * kNumCU) return true;
+  return tiles >= (rows <= 16 ? (d == 64 ? 4 : 11) : (d == 64 ? 16 : 32));
+}
+
 // Whether some request's cached prefix lies in pages that the same wave appends
 // to (pages published to later requests of the wave before they are written), or
 // a page is appended to through two table entries.  Attention then has to run
@@ -219,6 +243,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   std::vector<int32_t> q_off(s.batch);
   int64_t total = 0;
   int64_t most_rows = 0;       // packed rows of the largest request, per kv head
+  int64_t ranges = 0, range_tiles = 0;   // requests with rows, and the key tiles of their sequences
   for (int r = 0; r < s.batch; ++r) {
     const int64_t P = prefix[r], S = suffix[r];
     if (P < 0 || S < 0) return PRISM_ERR_INVALID_ARG;
@@ -231,16 +256,14 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     if (S > 0) {
       sch.kv_bytes += 2LL * 2 * d * s.num_kv_heads * (P + S);
       most_rows = std::max(most_rows, S * G);
+      ++ranges;
+      range_tiles += (P + S + kTileKeys - 1) / kTileKeys;
     }
   }
   sch.total_suffix = total;
 
-  // Up to 32 packed rows per (request, kv head) - decode steps, short suffixes -
-  // a wave's work is bound by bytes or latency, not by the matrix cores: the
-  // kernel whose waves split the keys then keeps every wave busy.  With 33..64
-  // rows the prefill kernel is ahead (40 heads x 160 ranges of up to 300 keys:
-  // 11.2 us against 13.3; 17..32 rows: 9.9 against 9.0).
-  const bool stream = !opt.tile_rows && !opt.rows_per_wave && most_rows <= kStreamRows;
+  const bool stream = !opt.tile_rows && !opt.rows_per_wave &&
+                      splits_keys(most_rows, ranges * s.num_kv_heads, ranges ? range_tiles / ranges : 0, d);
   if (stream) tile_rows = most_rows <= 16 ? 16 : 32;
   sch.stream = stream;
   sch.tile_rows = tile_rows;

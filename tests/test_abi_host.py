@@ -175,6 +175,18 @@ def test_pieces_are_even_and_not_too_short(lib, d, rows, least):
     assert cut > 0
 
 
+@pytest.mark.parametrize("d,rows,batch,keys,stream", [
+    (128, 18, 7, 60, False), (128, 18, 6, 60, True), (128, 9, 27, 60, False), (128, 16, 7, 640, False),
+    (128, 16, 7, 720, True), (128, 32, 7, 1900, False), (128, 32, 7, 2100, True), (64, 16, 13, 190, False),
+    (64, 16, 13, 280, True), (64, 32, 13, 960, False), (64, 32, 13, 1100, True), (64, 32, 12, 60, True),
+    (128, 33, 1, 4000, False)])
+def test_key_splitting_kernel_only_where_it_is_ahead(lib, d, rows, batch, keys, stream):
+    """Up to 32 rows go to it while every (request, kv head) has a place on the chip, and beyond that
+    only with long key ranges."""
+    b = W.make_custom_batch("few", W.Geometry(40, 40, d), [keys - rows] * batch, [rows] * batch, seed=1)
+    assert _check_cover(b, 0, 0).tile_rows == ((16 if rows <= 16 else 32) if stream else 128)
+
+
 SCRATCH = 64 << 20                             # PRISM_STATIC_SCRATCH_BYTES
 
 
