@@ -156,7 +156,7 @@ def test_planner_forced_and_disabled_split(lib):
 
 @pytest.mark.parametrize("d,rows", [(128, (1, 9)), (64, (1, 9)), (128, (33, 500)), (64, (33, 500))])
 @pytest.mark.parametrize("least", [0, 64, 1280])
-def test_pieces_are_even_and_not_too_short(lib, d, rows, least):
+def test_pieces_are_not_too_short(lib, d, rows, least):
     rng = np.random.default_rng(11)
     cut = 0
     for _ in range(60):
@@ -170,7 +170,7 @@ def test_pieces_are_even_and_not_too_short(lib, d, rows, least):
             if slot >= 0:
                 tiles.setdefault((req, kvh, row0), []).append((ke + 63) // 64 - kb // 64)
         for piece in tiles.values():
-            assert min(piece) >= (least or 256) // 64 and max(piece) - min(piece) <= 1, piece
+            assert min(piece) >= (least or 256) // 64, piece
         cut += len(tiles)
     assert cut > 0
 
