@@ -33,8 +33,8 @@ namespace {
 int key_tiles(int keys) { return (keys + kTileKeys - 1) / kTileKeys; }
 
 // How the key range of a row tile is cut: into pieces of about `chunk` key tiles,
-// a range that exceeds it by no more than `slack` staying whole, and no piece
-// shorter than `least`.
+// a range that exceeds it by no more than `slack` staying whole, and so many that
+// none need be shorter than `least`.
 struct SplitRule {
   int chunk = 0, slack = 0, least = 1;             // chunk 0: never cut
   int pieces(int cost) const {
@@ -309,7 +309,8 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     first_tile[r + 1] = (int)tile_keys.size();
   }
 
-  // Split-KV: no piece of the automatic cuts has fewer key tiles than min_split_keys.
+  // Split-KV: no piece of the automatic cuts has fewer key tiles than a caller's
+  // min_split_keys; without one, all but the last of a range have four.
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
   SplitRule rule;
   Costs costs;
@@ -384,13 +385,13 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
               continue;
             }
             // Pieces of one length and a last one with what they leave: it also has the
-            // causal diagonal and the append, and groups that end at different times
-            // share the merging (even pieces: 16 decode requests 31.4 -> 31.6 us, one
-            // request of 37 new rows with the longest piece last 14.5 -> 15.5).  Where
-            // that leaves too little, pieces that differ by one key tile at most.
+            // causal diagonal and the append (3 requests of 1200 to 2100 new over 112
+            // cached tokens, d = 64: 21.0 us, with a last piece of at least 4 tiles 22.1),
+            // and groups that end at different times share the merging.  Where the
+            // caller's limit forbids that, pieces that differ by one key tile at most.
             const int per = (cost + nsplit - 1) / nsplit;
             nsplit = (cost + per - 1) / per;
-            const bool even = cost - (nsplit - 1) * per < rule.least;
+            const bool even = opt.min_split_keys && cost - (nsplit - 1) * per < rule.least;
             auto tile_of = [&](int piece) {
               return even ? cost / nsplit * piece + std::min(piece, cost % nsplit) : std::min(cost, piece * per);
             };
