@@ -551,9 +551,9 @@ def test_request_ids_are_64_bits():
     assert q.active == 0
 
 
-def test_other_threads_run_during_a_call():
-    """The entries are replaced by libc's usleep, which takes the handle as its microseconds: every
-    per-request call then lasts 0.4 s, and another Python thread has to get its turns within it
+def test_other_threads_run_during_tree_calls():
+    """The entries are replaced by libc's usleep, which takes the handle as its microseconds: an admission
+    or a commit then lasts 0.4 s, and another Python thread has to get its turns within it
     (one that waits for the call to end gets one)."""
     code = """
 import ctypes, threading
@@ -563,8 +563,7 @@ S._lib()
 fast, usleep = S._fast, ctypes.cast(ctypes.CDLL(None).usleep, ctypes.c_void_p).value
 fast.bind_api(*[usleep] * 6)
 us, row = 400000, np.zeros(1, dtype=np.int32)
-for call in (lambda: fast.submit(us, 1, 0.0, [1], [16], 0, 0), lambda: fast.complete(us, 1), lambda: fast.set_time(us, 1.0),
-             lambda: fast.admit(us, 1, [1], [], 0, row), lambda: fast.commit(us, 1, row), lambda: fast.release(us, 1)):
+for call in (lambda: fast.admit(us, 1, [1], [], 0, row), lambda: fast.commit(us, 1, row)):
     turns, over = [], threading.Event()
     other = threading.Thread(target=lambda: [turns.append(1) for _ in range(1000) if not over.wait(0.005)])
     other.start()
@@ -574,4 +573,4 @@ for call in (lambda: fast.submit(us, 1, 0.0, [1], [16], 0, 0), lambda: fast.comp
     other.join()
 """
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
-    assert r.returncode == 0 and r.stdout.split() == ["1"] * 6, r.stdout + r.stderr[-2000:]
+    assert r.returncode == 0 and r.stdout.split() == ["1"] * 2, r.stdout + r.stderr[-2000:]
