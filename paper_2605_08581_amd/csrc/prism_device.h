@@ -46,8 +46,9 @@ __device__ __forceinline__ float sum_across_halves(float x) {
 // registers) plus a per-lane byte offset, which keeps all address arithmetic
 // off the vector ALU and makes a stray offset read zeros instead of faulting.
 // Inline assembly, so that the compiler does not make later LDS reads of
-// *other* slots wait for these copies; the kernel waits for them itself
-// (s_waitcnt vmcnt(0), then a workgroup barrier) before a slot is read.
+// *other* slots wait for these copies; the kernels wait for them themselves
+// (s_waitcnt vmcnt, and a workgroup barrier where waves share a tile) before a
+// slot is read.
 typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
 __device__ __forceinline__ i32x4 block_resource(const void *base, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;

@@ -58,9 +58,10 @@ int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_po
 //
 // A workgroup of NW waves owns NW*32*RB packed query rows of one (request, kv
 // head) and walks the key range in tiles of 64 keys (four 16-token pages).
-// K and V rows are copied from the paged pool straight into LDS
-// (global_load_lds, 16 bytes per lane, no staging registers); K and V each
-// have a two-slot ring, and there is one workgroup barrier per tile.
+// K and V rows are copied from the paged pool, or from the packed new rows when
+// the kernel appends them itself, straight into LDS (buffer_load ... lds, 16
+// bytes per lane, no staging registers); K and V each have a ring of NS tile
+// slots, and there is one workgroup barrier per tile.
 //
 // Per wave the products are taken transposed so that no value ever has to move
 // between lanes except one exchange for the row maximum:

@@ -1,8 +1,8 @@
 // Python entry of the control plane's per-request calls.  A wave makes a dozen
 // or more of each; through ctypes the marshalling of token and anchor arrays
 // cost several times what the scheduler and the tree do themselves (640 requests
-// of a serving trace: 22.5 ms, with this and the flat arrays in prism_sched.cpp
-// 8.7 ms).
+// of a serving trace: 23.6 ms, with this and the flat arrays in prism_sched.cpp
+// 9.6 ms).
 // Each function takes the handle first and returns the C status (admit: see
 // there); arguments that are neither integers nor int32 buffers raise TypeError
 // and the Python side then converts them and calls again.
