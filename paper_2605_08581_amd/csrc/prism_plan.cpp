@@ -42,16 +42,20 @@ struct SplitRule {
   }
 };
 
-// Row tiles of one kv head by their key tiles: (key tiles, how many), descending.
-using Costs = std::vector<std::pair<int, int64_t>>;
+// Row tiles of one kv head by their key tiles, descending.
+struct Cost {
+  int tiles;
+  int64_t count, rows;                             // how many, and the packed rows of all of them
+};
+using Costs = std::vector<Cost>;
 
 // Time, in key tiles, until `slots` workers have done all pieces, longest first.
 int64_t makespan(const Costs &costs, int heads, const SplitRule &rule, int slots) {
   std::vector<std::pair<int, int64_t>> pieces;     // length, how many
   int64_t total = 0;
   for (const auto &c : costs) {
-    const int n = rule.pieces(c.first), len = (c.first + n - 1) / n;
-    const int64_t count = c.second * n * heads;
+    const int n = rule.pieces(c.tiles), len = (c.tiles + n - 1) / n;
+    const int64_t count = c.count * n * heads;
     pieces.push_back({len, count});
     total += count * len;
   }
@@ -73,11 +77,11 @@ int64_t makespan(const Costs &costs, int heads, const SplitRule &rule, int slots
 
 // The smallest chunk >= min_chunk whose pieces number at most `items`.
 SplitRule fit(const Costs &costs, int heads, int min_chunk, int slack, int64_t items) {
-  int lo = min_chunk, hi = std::max(min_chunk, costs[0].first);
+  int lo = min_chunk, hi = std::max(min_chunk, costs[0].tiles);
   while (lo < hi) {
     const SplitRule mid{(lo + hi) / 2, slack, min_chunk};
     int64_t n = 0;
-    for (const auto &c : costs) n += c.second * mid.pieces(c.first);
+    for (const auto &c : costs) n += c.count * mid.pieces(c.tiles);
     if (n * heads <= items) hi = mid.chunk;
     else lo = mid.chunk + 1;
   }
@@ -89,23 +93,24 @@ SplitRule fit(const Costs &costs, int heads, int min_chunk, int slack, int64_t i
 SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t slots) {
   const bool follows = rule.slack == rule.chunk;
   auto with = [&](int chunk) { return SplitRule{chunk, follows ? chunk : rule.slack, rule.least}; };
-  int lo = rule.chunk + 1, hi = std::max(lo, costs[0].first);   // the largest cuts nothing
+  int lo = rule.chunk + 1, hi = std::max(lo, costs[0].tiles);   // the largest cuts nothing
   while (lo < hi) {
     const SplitRule mid = with((lo + hi) / 2);
     int64_t n = 0;
     for (const auto &c : costs)
-      if (mid.pieces(c.first) > 1) n += c.second * mid.pieces(c.first);
+      if (mid.pieces(c.tiles) > 1) n += c.count * mid.pieces(c.tiles);
     if (n * heads <= slots) hi = mid.chunk;
     else lo = mid.chunk + 1;
   }
   return with(lo);
 }
 
-SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream, int d) {
+// `sets` (cluster, kv head) sets, each of which runs on one die.
+SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool stream, int d) {
   int64_t total = 0, n = 0;
   for (const auto &c : costs) {
-    total += c.second * c.first * heads;
-    n += c.second * heads;
+    total += c.count * c.tiles * heads;
+    n += c.count * heads;
   }
   if (stream) {
     // One workgroup per CU (two at d = 64: LDS) and bound by bytes: cut to fill
@@ -119,30 +124,50 @@ SplitRule choose_split(const Costs &costs, int heads, int min_chunk, bool stream
     const int chunk = (int)std::max<int64_t>(min_chunk, total / slots);
     return SplitRule{chunk, chunk, min_chunk};
   }
-  // The prefill kernel takes about 1.1 us per key tile alone on a CU and 1.9 us
-  // beside a second workgroup; cutting costs another launch (5 us) and 0.02 us
-  // of partials per piece.  Waves that fill the chip several times are left
-  // alone but for extreme ranges; for the others the least estimate decides.
-  // (148 rows x 1040 keys x 8 heads: 16 workgroups 20.0 us, 64 of them 14.8;
-  // 3 requests of 100..300 rows x 1000..3300 keys, 8/2 heads: 31.4 -> 21.2 us.)
+  // Waves that fill the chip several times are left alone but for extreme ranges.
   if (n > 4 * kNumCU) {
     const int chunk = (int)std::max<int64_t>(min_chunk, (total + 3 * kNumCU - 1) / (3 * kNumCU));
     return SplitRule{chunk, chunk, min_chunk};
   }
-  auto estimate = [&](const SplitRule &r) {
-    int64_t cut = 0;
+  // For the others the least estimate decides, of no cuts and of those into at
+  // most one to four workgroups per CU, of the chip and of the dies that fewer than
+  // eight sets reach (a few more would wait for a round of their own).  In us: the
+  // longest piece takes `alone` per key tile, a CU that is never idle `busy`;
+  // cutting adds the launch of the merge, the serial reads of the group with the
+  // most pieces and, for 128 rows of partials, `partials` to write and read them.
+  // (At d = 64, with more workgroups on a CU, the time on all CUs was closer than
+  // that on those reached.)  Constants from 149 waves of 3 to 1000 row tiles of 8
+  // to 470 key tiles, each timed with up to 20 chunks.  Against one set of constants
+  // for both head dims without the terms for the merge, of 206 waves of 10 us and
+  // more 18 take 3 to 25 % less and two 4 % more.  (34 rows x 15.9k keys, 8/1 heads,
+  // d = 64: 50 pieces a group 38.8 us, 21 pieces 27.8, 4 pieces 44.8; 140 row tiles
+  // of 15 key tiles on two dies, d = 128: cut 58.1 us, uncut 45.5.)
+  const double alone = d == 64 ? 0.7 : 1.2, busy = d == 64 ? 0.47 : 0.95, partials = d == 64 ? 0.015 : 0.04;
+  const int64_t reached = std::min<int64_t>(sets, kNumXCD) * (kNumCU / kNumXCD);
+  const int cus = d == 64 ? kNumCU : (int)reached;
+  auto longest_piece = [&](const SplitRule &r) {
     int longest = 0;
     for (const auto &c : costs) {
-      const int k = r.pieces(c.first);
-      longest = std::max(longest, (c.first + k - 1) / k);
-      if (k > 1) cut += c.second * k * heads;
+      const int k = r.pieces(c.tiles);
+      longest = std::max(longest, (c.tiles + k - 1) / k);
     }
-    return std::max(1.1 * longest, 0.95 * (double)makespan(costs, heads, r, kNumCU)) + (cut ? 5.0 + 0.02 * cut : 0.0);
+    return longest;
+  };
+  auto estimate = [&](const SplitRule &r) {
+    int64_t rows = 0;
+    int most = 1;
+    for (const auto &c : costs) {
+      const int k = r.pieces(c.tiles);
+      if (k > 1) rows += c.rows * k * heads;
+      most = std::max(most, k);
+    }
+    return std::max(alone * longest_piece(r), busy * (double)makespan(costs, heads, r, cus)) +
+           (most > 1 ? 3.5 + 0.5 * most + partials * rows / 128 : 0.0);
   };
   SplitRule best;
   double best_time = estimate(best);
-  for (int64_t items : {1, 2, 3, 4}) {
-    const SplitRule r = fit(costs, heads, min_chunk, 6, items * kNumCU);
+  for (int64_t items : {reached, 2 * reached, (int64_t)kNumCU, (int64_t)2 * kNumCU, (int64_t)3 * kNumCU, (int64_t)4 * kNumCU}) {
+    const SplitRule r = fit(costs, heads, min_chunk, 6, items);
     const double t = estimate(r);
     if (t < best_time) {
       best_time = t;
@@ -291,15 +316,17 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // Row tiles, the same for every kv head: the keys that each one sees, by request.
   // (Everything up to the items is done once for all kv heads: with a list of all
   // (request, kv head, row tile) sorted as a whole, the plan of 32 requests x 40
-  // heads took 420 us, now 96.)
+  // heads took 441 us, now 108.)
   std::vector<int> first_tile(s.batch + 1, 0), tile_keys;
   std::vector<int64_t> cluster_cost(s.batch, 0);       // key tiles of the cluster, of one kv head
   std::vector<int> live;
   int most_cost = 0;
+  int64_t clusters = 0;
   for (int r = 0; r < s.batch; ++r) {
     const int P = prefix[r], S = suffix[r];
     const int rows = S * G;
     if (S > 0) live.push_back(r);
+    clusters += S > 0 && cluster[r] == r;
     for (int row0 = 0; row0 < rows; row0 += tile_rows) {
       const int kv_len = P + (std::min(rows, row0 + tile_rows) - 1) / G + 1;
       tile_keys.push_back(kv_len);
@@ -315,11 +342,16 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   SplitRule rule;
   Costs costs;
   if (opt.split_kv == 0 && !tile_keys.empty()) {
-    std::vector<int64_t> count(most_cost + 1, 0);
-    for (int keys : tile_keys) ++count[key_tiles(keys)];
+    std::vector<int64_t> count(most_cost + 1, 0), rows(most_cost + 1, 0);
+    for (int r : live)
+      for (int t = first_tile[r]; t < first_tile[r + 1]; ++t) {
+        const int c = key_tiles(tile_keys[t]);
+        ++count[c];
+        rows[c] += std::min(tile_rows, suffix[r] * G - (t - first_tile[r]) * tile_rows);
+      }
     for (int c = most_cost; c > 0; --c)
-      if (count[c]) costs.push_back({c, count[c]});
-    rule = choose_split(costs, s.num_kv_heads, min_chunk, stream, d);
+      if (count[c]) costs.push_back({c, count[c], rows[c]});
+    rule = choose_split(costs, s.num_kv_heads, clusters * s.num_kv_heads, min_chunk, stream, d);
   }
 
   // Heaviest cluster first; inside a (cluster, kv head) set the requests, the

@@ -188,11 +188,26 @@ def test_key_splitting_kernel_only_where_it_is_ahead(lib, d, rows, batch, keys, 
     assert _check_cover(b, 0, 0).tile_rows == ((16 if rows <= 16 else 32) if stream else 128)
 
 
+@pytest.mark.parametrize("heads,prefix,suffix,least,most", [
+    ((8, 1, 64), [15838], [34], 8, 30), ((8, 2, 128), [224, 480], [1116] * 2, 1, 1), ((32, 8, 64), [2448] * 22, [12] * 22, 2, 5)],
+    ids=["deep-merge", "full-tiles", "few-rows-d64"])
+def test_cuts_weigh_the_merge(lib, heads, prefix, suffix, least, most):
+    """Pieces of a row tile where the estimate has to see how deep the merge gets, how many rows of partials
+    it moves, how many dies the wave reaches, and that a key tile takes half the time at d = 64."""
+    b = W.make_custom_batch("merge", W.Geometry(*heads), prefix, suffix, seed=1,
+                            share_groups=[-1 if len(prefix) > 2 else 0] * len(prefix))
+    items = B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table)[2]
+    pieces = {}
+    for req, kvh, row0, *_ in items[items[:, 0] >= 0].tolist():
+        pieces[req, kvh, row0] = pieces.get((req, kvh, row0), 0) + 1
+    assert least <= min(pieces.values()) and max(pieces.values()) <= most, sorted(pieces.values())
+
+
 SCRATCH = 64 << 20                             # PRISM_STATIC_SCRATCH_BYTES
 
 
 @pytest.mark.parametrize("prefix,suffix", [([21234, 27950, 30066], [394, 200, 307]),
-                                           ([15614, 17014, 17805, 18118, 17242], [363, 252, 414, 373, 377])])
+                                           ([34959, 52451, 19008, 58356], [172, 398, 314, 113])])
 @pytest.mark.parametrize("tile_rows", [0, 64, 256])
 def test_automatic_cuts_fit_the_static_scratch(lib, prefix, suffix, tile_rows):
     """Waves whose pieces at four workgroups per CU would not fit it."""
