@@ -208,6 +208,7 @@ LaunchParams make_params(const prism_plan *p, const void *q, const void *k_new, 
   a.Hq = p->shape.num_q_heads;
   a.Hkv = p->shape.num_kv_heads;
   a.max_blocks = p->shape.max_blocks_per_req;
+  a.group = Divisor(a.Hq / a.Hkv);
   a.scale_log2e = p->scale_log2e;
   lp.num_items = (int)p->sch.items.size();
   lp.num_groups = (int)p->sch.groups.size();

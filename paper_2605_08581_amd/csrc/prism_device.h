@@ -106,6 +106,17 @@ __device__ __forceinline__ AttnItem load_item(const AttnItem *items, int i) {
   return it;
 }
 
+// Have these in scalar registers from here on.
+__device__ __forceinline__ void pin_args(const AttnArgs &p) {
+  __asm__ volatile("" : : "s"(p.q), "s"(p.k_pool), "s"(p.v_pool), "s"(p.k_new), "s"(p.v_new), "s"(p.block_table),
+                   "s"(p.items), "s"(p.Hq), "s"(p.Hkv), "s"(p.max_blocks), "s"(p.group.d), "s"(p.group.shift),
+                   "s"(p.group.multiplier), "s"(p.scale_log2e));
+}
+__device__ __forceinline__ void pin_item(const AttnItem &it) {
+  __asm__ volatile("" : : "s"(it.req), "s"(it.kv_head), "s"(it.row0), "s"(it.kv_begin), "s"(it.kv_end), "s"(it.part_slot),
+                   "s"(it.prefix), "s"(it.suffix), "s"(it.q_off));
+}
+
 // All of a group but its arrival counter.
 __device__ __forceinline__ ReduceGroup load_group(const ReduceGroup *groups, int i) {
   ConstantPtr<int32_t> w = constant_ptr((const int32_t *)(groups + i));

@@ -4,6 +4,8 @@
 #include <stdint.h>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "prism.h"
 
 namespace prism {
@@ -94,6 +96,24 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 int validate_table(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,
                    const int32_t *table);
 
+// Quotients by a number known on the host, of 0 <= n < 2^31, without a division:
+// (mulhi(n, multiplier) + n) >> shift with shift = ceil(log2 d) and multiplier =
+// floor(2^32 (2^shift - d) / d) + 1 (Granlund and Montgomery, 1994).  The
+// compiler's own sequence for a runtime divisor takes some 25 instructions, and
+// the prefill kernel has seven of them on its way in and out.
+struct Divisor {
+  int32_t d = 1, shift = 0;
+  uint32_t multiplier = 1;
+  Divisor() = default;
+  explicit Divisor(int32_t n) : d(n) {
+    while (((int64_t)1 << shift) < n) ++shift;
+    multiplier = (uint32_t)(((((uint64_t)1 << shift) - (uint64_t)n) << 32) / (uint64_t)n) + 1u;
+  }
+  __host__ __device__ __forceinline__ int quotient(int n) const {
+    return (int)(((uint32_t)(((uint64_t)(uint32_t)n * multiplier) >> 32) + (uint32_t)n) >> shift);
+  }
+};
+
 // What every attention kernel reads, passed by value.
 struct AttnArgs {
   const void *q;
@@ -105,6 +125,7 @@ struct AttnArgs {
   const AttnItem *items;
   ReduceGroup *groups;
   int Hq, Hkv, max_blocks;
+  Divisor group;                 // query heads per kv head
   float scale_log2e;
 };
 

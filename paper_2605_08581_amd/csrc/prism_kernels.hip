@@ -116,82 +116,27 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   auto k_slot = [&](int t) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(t % NS) * TILE_BYTES; };
   auto v_slot = [&](int t) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(NS + t % NS) * TILE_BYTES; };
 
+  // The way to the first K tile is a chain of reads that miss the caches -
+  // arguments, item, block table, K rows - and its length is what a workgroup
+  // costs beside its tiles.  So each link asks for all it will need at once (the
+  // compiler would fetch most arguments where they are first used, one wait
+  // each), the page ids come before the Q rows, and no division is in between.
+  pin_args(p);
   const AttnItem it = load_item(p.items, blockIdx.x);
-  if (it.req < 0) return;                        // idle padding entry
-  const int Hq = p.Hq, Hkv = p.Hkv;
+  const int Hq = p.Hq;
   const float scale_log2e = p.scale_log2e;
-  const int G = Hq / Hkv;
+  const Divisor G = p.group;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31;
   const int hh = lane >> 5;
-  const int P = it.prefix, S = it.suffix;
-  const int rows_total = S * G;
-  const int T = P + S;
-  const int nblk = (T + kPage - 1) / kPage;
-  const ConstantPtr<int32_t> bt = constant_ptr(p.block_table + (int64_t)it.req * p.max_blocks);
-
-  // ---- Q fragments (B operand of S^T): lane holds row l32, dims 16kk+8hh..+7
-  const int wrow0 = it.row0 + wave * (32 * RB);
-  bf16x8 qf[RB][KK];
-  int limit[RB];                                  // last visible key of the lane's row
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int row = wrow0 + rb * 32 + l32;
-    const bool valid = row < rows_total;
-    const int tok = valid ? row / G : 0;
-    const int g = valid ? row % G : 0;
-    limit[rb] = valid ? P + tok : -1;
-    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G + g) * D + 8 * hh;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      bf16x8 v = {};
-      if (valid) v = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
-      qf[rb][kk] = v;
-    }
-  }
-  // Wave-uniform key bounds: at or below lo_limit no row of the wave is
-  // masked, above hi_limit every row is.
-  const int first_row = wrow0 < rows_total ? wrow0 : rows_total - 1;
-  int last_row = wrow0 + 32 * RB - 1;
-  if (last_row > rows_total - 1) last_row = rows_total - 1;
-  const int lo_limit = P + first_row / G;
-  const int hi_limit = P + last_row / G;
-
-  const int kv_begin = it.kv_begin, kv_end = it.kv_end;
-  const int nt = (kv_end - kv_begin + BN - 1) / BN;          // tiles of the workgroup
-  int my_nt = 0;                                             // tiles this wave computes on
-  if (wrow0 < rows_total && hi_limit >= kv_begin) {
-    my_nt = (hi_limit - kv_begin) / BN + 1;
-    if (my_nt > nt) my_nt = nt;
-  }
-
-  f32x16 oacc[DB][RB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[db][rb][r] = 0.f;
-  // m_run: running maximum (raw score units), l_run: running sum, bound: the
-  // raw score above which the maximum has to be raised before exponentiating
-  float m_run[RB], l_run[RB], bound[RB];
-  const float slack = kRescaleThreshold / scale_log2e;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    m_run[rb] = -1e30f;
-    l_run[rb] = 0.f;
-    bound[rb] = -1e30f;
-  }
 
   // ---- paged copy: wave w moves units w*UPW .. w*UPW+UPW-1 of a tile; a unit
   // is 1 KB = KPU whole key rows, and consecutive units stay inside one
   // (page, head) block as long as possible so a wave needs few page ids.
   // Lane l fills LDS slot (row l/CPR, chunk l%CPR) of the unit and therefore
   // fetches chunk (l%CPR) ^ swz(row).
-  const PageSource src(p, it, ROW);
-  const int wave_blk = (wave * UPW) / UPP;        // first page of a tile this wave copies from
   constexpr int NL = UPW < UPP ? UPW : UPP;       // copies repeat with the page
   uint32_t lane_old[NL], lane_new[NL];            // byte offset of the lane's chunk: pool block / packed rows
   auto lane_row = [&](int i) __attribute__((always_inline)) -> int {             // the page's row that copy i of this lane fetches
@@ -201,9 +146,46 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   for (int i = 0; i < NL; ++i) {
     const uint32_t chunk = (uint32_t)(((lane % CPR) ^ swz<D>(lane_row(i))) << 4);
     lane_old[i] = (uint32_t)(lane_row(i) * ROW) + chunk;
-    lane_new[i] = (uint32_t)lane_row(i) * src.new_stride + chunk;
+    lane_new[i] = (uint32_t)lane_row(i) * (uint32_t)(p.Hkv * ROW) + chunk;
   }
   const uint32_t lds_base = lds_address(lds);
+  const int i16 = lane & 15;
+  const int grp = (lane >> 4) & 1;
+
+  // Per-lane LDS addresses of the fragment reads, relative to the start of a
+  // tile slot; everything else (ring slot, 32-key block, k-step) is a constant
+  // added on top, so a read is one address register plus an immediate.
+  typedef __attribute__((address_space(3))) const bf16x8 *lds_b128_ptr;
+  typedef __attribute__((address_space(3))) s16x4 *lds_tr_ptr;
+  uint32_t k_lane[KK];                            // row l32, chunk 2kk+hh
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) k_lane[kk] = lds_base + (uint32_t)lds_off<D>(l32, 2 * kk + hh);
+  uint32_t v_lane[DB][2];                         // key 4hh + i16/4 (+8), 4 head dims of block db
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    const int key = 4 * hh + (i16 >> 2);
+    const int chunk = 4 * db + 2 * grp + ((i16 & 3) >> 1);
+    const int sub = (i16 & 1) << 3;
+    v_lane[db][0] = lds_base + (uint32_t)(lds_off<D>(key, chunk) + sub);
+    v_lane[db][1] = lds_base + (uint32_t)(lds_off<D>(key + 8, chunk) + sub);
+  }
+  const float slack = kRescaleThreshold / scale_log2e;
+  // all of which is worked out while the item is on its way
+#pragma unroll
+  for (int i = 0; i < NL; ++i) __asm__ volatile("" : "+v"(lane_old[i]), "+v"(lane_new[i]));
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) __asm__ volatile("" : "+v"(k_lane[kk]));
+#pragma unroll
+  for (int db = 0; db < DB; ++db) __asm__ volatile("" : "+v"(v_lane[db][0]), "+v"(v_lane[db][1]));
+  pin_item(it);
+  if (it.req < 0) return;                        // idle padding entry
+  const int P = it.prefix, S = it.suffix;
+  const int rows_total = S * G.d;
+  const int T = P + S;
+  const int nblk = (T + kPage - 1) / kPage;
+  const ConstantPtr<int32_t> bt = constant_ptr(p.block_table + (int64_t)it.req * p.max_blocks);
+  const int kv_begin = it.kv_begin, kv_end = it.kv_end;
+  const int wave_blk = (wave * UPW) / UPP;        // first page of a tile this wave copies from
   struct PageIds {
     int32_t p[PPW];
   };
@@ -217,6 +199,47 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     for (int j = 0; j < PPW; ++j) r.p[j] = bt[blk_of(t, j)];
     return r;
   };
+  const PageIds first_pages = pages_of(0), second_pages = pages_of(1);
+  __builtin_amdgcn_sched_barrier(0);             // on their way before the Q rows' addresses are formed
+
+  // ---- Q fragments (B operand of S^T): lane holds row l32, dims 16kk+8hh..+7
+  const int wrow0 = it.row0 + wave * (32 * RB);
+  bf16x8 qf[RB][KK];
+  int limit[RB];                                  // last visible key of the lane's row
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = wrow0 + rb * 32 + l32;
+    const bool valid = row < rows_total;
+    const int from = valid ? row : 0;             // rows past the end are cleared once they are here
+    const int tok = G.quotient(from), g = from - tok * G.d;
+    limit[rb] = valid ? P + tok : -1;
+    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D + 8 * hh;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
+  }
+#pragma unroll
+  for (int j = 0; j < PPW; ++j) __asm__ volatile("" : : "s"(first_pages.p[j]), "s"(second_pages.p[j]));
+  const PageSource src(p, it, ROW);
+  // Wave-uniform key bounds: at or below lo_limit no row of the wave is
+  // masked, above hi_limit every row is.
+  const int first_row = wrow0 < rows_total ? wrow0 : rows_total - 1;
+  int last_row = wrow0 + 32 * RB - 1;
+  if (last_row > rows_total - 1) last_row = rows_total - 1;
+  const int lo_limit = P + G.quotient(first_row);
+  const int hi_limit = P + G.quotient(last_row);
+
+  const int nt = (kv_end - kv_begin + BN - 1) / BN;          // tiles of the workgroup, at least one
+  int my_nt = 0;                                             // tiles this wave computes on
+  if (wrow0 < rows_total && hi_limit >= kv_begin) {
+    my_nt = (hi_limit - kv_begin) / BN + 1;
+    if (my_nt > nt) my_nt = nt;
+  }
+
+  f32x16 oacc[DB][RB];
+  // m_run: running maximum (raw score units), l_run: running sum, bound: the
+  // raw score above which the maximum has to be raised before exponentiating
+  float m_run[RB], l_run[RB], bound[RB];
+
   // This wave's share of tile t into a ring slot, wherever its rows come from.
   auto copy_rows = [&](int which, int slot, int t, const PageIds &pg) __attribute__((always_inline)) {
     static_for<0, PPW>([&](auto jt) __attribute__((always_inline)) {
@@ -252,8 +275,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // 3.6 ms on 92 765 new tokens x 40 heads: its load latency is not covered.)
   int own_lo = 0x7fffffff, own_hi = 0x7fffffff;   // positions
   if (p.k_new) {
-    own_lo = P + (it.row0 + G - 1) / G;
-    own_hi = P + (it.row0 + BM + G - 1) / G;
+    own_lo = P + G.quotient(it.row0 + G.d - 1);
+    own_hi = P + G.quotient(it.row0 + BM + G.d - 1);
     if (own_hi > T) own_hi = T;
     if (own_hi > kv_end) own_hi = kv_end;
   }
@@ -290,26 +313,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if constexpr (decltype(new_tag)::value) copy16_to_lds(src.new_rows(which, blk_of(t, j) * kPage - P), lane_new[i % NL], to);
     else copy16_to_lds(src.old_rows(which, pg.p[j]), lane_old[i % NL], to);
   };
-  const int i16 = lane & 15;
-  const int grp = (lane >> 4) & 1;
-
-  // Per-lane LDS addresses of the fragment reads, relative to the start of a
-  // tile slot; everything else (ring slot, 32-key block, k-step) is a constant
-  // added on top, so a read is one address register plus an immediate.
-  typedef __attribute__((address_space(3))) const bf16x8 *lds_b128_ptr;
-  typedef __attribute__((address_space(3))) s16x4 *lds_tr_ptr;
-  uint32_t k_lane[KK];                            // row l32, chunk 2kk+hh
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) k_lane[kk] = lds_base + (uint32_t)lds_off<D>(l32, 2 * kk + hh);
-  uint32_t v_lane[DB][2];                         // key 4hh + i16/4 (+8), 4 head dims of block db
-#pragma unroll
-  for (int db = 0; db < DB; ++db) {
-    const int key = 4 * hh + (i16 >> 2);
-    const int chunk = 4 * db + 2 * grp + ((i16 & 3) >> 1);
-    const int sub = (i16 & 1) << 3;
-    v_lane[db][0] = lds_base + (uint32_t)(lds_off<D>(key, chunk) + sub);
-    v_lane[db][1] = lds_base + (uint32_t)(lds_off<D>(key + 8, chunk) + sub);
-  }
   // K fragment i (0 .. KB*KK-1) of the tile in K ring slot at byte offset
   // slot_off: rows kb*32+l32, dims 16kk+8hh..+7
   auto k_frag = [&](uint32_t slot_off, int i) __attribute__((always_inline)) -> bf16x8 {
@@ -550,7 +553,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   };
   const bool wave_live = my_nt > 0;
   f32x16 s_a[KB][RB], s_b[KB][RB];
-  if (nt > 0) copy_rows(0, 0, 0, pages_of(0));
+  copy_rows(0, 0, 0, first_pages);
   if constexpr (NS > 2) {
     // With rings deeper than two slots copies stay in flight across
     // iterations.  The compiler cannot count them (they are inline assembly),
@@ -564,10 +567,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) __asm__ volatile("" : "+v"(qf[rb][kk]));
   }
-  if (nt > 0) {
-    PageIds pg = pages_of(0);
+  {
+    PageIds pg = first_pages;
     copy_rows(1, 0, 0, pg);
-    pg = pages_of(1);
+    pg = second_pages;
     const bool second = NS > 2 || nt > 1;
 #pragma unroll
     for (int j = 1; j < NS - 1; ++j) {
@@ -578,9 +581,25 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if (second) copy_rows(0, NS - 1, NS - 1, pg);
     pg_v = pg;
     pg_k = pages_of(NS);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[db][rb][r] = 0.f;
+      m_run[rb] = -1e30f;
+      l_run[rb] = 0.f;
+      bound[rb] = -1e30f;
+    }
     if (second) wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
     else wait_pending(std::integral_constant<int, 0>{});
     __syncthreads();
+    if (wrow0 + 32 * RB > rows_total)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+          if (limit[rb] < 0) qf[rb][kk] = bf16x8{};
     if (wave_live) plain_scores(s_a, k_slot(0), kv_begin, kv_begin + BN - 1 > lo_limit);
   }
   // j is the tile index modulo NS, known at compile time in the fast loop so
@@ -601,7 +620,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // every LDS address is a register plus an immediate.
   int n_fast = 0;
   {
-    const int blk_limit = P + it.row0 / G;        // last key visible to the workgroup's first row
+    const int blk_limit = P + G.quotient(it.row0);        // last key visible to the workgroup's first row
     if (blk_limit >= kv_begin + 2 * BN - 1) n_fast = (blk_limit + 1 - kv_begin) / BN - 1;
     const int most = NS > 2 ? nt - 1 : nt - NS;   // their copies end inside the key range
     if (n_fast > most) n_fast = most;
@@ -680,7 +699,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
       }
     }
   }
-  if (nt > 0) {                                   // the last tile: softmax and PV only
+  {                                               // the last tile: softmax and PV only
     const uint32_t v_cur = v_slot(t);
     arrive();
     append_tile(t);
@@ -705,8 +724,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if (row >= rows_total) continue;
     if (it.part_slot < 0) {
       const float inv = 1.0f / l_tot;
-      const int tok = row / G, g = row % G;
-      __bf16 *op = (__bf16 *)p.out + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G + g) * D;
+      const int tok = G.quotient(row), g = row - tok * G.d;
+      __bf16 *op = (__bf16 *)p.out + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
