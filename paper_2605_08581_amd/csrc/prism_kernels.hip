@@ -332,9 +332,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     a.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(uintptr_t)(v_lane[db][1] + step_off));
     return a.v;
   };
+  // (64 compares and selects per tile: only for 32-key blocks past the wave's first row)
   auto mask_tile = [&](f32x16 (&sx)[KB][RB], int key0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
+    for (int kb = 0; kb < KB; ++kb) {
+      if (key0 + kb * 32 + 31 <= lo_limit) continue;
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -342,6 +344,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
           const int key = key0 + kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
           if (key > limit[rb]) sx[kb][rb][r] = -INFINITY;
         }
+    }
   };
   // The lane's own maximum of a score tile against a precomputed bound (the
   // running maximum plus the slack): no cross-lane traffic on the common path.
@@ -393,7 +396,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 
   // Scores of one tile, not overlapped with anything (first tile, and tiles
   // that need the causal mask).
-  auto plain_scores = [&](f32x16 (&sx)[KB][RB], uint32_t k_lds, int key0, bool masked) __attribute__((always_inline)) {
+  auto plain_scores = [&](f32x16 (&sx)[KB][RB], uint32_t k_lds, int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -407,17 +410,18 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
       for (int rb = 0; rb < RB; ++rb)
         sx[i / KK][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[rb][i % KK], sx[i / KK][rb], 0, 0, 0);
     }
-    if (masked) mask_tile(sx, key0);
+    mask_tile(sx, key0);
     raise_max(sx);
   };
-  // Softmax and O^T update of the current tile, nothing overlapped (tiles on
-  // the causal diagonal and the last tile).
-  auto tail_step = [&](f32x16 (&sc)[KB][RB], uint32_t v_cur) __attribute__((always_inline)) {
+  // Softmax and O^T update of the wave's last tile, nothing overlapped.  Where
+  // its rows see none of the tile's upper 32 keys, those probabilities are zeros.
+  auto tail_step = [&](f32x16 (&sc)[KB][RB], uint32_t v_cur, bool lower_half) __attribute__((always_inline)) {
     float mc[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) mc[rb] = m_run[rb] * scale_log2e;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
+      if (ks >= KS / 2 && lower_half) continue;
       bf16x8 pf[RB];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) pf[rb] = p_frag(sc, ks, rb, mc[rb]);
@@ -600,7 +604,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
           if (limit[rb] < 0) qf[rb][kk] = bf16x8{};
-    if (wave_live) plain_scores(s_a, k_slot(0), kv_begin, kv_begin + BN - 1 > lo_limit);
+    if (wave_live) plain_scores(s_a, k_slot(0), kv_begin);
   }
   // j is the tile index modulo NS, known at compile time in the fast loop so
   // that every LDS address there is a register plus an immediate.
@@ -626,81 +630,72 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if (n_fast > most) n_fast = most;
     if (n_fast < 0) n_fast = 0;
   }
-  // How an iteration gets its copies: all pages cached, all new, or whichever
-  // they are.  The first two are single instructions between the chunks of the
-  // step; the last, for the few iterations around the end of the cached prefix,
-  // is a burst before it.
-  enum { kOld, kNew, kAny };
-  auto fast_iteration = [&](int t, auto j_tag, auto from_tag) __attribute__((always_inline)) {
-    constexpr int j = decltype(j_tag)::value, FROM = decltype(from_tag)::value;
+  // How an iteration of the loops for cached and for new pages gets its copies:
+  // single instructions between the chunks of the step.
+  auto fast_iteration = [&](int t, auto j_tag, auto new_tag) __attribute__((always_inline)) {
+    constexpr int j = decltype(j_tag)::value;
     static_assert(NS % 2 == 0, "score buffers alternate with the tile parity");
     constexpr uint32_t k_next = (uint32_t)((j + 1) % NS) * TILE_BYTES;
     constexpr uint32_t v_cur = (uint32_t)(NS + j) * TILE_BYTES;
-    constexpr int VSLOT = (j + NS - 1) % NS, KSLOT = j;
+    using VSlot = std::integral_constant<int, (j + NS - 1) % NS>;
+    using KSlot = std::integral_constant<int, j>;
     arrive();
-    if constexpr (FROM == kAny) issue_copies(VSLOT, KSLOT, t);
-    using VSlot = std::integral_constant<int, FROM == kAny ? -1 : VSLOT>;
-    using KSlot = std::integral_constant<int, FROM == kAny ? -1 : KSLOT>;
-    using New = std::integral_constant<bool, FROM == kNew>;
-    if (j % 2 == 0) step(s_a, s_b, k_next, v_cur, t, std::false_type{}, VSlot{}, KSlot{}, New{});
-    else step(s_b, s_a, k_next, v_cur, t, std::false_type{}, VSlot{}, KSlot{}, New{});
-    if constexpr (FROM == kOld) {
+    if (j % 2 == 0) step(s_a, s_b, k_next, v_cur, t, std::false_type{}, VSlot{}, KSlot{}, new_tag);
+    else step(s_b, s_a, k_next, v_cur, t, std::false_type{}, VSlot{}, KSlot{}, new_tag);
+    if constexpr (!decltype(new_tag)::value) {
       pg_v = pg_k;
       pg_k = pages_of(t + NS + 1);
     }
   };
   static_assert(NS == 2 || NS == 4, "the loop is unrolled for rings of 2 or 4 slots");
   int t = 0;
-  auto fast_loop = [&](int end, auto from_tag) __attribute__((always_inline)) {
+  auto fast_loop = [&](int end, auto new_tag) __attribute__((always_inline)) {
     for (; t + NS <= end; t += NS) {
-      fast_iteration(t, std::integral_constant<int, 0>{}, from_tag);
-      fast_iteration(t + 1, std::integral_constant<int, 1>{}, from_tag);
+      fast_iteration(t, std::integral_constant<int, 0>{}, new_tag);
+      fast_iteration(t + 1, std::integral_constant<int, 1>{}, new_tag);
       if (NS > 2) {
-        fast_iteration(t + 2, std::integral_constant<int, 2 % NS>{}, from_tag);
-        fast_iteration(t + 3, std::integral_constant<int, 3 % NS>{}, from_tag);
+        fast_iteration(t + 2, std::integral_constant<int, 2 % NS>{}, new_tag);
+        fast_iteration(t + 3, std::integral_constant<int, 3 % NS>{}, new_tag);
       }
     }
   };
-  if (!wave_live) {                               // a wave without rows only copies
-    for (; t + 1 < nt; ++t) {
-      arrive();
-      append_tile(t);
-      issue_copies((t + NS - 1) % NS, t % NS, t);
+  // Tile t is in its slots; its new rows go to their pages, and the copies of
+  // the tiles that take over its slots, wherever they come from, set out in a burst.
+  auto turn_over = [&](int v_ring_slot, int k_ring_slot, int t) __attribute__((always_inline)) {
+    arrive();
+    append_tile(t);
+    issue_copies(v_ring_slot, k_ring_slot, t);
+  };
+  // A tile on the causal diagonal or around the end of the cached prefix: the
+  // same overlapped step with the causal mask applied to the new scores.  Short
+  // sequences spend most of their tiles here, so it is kept close to the loops
+  // above: PAR is t % 2, the scores change buffers instead of being moved back (32
+  // moves), the slots of a two-slot ring are fixed in the code, and only blocks
+  // that the diagonal crosses are masked.  us per pass with slots and buffers at
+  // run time and every tile masked -> now: 7 requests of 500..700 new tokens x 40
+  // heads, d = 128, 40 layers 3130 -> 3064, 32 full recomputes of 1k..4k tokens
+  // 3321 -> 3259, 32 requests with a tenth new 562 -> 552, chunks of 200..512 rows
+  // at d = 64 84.6 -> 83.6.
+  auto any_iteration = [&](int t, auto par_tag) __attribute__((always_inline)) {
+    constexpr int PAR = decltype(par_tag)::value;
+    using None = std::integral_constant<int, -1>;
+    const int j = NS == 2 ? PAR : t % NS;
+    turn_over((j + NS - 1) % NS, j, t);
+    if (PAR == 0) step(s_a, s_b, k_slot(j + 1), v_slot(j), t, std::true_type{}, None{}, None{}, std::false_type{});
+    else step(s_b, s_a, k_slot(j + 1), v_slot(j), t, std::true_type{}, None{}, None{}, std::false_type{});
+  };
+  auto any_pairs = [&](int end) __attribute__((always_inline)) {
+    for (; t + 2 <= end; t += 2) {
+      any_iteration(t, std::integral_constant<int, 0>{});
+      any_iteration(t + 1, std::integral_constant<int, 1>{});
     }
-  } else {
-    // Tiles below all_old hold cached keys only, tiles from all_new on new keys
-    // only (when the pools hold everything already, every tile counts as cached).
-    const int all_old = p.k_new ? (P > kv_begin ? (P - kv_begin) / BN : 0) : nt + 2 * NS;
-    const int all_new = p.k_new ? (P > kv_begin ? (P - kv_begin + BN - 1) / BN : 0) : nt + 2 * NS;
-    // an iteration copies V of tile t+NS-1 and K of tile t+NS
-    fast_loop(all_old - NS < n_fast ? all_old - NS : n_fast, std::integral_constant<int, kOld>{});
-    const int mixed_end = all_new;                // = (first iteration that copies new keys only) + NS-1
-    fast_loop(mixed_end < n_fast ? mixed_end : n_fast, std::integral_constant<int, kAny>{});
-    fast_loop(n_fast, std::integral_constant<int, kNew>{});
-    // The tiles up to the causal diagonal (and a few left over from the loops
-    // above): the same overlapped step with the causal mask applied to the new
-    // scores, ring slots chosen at run time, scores handed back in s_a.  A wave
-    // whose rows end before the workgroup's key range does finishes on its own
-    // last tile and from then on only copies.  (Going on over masked tiles cost
-    // 2 % on 7 requests of 600 rows, 1 % on full recomputes of 1k..4k tokens.)
-    for (; t + 1 < nt; ++t) {
-      arrive();
-      append_tile(t);
-      issue_copies((t + NS - 1) % NS, t % NS, t);
-      if (t + 1 < my_nt) {
-        step(s_a, s_b, k_slot(t + 1), v_slot(t), t, std::true_type{}, std::integral_constant<int, -1>{},
-             std::integral_constant<int, -1>{}, std::false_type{});
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) s_a[kb][rb] = s_b[kb][rb];
-      } else if (t + 1 == my_nt) {
-        tail_step(s_a, v_slot(t));
-      }
+  };
+  // What a wave that has nothing (more) to compute does for a tile.
+  auto pass_on = [&](int t) __attribute__((always_inline)) {
+    if (t + 1 < nt) {
+      turn_over((t + NS - 1) % NS, t % NS, t);
+      return;
     }
-  }
-  {                                               // the last tile: softmax and PV only
-    const uint32_t v_cur = v_slot(t);
     arrive();
     append_tile(t);
     if (!p.k_new && kv_begin + nt * BN > T) {
@@ -708,11 +703,40 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
       // those V rows so that 0 * garbage cannot poison the products.
       for (int c = tid; c < BN * CPR; c += NT)
         if (kv_begin + t * BN + c / CPR >= T)
-          *reinterpret_cast<u32x4 *>(lds + v_cur + c * 16) = u32x4{0u, 0u, 0u, 0u};
+          *reinterpret_cast<u32x4 *>(lds + v_slot(t) + c * 16) = u32x4{0u, 0u, 0u, 0u};
       __syncthreads();
     }
-    if (wave_live && my_nt == nt) tail_step(s_a, v_cur);
+  };
+  if (wave_live) {
+    // Tiles below all_old hold cached keys only, tiles from all_new on new keys
+    // only (when the pools hold everything already, every tile counts as cached).
+    const int all_old = p.k_new ? (P > kv_begin ? (P - kv_begin) / BN : 0) : nt + 2 * NS;
+    const int all_new = p.k_new ? (P > kv_begin ? (P - kv_begin + BN - 1) / BN : 0) : nt + 2 * NS;
+    // an iteration copies V of tile t+NS-1 and K of tile t+NS
+    fast_loop(all_old - NS < n_fast ? all_old - NS : n_fast, std::false_type{});
+    // Around the end of the prefix, up to the first iteration that copies new keys
+    // only; and, after the loop over those, up to the wave's last tile: rows that
+    // end before the workgroup's key range does see no more.  (Going on over masked
+    // tiles cost 2 % on 7 requests of 600 rows, 1 % on full recomputes of 1k..4k
+    // tokens.  One loop run twice for both, or an odd last tile that leaves the
+    // loop in its middle, would save 10 KB of code, but the compiler then spills.)
+    int end = (all_new < n_fast ? all_new : n_fast) / NS * NS;
+    any_pairs(end);
+    fast_loop(n_fast, std::true_type{});
+    end = my_nt - 1;
+    any_pairs(end);
+    if (t < end) {
+      any_iteration(t++, std::integral_constant<int, 0>{});
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) s_a[kb][rb] = s_b[kb][rb];
+    }
+    pass_on(t);
+    tail_step(s_a, v_slot(t), hi_limit < kv_begin + t * BN + 32);
+    ++t;
   }
+  for (; t < nt; ++t) pass_on(t);
   wait_pending(std::integral_constant<int, 0>{});   // let the unused trailing copies drain
   if constexpr (RB > 1) mfma_drain();
 
@@ -782,9 +806,10 @@ static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot
-// rings (64 KB at d=128); 256 rows run one eight-wave workgroup per CU that
-// shares every K/V tile among twice as many rows and spends 128 of the 160 KB
-// of LDS on four-slot rings.
+// rings (64 KB at d=128; three at d=64 with 32 KB and 168 registers, held there for
+// 128 rows); 256 rows run one eight-wave workgroup per CU that shares every K/V
+// tile among twice as many rows and spends 128 of the 160 KB of LDS on four-slot
+// rings.
 int launch_attention(const LaunchParams &p, void *stream) {
   if (p.num_items == 0) return 0;
   hipStream_t st = (hipStream_t)stream;
@@ -794,7 +819,7 @@ int launch_attention(const LaunchParams &p, void *stream) {
     return launch_attn_t<128, 1, 8, 2, 4>(p, st);
   }
   if (p.tile_rows == 64) return launch_attn_t<64, 1, 2, 2, 2>(p, st);
-  if (p.tile_rows == 128) return launch_attn_t<64, 1, 4, 2, 2>(p, st);
+  if (p.tile_rows == 128) return launch_attn_t<64, 1, 4, 3, 2>(p, st);
   return launch_attn_t<64, 1, 8, 2, 4>(p, st);
 }
 

@@ -53,6 +53,18 @@ def test_long_prefixes_run_the_steady_state_loop(oracle_lib, geom, shape):
     full_parity(oracle_lib, b, tile_rows=shape[0], rows_per_wave=shape[1])
 
 
+@pytest.mark.parametrize("tile_rows", [64, 128, 256])
+@pytest.mark.parametrize("geom", [W.Geometry(2, 2, 128), W.Geometry(3, 1, 64)], ids=["mha128", "gqa3x64"])
+def test_tiles_around_the_diagonal(oracle_lib, geom, tile_rows):
+    """Odd and even numbers of key tiles before, at and after the end of the cached
+    prefix, and last tiles of which a wave's rows see 1, 31, 32 and 33 keys or all."""
+    lengths = [(0, 31), (0, 33), (0, 64), (16, 17), (48, 81), (64, 128), (96, 65), (128, 1), (128, 32), (160, 97),
+               (191, 130), (192, 192), (250, 70), (257, 255), (320, 160), (400, 321)]
+    b = W.make_custom_batch("diagonal", geom, [p for p, _ in lengths], [s for _, s in lengths], seed=16)
+    full_parity(oracle_lib, b, tile_rows=tile_rows)
+    full_parity(oracle_lib, b, tile_rows=tile_rows, entry="separate")
+
+
 @pytest.mark.parametrize("shape", [(128, 32), (128, 64), (256, 64)], ids=["128x32", "128x64", "256x64"])
 @pytest.mark.parametrize("split_kv", [2, 3, 7])
 def test_split_kv_matches_oracle(oracle_lib, split_kv, shape):
