@@ -59,6 +59,8 @@ __device__ __forceinline__ i32x4 block_resource(const void *base, uint32_t bytes
   r[3] = 0x00020000;                                 // 32-bit untyped data
   return r;
 }
+// ONCE: rows that nothing else will ask for (no reuse in the caches).
+template <bool ONCE = false>
 __device__ __forceinline__ void copy16_to_lds(i32x4 rsrc, uint32_t lane_off, uint32_t lds_base) {
   // wave-uniform by construction; say so, in case the value was computed on the vector ALU
 #pragma unroll
@@ -69,10 +71,16 @@ __device__ __forceinline__ void copy16_to_lds(i32x4 rsrc, uint32_t lane_off, uin
   // kernels that copy this way use nothing for which the compiler would set
   // M0 itself (no LDS-DMA builtins, no indexed register moves, no messages);
   // tests/test_kernel_assembly.py checks the generated code for that.
-  __asm__ volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %0, 0 offen lds"
-                   :
-                   : "s"(rsrc), "v"(lane_off), "s"(lds_base)
-                   : "memory");
+  if constexpr (ONCE)
+    __asm__ volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %0, 0 offen nt lds"
+                     :
+                     : "s"(rsrc), "v"(lane_off), "s"(lds_base)
+                     : "memory");
+  else
+    __asm__ volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %0, 0 offen lds"
+                     :
+                     : "s"(rsrc), "v"(lane_off), "s"(lds_base)
+                     : "memory");
 }
 
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
@@ -103,6 +111,7 @@ __device__ __forceinline__ AttnItem load_item(const AttnItem *items, int i) {
   AttnItem it;
   it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.kv_begin = w[3]; it.kv_end = w[4];
   it.part_slot = w[5]; it.prefix = w[6]; it.suffix = w[7]; it.q_off = w[8]; it.group = w[9];
+  it.read_once = w[10];
   return it;
 }
 

@@ -30,7 +30,8 @@ struct AttnItem {
   int32_t suffix;      // S_r
   int32_t q_off;       // token offset of the request in the packed q/out arrays
   int32_t group;       // part_slot >= 0: the ReduceGroup that merges it
-  int32_t pad[6];
+  int32_t read_once;   // nothing else will ask for these cached pages soon: read them past the caches
+  int32_t pad[5];
 };
 static_assert(sizeof(AttnItem) == 64, "AttnItem is 64 bytes");
 
@@ -66,6 +67,7 @@ struct Schedule {
   int rows_per_wave = 32;
   bool stream = false;         // few rows per kv head: the kernel whose waves split the keys
   bool fused_append = false;   // attention may read new tokens from the packed arrays and append them itself
+  bool read_once = false;      // some item has the flag of that name
   std::vector<AttnItem> items;
   std::vector<ReduceGroup> groups;
   std::vector<int32_t> q_off;   // per request: first row in the packed q / k_suffix / v_suffix arrays
@@ -134,6 +136,7 @@ struct LaunchParams {
   AttnArgs args;
   int num_items;
   int num_groups;
+  bool read_once;
   int tile_rows;
   int rows_per_wave;
   int d;

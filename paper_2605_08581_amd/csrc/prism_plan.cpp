@@ -364,10 +364,20 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     return ka != kb ? ka > kb : a < b;
   });
 
+  // The key-splitting kernel reads every key of an item once: pages of one request
+  // alone can pass the caches by, if the wave is more than those of the dies hold
+  // (8 x 4 MB; below, the step before may have left them there).  us, kept -> passed
+  // by: 16 requests x 300..4100 keys x 8 heads (143 MB) 31.1 -> 27.4, 64 x 4096 x 40
+  // (4.4 GB) 733 -> 703, 65 MB 14.8 -> 14.6, but 20 MB 11.3 -> 11.5 and 5 MB 6.2 ->
+  // 6.7; with pages shared by two, eight and 32 of 32 requests x 4096 keys x 40 heads
+  // 258 -> 270, 168 -> 190 and 156 -> 162.
+  const bool reads_once = stream && opt.block_table_host && sch.kv_bytes > (int64_t)kNumXCD * (4 << 20);
+
   auto deal = [&](const SplitRule &rule) {
     sch.items.clear();
     sch.groups.clear();
     sch.num_split_items = 0;
+    sch.read_once = false;
     // Workgroup b runs on accelerator die b % 8, and each die has its own L2.
     // Row tiles (and key chunks) of one (request, kv head), and of requests with
     // a common cached prefix, read the same K/V pages, so each (cluster, kv
@@ -409,6 +419,8 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
             it.prefix = prefix[req];
             it.suffix = suffix[req];
             it.q_off = q_off[req];
+            it.read_once = j - i == 1 && reads_once;
+            sch.read_once |= it.read_once != 0;
             if (nsplit <= 1) {
               it.kv_begin = 0;
               it.kv_end = kv_len;

@@ -18,8 +18,9 @@
 // tile) the same work left three of four waves without rows, took two barriers
 // per tile and ran a chain of 64-key steps per workgroup.  16 requests x 300 to
 // 4100 keys, 32/8 heads, d = 128 (143 MB): three launches 49 us, now one of
-// 31.5 us = 4.5 TB/s; 64 x 4096 keys, 40 heads (4.37 GB): 771 -> 753 us =
-// 5.8 TB/s, where a plain streaming read reaches 6.5.
+// 31.5 us; 64 x 4096 keys, 40 heads (4.37 GB): 771 -> 753 us.  With the pages
+// of one request alone read past the caches (AttnItem::read_once) 27.4 us =
+// 5.2 TB/s and 699 us = 6.25 TB/s, where a plain streaming read reaches 6.5.
 //
 // Products are taken transposed as in the prefill kernel, with the 16x16x32
 // MFMA because rows come in blocks of 16:
@@ -62,7 +63,8 @@ __device__ __forceinline__ float sum_across_groups(float x) {
   return sum_across_halves(__uint_as_float(a[0]) + __uint_as_float(a[1]));
 }
 
-template <int D, int RB>
+// ONCE: items may have their cached pages to themselves (AttnItem::read_once).
+template <int D, int RB, bool ONCE>
 __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   using Shape = StreamShape<D, RB>;
   constexpr int NW = Shape::NW, NS = Shape::NS;
@@ -183,12 +185,16 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
       if (cached >= kPage) {
         const int valid = T - pos0 < kPage ? T - pos0 : kPage;   // the last page may hold anything past the sequence
         const i32x4 rk = src.old_rows(0, pages.p[pg], valid), rv = src.old_rows(1, pages.p[pg], valid);
+        auto copy_page = [&](auto once) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < UPP; ++i) {
-          const uint32_t off = (uint32_t)((i * KPU + lane_row) * ROW) + lane_chunk[i];
-          copy16_to_lds(rk, off, dst + (uint32_t)(i * 1024));
-          copy16_to_lds(rv, off, dst + (uint32_t)(TK * ROW + i * 1024));
-        }
+          for (int i = 0; i < UPP; ++i) {
+            const uint32_t off = (uint32_t)((i * KPU + lane_row) * ROW) + lane_chunk[i];
+            copy16_to_lds<decltype(once)::value>(rk, off, dst + (uint32_t)(i * 1024));
+            copy16_to_lds<decltype(once)::value>(rv, off, dst + (uint32_t)(TK * ROW + i * 1024));
+          }
+        };
+        if (ONCE && it.read_once) copy_page(std::true_type{});
+        else copy_page(std::false_type{});
       } else if (cached <= 0) {
         const i32x4 rk = src.new_rows(0, pos0 - P), rv = src.new_rows(1, pos0 - P);
 #pragma unroll
@@ -401,10 +407,10 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   }
 }
 
-template <int D, int RB>
+template <int D, int RB, bool ONCE>
 static int launch_stream_t(const LaunchParams &p, hipStream_t st) {
   constexpr size_t lds_bytes = StreamShape<D, RB>::kLdsBytes;
-  auto kernel = stream_attn_kernel<D, RB>;
+  auto kernel = stream_attn_kernel<D, RB, ONCE>;
   static const hipError_t attr = hipFuncSetAttribute(
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (attr != hipSuccess) return (int)attr;
@@ -413,7 +419,8 @@ static int launch_stream_t(const LaunchParams &p, hipStream_t st) {
 
 template <int D>
 static int launch_stream_d(const LaunchParams &p, hipStream_t st) {
-  return p.tile_rows == 16 ? launch_stream_t<D, 1>(p, st) : launch_stream_t<D, 2>(p, st);
+  if (p.read_once) return p.tile_rows == 16 ? launch_stream_t<D, 1, true>(p, st) : launch_stream_t<D, 2, true>(p, st);
+  return p.tile_rows == 16 ? launch_stream_t<D, 1, false>(p, st) : launch_stream_t<D, 2, false>(p, st);
 }
 
 int launch_stream(const LaunchParams &p, void *stream) {

@@ -54,6 +54,22 @@ def test_wave_larger_than_the_chip(oracle_lib, geom):
     assert np.array_equal(W.bf16_bits(t["k_pool"]), kp) and np.array_equal(W.bf16_bits(t["v_pool"]), vp)
 
 
+@pytest.mark.parametrize("geom", [W.Geometry(8, 8, 128), W.Geometry(40, 8, 128), W.Geometry(16, 16, 64)],
+                         ids=["mha128", "g5x128", "mha64"])
+@pytest.mark.parametrize("suffix", [1, 4], ids=["one-row", "four"])
+def test_waves_larger_than_the_l2_caches(oracle_lib, geom, suffix):
+    """Just above and below 32 MB of keys and values, beyond which pages of one request
+    alone are read past the caches: shared and private prefixes in one wave, some
+    ending inside a page."""
+    token = 4 * geom.num_kv_heads * geom.head_dim   # bytes of K and V
+    for total in ((32 << 20) // token + 200, (32 << 20) // token - 200):
+        each = total // 12
+        prefix = [each - 7] * 6 + [each // 16 * 16] * 6
+        prefix[0] += total - sum(prefix) - 12 * suffix
+        b = W.make_custom_batch("once", geom, prefix, [suffix] * 12, seed=66, share_groups=[-1] * 6 + [0, 0, 0, 1, 1, -1])
+        full_parity(oracle_lib, b)
+
+
 @pytest.mark.parametrize("suffix", [[20, 20], [150, 40]], ids=["stream", "tile"])
 @pytest.mark.parametrize("hint", [True, False], ids=["table", "no-table"])
 def test_prefix_pages_written_by_the_same_wave(oracle_lib, suffix, hint):
