@@ -182,9 +182,10 @@ __device__ __forceinline__ float2 load_shared(const float *src) {
 }
 
 template <int D>
-__device__ __forceinline__ void store_out_row(const AttnArgs &p, int q_off, int kv_head, int G, int row, int c4,
+__device__ __forceinline__ void store_out_row(const AttnArgs &p, int q_off, int kv_head, const Divisor &G, int row, int c4,
                                               const __attribute__((ext_vector_type(4))) float &acc, float scale) {
-  __bf16 *op = (__bf16 *)p.out + ((int64_t)(q_off + row / G) * p.Hq + kv_head * G + row % G) * D + c4;
+  const int tok = G.quotient(row);
+  __bf16 *op = (__bf16 *)p.out + ((int64_t)(q_off + tok) * p.Hq + kv_head * G.d + (row - tok * G.d)) * D + c4;
   bf16x4 o4;
 #pragma unroll
   for (int r = 0; r < 4; ++r) o4[r] = (__bf16)(acc[r] * scale);
@@ -219,14 +220,14 @@ __device__ __forceinline__ float2 load_part(const float *src) {
   else return *reinterpret_cast<const float2 *>(src);
 }
 template <int D, int R, int BATCH, bool SHARED>
-__device__ __forceinline__ void merge_group(const AttnArgs &p, int group, int G, int tile_rows, int tid, int threads,
+__device__ __forceinline__ void merge_group(const AttnArgs &p, int group, const Divisor &G, int tile_rows, int tid, int threads,
                                             int begin, int end) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_;
   constexpr int TPR = D / 4;
   const ReduceGroup g = load_group(p.groups, group);
   const size_t slot_f = (size_t)tile_rows * (D + 2);
   const float *base = p.partials + (size_t)g.first_slot * slot_f;
-  int n = g.suffix * G - g.row0;
+  int n = g.suffix * G.d - g.row0;
   if (n > tile_rows) n = tile_rows;
   if (n > end) n = end;
   const int c4 = (tid % TPR) * 4, step = threads / TPR;

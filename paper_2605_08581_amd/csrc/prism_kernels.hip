@@ -784,15 +784,14 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 // the key-splitting kernel merges its few rows itself).  A merge inside the
 // attention kernel was 40 us slower on 8 requests x 16k-32k keys: partials of
 // 64 KB have to be written through to memory, and one workgroup then reads
-// hundreds of KB while its CU half idles.  Here a thread takes four dims of two
-// rows, up to four partials of each in flight at once.
+// hundreds of KB while its CU half idles.  Here a thread takes four dims of R
+// rows, up to BATCH partials of each in flight at once.
 // --------------------------------------------------------------------------
-constexpr int kReduceRows = 2;                    // rows per thread
-template <int D>
+template <int D, int R, int BATCH>
 __global__ __launch_bounds__(256) void split_reduce_kernel(const AttnArgs p, int tile_rows) {
-  constexpr int ROWS = 256 / (D / 4) * kReduceRows;
-  merge_group<D, kReduceRows, 4, false>(p, blockIdx.x, p.Hq / p.Hkv, tile_rows, threadIdx.x, 256, blockIdx.y * ROWS,
-                                        (blockIdx.y + 1) * ROWS);
+  constexpr int ROWS = 256 / (D / 4) * R;
+  merge_group<D, R, BATCH, false>(p, blockIdx.x, p.group, tile_rows, threadIdx.x, 256, blockIdx.y * ROWS,
+                                  (blockIdx.y + 1) * ROWS);
 }
 
 template <int D, int RB, int NW, int WPE, int NS>
@@ -825,10 +824,19 @@ int launch_attention(const LaunchParams &p, void *stream) {
 
 int launch_reduce(const LaunchParams &p, void *stream) {
   if (p.num_groups == 0) return 0;
-  const int rows = 256 / (p.d / 4) * kReduceRows;
-  const dim3 grid((unsigned)p.num_groups, (unsigned)((p.tile_rows + rows - 1) / rows));
-  return launch_kernel(p.d == 128 ? split_reduce_kernel<128> : split_reduce_kernel<64>, grid, dim3(256), 0,
-                       (hipStream_t)stream, p.args, p.tile_rows);
+  const int pass = 256 / (p.d / 4);               // rows of a workgroup at one per thread
+  const int per = (p.tile_rows + pass - 1) / pass;
+  // Merges of few rows are bound by their chain of reads: eight partials at once in
+  // twice the workgroups, as long as those find room together.  us per pass, two
+  // rows and four partials -> one row and eight, 32/8 heads: 37 new over 1003 / 8003
+  // cached tokens 14.2 -> 13.9 / 20.9 -> 18.7, 64 over 16001 at d = 64 22.1 -> 20.0;
+  // 640 workgroups (100 over 4001, 40 heads) 26.9 -> 26.4, but 1024 (four of 60 over
+  // 6001) 41.8 -> 42.1.
+  const bool few = (int64_t)p.num_groups * per <= 3 * kNumCU;
+  const dim3 grid((unsigned)p.num_groups, (unsigned)(few ? per : (per + 1) / 2));
+  auto kernel = p.d == 128 ? (few ? split_reduce_kernel<128, 1, 8> : split_reduce_kernel<128, 2, 4>)
+                           : (few ? split_reduce_kernel<64, 1, 8> : split_reduce_kernel<64, 2, 4>);
+  return launch_kernel(kernel, grid, dim3(256), 0, (hipStream_t)stream, p.args, p.tile_rows);
 }
 
 // --------------------------------------------------------------------------

@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
       for (int r = 0; r < 4; ++r) acc[r] += e * o[r];
     }
     if (!slot_out) {
-      store_out_row<D>(p, it.q_off, it.kv_head, G.d, row, c4, acc, 1.0f / l);
+      store_out_row<D>(p, it.q_off, it.kv_head, G, row, c4, acc, 1.0f / l);
     } else {
       store_shared(slot_out + (size_t)row * D + c4, acc[0], acc[1]);
       store_shared(slot_out + (size_t)row * D + c4 + 2, acc[2], acc[3]);
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   }
   if (slot_out) {
     int *flag = reinterpret_cast<int *>(lds + Shape::kRingBytes);   // Q is no longer needed
-    if (last_of_group(p, it.group, tid, flag)) merge_group<D, 1, 8, true>(p, it.group, G.d, Shape::kRows, tid, NT, 0, Shape::kRows);
+    if (last_of_group(p, it.group, tid, flag)) merge_group<D, 1, 8, true>(p, it.group, G, Shape::kRows, tid, NT, 0, Shape::kRows);
   }
 }
 

@@ -73,6 +73,19 @@ def test_split_kv_matches_oracle(oracle_lib, split_kv, shape):
     assert info.num_reduce_groups > 0
 
 
+@pytest.mark.parametrize("requests", [3, 48, 49], ids=["small", "few", "many"])
+@pytest.mark.parametrize("split_kv", [5, 8, 9])
+@pytest.mark.parametrize("geom", [W.Geometry(6, 2, 128), W.Geometry(4, 4, 64)], ids=["gqa3x128", "mha64"])
+def test_merge_of_few_and_of_many_rows(oracle_lib, geom, split_kv, requests):
+    """Up to 768 workgroups at one row per thread (48 requests of one tile) a merge
+    reads eight partials at once, beyond them four: below, at and above those numbers."""
+    prefix = [64 * split_kv - 60 + r % 30 for r in range(requests)]      # one key tile a piece
+    b = W.make_custom_batch("merge", geom, prefix, [11 + r % 10 for r in range(requests)], seed=17)
+    info = full_parity(oracle_lib, b, split_kv=split_kv, tile_rows=64)
+    assert info.num_reduce_groups == requests * geom.num_kv_heads
+    assert info.num_split_items == split_kv * info.num_reduce_groups
+
+
 def test_split_and_unsplit_agree():
     b = W.make_custom_batch("split", W.Geometry(4, 4, 128), [900, 130], [100, 260], seed=7)
     t = W.make_tensors(b, "cuda")
