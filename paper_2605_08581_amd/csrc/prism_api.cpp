@@ -212,6 +212,7 @@ LaunchParams make_params(const prism_plan *p, const void *q, const void *k_new, 
   a.scale_log2e = p->scale_log2e;
   lp.num_items = (int)p->sch.items.size();
   lp.num_groups = (int)p->sch.groups.size();
+  lp.most_pieces = p->sch.most_pieces;
   lp.read_once = p->sch.read_once;
   lp.tile_rows = p->sch.tile_rows;
   lp.rows_per_wave = p->sch.rows_per_wave;

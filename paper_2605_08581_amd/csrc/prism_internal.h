@@ -68,6 +68,7 @@ struct Schedule {
   bool stream = false;         // few rows per kv head: the kernel whose waves split the keys
   bool fused_append = false;   // attention may read new tokens from the packed arrays and append them itself
   bool read_once = false;      // some item has the flag of that name
+  int most_pieces = 0;         // of any group
   std::vector<AttnItem> items;
   std::vector<ReduceGroup> groups;
   std::vector<int32_t> q_off;   // per request: first row in the packed q / k_suffix / v_suffix arrays
@@ -136,6 +137,7 @@ struct LaunchParams {
   AttnArgs args;
   int num_items;
   int num_groups;
+  int most_pieces;
   bool read_once;
   int tile_rows;
   int rows_per_wave;

@@ -826,16 +826,23 @@ int launch_reduce(const LaunchParams &p, void *stream) {
   if (p.num_groups == 0) return 0;
   const int pass = 256 / (p.d / 4);               // rows of a workgroup at one per thread
   const int per = (p.tile_rows + pass - 1) / pass;
-  // Merges of few rows are bound by their chain of reads: eight partials at once in
-  // twice the workgroups, as long as those find room together.  us per pass, two
-  // rows and four partials -> one row and eight, 32/8 heads: 37 new over 1003 / 8003
-  // cached tokens 14.2 -> 13.9 / 20.9 -> 18.7, 64 over 16001 at d = 64 22.1 -> 20.0;
-  // 640 workgroups (100 over 4001, 40 heads) 26.9 -> 26.4, but 1024 (four of 60 over
-  // 6001) 41.8 -> 42.1.
+  // Merges of few rows are bound by their chain of reads: all partials at once, up
+  // to sixteen, in twice the workgroups, as long as those find room together.  us per
+  // pass, two rows and four partials -> one row and as many as there are, 32/8 heads:
+  // 37 new over 1003 cached tokens (3 pieces) 14.2 -> 13.6, over 8003 (14) 20.4 -> 18.3,
+  // 64 over 16001 at d = 64 (16) 22.1 -> 19.3; 100 over 4001, 40 heads (640 workgroups, 6 pieces) 26.8 -> 26.4, but
+  // 1024 (four of 60 over 6001) 41.8 -> 42.1.  Asking for more than there are costs as
+  // much as it gives: those 3 pieces 13.9 with eight, 14.5 with sixteen.
   const bool few = (int64_t)p.num_groups * per <= 3 * kNumCU;
   const dim3 grid((unsigned)p.num_groups, (unsigned)(few ? per : (per + 1) / 2));
-  auto kernel = p.d == 128 ? (few ? split_reduce_kernel<128, 1, 8> : split_reduce_kernel<128, 2, 4>)
-                           : (few ? split_reduce_kernel<64, 1, 8> : split_reduce_kernel<64, 2, 4>);
+  auto pick = [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    return !few                 ? split_reduce_kernel<D, 2, 4>
+           : p.most_pieces <= 4 ? split_reduce_kernel<D, 1, 4>
+           : p.most_pieces <= 8 ? split_reduce_kernel<D, 1, 8>
+                                : split_reduce_kernel<D, 1, 16>;
+  };
+  auto kernel = p.d == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
   return launch_kernel(kernel, grid, dim3(256), 0, (hipStream_t)stream, p.args, p.tile_rows);
 }
 

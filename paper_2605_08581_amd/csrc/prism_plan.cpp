@@ -378,6 +378,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     sch.groups.clear();
     sch.num_split_items = 0;
     sch.read_once = false;
+    sch.most_pieces = 0;
     // Workgroup b runs on accelerator die b % 8, and each die has its own L2.
     // Row tiles (and key chunks) of one (request, kv head), and of requests with
     // a common cached prefix, read the same K/V pages, so each (cluster, kv
@@ -444,6 +445,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
             g.kv_head = h;
             g.row0 = it.row0;
             g.nsplit = nsplit;
+            sch.most_pieces = std::max(sch.most_pieces, nsplit);
             g.first_slot = next_slot;
             g.suffix = suffix[req];
             g.q_off = q_off[req];

@@ -74,11 +74,12 @@ def test_split_kv_matches_oracle(oracle_lib, split_kv, shape):
 
 
 @pytest.mark.parametrize("requests", [3, 48, 49], ids=["small", "few", "many"])
-@pytest.mark.parametrize("split_kv", [5, 8, 9])
+@pytest.mark.parametrize("split_kv", [4, 5, 8, 9, 17])
 @pytest.mark.parametrize("geom", [W.Geometry(6, 2, 128), W.Geometry(4, 4, 64)], ids=["gqa3x128", "mha64"])
 def test_merge_of_few_and_of_many_rows(oracle_lib, geom, split_kv, requests):
     """Up to 768 workgroups at one row per thread (48 requests of one tile) a merge
-    reads eight partials at once, beyond them four: below, at and above those numbers."""
+    reads up to four, eight or sixteen partials at once, beyond them four: below, at
+    and above those numbers."""
     prefix = [64 * split_kv - 60 + r % 30 for r in range(requests)]      # one key tile a piece
     b = W.make_custom_batch("merge", geom, prefix, [11 + r % 10 for r in range(requests)], seed=17)
     info = full_parity(oracle_lib, b, split_kv=split_kv, tile_rows=64)
