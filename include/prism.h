@@ -151,6 +151,16 @@ int prism_plan_dry_run(const prism_shape_t *shape, const int32_t *prefix_len_hos
                        prism_plan_info_t *info, size_t *workspace_bytes, int32_t *items_out,
                        int32_t items_capacity);
 
+/*
+ * Of the work items that prism_plan_dry_run lists for the same arguments, in that
+ * order: 1 where the kernel reads the item's cached pages past the caches, which it
+ * does with pages that nothing else in a large wave reads (a hint to the hardware;
+ * results do not depend on it).  Returns the number of items or an error code.
+ */
+int prism_plan_dry_run_read_once(const prism_shape_t *shape, const int32_t *prefix_len_host,
+                                 const int32_t *suffix_len_host, const prism_plan_options_t *options,
+                                 uint8_t *flags_out, int32_t flags_capacity);
+
 /* Bytes of caller workspace that prism_prefix_prefill / prism_prefix_attention
  * need with this plan: the work lists, then the split-KV partial slots.  0 only
  * for a plan without suffix tokens. */

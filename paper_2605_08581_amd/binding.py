@@ -25,7 +25,7 @@ ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE_TOO_SMALL, ERR_HIP, ERR_NO_MEMOR
 
 EXPORTS = (
     "prism_version", "prism_strerror", "prism_last_hip_error", "prism_plan_create",
-    "prism_plan_dry_run", "prism_plan_workspace_bytes", "prism_plan_get_info", "prism_plan_forget_workspace",
+    "prism_plan_dry_run", "prism_plan_dry_run_read_once", "prism_plan_workspace_bytes", "prism_plan_get_info", "prism_plan_forget_workspace",
     "prism_plan_destroy", "prism_kv_append",
     "prism_prefix_attention", "prism_prefix_prefill", "prism_prefix_prefill_static", "prism_validate",
     "prism_plan_profile_enable", "prism_plan_profile_read", "prism_measure_peaks",
@@ -93,6 +93,9 @@ def load():
     lib.prism_plan_dry_run.argtypes = [ctypes.POINTER(Shape), vp, vp, ctypes.POINTER(PlanOptions),
                                        ctypes.POINTER(PlanInfo), ctypes.POINTER(ctypes.c_size_t), vp,
                                        ctypes.c_int32]
+    lib.prism_plan_dry_run_read_once.restype = ctypes.c_int
+    lib.prism_plan_dry_run_read_once.argtypes = [ctypes.POINTER(Shape), vp, vp, ctypes.POINTER(PlanOptions), vp,
+                                                 ctypes.c_int32]
     lib.prism_plan_workspace_bytes.restype = ctypes.c_size_t
     lib.prism_plan_workspace_bytes.argtypes = [vp]
     lib.prism_plan_get_info.restype = ctypes.c_int
@@ -199,6 +202,23 @@ def prism_plan_dry_run(shape: Shape, prefix_len, suffix_len, tile_rows: int = 0,
         lib.prism_plan_dry_run(ctypes.byref(shape), pl.ctypes.data, sl.ctypes.data, ctypes.byref(opt),
                                None, None, items.ctypes.data, n)
     return info, int(ws.value), items
+
+
+def prism_plan_dry_run_read_once(shape: Shape, prefix_len, suffix_len, tile_rows: int = 0, split_kv: int = 0,
+                                 min_split_keys: int = 0, block_table=None, rows_per_wave: int = 0,
+                                 table_is_final: bool = True):
+    """For each item of ``prism_plan_dry_run`` with the same arguments: whether its cached pages are read past the caches."""
+    lib = load()
+    pl, sl = _host_i32(prefix_len), _host_i32(suffix_len)
+    opt, _bt = _options(tile_rows, split_kv, min_split_keys, block_table, rows_per_wave, table_is_final)
+    args = (ctypes.byref(shape), pl.ctypes.data, sl.ctypes.data, ctypes.byref(opt))
+    n = lib.prism_plan_dry_run_read_once(*args, None, 0)
+    if n < 0:
+        raise PrismError(n, "prism_plan_dry_run_read_once")
+    flags = np.zeros(n, dtype=np.uint8)
+    if n:
+        lib.prism_plan_dry_run_read_once(*args, flags.ctypes.data, n)
+    return flags != 0
 
 
 class Plan:

@@ -439,6 +439,26 @@ int prism_plan_dry_run(const prism_shape_t *shape, const int32_t *prefix_len_hos
   return (int)sch.items.size();
 }
 
+int prism_plan_dry_run_read_once(const prism_shape_t *shape, const int32_t *prefix_len_host,
+                                 const int32_t *suffix_len_host, const prism_plan_options_t *options,
+                                 uint8_t *flags_out, int32_t flags_capacity) {
+  if (!shape || !prefix_len_host || !suffix_len_host) return PRISM_ERR_INVALID_ARG;
+  prism_plan_options_t opt;
+  std::memset(&opt, 0, sizeof opt);
+  if (options) opt = *options;
+  Schedule sch;
+  int rc;
+  try {
+    rc = build_schedule(*shape, prefix_len_host, suffix_len_host, opt, &sch);
+  } catch (const std::bad_alloc &) {
+    rc = PRISM_ERR_NO_MEMORY;
+  }
+  if (rc != PRISM_OK) return rc;
+  for (size_t i = 0; flags_out && i < sch.items.size() && (int32_t)i < flags_capacity; ++i)
+    flags_out[i] = sch.items[i].read_once != 0;
+  return (int)sch.items.size();
+}
+
 size_t prism_plan_workspace_bytes(const prism_plan_t *plan) { return plan ? plan->total_bytes : 0; }
 
 int prism_plan_get_info(const prism_plan_t *plan, prism_plan_info_t *out) {

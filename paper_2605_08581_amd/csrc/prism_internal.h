@@ -15,6 +15,7 @@ constexpr int kTileKeys = 64;      // keys per inner iteration of the attention 
 constexpr int kStreamRows = 32;    // most packed rows per (request, kv head) of the key-splitting kernel
 constexpr int kNumCU = 256;        // MI355X compute units
 constexpr int kNumXCD = 8;         // accelerator complex dies, each with its own L2
+constexpr int64_t kCacheBytes = (int64_t)kNumXCD * (4 << 20);   // of those L2s together
 
 // One attention workgroup: a tile of packed query rows of one (request, kv
 // head) against the key range [kv_begin, kv_end).  Packed row rho of a kv head

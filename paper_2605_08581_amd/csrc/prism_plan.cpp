@@ -9,6 +9,7 @@
 // longest first.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <map>
 #include <set>
 #include <tuple>
@@ -248,6 +249,41 @@ bool reads_pages_of_this_wave(const prism_shape_t &s, const int32_t *prefix, con
   return false;
 }
 
+// Whether the tables of `requests` name more than `limit` different pages.  Stops
+// looking there: the set, open addressing again, stays at most half full.  What a
+// request's table has in common with the first of its cluster, which is one of them
+// too, is compared and not looked up (a plan of 63 requests sharing 1000 pages:
+// 226 us, now 154, without the count 133).
+bool distinct_pages_exceed(const prism_shape_t &s, const std::vector<int> &requests, const std::vector<int> &cluster,
+                           const int32_t *prefix, const int32_t *suffix, const int32_t *table, int64_t limit) {
+  auto row = [&](int r) { return table + (size_t)r * s.max_blocks_per_req; };
+  auto pages = [&](int r) { return (prefix[r] + suffix[r] + kPage - 1) / kPage; };
+  int64_t entries = 0, distinct = 0;
+  for (int r : requests) entries += pages(r);
+  if (entries <= limit) return false;
+  int bits = 4;
+  while (((int64_t)1 << bits) < 2 * (limit + 1)) ++bits;
+  std::vector<int32_t> seen((size_t)1 << bits, -1);
+  for (int r : requests) {
+    const int first = cluster[r];
+    const int32_t *page = row(r), *end = page + pages(r);
+    if (r != first) {
+      constexpr int kRun = 16;
+      const int common = std::min(pages(r), pages(first));
+      for (int b = 0; b + kRun <= common && !std::memcmp(row(r) + b, row(first) + b, kRun * sizeof *page); b += kRun) page += kRun;
+    }
+    for (; page < end; ++page) {
+      if (*page < 0) continue;
+      size_t i = (uint32_t)*page * 0x9E3779B1u >> (32 - bits);
+      while (seen[i] != -1 && seen[i] != *page) i = (i + 1) & (seen.size() - 1);
+      if (seen[i] == *page) continue;
+      if (++distinct > limit) return true;
+      seen[i] = *page;
+    }
+  }
+  return false;
+}
+
 }  // namespace
 
 int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t *suffix,
@@ -263,6 +299,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   if (opt.split_kv < 0 || opt.min_split_keys < 0 || opt.min_split_keys % kTileKeys != 0)
     return PRISM_ERR_UNSUPPORTED;
   const int d = s.head_dim;
+  const int64_t token_bytes = 2LL * 2 * d * s.num_kv_heads;   // K and V
 
   Schedule sch;
   std::vector<int32_t> q_off(s.batch);
@@ -279,7 +316,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     total += S;
     sch.flops += 4LL * d * s.num_q_heads * (S * P + S * (S + 1) / 2);
     if (S > 0) {
-      sch.kv_bytes += 2LL * 2 * d * s.num_kv_heads * (P + S);
+      sch.kv_bytes += token_bytes * (P + S);
       most_rows = std::max(most_rows, S * G);
       ++ranges;
       range_tiles += (P + S + kTileKeys - 1) / kTileKeys;
@@ -319,13 +356,16 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // heads took 441 us, now 108.)
   std::vector<int> first_tile(s.batch + 1, 0), tile_keys;
   std::vector<int64_t> cluster_cost(s.batch, 0);       // key tiles of the cluster, of one kv head
-  std::vector<int> live;
+  std::vector<int> live, sharers(s.batch, 0);          // requests with rows; how many of them are in the cluster
   int most_cost = 0;
   int64_t clusters = 0;
   for (int r = 0; r < s.batch; ++r) {
     const int P = prefix[r], S = suffix[r];
     const int rows = S * G;
-    if (S > 0) live.push_back(r);
+    if (S > 0) {
+      live.push_back(r);
+      ++sharers[cluster[r]];
+    }
     clusters += S > 0 && cluster[r] == r;
     for (int row0 = 0; row0 < rows; row0 += tile_rows) {
       const int kv_len = P + (std::min(rows, row0 + tile_rows) - 1) / G + 1;
@@ -366,12 +406,35 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 
   // The key-splitting kernel reads every key of an item once: pages of one request
   // alone can pass the caches by, if the wave is more than those of the dies hold
-  // (8 x 4 MB; below, the step before may have left them there).  us, kept -> passed
-  // by: 16 requests x 300..4100 keys x 8 heads (143 MB) 31.1 -> 27.4, 64 x 4096 x 40
-  // (4.4 GB) 733 -> 703, 65 MB 14.8 -> 14.6, but 20 MB 11.3 -> 11.5 and 5 MB 6.2 ->
-  // 6.7; with pages shared by two, eight and 32 of 32 requests x 4096 keys x 40 heads
-  // 258 -> 270, 168 -> 190 and 156 -> 162.
-  const bool reads_once = stream && opt.block_table_host && sch.kv_bytes > (int64_t)kNumXCD * (4 << 20);
+  // (8 x 4 MB), a page counting once however many requests share it.  us per pass,
+  // kept -> passed by, with more pools in rotation than the 256 MB memory-side cache
+  // holds, as in a model whose layers have a pool each | on one pool again and again;
+  // one new token a request, d = 128 but where said:
+  //   20 MB (16 x 300 keys, 8 heads)     8.10 ->  7.98 |  6.26 ->  6.37
+  //   34 MB (16 x 500)                   9.96 ->  9.60 |  7.48 ->  8.16
+  //   46 MB (16 x 700)                  13.65 -> 12.63 | 11.95 -> 10.57
+  //   66 MB (16 x 1000)                 16.82 -> 15.46 | 14.95 -> 13.13
+  //   155 MB (16 x 300..4100)           32.31 -> 29.49 | 26.76 -> 27.39
+  //   5.4 GB (64 x 4096, 40 heads)     897 -> 808
+  //   33 MB (16 x 1000, d = 64)         11.24 -> 10.84 |  8.02 ->  8.62
+  // Below the line the gain on pools in rotation (2 %) is no more than the cost on
+  // one that the step before left in the caches (8 new tokens a request would gain
+  // there already: 21 MB 11.13 -> 10.42 | 9.27 -> 9.08).  Pages that several share
+  // are kept: passed by, 32 requests x 4096 keys x 40 heads that share by two, eight
+  // and 32 took 258 -> 270, 168 -> 190 and 156 -> 162.
+  bool reads_once = stream && opt.block_table_host && sch.kv_bytes > kCacheBytes;
+  if (reads_once) {
+    int64_t own = 0;                                 // bytes of requests that share no prefix
+    for (int r : live)
+      if (sharers[cluster[r]] == 1) own += (int64_t)(prefix[r] + suffix[r]) * token_bytes;
+    if (own <= kCacheBytes) {
+      std::vector<int> sharing;
+      for (int r : live)
+        if (sharers[cluster[r]] > 1) sharing.push_back(r);
+      const int64_t room = (kCacheBytes - own) / (kPage * token_bytes);
+      reads_once = own > 0 && distinct_pages_exceed(s, sharing, cluster, prefix, suffix, opt.block_table_host, room);
+    }
+  }
 
   auto deal = [&](const SplitRule &rule) {
     sch.items.clear();
@@ -420,7 +483,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
             it.prefix = prefix[req];
             it.suffix = suffix[req];
             it.q_off = q_off[req];
-            it.read_once = j - i == 1 && reads_once;
+            it.read_once = reads_once && j - i == 1;
             sch.read_once |= it.read_once != 0;
             if (nsplit <= 1) {
               it.kv_begin = 0;

@@ -245,6 +245,34 @@ def test_placement_hint_keeps_prefix_sharers_on_one_die(lib):
     assert all(len(v) == 1 for v in die.values())
 
 
+MIB = 1 << 20
+
+
+@pytest.mark.parametrize("private,shared,flagged", [
+    (32, [], False), (32 + 1 / 16, [], True), (64, [], True), (0, [(64, 2)], False),
+    (2, [(8, 28)], False), (24, [(3, 10), (2, 3)], False), (24, [(4, 10), (5, 2)], True), (33, [(1, 2)], True)],
+    ids=["at-the-line", "a-page-more", "private", "no-private", "many-sharers", "two-clusters-below", "two-clusters-above",
+         "private-above"])
+@pytest.mark.parametrize("geom", [W.Geometry(32, 8, 128), W.Geometry(40, 40, 64)], ids=["gqa128", "mha64"])
+def test_pages_read_past_the_caches(lib, geom, private, shared, flagged):
+    """The pages of requests that share none, if the wave's distinct pages (private: MiB of four requests'
+    own; shared: MiB of a prefix and how many have it) are more than the 32 MiB of the dies' L2 caches."""
+    token = 4 * geom.num_kv_heads * geom.head_dim                # bytes of K and V
+    total = int(private * MIB / token)
+    own = [total // 4] * 3 + [total - total // 4 * 3] if private else []
+    prefix, groups = [n - 1 for n in own], [-1] * len(own)
+    for g, (size, sharers) in enumerate(shared):
+        prefix += [int(size * MIB / token) // 16 * 16] * sharers   # and a page each for the new token
+        groups += [g] * sharers
+    b = W.make_custom_batch("once", geom, prefix, [1] * len(prefix), seed=1, share_groups=groups)
+    args = (B.shape_of(b), b.prefix_len, b.suffix_len)
+    once = lambda **kw: B.prism_plan_dry_run_read_once(*args, **kw)
+    info, _, items = B.prism_plan_dry_run(*args, block_table=b.block_table)
+    assert info.tile_rows == 16
+    assert np.array_equal(once(block_table=b.block_table), flagged & (items[:, 0] >= 0) & (items[:, 0] < len(own)))
+    assert not once().any() and not once(block_table=b.block_table, tile_rows=128).any()
+
+
 def test_append_inside_attention_needs_a_final_table(lib):
     """A table that is only a placement hint may differ from the one on the device: nothing but the order
     of the work follows from it.  Options that a caller has zeroed say just that."""
