@@ -54,20 +54,31 @@ def test_wave_larger_than_the_chip(oracle_lib, geom):
     assert np.array_equal(W.bf16_bits(t["k_pool"]), kp) and np.array_equal(W.bf16_bits(t["v_pool"]), vp)
 
 
-@pytest.mark.parametrize("geom", [W.Geometry(8, 8, 128), W.Geometry(40, 8, 128), W.Geometry(16, 16, 64)],
-                         ids=["mha128", "g5x128", "mha64"])
-@pytest.mark.parametrize("suffix", [1, 4], ids=["one-row", "four"])
-def test_waves_larger_than_the_l2_caches(oracle_lib, geom, suffix):
-    """Just above and below 32 MB of keys and values, beyond which pages of one request
-    alone are read past the caches: shared and private prefixes in one wave, some
-    ending inside a page."""
+@pytest.mark.parametrize("geom,suffix,rows", [
+    (W.Geometry(8, 8, 128), 1, 16), (W.Geometry(8, 8, 128), 4, 16), (W.Geometry(40, 8, 128), 1, 16),
+    (W.Geometry(40, 8, 128), 4, 32), (W.Geometry(16, 16, 64), 1, 16), (W.Geometry(16, 16, 64), 4, 16),
+    (W.Geometry(32, 8, 64), 8, 32)],
+    ids=["mha128-one", "mha128-four", "g5x128-one", "g5x128-four", "mha64-one", "mha64-four", "g4x64-eight"])
+def test_waves_larger_than_the_l2_caches(oracle_lib, geom, suffix, rows):
+    """Just above and below 32 MiB of different pages, beyond which those of one request alone are read
+    past the caches: shared and private prefixes in one wave, some ending inside a page."""
     token = 4 * geom.num_kv_heads * geom.head_dim   # bytes of K and V
-    for total in ((32 << 20) // token + 200, (32 << 20) // token - 200):
-        each = total // 12
-        prefix = [each - 7] * 6 + [each // 16 * 16] * 6
-        prefix[0] += total - sum(prefix) - 12 * suffix
-        b = W.make_custom_batch("once", geom, prefix, [suffix] * 12, seed=66, share_groups=[-1] * 6 + [0, 0, 0, 1, 1, -1])
-        full_parity(oracle_lib, b)
+    line = (32 << 20) // token
+    groups = [-1] * 6 + [0, 0, 0, 1, 1, -1]
+    own = [r for r, g in enumerate(groups) if g < 0]
+    each = line // 10
+    prefix = [each - 7] * 6 + [each // 16 * 16] * 6
+    make = lambda: W.make_custom_batch("once", geom, prefix, [suffix] * 12, seed=66, share_groups=groups)
+    shared = {int(p) for r in range(12) if r not in own
+              for p in make().block_table[r, :-(-(prefix[r] + suffix) // 16)]}
+    for total in (line + 200, line - 200):
+        prefix[0] += total - sum(prefix[r] + suffix for r in own) - 16 * len(shared)
+        b = make()
+        args = (B.shape_of(b), b.prefix_len, b.suffix_len)
+        items = B.prism_plan_dry_run(*args, block_table=b.block_table)[2]
+        once = B.prism_plan_dry_run_read_once(*args, block_table=b.block_table)
+        assert np.array_equal(once, np.isin(items[:, 0], own) & (total > line))
+        assert full_parity(oracle_lib, b).tile_rows == rows
 
 
 @pytest.mark.parametrize("suffix", [[20, 20], [150, 40]], ids=["stream", "tile"])
