@@ -269,10 +269,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // ---- append: new rows are written to their pages straight from the ring
   // slots they were copied into.  The workgroup owns the tokens whose first
   // packed row lies in its row tile and whose position lies in its key range -
-  // every new row once per kv head - and they all lie in the tiles of the last
-  // loop below, each wave writing the rows it copied.  (As a copy of its own at
-  // the end of the workgroup, global to global, the same bytes cost 0.35 ms of
-  // 3.6 ms on 92 765 new tokens x 40 heads: its load latency is not covered.)
+  // every new row once per kv head - each wave writing the rows it copied.  The
+  // loops of fast_iteration do not append: their tiles, those below n_fast, end at
+  // least BN-1 keys before own_lo, which is the last key that the workgroup's first
+  // row sees or the one after it.  (As a copy of its own at the end of the workgroup,
+  // global to global, the same bytes cost 0.35 ms of 3.6 ms on 92 765 new tokens
+  // x 40 heads: its load latency is not covered.)
   int own_lo = 0x7fffffff, own_hi = 0x7fffffff;   // positions
   if (p.k_new) {
     own_lo = P + G.quotient(it.row0 + G.d - 1);
@@ -394,8 +396,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     return pf;
   };
 
-  // Scores of one tile, not overlapped with anything (first tile, and tiles
-  // that need the causal mask).
+  // Scores of the first tile, not overlapped with anything.
   auto plain_scores = [&](f32x16 (&sx)[KB][RB], uint32_t k_lds, int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
@@ -805,10 +806,14 @@ static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot
-// rings (64 KB at d=128; three at d=64 with 32 KB and 168 registers, held there for
-// 128 rows); 256 rows run one eight-wave workgroup per CU that shares every K/V
-// tile among twice as many rows and spends 128 of the 160 KB of LDS on four-slot
-// rings.
+// rings (64 KB at d=128, 32 KB at d=64); 256 rows run one eight-wave workgroup per
+// CU that shares every K/V tile among twice as many rows and spends 128 of the 160
+// KB of LDS (64 at d=64) on four-slot rings.  At d=64, 128 rows are held to the 168
+// registers of three waves per SIMD, for three workgroups per CU.  64 rows are not:
+// four workgroups of two waves at two per SIMD (173 registers) are ahead of the five
+// that three would let live.  us, three -> two: 12 requests of 200..512 rows over
+// 130..3000 keys x 8 heads 96.1 -> 91.4, 24 of 20..60 rows 10.4 -> 9.7, 8 full
+// recomputes of 1k..4k tokens x 32 heads 442 -> 424.
 int launch_attention(const LaunchParams &p, void *stream) {
   if (p.num_items == 0) return 0;
   hipStream_t st = (hipStream_t)stream;

@@ -17,10 +17,10 @@
 // With the row tile of the prefill kernel (128 rows, four waves sharing one
 // tile) the same work left three of four waves without rows, took two barriers
 // per tile and ran a chain of 64-key steps per workgroup.  16 requests x 300 to
-// 4100 keys, 32/8 heads, d = 128 (143 MB): three launches 49 us, now one of
-// 31.5 us; 64 x 4096 keys, 40 heads (4.37 GB): 771 -> 753 us.  With the pages
-// of one request alone read past the caches (AttnItem::read_once) 27.4 us =
-// 5.2 TB/s and 699 us = 6.25 TB/s, where a plain streaming read reaches 6.5.
+// 4100 keys, 32/8 heads, d = 128 (143 MB): three launches 49 us, then one of
+// 31.5 us; 64 x 4096 keys, 40 heads (4.37 GB): 771 -> 753 us.  Now, with the pages
+// of one request alone read past the caches (AttnItem::read_once), 27.3 us =
+// 5.2 TB/s and 694 us = 6.3 TB/s, where a plain streaming read reaches 6.5.
 //
 // Products are taken transposed as in the prefill kernel, with the 16x16x32
 // MFMA because rows come in blocks of 16:
