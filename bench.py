@@ -10,9 +10,11 @@ line carries, under "configs", the attention kernel's time and roofline
 fraction on the other benchmark waves.
 """
 import argparse
+import csv
 import hashlib
 import json
 import os
+import re
 import subprocess
 import sys
 import time
@@ -31,6 +33,27 @@ def kernel_source_sha():
     for f in KERNEL_SOURCES:
         h.update(open(os.path.join(ROOT, "paper_2605_08581_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
+
+
+def record_traffic(prof, workload, out):
+    """HBM traffic of one attention launch from the counter runs fetch, write, calf and calw under `prof`
+    (rocprofv3 --pmc, csv; the last two over --calibrate-copy 1024), with the hash of the sources in this tree."""
+    def mean(run, counter, kernel):
+        with open(os.path.join(prof, run, "run_counter_collection.csv")) as f:
+            rows = [r for r in csv.DictReader(f) if r["Counter_Name"] == counter and kernel in r["Kernel_Name"]]
+        names = {re.search(kernel + r"(<[^>]*>)?", r["Kernel_Name"]).group().replace(" ", "") for r in rows}
+        assert len(names) == 1, (run, counter, names)
+        return sum(float(r["Counter_Value"]) for r in rows) / len(rows), names.pop()
+    fetch, name = mean("fetch", "FETCH_SIZE", "prefill_attn_kernel")
+    write, _ = mean("write", "WRITE_SIZE", "prefill_attn_kernel")
+    copied = 1024 * 1024.0                            # KiB
+    fscale = copied / mean("calf", "FETCH_SIZE", "__amd_rocclr_copyBuffer")[0]
+    wscale = copied / mean("calw", "WRITE_SIZE", "__amd_rocclr_copyBuffer")[0]
+    with open(out, "w") as f:
+        json.dump({"workload": workload, "kernel": name, "kernel_source_sha": kernel_source_sha(),
+                   "fetch_kib_per_dispatch": fetch, "write_kib_per_dispatch": write, "fetch_scale": fscale,
+                   "write_scale": wscale, "bytes_per_launch": 1024 * (fetch * fscale + write * wscale)}, f, indent=1)
+        f.write("\n")
 
 
 def accounting(b):
@@ -277,6 +300,8 @@ def main():
                     help="diagnostic: 'zero' fills q and the pools with zeros - the same instruction stream with "
                          "no operand switching, to show how much of the clock the data values cost")
     ap.add_argument("--traffic-json", default=os.path.join(ROOT, "profiles", "traffic.json"))
+    ap.add_argument("--record-traffic", default=None, metavar="DIR",
+                    help="only write --traffic-json from the counter runs under DIR, in the tree that they profiled")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this path runs on one GPU only (no sharding, no collectives); use --gpus 1",
@@ -288,6 +313,9 @@ def main():
     from paper_2605_08581_amd import binding as B
     from paper_2605_08581_amd import workload as W
 
+    if args.record_traffic:
+        record_traffic(args.record_traffic, W.make_config(args.config).name, args.traffic_json)
+        return
     if not torch.cuda.is_available():
         print("bench.py: no GPU visible", file=sys.stderr)
         sys.exit(2)
