@@ -113,7 +113,8 @@ typedef struct prism_plan prism_plan_t;
 
 typedef struct prism_plan_info {
   int32_t tile_rows;           /* query rows per workgroup (16 or 32: few rows per
-                                  kv head, the kernel whose waves split the keys)      */
+                                  kv head or few workgroups, the kernel whose waves
+                                  split the keys)                                      */
   int32_t tile_keys;           /* keys per inner iteration                             */
   int32_t num_items;           /* attention workgroups per call                        */
   int32_t num_split_items;     /* of those, how many write fp32 partials               */

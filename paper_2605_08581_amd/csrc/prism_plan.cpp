@@ -107,7 +107,7 @@ SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t 
 }
 
 // `sets` (cluster, kv head) sets, each of which runs on one die.
-SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool stream, int d) {
+SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool stream, bool in_tiles, int d) {
   int64_t total = 0, n = 0;
   for (const auto &c : costs) {
     total += c.count * c.tiles * heads;
@@ -120,6 +120,12 @@ SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chun
     // 8 key tiles alone.  16 requests x 300..4100 keys x 8 heads: uncut 45.9 us,
     // 2 pieces each 35.6, 4 pieces 33.7, cut to 256 items 31.5; 320 ranges of
     // 1000..4000 keys: uncut 72.6 us, cut to two rounds 77.9.
+    // Ranges of a CU's time for 12 tiles and less end sooner whole: decode steps of 10
+    // tiles x 8 heads, d = 128, in two or three pieces -> whole: 8 ranges 8.6 -> 7.9, 32
+    // 10.3 -> 8.0; d = 64: 36 of up to 9 tiles 6.6 -> 5.6, 192 of 10 10.8 -> 8.1; of 16
+    // tiles and more 6.8 -> 7.5 and, at d = 128, 9.3 -> 11.0.  Nor are row tiles of 16
+    // cut, which are chosen for what they take whole.
+    if (in_tiles || costs[0].tiles <= 12) return SplitRule{};
     const int64_t slots = (d == 64 ? 2 : 1) * kNumCU;
     if (n <= slots) return fit(costs, heads, min_chunk, 4, slots);
     const int chunk = (int)std::max<int64_t>(min_chunk, total / slots);
@@ -200,6 +206,36 @@ bool splits_keys(int64_t rows, int64_t ranges, int64_t tiles, int d) {
   if (rows > kStreamRows) return false;
   if (ranges <= (d == 64 ? 2 : 1) * kNumCU) return true;
   return tiles >= (rows <= 16 ? (d == 64 ? 4 : 11) : (d == 64 ? 16 : 32));
+}
+
+// Whether a wave of more rows goes to that kernel in row tiles of 16: if they all find
+// a place at once, on the die of their (cluster, kv head) set, and the longest range is
+// short enough to be read by four waves alone.  `sets` has the costs of the tiles of
+// one kv head by cluster, `longest` the most key tiles.  Time of that kernel over the
+// prefill kernel's, with its cuts, on 300 waves of 2 to 1400 such tiles:
+//   key tiles               1     2     3..4   5..8   9..12  13..16  17..20  21..26
+//   d = 128, with a place  .97   .81    .76    .72     .70   .73..97  .75..82  .96..1.3
+//            2 to 4 a place 1.8  2.2    1.5    1.4     1.5    1.5     1.8     1.5
+//   d = 64,  with a place 1.00   .99    .86    .69     .61    .68     .77     .74..1.0
+//            1.5 a place          -     1.05  .83..1.2 .76..97 -      .94      -
+// (Sets that a die has no room for, 668 rows x 2 heads: 1.5.)  With 17 to 32 rows it
+// is ahead of a workgroup for all of them too: 4 ranges of 26 rows x 10 tiles, d = 64,
+// 9.9 -> 5.7, 24 of 24 rows x 6 tiles, d = 128, 9.1 -> 6.6.
+bool fits_in_row_tiles(std::vector<std::pair<int64_t, int64_t>> sets, int heads, int longest, int d) {
+  if (longest > (d == 64 ? 22 : 20)) return false;
+  const int64_t places = (d == 64 ? 2 : 1) * kNumCU / kNumXCD;
+  std::sort(sets.rbegin(), sets.rend());             // dealt as build_schedule deals them
+  int64_t load[kNumXCD] = {0}, taken[kNumXCD] = {0};
+  for (const auto &set : sets)
+    for (int h = 0; h < heads; ++h) {
+      int die = 0;
+      for (int x = 1; x < kNumXCD; ++x)
+        if (load[x] < load[die]) die = x;
+      load[die] += set.first;
+      taken[die] += set.second;
+      if (taken[die] > places) return false;
+    }
+  return true;
 }
 
 // Whether some request's cached prefix lies in pages that the same wave appends
@@ -306,6 +342,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   int64_t total = 0;
   int64_t most_rows = 0;       // packed rows of the largest request, per kv head
   int64_t ranges = 0, range_tiles = 0;   // requests with rows, and the key tiles of their sequences
+  int64_t row_tiles = 0;       // of 16 packed rows, per kv head
   for (int r = 0; r < s.batch; ++r) {
     const int64_t P = prefix[r], S = suffix[r];
     if (P < 0 || S < 0) return PRISM_ERR_INVALID_ARG;
@@ -318,23 +355,12 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     if (S > 0) {
       sch.kv_bytes += token_bytes * (P + S);
       most_rows = std::max(most_rows, S * G);
+      row_tiles += (S * G + 15) / 16;
       ++ranges;
       range_tiles += (P + S + kTileKeys - 1) / kTileKeys;
     }
   }
   sch.total_suffix = total;
-
-  const bool stream = !opt.tile_rows && !opt.rows_per_wave &&
-                      splits_keys(most_rows, ranges * s.num_kv_heads, ranges ? range_tiles / ranges : 0, d);
-  if (stream) tile_rows = most_rows <= 16 ? 16 : 32;
-  sch.stream = stream;
-  sch.tile_rows = tile_rows;
-  sch.rows_per_wave = stream ? tile_rows : rows_per_wave;
-  // Both kernels that do it take 32 rows a wave at most.
-  sch.fused_append = (stream || rows_per_wave == 32) && opt.block_table_host && opt.table_is_final &&
-                     !reads_pages_of_this_wave(s, prefix, suffix, opt.block_table_host);
-
-  sch.q_off = q_off;
 
   // Requests that share a cached prefix start with the same page: give them
   // one cluster id (the smallest request index of the cluster).
@@ -349,6 +375,36 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       cluster[r] = ins.first->second;
     }
   }
+
+  // More than 16 rows, in tiles of 16 rows each.
+  bool in_tiles = false;
+  const int64_t places = (d == 64 ? 2 : 1) * kNumCU;
+  if (!opt.tile_rows && !opt.rows_per_wave && most_rows > 16 && row_tiles * s.num_kv_heads <= places) {
+    std::map<int, std::pair<int64_t, int64_t>> by_cluster;
+    int longest = 0;
+    for (int r = 0; r < s.batch; ++r)
+      for (int rows = suffix[r] * G, row0 = 0; row0 < rows; row0 += 16) {
+        const int cost = key_tiles(prefix[r] + (std::min(rows, row0 + 16) - 1) / G + 1);
+        auto &set = by_cluster[cluster[r]];
+        set.first += cost;
+        ++set.second;
+        longest = std::max(longest, cost);
+      }
+    std::vector<std::pair<int64_t, int64_t>> sets;
+    for (const auto &c : by_cluster) sets.push_back(c.second);
+    in_tiles = fits_in_row_tiles(std::move(sets), s.num_kv_heads, longest, d);
+  }
+  const bool stream = in_tiles || (!opt.tile_rows && !opt.rows_per_wave &&
+                                   splits_keys(most_rows, ranges * s.num_kv_heads, ranges ? range_tiles / ranges : 0, d));
+  if (stream) tile_rows = in_tiles || most_rows <= 16 ? 16 : 32;
+  sch.stream = stream;
+  sch.tile_rows = tile_rows;
+  sch.rows_per_wave = stream ? tile_rows : rows_per_wave;
+  // Both kernels that do it take 32 rows a wave at most.
+  sch.fused_append = (stream || rows_per_wave == 32) && opt.block_table_host && opt.table_is_final &&
+                     !reads_pages_of_this_wave(s, prefix, suffix, opt.block_table_host);
+
+  sch.q_off = q_off;
 
   // Row tiles, the same for every kv head: the keys that each one sees, by request.
   // (Everything up to the items is done once for all kv heads: with a list of all
@@ -391,7 +447,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       }
     for (int c = most_cost; c > 0; --c)
       if (count[c]) costs.push_back({c, count[c], rows[c]});
-    rule = choose_split(costs, s.num_kv_heads, clusters * s.num_kv_heads, min_chunk, stream, d);
+    rule = choose_split(costs, s.num_kv_heads, clusters * s.num_kv_heads, min_chunk, stream, in_tiles, d);
   }
 
   // Heaviest cluster first; inside a (cluster, kv head) set the requests, the
@@ -405,7 +461,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   });
 
   // The key-splitting kernel reads every key of an item once: pages of one request
-  // alone can pass the caches by, if the wave is more than those of the dies hold
+  // alone, whose rows are one tile, can pass the caches by, if the wave is more than those of the dies hold
   // (8 x 4 MB), a page counting once however many requests share it.  us per pass,
   // kept -> passed by, with more pools in rotation than the 256 MB memory-side cache
   // holds, as in a model whose layers have a pool each | on one pool again and again;
@@ -483,7 +539,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
             it.prefix = prefix[req];
             it.suffix = suffix[req];
             it.q_off = q_off[req];
-            it.read_once = reads_once && j - i == 1;
+            it.read_once = reads_once && j - i == 1 && first_tile[req + 1] - first_tile[req] == 1;
             sch.read_once |= it.read_once != 0;
             if (nsplit <= 1) {
               it.kv_begin = 0;

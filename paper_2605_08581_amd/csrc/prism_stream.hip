@@ -3,7 +3,15 @@
 // 32 flop per byte and the kernel is bound by how many bytes it keeps in flight
 // from HBM, or, for small waves, by latency.
 //
-// One workgroup serves one (request, kv head, key range).  Its four waves split
+// Waves too small to fill the chip come here as well, with more rows in tiles of
+// 16: the tiles of a (request, kv head) read its keys again each, from the die's
+// L2, but every CU works, a chain of key steps is a quarter as long, and nothing
+// has to be merged by a second launch.  us per pass, prefill kernel -> this one:
+// 37 rows x 4 over 1003 cached keys, 8 kv heads, d = 128 (80 tiles) 13.6 -> 11.3,
+// 64 x 4 over 300 (128 tiles) 10.3 -> 6.4, four requests of 48 over 200 keys x 4
+// heads, d = 64 (48 tiles) 6.4 -> 5.0.
+//
+// One workgroup serves one (request, kv head, row tile, key range).  Its four waves split
 // the KEYS, not the rows: wave w takes the 32-key tiles w, w+4, ... for all rows.
 // No K/V byte is shared between waves, so each wave streams into LDS rings of
 // its own with direct-to-LDS copies and waits for its own copies only; there is
@@ -119,7 +127,9 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   pin_item(it);
   if (it.req < 0) return;                        // idle padding entry
   const int P = it.prefix, S = it.suffix, T = P + S;
-  const int rows = S * G.d;                      // <= 16*RB: the planner's rule for this kernel
+  const int row0 = it.row0;                      // the tile's packed rows: row0 .. row0+rows-1
+  const int rows = S * G.d - row0 < Shape::kRows ? S * G.d - row0 : Shape::kRows;
+  const int tok0 = G.quotient(row0);
   const ConstantPtr<int32_t> bt = constant_ptr(p.block_table + (int64_t)it.req * p.max_blocks);
   struct PageIds {
     int32_t p[2];
@@ -144,23 +154,23 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   // go through registers, element by element.
   const uint32_t q_lds = lds_address(lds) + (uint32_t)(Shape::kRingBytes + wave * Shape::kQBytes);
   int limit[RB];                                 // last visible key of the lane's row
-  const i32x4 q_rows = block_resource((const __bf16 *)p.q + ((int64_t)it.q_off * p.Hq + it.kv_head * G.d) * D,
-                                      (uint32_t)(((S - 1) * p.Hq + G.d) * ROW));
+  const __bf16 *q0 = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok0) * p.Hq + it.kv_head * G.d) * D;
+  const i32x4 q_rows = block_resource(q0, (uint32_t)((G.quotient(row0 + rows - 1) - tok0) * p.Hq + G.d) * ROW);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = rb * 16 + c16;
     const bool valid = row < rows;
-    const int from = valid ? row : 0;
+    const int from = row0 + (valid ? row : 0);
     const int tok = G.quotient(from), g = from - tok * G.d;
     limit[rb] = valid ? P + tok : -1;
-    const uint32_t off = (uint32_t)((tok * p.Hq + g) * ROW + 16 * g4);
+    const uint32_t off = (uint32_t)(((tok - tok0) * p.Hq + g) * ROW + 16 * g4);
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       const uint32_t dst = q_lds + (uint32_t)((rb * KK + kk) * 1024);
       if (((uintptr_t)p.q & 15) == 0) {
         copy16_to_lds(q_rows, off + (uint32_t)(64 * kk), dst);
       } else {
-        const __bf16 *from = (const __bf16 *)p.q + ((int64_t)it.q_off * p.Hq + it.kv_head * G.d) * D + off / 2 + 32 * kk;
+        const __bf16 *from = q0 + off / 2 + 32 * kk;
         bf16x8 x;
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = from[e];
@@ -223,13 +233,19 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
     }
   };
 
-  // The new rows of a tile, from its ring slot to their pages: every position
-  // belongs to one tile of one workgroup per kv head.
+  // The new rows of a tile, from its ring slot to their pages, of the tokens whose
+  // first packed row lies in the workgroup's row tile: every position belongs to
+  // one tile of one workgroup per kv head.
+  int own_lo = 0x7fffffff, own_hi = 0;
+  if (p.k_new) {
+    own_lo = P + G.quotient(row0 + G.d - 1);
+    own_hi = P + G.quotient(row0 + rows + G.d - 1);
+  }
   auto append_tile = [&](int key0, uint32_t slot) __attribute__((always_inline)) {
 #pragma unroll
     for (int pg = 0; pg < 2; ++pg) {
       const int pos0 = key0 + pg * kPage;
-      if (pos0 + kPage <= P || pos0 >= T) continue;
+      if (pos0 + kPage <= own_lo || pos0 >= own_hi) continue;
       const int64_t block = src.block_of(bt[pos0 / kPage]);
 #pragma unroll
       for (int kv = 0; kv < 2; ++kv) {
@@ -239,7 +255,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
           const int row = i * KPU + lane_row;
           const u32x4 data = *(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)(
               lds_base + slot + (uint32_t)(kv * TK * ROW + pg * kPage * ROW + i * 1024 + lane * 16));
-          if (pos0 + row >= P && pos0 + row < T) *reinterpret_cast<u32x4 *>(dst + row * ROW + lane_chunk[i]) = data;
+          if (pos0 + row >= own_lo && pos0 + row < own_hi) *reinterpret_cast<u32x4 *>(dst + row * ROW + lane_chunk[i]) = data;
         }
       }
     }
@@ -275,7 +291,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
     const PageIds ahead = pages_of(t + NS < mine ? key0_of(t + NS) : it.kv_begin);
     if (t + NS <= mine) wait_vmem<(NS - 1) * COPIES>();   // only later tiles' copies may still be on their way
     else wait_vmem<0>();
-    if (p.k_new && key0_of(t) + TK > P) append_tile(key0_of(t), slot);
+    if (key0_of(t) + TK > own_lo) append_tile(key0_of(t), slot);
     f32x4 s[2][RB];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
@@ -290,7 +306,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
       }
     }
     const int key0 = key0_of(t);
-    if (key0 + TK - 1 > P) {                     // some row may not see all of these keys
+    if (key0 + TK - 1 > P + tok0) {              // some row may not see all of these keys
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -394,7 +410,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
       for (int r = 0; r < 4; ++r) acc[r] += e * o[r];
     }
     if (!slot_out) {
-      store_out_row<D>(p, it.q_off, it.kv_head, G, row, c4, acc, 1.0f / l);
+      store_out_row<D>(p, it.q_off, it.kv_head, G, row0 + row, c4, acc, 1.0f / l);
     } else {
       store_shared(slot_out + (size_t)row * D + c4, acc[0], acc[1]);
       store_shared(slot_out + (size_t)row * D + c4 + 2, acc[2], acc[3]);

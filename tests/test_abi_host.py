@@ -188,6 +188,20 @@ def test_key_splitting_kernel_only_where_it_is_ahead(lib, d, rows, batch, keys, 
     assert _check_cover(b, 0, 0).tile_rows == ((16 if rows <= 16 else 32) if stream else 128)
 
 
+@pytest.mark.parametrize("heads,prefix,suffix,rows", [
+    ((8, 8, 128), [0], [512], 16), ((8, 8, 128), [0], [513], 128), ((8, 8, 64), [0], [1024], 16), ((8, 8, 64), [0], [1025], 128),
+    ((8, 2, 128), [200], [128], 16), ((8, 2, 128), [200], [129], 128), ((32, 8, 128), [1240], [40], 16),
+    ((32, 8, 128), [1241], [40], 128), ((32, 8, 64), [1368], [40], 16), ((32, 8, 64), [1369], [40], 128),
+    ((40, 40, 128), [100] * 2, [33, 17], 16), ((40, 40, 128), [100] * 2, [33, 49], 128), ((40, 40, 128), [100] * 4, [17] * 4, 32)],
+    ids=["places128", "above128", "places64", "above64", "die", "above-die", "longest128", "longer128", "longest64", "longer64",
+         "heads-over-dies", "more-than-places", "too-many-few-rows"])
+def test_row_tiles_of_sixteen_while_they_find_places(lib, heads, prefix, suffix, rows):
+    """Every tile a place at once, on its set's die, over ranges that four waves read alone; whole ranges."""
+    b = W.make_custom_batch("tiles", W.Geometry(*heads), prefix, suffix, seed=1)
+    info = _check_cover(b, 0, 0)
+    assert info.tile_rows == rows and (rows > 16 or info.num_split_items == 0)
+
+
 @pytest.mark.parametrize("heads,prefix,suffix,least,most", [
     ((8, 1, 64), [15838], [34], 8, 30), ((8, 2, 128), [224, 480], [1116] * 2, 1, 1), ((32, 8, 64), [2448] * 22, [12] * 22, 2, 5)],
     ids=["deep-merge", "full-tiles", "few-rows-d64"])

@@ -29,6 +29,19 @@ def test_row_blocks_and_page_edges(oracle_lib, group, suffix, d):
     full_parity(oracle_lib, b, split_kv=3)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group,prefix,suffix", [
+    (1, [0, 37, 1100], [17, 33, 20]), (4, [1003], [37]), (5, [0, 16, 250], [13, 7, 1]), (3, [31, 640], [47, 16]),
+    (8, [5], [61]), (1, [0], [256])], ids=["mha", "one-request", "g5", "g3", "g8", "one-place-each"])
+def test_more_rows_in_tiles_of_sixteen(oracle_lib, group, prefix, suffix, d):
+    """Waves that find a place for every row tile at once: tiles that begin and end inside a token's group of
+    heads, last tiles of one row, new rows appended by the tile that owns their token, keys cut by the caller."""
+    b = W.make_custom_batch("row-tiles", W.Geometry(4 * group, 4, d), prefix, suffix, seed=67)
+    assert full_parity(oracle_lib, b).tile_rows == 16
+    full_parity(oracle_lib, b, entry="separate")
+    full_parity(oracle_lib, b, split_kv=3)
+
+
 @pytest.mark.parametrize("geom", [W.Geometry(8, 8, 128), W.Geometry(32, 8, 128), W.Geometry(8, 1, 64)],
                          ids=["mha128", "gqa128", "mqa64"])
 def test_wave_larger_than_the_chip(oracle_lib, geom):
