@@ -14,6 +14,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
@@ -183,7 +184,7 @@ __device__ __forceinline__ float2 load_shared(const float *src) {
 
 template <int D>
 __device__ __forceinline__ void store_out_row(const AttnArgs &p, int q_off, int kv_head, const Divisor &G, int row, int c4,
-                                              const __attribute__((ext_vector_type(4))) float &acc, float scale) {
+                                              const f32x4 &acc, float scale) {
   const int tok = G.quotient(row);
   __bf16 *op = (__bf16 *)p.out + ((int64_t)(q_off + tok) * p.Hq + kv_head * G.d + (row - tok * G.d)) * D + c4;
   bf16x4 o4;
@@ -222,7 +223,6 @@ __device__ __forceinline__ float2 load_part(const float *src) {
 template <int D, int R, int BATCH, bool SHARED>
 __device__ __forceinline__ void merge_group(const AttnArgs &p, int group, const Divisor &G, int tile_rows, int tid, int threads,
                                             int begin, int end) {
-  typedef __attribute__((ext_vector_type(4))) float f32x4_;
   constexpr int TPR = D / 4;
   const ReduceGroup g = load_group(p.groups, group);
   const size_t slot_f = (size_t)tile_rows * (D + 2);
@@ -233,12 +233,12 @@ __device__ __forceinline__ void merge_group(const AttnArgs &p, int group, const 
   const int c4 = (tid % TPR) * 4, step = threads / TPR;
   for (int row0 = begin + tid / TPR; row0 < n; row0 += R * step) {
     float m[R], l[R];
-    f32x4_ acc[R];
+    f32x4 acc[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       m[k] = -INFINITY;
       l[k] = 0.f;
-      acc[k] = f32x4_{0.f, 0.f, 0.f, 0.f};
+      acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     for (int s0 = 0; s0 < g.nsplit; s0 += BATCH) {
       float2 a[R][BATCH], x[R][BATCH], y[R][BATCH];

@@ -43,8 +43,6 @@
 
 namespace prism {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 template <int D, int RB>
 struct StreamShape {
   static constexpr int NW = 4;                              // waves per workgroup

@@ -65,6 +65,29 @@ def test_tiles_around_the_diagonal(oracle_lib, geom, tile_rows):
     full_parity(oracle_lib, b, tile_rows=tile_rows, entry="separate")
 
 
+@pytest.mark.parametrize("tile_rows", [64, 128, 256])
+@pytest.mark.parametrize("geom", [W.Geometry(3, 1, 128), W.Geometry(2, 2, 64)], ids=["g3x128", "mha64"])
+@pytest.mark.parametrize("split_kv", [1, 3])
+def test_out_anywhere_in_a_larger_buffer(geom, tile_rows, split_kv):
+    """Whole rows are stored 16 bytes at a time wherever out starts, nothing beside it is touched, and
+    the values do not depend on it: row blocks of 32 that end after 1, 31, 32 and 33 rows."""
+    b = W.make_custom_batch("out", geom, [0, 70, 300, 16], [11, 31, 32, 97], seed=17)
+    t = W.make_tensors(b, "cuda")
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table, tile_rows=tile_rows, split_kv=split_kv)
+    ws = torch.empty(max(256, plan.prism_plan_workspace_bytes()), dtype=torch.uint8, device="cuda")
+    bt = torch.from_numpy(b.block_table).cuda()
+    n, results = t["q"].numel(), []
+    for start in (0, 4, 1):
+        buf = torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+        plan.prism_prefix_prefill(t["q"], t["k_suffix"], t["v_suffix"], t["k_pool"], t["v_pool"], bt,
+                                  buf[start:start + n].view(t["q"].shape), ws)
+        torch.cuda.synchronize()
+        assert bool((buf[:start] == 7.0).all()) and bool((buf[start + n:] == 7.0).all())
+        results.append(W.bf16_bits(buf[start:start + n]))
+    plan.close()
+    assert np.array_equal(results[0], results[1]) and np.array_equal(results[0], results[2])
+
+
 @pytest.mark.parametrize("shape", [(128, 32), (128, 64), (256, 64)], ids=["128x32", "128x64", "256x64"])
 @pytest.mark.parametrize("split_kv", [2, 3, 7])
 def test_split_kv_matches_oracle(oracle_lib, split_kv, shape):
