@@ -90,6 +90,13 @@ int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_po
 // accumulator rescale is skipped on almost every tile.
 // --------------------------------------------------------------------------
 
+constexpr bool q_by_lds(int d, int rb, int ns) { return d == 128 && rb == 1 && ns == 2; }
+// Bytes of LDS: the rings, and what of the Q rows finds no room in the last V slot.
+constexpr size_t attn_lds_bytes(int d, int rb, int nw, int ns) {
+  const size_t tile = (size_t)kTileKeys * d * 2, q = (size_t)nw * 32 * d * 2;
+  return 2 * ns * tile + (q_by_lds(d, rb, ns) && q > tile ? q - tile : 0);
+}
+
 template <int D, int RB, int NW, int WPE, int NS>
 __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnArgs p) {
   constexpr int BN = kTileKeys;
@@ -108,6 +115,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   constexpr int DB = D / 32;                     // 32-wide head-dim blocks of O^T
   constexpr int KB = BN / 32;                    // 32-key blocks per tile
   constexpr int KS = BN / 16;                    // 16-key MFMA k-steps of O^T per tile
+  constexpr bool Q_BY_LDS = q_by_lds(D, RB, NS);
 
   // LDS: a ring of NS tile slots for K followed by a ring of NS slots for V
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -202,10 +210,22 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   const PageIds first_pages = pages_of(0), second_pages = pages_of(1);
   __builtin_amdgcn_sched_barrier(0);             // on their way before the Q rows' addresses are formed
 
-  // ---- Q fragments (B operand of S^T): lane holds row l32, dims 16kk+8hh..+7
+  // ---- Q fragments (B operand of S^T): lane holds row l32, dims 16kk+8hh..+7.
+  // Loaded as they are held, 32 rows with 32 bytes of each at a time, a line of them
+  // is asked for four times, and the rows of a CU's eight waves, 64 KB at d = 128, do
+  // not stay in its 32 KB of L1 between.  There, with two-slot rings, they come by
+  // copies of whole rows into LDS, in the layout of 32 rows of a K tile, and are read
+  // from there once K of the first tile has landed: into the wave's own part of the
+  // last V slot, which is free until the first iteration, and what does not fit there
+  // behind the rings (16 KB at 128 rows: two workgroups then fill the CU's LDS).  us
+  // per pass, loaded -> copied: 7 requests of 500..700 new tokens x 40 heads, 40
+  // layers 2755 -> 2716, 32 full recomputes 3225 -> 3198; at d = 64 the same, so loaded.
   const int wrow0 = it.row0 + wave * (32 * RB);
   bf16x8 qf[RB][KK];
   int limit[RB];                                  // last visible key of the lane's row
+  constexpr uint32_t Q_PART = UPW * 1024 < 32 * ROW ? UPW * 1024 : 32 * ROW;   // bytes of the wave's rows in the V slot
+  const uint32_t q_slot = (uint32_t)((2 * NS - 1) * TILE_BYTES + wave * (UPW * 1024));
+  const uint32_t q_rest = (uint32_t)(2 * NS * TILE_BYTES) + (uint32_t)wave * (32 * ROW - Q_PART) - Q_PART;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = wrow0 + rb * 32 + l32;
@@ -213,9 +233,29 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     const int from = valid ? row : 0;             // rows past the end are cleared once they are here
     const int tok = G.quotient(from), g = from - tok * G.d;
     limit[rb] = valid ? P + tok : -1;
-    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D + 8 * hh;
+    if constexpr (!Q_BY_LDS) {
+      const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D + 8 * hh;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
+      for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
+    }
+  }
+  if (Q_BY_LDS && wrow0 < rows_total) {
+    const int last = rows_total - 1 < wrow0 + 31 ? rows_total - 1 : wrow0 + 31, tok0 = G.quotient(wrow0);
+    auto offset_of = [&](int row) __attribute__((always_inline)) {   // row rho lies at rho + token(rho) (Hq - G) in units of a row
+      return (uint32_t)(row - wrow0 + (G.quotient(row) - tok0) * (Hq - G.d)) * (uint32_t)ROW;
+    };
+    const unsigned char *q0 =
+        (const unsigned char *)p.q + ((int64_t)(it.q_off + tok0) * Hq + it.kv_head * G.d + (wrow0 - tok0 * G.d)) * ROW;
+    const i32x4 rows = block_resource(q0, offset_of(last) + ROW);
+#pragma unroll
+    for (int i = 0; i < 32 * ROW / 1024; ++i) {
+      const int r = i * KPU + lane / CPR, row = wrow0 + r < last ? wrow0 + r : last;
+      const uint32_t off = offset_of(row) + (uint32_t)(((lane % CPR) ^ swz<D>(r)) << 4);
+      const uint32_t to = lds_base + (i * 1024 < (int)Q_PART ? q_slot : q_rest) + (uint32_t)(i * 1024);
+      // copies into LDS promise nothing for rows that do not lie on 16 bytes
+      if (((uintptr_t)p.q & 15) == 0) copy16_to_lds(rows, off, to);
+      else *(__attribute__((address_space(3))) u32x4 *)(uintptr_t)(to + (uint32_t)(lane * 16)) = *reinterpret_cast<const u32x4 *>(q0 + off);
+    }
   }
 #pragma unroll
   for (int j = 0; j < PPW; ++j) __asm__ volatile("" : : "s"(first_pages.p[j]), "s"(second_pages.p[j]));
@@ -602,6 +642,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     }
     if (second) wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
     else wait_pending(std::integral_constant<int, 0>{});
+    if (Q_BY_LDS && wave_live) {
+      const uint32_t at = l32 * ROW < (int)Q_PART ? q_slot : q_rest;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) qf[0][kk] = *(lds_b128_ptr)(uintptr_t)(k_lane[kk] + at);
+    }
     __syncthreads();
     if (wrow0 + 32 * RB > rows_total)
 #pragma unroll
@@ -843,7 +888,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const AttnArgs p, int
 
 template <int D, int RB, int NW, int WPE, int NS>
 static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
-  constexpr size_t lds_bytes = (size_t)2 * NS * kTileKeys * D * 2;
+  constexpr size_t lds_bytes = attn_lds_bytes(D, RB, NW, NS);
   auto kernel = prefill_attn_kernel<D, RB, NW, WPE, NS>;
   static const hipError_t attr = hipFuncSetAttribute(
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
