@@ -186,6 +186,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 #pragma unroll
   for (int db = 0; db < DB; ++db) __asm__ volatile("" : "+v"(v_lane[db][0]), "+v"(v_lane[db][1]));
   pin_item(it);
+  __asm__ volatile("" : : "s"(it.alone));        // (its own load, later, cost 0.3 us a workgroup)
   if (it.req < 0) return;                        // idle padding entry
   const int P = it.prefix, S = it.suffix;
   const int rows_total = S * G.d;
@@ -222,6 +223,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // layers 2755 -> 2716, 32 full recomputes 3225 -> 3198; at d = 64 the same, so loaded.
   const int wrow0 = it.row0 + wave * (32 * RB);
   bf16x8 qf[RB][KK];
+  // Few rows are few lines, and without a second workgroup there is nothing to make
+  // room for: such waves load Q, and store out, the short way.  us per pass, all
+  // turned through LDS -> these not: 29 requests of one new over 32 cached tokens x 40
+  // heads 13.1 -> 11.9, 27 of ten over up to 174 17.9 -> 17.2; 80 workgroups of one key
+  // tile 6.0 -> 5.5.
+  const bool few = it.alone || rows_total - wrow0 <= 16;
   int limit[RB];                                  // last visible key of the lane's row
   constexpr uint32_t Q_PART = UPW * 1024 < 32 * ROW ? UPW * 1024 : 32 * ROW;   // bytes of the wave's rows in the V slot
   const uint32_t q_slot = (uint32_t)((2 * NS - 1) * TILE_BYTES + wave * (UPW * 1024));
@@ -233,28 +240,44 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     const int from = valid ? row : 0;             // rows past the end are cleared once they are here
     const int tok = G.quotient(from), g = from - tok * G.d;
     limit[rb] = valid ? P + tok : -1;
-    if constexpr (!Q_BY_LDS) {
+    if (!Q_BY_LDS || few) {
       const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D + 8 * hh;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
     }
   }
-  if (Q_BY_LDS && wrow0 < rows_total) {
-    const int last = rows_total - 1 < wrow0 + 31 ? rows_total - 1 : wrow0 + 31, tok0 = G.quotient(wrow0);
-    auto offset_of = [&](int row) __attribute__((always_inline)) {   // row rho lies at rho + token(rho) (Hq - G) in units of a row
-      return (uint32_t)(row - wrow0 + (G.quotient(row) - tok0) * (Hq - G.d)) * (uint32_t)ROW;
-    };
-    const unsigned char *q0 =
-        (const unsigned char *)p.q + ((int64_t)(it.q_off + tok0) * Hq + it.kv_head * G.d + (wrow0 - tok0 * G.d)) * ROW;
-    const i32x4 rows = block_resource(q0, offset_of(last) + ROW);
+  // Bytes from the wave's first row in q and out to its row r, for the lanes of row
+  // l32: row rho of a kv head lies at rho + token(rho) (Hq - G) in units of a row.
+  const int tok0 = G.quotient(wrow0);
+  const int64_t wave_rows = ((int64_t)(it.q_off + tok0) * Hq + it.kv_head * G.d + (wrow0 - tok0 * G.d)) * ROW;
+  auto row_offset = [&](int r) __attribute__((always_inline)) -> uint32_t {
+    if (wrow0 + r > rows_total - 1) r = rows_total - 1 - wrow0;
+    return (uint32_t)(r + (G.quotient(wrow0 + r) - tok0) * (Hq - G.d)) * (uint32_t)ROW;
+  };
+  // ... and for every lane of a wave-wide copy of whole rows, the i-th of a block, to
+  // its row there, from the lane that has it: products and quotients of whole
+  // numbers take four times as long as anything else here.
+  auto copied_row = [&](int i, uint32_t own) __attribute__((always_inline)) -> uint32_t {
+    return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (i * KPU + lane / CPR), (int)own);
+  };
+  if (Q_BY_LDS && !few) {
+    const uint32_t own = row_offset(l32);
+    uint32_t off[32 / KPU];
 #pragma unroll
-    for (int i = 0; i < 32 * ROW / 1024; ++i) {
-      const int r = i * KPU + lane / CPR, row = wrow0 + r < last ? wrow0 + r : last;
-      const uint32_t off = offset_of(row) + (uint32_t)(((lane % CPR) ^ swz<D>(r)) << 4);
-      const uint32_t to = lds_base + (i * 1024 < (int)Q_PART ? q_slot : q_rest) + (uint32_t)(i * 1024);
-      // copies into LDS promise nothing for rows that do not lie on 16 bytes
-      if (((uintptr_t)p.q & 15) == 0) copy16_to_lds(rows, off, to);
-      else *(__attribute__((address_space(3))) u32x4 *)(uintptr_t)(to + (uint32_t)(lane * 16)) = *reinterpret_cast<const u32x4 *>(q0 + off);
+    for (int i = 0; i < 32 / KPU; ++i)
+      off[i] = copied_row(i, own) + (uint32_t)(((lane % CPR) ^ swz<D>(i * KPU + lane / CPR)) << 4);
+    const unsigned char *q0 = (const unsigned char *)p.q + wave_rows;
+    auto to = [&](int i) __attribute__((always_inline)) {
+      return lds_base + (i * 1024 < (int)Q_PART ? q_slot : q_rest) + (uint32_t)(i * 1024);
+    };
+    if (((uintptr_t)p.q & 15) == 0) {
+      const i32x4 rows = block_resource(q0, (uint32_t)__builtin_amdgcn_readlane((int)own, 31) + ROW);
+#pragma unroll
+      for (int i = 0; i < 32 / KPU; ++i) copy16_to_lds(rows, off[i], to(i));
+    } else {                                      // copies into LDS promise nothing for such rows
+#pragma unroll
+      for (int i = 0; i < 32 / KPU; ++i)
+        *(__attribute__((address_space(3))) u32x4 *)(uintptr_t)(to(i) + (uint32_t)(lane * 16)) = *reinterpret_cast<const u32x4 *>(q0 + off[i]);
     }
   }
 #pragma unroll
@@ -326,12 +349,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if (own_hi > T) own_hi = T;
     if (own_hi > kv_end) own_hi = kv_end;
   }
-  auto write_rows = [&](int which, uint32_t slot_off, int t) __attribute__((always_inline)) {
+  auto write_rows = [&](int which, uint32_t slot_off, int t, const PageIds &pg) __attribute__((always_inline)) {
     static_for<0, PPW>([&](auto jt) __attribute__((always_inline)) {
       constexpr int j = decltype(jt)::value;
       const int pos0 = kv_begin + t * BN + (wave_blk + j) * kPage;
       if (pos0 + kPage <= own_lo || pos0 >= own_hi) return;
-      unsigned char *block = (unsigned char *)(which ? p.v_pool : p.k_pool) + src.block_of(bt[pos0 / kPage]);
+      unsigned char *block = (unsigned char *)(which ? p.v_pool : p.k_pool) + src.block_of(pg.p[j]);
       u32x4 data[NL];
 #pragma unroll
       for (int l = 0; l < NL; ++l)
@@ -345,8 +368,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   };
   auto append_tile = [&](int t) __attribute__((always_inline)) {   // K and V of tile t are in their slots
     if (kv_begin + (t + 1) * BN <= own_lo) return;
-    write_rows(0, k_slot(t), t);
-    write_rows(1, v_slot(t), t);
+    const PageIds pg = pages_of(t);
+    write_rows(0, k_slot(t), t, pg);
+    write_rows(1, v_slot(t), t, pg);
     wait_lds_reads();                             // before K of a later tile is copied over it
   };
 
@@ -642,7 +666,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     }
     if (second) wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
     else wait_pending(std::integral_constant<int, 0>{});
-    if (Q_BY_LDS && wave_live) {
+    if (Q_BY_LDS && wave_live && !few) {
       const uint32_t at = l32 * ROW < (int)Q_PART ? q_slot : q_rest;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) qf[0][kk] = *(lds_b128_ptr)(uintptr_t)(k_lane[kk] + at);
@@ -787,7 +811,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     ++t;
   }
   for (; t < nt; ++t) pass_on(t);
-  wait_pending(std::integral_constant<int, 0>{});   // let the unused trailing copies drain
+  // The unused trailing copies of a deep ring drain.  With two slots none are left,
+  // only the last tile's appended rows, and their stores take a microsecond.
+  if constexpr (NS > 2) wait_pending(std::integral_constant<int, 0>{});
   if constexpr (RB > 1) mfma_drain();
 
   // ---- epilogue.  A lane holds 4 dims here and 4 dims there of one row, so stores
@@ -804,7 +830,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     constexpr uint32_t PART = UPW * 1024;         // bytes of a K slot that this wave fills
     static_assert(NS * PART >= 32 * ROW, "32 rows of bf16 fit the wave's part of the K ring");
     auto spread = [](uint32_t off) __attribute__((always_inline)) { return off / PART * TILE_BYTES + off % PART; };
-    constexpr int PER = 64 / CPR;                 // rows of a wave-wide store of 16 bytes a lane
     int here = lane;                              // or what follows is worked out, and kept, before the loops
     __asm__ volatile("" : "+v"(here));
     const int l32 = here & 31, hh = here >> 5, from_row = here / CPR, from_chunk = here % CPR;
@@ -813,21 +838,36 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     const uint32_t part = lds_base + (uint32_t)wave * PART;
     const uint32_t to = part + spread(l32 * ROW) + (swz<D>(l32) << 4);
     const uint32_t from = part + spread(from_row * ROW) + ((from_chunk ^ swz<D>(from_row)) << 4);
-    // store(row, its 16 bytes) for every row of the block
-    auto for_rows = [&](int rb, auto store) __attribute__((always_inline)) {
+    // store(16 bytes, their offset) for every row of the block; offset(i): of the row of copy i
+    auto for_rows = [&](int rb, auto offset, auto store) __attribute__((always_inline)) {
+      uint32_t off[32 / KPU];
+#pragma unroll
+      for (int i = 0; i < 32 / KPU; ++i) off[i] = offset(i) + 16u * from_chunk;
       wait_lds_reads();
 #pragma unroll
-      for (int i = 0; i < 32 / PER; ++i) {
-        const int row = wrow0 + rb * 32 + i * PER + from_row;
-        const uint32_t at = (from ^ (uint32_t)(swz<D>(i * PER) << 4)) + spread(i * PER * ROW);
-        if (row < rows_total) store(row, *(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)at);
+      for (int i = 0; i < 32 / KPU; ++i) {
+        const uint32_t at = (from ^ (uint32_t)(swz<D>(i * KPU) << 4)) + spread(i * KPU * ROW);
+        if (wrow0 + rb * 32 + i * KPU + from_row < rows_total) store(*(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)at, off[i]);
       }
       wait_lds_reads();                           // before the next block is written over it
     };
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const float l_tot = sum_across_halves(l_run[rb]);
-      if (it.part_slot < 0) {
+      if (it.part_slot < 0 && few) {
+        const float inv = 1.0f / l_tot;
+        unsigned char *op = (unsigned char *)p.out + wave_rows + row_offset(rb * 32 + l32) + 8 * hh;
+        if (wrow0 + rb * 32 + l32 < rows_total)
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+              bf16x4 o4;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][rb][4 * g4 + e] * inv);
+              *reinterpret_cast<bf16x4 *>(op + (4 * db + g4) * 16) = o4;
+            }
+      } else if (it.part_slot < 0) {
         const float inv = 1.0f / l_tot;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -838,13 +878,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
             for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][rb][4 * g4 + e] * inv);
             *(__attribute__((address_space(3))) bf16x4 *)(uintptr_t)((to ^ (uint32_t)((4 * db + g4) << 4)) + 8 * hh) = o4;
           }
-        // row rho of the kv head lies at rho + token(rho) (Hq - G) in units of a row
-        const int tok0 = G.quotient(wrow0);
-        unsigned char *out0 = (unsigned char *)p.out + ((int64_t)(it.q_off + tok0) * Hq + it.kv_head * G.d + (wrow0 - tok0 * G.d)) * ROW;
-        for_rows(rb, [&](int row, u32x4 data) __attribute__((always_inline)) {
-          const uint32_t off = (uint32_t)(row - wrow0 + (G.quotient(row) - tok0) * (Hq - G.d)) * ROW + 16u * from_chunk;
-          *reinterpret_cast<u32x4 *>(out0 + off) = data;
-        });
+        unsigned char *out0 = (unsigned char *)p.out + wave_rows;
+        const uint32_t own = row_offset(rb * 32 + l32);
+        for_rows(rb, [&](int i) __attribute__((always_inline)) { return copied_row(i, own); },
+                 [&](u32x4 data, uint32_t off) __attribute__((always_inline)) { *reinterpret_cast<u32x4 *>(out0 + off) = data; });
       } else {
         float *slot = p.partials + (size_t)it.part_slot * ((size_t)BM * (D + 2));
         unsigned char *po = (unsigned char *)(slot + (size_t)(wrow0 - it.row0) * D);
@@ -859,9 +896,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
               for (int e = 0; e < 4; ++e) o4[e] = oacc[half * (DB / 2) + db][rb][4 * g4 + e];
               *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(to ^ (uint32_t)((8 * db + 2 * g4 + hh) << 4)) = o4;
             }
-          for_rows(rb, [&](int row, u32x4 data) __attribute__((always_inline)) {
-            *reinterpret_cast<u32x4 *>(po + (uint32_t)((row - wrow0) * 2 * ROW + half * ROW + 16 * from_chunk)) = data;
-          });
+          for_rows(rb, [&](int i) __attribute__((always_inline)) { return (uint32_t)((rb * 32 + i * KPU + from_row) * 2 * ROW + half * ROW); },
+                   [&](u32x4 data, uint32_t off) __attribute__((always_inline)) { *reinterpret_cast<u32x4 *>(po + off) = data; });
         }
         const int row = wrow0 + rb * 32 + l32;
         if (hh == 0 && row < rows_total)

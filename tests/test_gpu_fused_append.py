@@ -55,11 +55,13 @@ def test_rows_off_the_16_byte_grid(oracle_lib, suffix, moved):
 @pytest.mark.parametrize("elements", [1, 4])
 @pytest.mark.parametrize("tile_rows", [64, 128, 256])
 @pytest.mark.parametrize("geom", [W.Geometry(4, 2, 128), W.Geometry(3, 1, 128), W.Geometry(2, 2, 64)], ids=["g2x128", "g3x128", "mha64"])
-def test_query_rows_off_the_16_byte_grid(oracle_lib, geom, tile_rows, elements):
-    """The row tiles' kernel takes query rows from any address: blocks of 32 that end after 1, 31, 32 and 33 rows."""
+@pytest.mark.parametrize("copies", [1, 70], ids=["alone", "shared"])
+def test_query_rows_off_the_16_byte_grid(oracle_lib, geom, tile_rows, elements, copies):
+    """The row tiles' kernel takes query rows from any address: blocks of 32 that end after 1, 31, 32 and 33 rows,
+    with one workgroup to a compute unit and more."""
     def mutate(t):
         buf = torch.empty(t["q"].numel() + 8, dtype=t["q"].dtype, device=t["q"].device)
         q = buf[elements:elements + t["q"].numel()].view(t["q"].shape)
         t["q"] = q.copy_(t["q"])
-    b = W.make_custom_batch("q-views", geom, [0, 37, 500, 16], [11, 31, 32, 97], seed=74)
+    b = W.make_custom_batch("q-views", geom, [0, 37, 500, 16] * copies, [11, 31, 32, 97] * copies, seed=74)
     full_parity(oracle_lib, b, mutate=mutate, tile_rows=tile_rows)

@@ -68,10 +68,12 @@ def test_tiles_around_the_diagonal(oracle_lib, geom, tile_rows):
 @pytest.mark.parametrize("tile_rows", [64, 128, 256])
 @pytest.mark.parametrize("geom", [W.Geometry(3, 1, 128), W.Geometry(2, 2, 64)], ids=["g3x128", "mha64"])
 @pytest.mark.parametrize("split_kv", [1, 3])
-def test_out_anywhere_in_a_larger_buffer(geom, tile_rows, split_kv):
-    """Whole rows are stored 16 bytes at a time wherever out starts, nothing beside it is touched, and
-    the values do not depend on it: row blocks of 32 that end after 1, 31, 32 and 33 rows."""
-    b = W.make_custom_batch("out", geom, [0, 70, 300, 16], [11, 31, 32, 97], seed=17)
+@pytest.mark.parametrize("copies", [1, 70], ids=["alone", "shared"])
+def test_out_anywhere_in_a_larger_buffer(geom, tile_rows, split_kv, copies):
+    """Rows are stored whole, or by pieces where a wave has few or its workgroup a compute unit to itself,
+    wherever out starts; nothing beside it is touched, and the values do not depend on it: blocks that end after 1, 31,
+    32 and 33 rows, with one workgroup to a compute unit and more."""
+    b = W.make_custom_batch("out", geom, [0, 70, 300, 16] * copies, [11, 31, 32, 97] * copies, seed=17)
     t = W.make_tensors(b, "cuda")
     plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table, tile_rows=tile_rows, split_kv=split_kv)
     ws = torch.empty(max(256, plan.prism_plan_workspace_bytes()), dtype=torch.uint8, device="cuda")
