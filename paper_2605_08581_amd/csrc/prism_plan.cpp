@@ -106,6 +106,12 @@ SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t 
   return with(lo);
 }
 
+// Workgroups of the prefill kernels that run on a compute unit at once.
+int workgroups_per_cu(int tile_rows, int d) {
+  if (tile_rows == 256) return 1;
+  return d == 64 ? (tile_rows == 64 ? 4 : 3) : 2;
+}
+
 // `sets` (cluster, kv head) sets, each of which runs on one die.
 SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool stream, bool in_tiles, int d) {
   int64_t total = 0, n = 0;
@@ -434,6 +440,25 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 
   // Split-KV: no piece of the automatic cuts has fewer key tiles than a caller's
   // min_split_keys; without one, all but the last of a range have four.
+  // A (cluster, kv head) set of more row tiles than a die runs at once is dealt to as
+  // many dies as it takes to give each an eighth of the wave: with fewer sets than
+  // dies, or a few more, most of the chip waited for those that had them, and what
+  // the others read again is little beside that.  us per pass, whole -> dealt out: 8/1
+  // heads, d = 64, one request of 4096 new 126.6 -> 33.0, 3 of 1648..3297 over 18612 cached
+  // tokens 916 -> 354, 9 of 2500..3000 over 100..3000 199 -> 173; 8/2 heads, d = 128, 3 of 2685
+  // over 373 80.3 -> 63.6, one of 4000 over 1000 173 -> 58.  (Smaller sets are left whole:
+  // two of 70 tiles over 8 dies 27.0 -> 27.2.)
+  const int64_t die_round = (int64_t)workgroups_per_cu(tile_rows, d) * kNumCU / kNumXCD;
+  std::vector<int64_t> set_tiles(s.batch, 0);          // row tiles of a cluster, of one kv head
+  int64_t wave_cost = 0, sets = clusters * s.num_kv_heads;   // key tiles of all kv heads; sets, for the cuts
+  for (int r : live) {
+    const int tiles = first_tile[r + 1] - first_tile[r];
+    set_tiles[cluster[r]] += tiles;
+    if (!stream && tiles > die_round) sets = std::max<int64_t>(sets, kNumXCD);   // one request alone reaches every die
+  }
+  for (int c = 0; c < s.batch; ++c) wave_cost += cluster_cost[c] * s.num_kv_heads;
+  auto dealt_out = [&](int c) { return !stream && set_tiles[c] > die_round; };
+
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
   SplitRule rule;
   Costs costs;
@@ -447,7 +472,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       }
     for (int c = most_cost; c > 0; --c)
       if (count[c]) costs.push_back({c, count[c], rows[c]});
-    rule = choose_split(costs, s.num_kv_heads, clusters * s.num_kv_heads, min_chunk, stream, in_tiles, d);
+    rule = choose_split(costs, s.num_kv_heads, sets, min_chunk, stream, in_tiles, d);
   }
 
   // Heaviest cluster first; inside a (cluster, kv head) set the requests, the
@@ -517,18 +542,34 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       while (j < live.size() && cluster[live[j]] == cluster[live[i]]) ++j;
       for (int h = 0; h < s.num_kv_heads; ++h) {
         int die = 0;
-        for (int x = 1; x < kNumXCD; ++x)
-          if (die_load[x] < die_load[die]) die = x;
-        die_load[die] += cluster_cost[cluster[live[i]]];
-        std::vector<AttnItem> &items = die_items[die];
-        ItemSet set{0, items.size(), 0};
+        int64_t run = 0;               // row tiles dealt to this die
+        ItemSet set{};
+        auto open = [&]() {
+          for (int x = 0; x < kNumXCD; ++x)
+            if (die_load[x] < die_load[die]) die = x;
+          set = ItemSet{0, die_items[die].size(), 0};
+          run = 0;
+        };
+        auto close = [&]() {
+          set.end = die_items[die].size();
+          die_sets[die].push_back(set);
+        };
         auto add = [&](const AttnItem &it) {
           set.longest = std::max(set.longest, it.kv_end - it.kv_begin);
-          items.push_back(it);
+          die_items[die].push_back(it);
         };
+        open();
+        const bool out = dealt_out(cluster[live[i]]);
         for (size_t m = i; m < j; ++m)
           for (int tile = first_tile[live[m] + 1] - 1; tile >= first_tile[live[m]]; --tile) {
+            // (a dozen at least: they share what they read)
+            if (out && run >= 12 && die_load[die] * kNumXCD >= wave_cost) {
+              close();
+              open();
+            }
             const int req = live[m], kv_len = tile_keys[tile], cost = key_tiles(kv_len);
+            ++run;
+            die_load[die] += cost;
             int nsplit = 1;
             if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, cost);
             else if (opt.split_kv == 0) nsplit = rule.pieces(cost);
@@ -578,8 +619,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
               ++sch.num_split_items;
             }
           }
-        set.end = items.size();
-        die_sets[die].push_back(set);
+        close();
       }
     }
     // The sets of a die start in the order of their longest workgroup: a long one

@@ -202,6 +202,32 @@ def test_row_tiles_of_sixteen_while_they_find_places(lib, heads, prefix, suffix,
     assert info.tile_rows == rows and (rows > 16 or info.num_split_items == 0)
 
 
+@pytest.mark.parametrize("heads,prefix,suffix,groups,tile_rows", [
+    ((8, 1, 64), [0], [4096], [-1], 0), ((8, 1, 64), [18612] * 3, [1648, 2400, 3297], [-1] * 3, 0), ((8, 2, 128), [373] * 3, [2685] * 3, [-1] * 3, 0),
+    ((4, 1, 128), [512] * 5, [700, 300, 500, 600, 400], [0] * 5, 0), ((8, 1, 128), [0, 100], [520, 37], [-1] * 2, 64),
+    ((8, 2, 128), [0, 9, 500, 16] * 3, [2100, 2050, 40, 2200] * 3, [-1] * 12, 0)],
+    ids=["one-request", "cut-too", "three", "sharers", "64-rows", "more-sets-than-dies"])
+def test_sets_larger_than_a_die_are_dealt_out(lib, heads, prefix, suffix, groups, tile_rows):
+    """More row tiles in one (cluster, kv head) set than a die runs at once: no die has much more than an eighth
+    of the wave, and every key of every row tile belongs to one workgroup."""
+    b = W.make_custom_batch("dealt", W.Geometry(*heads), prefix, suffix, seed=1, share_groups=groups)
+    info, _, items = B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, tile_rows=tile_rows, block_table=b.block_table)
+    load, ranges = np.zeros(8, np.int64), {}
+    for pos, (req, kvh, row0, kb, ke, *_) in enumerate(items.tolist()):
+        if req >= 0:
+            load[pos % 8] += (ke - kb + 63) // 64
+            ranges.setdefault((req, kvh, row0), []).append((kb, ke))
+    G, tr = b.geom.group, info.tile_rows
+    want = {(r, h, row0): b.prefix_len[r] + (min(b.suffix_len[r] * G, row0 + tr) - 1) // G + 1 for r in range(b.batch)
+            for h in range(b.geom.num_kv_heads) for row0 in range(0, int(b.suffix_len[r]) * G, tr)}
+    assert set(ranges) == set(want)
+    for key, pieces in ranges.items():
+        pieces.sort()
+        assert pieces[0][0] == 0 and pieces[-1][1] == want[key] and all(x[1] == y[0] for x, y in zip(pieces, pieces[1:]))
+    longest = max((int(k) + 63) // 64 for k in want.values())
+    assert load.max() <= load.sum() / 8 + 12 * longest, load.tolist()
+
+
 @pytest.mark.parametrize("heads,prefix,suffix,least,most", [
     ((8, 1, 64), [15838], [34], 8, 30), ((8, 2, 128), [224, 480], [1116] * 2, 1, 1), ((32, 8, 64), [2448] * 22, [12] * 22, 2, 5)],
     ids=["deep-merge", "full-tiles", "few-rows-d64"])
