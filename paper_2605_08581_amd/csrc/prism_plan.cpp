@@ -106,12 +106,6 @@ SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t 
   return with(lo);
 }
 
-// Workgroups of the prefill kernels that run on a compute unit at once.
-int workgroups_per_cu(int tile_rows, int d) {
-  if (tile_rows == 256) return 1;
-  return d == 64 ? (tile_rows == 64 ? 4 : 3) : 2;
-}
-
 // `sets` (cluster, kv head) sets, each of which runs on one die.
 SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool stream, bool in_tiles, int d) {
   int64_t total = 0, n = 0;
@@ -440,24 +434,25 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
 
   // Split-KV: no piece of the automatic cuts has fewer key tiles than a caller's
   // min_split_keys; without one, all but the last of a range have four.
-  // A (cluster, kv head) set of more row tiles than a die runs at once is dealt to as
-  // many dies as it takes to give each an eighth of the wave: with fewer sets than
-  // dies, or a few more, most of the chip waited for those that had them, and what
-  // the others read again is little beside that.  us per pass, whole -> dealt out: 8/1
-  // heads, d = 64, one request of 4096 new 126.6 -> 33.0, 3 of 1648..3297 over 18612 cached
-  // tokens 916 -> 354, 9 of 2500..3000 over 100..3000 199 -> 173; 8/2 heads, d = 128, 3 of 2685
-  // over 373 80.3 -> 63.6, one of 4000 over 1000 173 -> 58.  (Smaller sets are left whole:
-  // two of 70 tiles over 8 dies 27.0 -> 27.2.)
-  const int64_t die_round = (int64_t)workgroups_per_cu(tile_rows, d) * kNumCU / kNumXCD;
+  // A (cluster, kv head) set of more row tiles than one and a half for each CU of a die
+  // is dealt to as many dies as it takes to give each an eighth of the wave: with
+  // fewer sets than dies, or a few more, most of the chip waited for those that had
+  // them, and what the others read again is little beside that.  us per pass, whole ->
+  // dealt out: 8/1 heads, d = 64, one request of 4096 new 126.6 -> 33.0, 3 of 1648..3297 over
+  // 18612 cached tokens 916 -> 354, 9 of 2500..3000 over 100..3000 199 -> 173, 12 of 1300 over
+  // 500 61.2 -> 47.6; 8/2 heads, d = 128, 3 of 2685 over 373 80.3 -> 63.6, one of 1800 34.0 -> 21.9,
+  // one of 1700 over 8000 228 -> 83.  Smaller sets keep their die, as most waves have
+  // many (33 to 44 tiles would gain 1.05 to 1.5 where they are alone, 17 to 32 up to 1.7).
+  const int64_t die_tiles = kNumCU / kNumXCD * 3 / 2;
   std::vector<int64_t> set_tiles(s.batch, 0);          // row tiles of a cluster, of one kv head
   int64_t wave_cost = 0, sets = clusters * s.num_kv_heads;   // key tiles of all kv heads; sets, for the cuts
   for (int r : live) {
     const int tiles = first_tile[r + 1] - first_tile[r];
     set_tiles[cluster[r]] += tiles;
-    if (!stream && tiles > die_round) sets = std::max<int64_t>(sets, kNumXCD);   // one request alone reaches every die
+    if (!stream && tiles > die_tiles) sets = std::max<int64_t>(sets, kNumXCD);   // one request alone reaches every die
   }
   for (int c = 0; c < s.batch; ++c) wave_cost += cluster_cost[c] * s.num_kv_heads;
-  auto dealt_out = [&](int c) { return !stream && set_tiles[c] > die_round; };
+  auto dealt_out = [&](int c) { return !stream && set_tiles[c] > die_tiles; };
 
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
   SplitRule rule;

@@ -204,12 +204,12 @@ def test_row_tiles_of_sixteen_while_they_find_places(lib, heads, prefix, suffix,
 
 @pytest.mark.parametrize("heads,prefix,suffix,groups,tile_rows", [
     ((8, 1, 64), [0], [4096], [-1], 0), ((8, 1, 64), [18612] * 3, [1648, 2400, 3297], [-1] * 3, 0), ((8, 2, 128), [373] * 3, [2685] * 3, [-1] * 3, 0),
-    ((4, 1, 128), [512] * 5, [700, 300, 500, 600, 400], [0] * 5, 0), ((8, 1, 128), [0, 100], [520, 37], [-1] * 2, 64),
+    ((4, 1, 128), [512] * 5, [700, 300, 500, 600, 400], [0] * 5, 0), ((8, 1, 128), [0, 100], [400, 37], [-1] * 2, 64), ((4, 4, 64), [0, 100], [6200, 37], [-1] * 2, 0),
     ((8, 2, 128), [0, 9, 500, 16] * 3, [2100, 2050, 40, 2200] * 3, [-1] * 12, 0)],
-    ids=["one-request", "cut-too", "three", "sharers", "64-rows", "more-sets-than-dies"])
+    ids=["one-request", "cut-too", "three", "sharers", "64-rows", "four-heads", "more-sets-than-dies"])
 def test_sets_larger_than_a_die_are_dealt_out(lib, heads, prefix, suffix, groups, tile_rows):
-    """More row tiles in one (cluster, kv head) set than a die runs at once: no die has much more than an eighth
-    of the wave, and every key of every row tile belongs to one workgroup."""
+    """More row tiles in one (cluster, kv head) set than one and a half for each CU of a die: no die has much
+    more than an eighth of the wave, and every key of every row tile belongs to one workgroup."""
     b = W.make_custom_batch("dealt", W.Geometry(*heads), prefix, suffix, seed=1, share_groups=groups)
     info, _, items = B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, tile_rows=tile_rows, block_table=b.block_table)
     load, ranges = np.zeros(8, np.int64), {}
