@@ -933,7 +933,7 @@ static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot
-// rings (64 KB at d=128, 32 KB at d=64); 256 rows run one eight-wave workgroup per
+// rings (64 KB at d=128, and 16 for the Q rows of 128; 32 KB at d=64); 256 rows run one eight-wave workgroup per
 // CU that shares every K/V tile among twice as many rows and spends 128 of the 160
 // KB of LDS (64 at d=64) on four-slot rings.  At d=64, 128 rows are held to the 168
 // registers of three waves per SIMD, for three workgroups per CU.  64 rows are not:
