@@ -228,7 +228,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // turned through LDS -> these not: 29 requests of one new over 32 cached tokens x 40
   // heads 13.1 -> 11.9, 27 of ten over up to 174 17.9 -> 17.2; 80 workgroups of one key
   // tile 6.0 -> 5.5.
-  const bool few = it.alone || rows_total - wrow0 <= 16;
+  // So do waves whose rows lie further apart than the 32-bit offsets of the copies
+  // reach: a token's row of 2^18 heads and more (2^19 at d = 64).
+  constexpr int kMostHeads = (int)((1u << 31) / (32 * ROW));
+  const bool few = it.alone || rows_total - wrow0 <= 16 || Hq > kMostHeads;
   int limit[RB];                                  // last visible key of the lane's row
   constexpr uint32_t Q_PART = UPW * 1024 < 32 * ROW ? UPW * 1024 : 32 * ROW;   // bytes of the wave's rows in the V slot
   const uint32_t q_slot = (uint32_t)((2 * NS - 1) * TILE_BYTES + wave * (UPW * 1024));
@@ -246,19 +249,19 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
       for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
     }
   }
-  // Bytes from the wave's first row in q and out to its row r, for the lanes of row
-  // l32: row rho of a kv head lies at rho + token(rho) (Hq - G) in units of a row.
+  // How far from the wave's first row its row r lies in q and out, for the lanes of row
+  // l32, in rows: row rho of a kv head lies at rho + token(rho) (Hq - G).
   const int tok0 = G.quotient(wrow0);
   const int64_t wave_rows = ((int64_t)(it.q_off + tok0) * Hq + it.kv_head * G.d + (wrow0 - tok0 * G.d)) * ROW;
   auto row_offset = [&](int r) __attribute__((always_inline)) -> uint32_t {
     if (wrow0 + r > rows_total - 1) r = rows_total - 1 - wrow0;
-    return (uint32_t)(r + (G.quotient(wrow0 + r) - tok0) * (Hq - G.d)) * (uint32_t)ROW;
+    return (uint32_t)(r + (G.quotient(wrow0 + r) - tok0) * (Hq - G.d));
   };
-  // ... and for every lane of a wave-wide copy of whole rows, the i-th of a block, to
-  // its row there, from the lane that has it: products and quotients of whole
+  // ... and, in bytes, for every lane of a wave-wide copy of whole rows, the i-th of a
+  // block, its row there, from the lane that has it: products and quotients of whole
   // numbers take four times as long as anything else here.
   auto copied_row = [&](int i, uint32_t own) __attribute__((always_inline)) -> uint32_t {
-    return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (i * KPU + lane / CPR), (int)own);
+    return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (i * KPU + lane / CPR), (int)own) * (uint32_t)ROW;
   };
   if (Q_BY_LDS && !few) {
     const uint32_t own = row_offset(l32);
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
       return lds_base + (i * 1024 < (int)Q_PART ? q_slot : q_rest) + (uint32_t)(i * 1024);
     };
     if (((uintptr_t)p.q & 15) == 0) {
-      const i32x4 rows = block_resource(q0, (uint32_t)__builtin_amdgcn_readlane((int)own, 31) + ROW);
+      const i32x4 rows = block_resource(q0, (uint32_t)(__builtin_amdgcn_readlane((int)own, 31) + 1) * (uint32_t)ROW);
 #pragma unroll
       for (int i = 0; i < 32 / KPU; ++i) copy16_to_lds(rows, off[i], to(i));
     } else {                                      // copies into LDS promise nothing for such rows
@@ -856,7 +859,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
       const float l_tot = sum_across_halves(l_run[rb]);
       if (it.part_slot < 0 && few) {
         const float inv = 1.0f / l_tot;
-        unsigned char *op = (unsigned char *)p.out + wave_rows + row_offset(rb * 32 + l32) + 8 * hh;
+        unsigned char *op = (unsigned char *)p.out + wave_rows + (int64_t)row_offset(rb * 32 + l32) * ROW + 8 * hh;
         if (wrow0 + rb * 32 + l32 < rows_total)
 #pragma unroll
           for (int db = 0; db < DB; ++db)

@@ -90,6 +90,32 @@ def test_out_anywhere_in_a_larger_buffer(geom, tile_rows, split_kv, copies):
     assert np.array_equal(results[0], results[1]) and np.array_equal(results[0], results[2])
 
 
+def test_rows_of_a_wave_over_four_gigabytes():
+    """Token rows of 140 MB: the 32 query rows of one wave lie over more bytes than 32 bits count."""
+    heads, S, d = 550_000, 33, 128
+    b = W.make_custom_batch("wide", W.Geometry(heads, heads, d), [0], [S], seed=18)
+    gen = torch.Generator(device="cuda").manual_seed(18)
+    normal = lambda *n: torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    q, k, v = (normal(S, heads, d) for _ in range(3))
+    pools = [torch.zeros(b.num_pages, heads, W.PAGE_SIZE, d, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    plan = B.Plan(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table)
+    assert plan.prism_plan_get_info().tile_rows == 128 and 31 * heads * d * 2 > 2 ** 32
+    ws = torch.empty(max(256, plan.prism_plan_workspace_bytes()), dtype=torch.uint8, device="cuda")
+    out = torch.full_like(q, float("nan"))
+    plan.prism_prefix_prefill(q, k, v, *pools, torch.from_numpy(b.block_table).cuda(), out, ws)
+    torch.cuda.synchronize()
+    plan.close()
+    some = torch.cat([torch.tensor([0, 1, heads // 2, heads - 1]), torch.arange(7, heads, 9973)]).cuda()
+    x, y, z = (t[:, some].transpose(0, 1).float().contiguous() for t in (q, k, v))
+    scores = (x @ y.transpose(1, 2).contiguous()) * b.softmax_scale
+    scores.masked_fill_(torch.ones(S, S, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    check_close(out[:, some].transpose(0, 1).double().cpu().numpy(), (scores.softmax(-1) @ z).double().cpu().numpy(), "wide")
+    pages = torch.from_numpy(b.block_table[0, :3].astype(np.int64)).cuda()
+    for pool, new in zip(pools, (k, v)):
+        rows = pool[:, some].index_select(0, pages).permute(0, 2, 1, 3).reshape(-1, len(some), d)
+        assert torch.equal(rows[:S], new[:, some]) and not rows[S:].any()
+
+
 @pytest.mark.parametrize("shape", [(128, 32), (128, 64), (256, 64)], ids=["128x32", "128x64", "256x64"])
 @pytest.mark.parametrize("split_kv", [2, 3, 7])
 def test_split_kv_matches_oracle(oracle_lib, split_kv, shape):
