@@ -88,7 +88,8 @@ typedef struct prism_plan_options {
   int32_t split_kv;            /* 0 auto, 1 never split, n>1 force n-way split         */
   int32_t min_split_keys;      /* auto split: smallest KV chunk, multiple of 64, counted in
                                   whole tiles of 64 keys; default: 256, the last of a
-                                  range may be smaller                                 */
+                                  range may be smaller, and few rows over ranges of up
+                                  to 12 tiles, or rows in tiles of 16, are left whole   */
   int32_t rows_per_wave;       /* query rows per wavefront: 32 or 64 (64 needs tile_rows
                                   128 or 256: two or four waves, one per SIMD)         */
   int32_t table_is_final;      /* nonzero: block_table_host is the table that every call

@@ -106,8 +106,8 @@ SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t 
   return with(lo);
 }
 
-// `sets` (cluster, kv head) sets, each of which runs on one die.
-SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool stream, bool in_tiles, int d) {
+// `sets` (cluster, kv head) sets, each of which runs on one die.  `asked`: min_chunk is the caller's.
+SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool asked, bool stream, bool in_tiles, int d) {
   int64_t total = 0, n = 0;
   for (const auto &c : costs) {
     total += c.count * c.tiles * heads;
@@ -124,8 +124,9 @@ SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chun
     // tiles x 8 heads, d = 128, in two or three pieces -> whole: 8 ranges 8.6 -> 7.9, 32
     // 10.3 -> 8.0; d = 64: 36 of up to 9 tiles 6.6 -> 5.6, 192 of 10 10.8 -> 8.1; of 16
     // tiles and more 6.8 -> 7.5 and, at d = 128, 9.3 -> 11.0.  Nor are row tiles of 16
-    // cut, which are chosen for what they take whole.
-    if (in_tiles || costs[0].tiles <= 12) return SplitRule{};
+    // cut, which are chosen for what they take whole.  A caller who names the
+    // smallest piece gets pieces.
+    if (!asked && (in_tiles || costs[0].tiles <= 12)) return SplitRule{};
     const int64_t slots = (d == 64 ? 2 : 1) * kNumCU;
     if (n <= slots) return fit(costs, heads, min_chunk, 4, slots);
     const int chunk = (int)std::max<int64_t>(min_chunk, total / slots);
@@ -467,7 +468,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       }
     for (int c = most_cost; c > 0; --c)
       if (count[c]) costs.push_back({c, count[c], rows[c]});
-    rule = choose_split(costs, s.num_kv_heads, sets, min_chunk, stream, in_tiles, d);
+    rule = choose_split(costs, s.num_kv_heads, sets, min_chunk, opt.min_split_keys != 0, stream, in_tiles, d);
   }
 
   // Heaviest cluster first; inside a (cluster, kv head) set the requests, the

@@ -202,6 +202,18 @@ def test_row_tiles_of_sixteen_while_they_find_places(lib, heads, prefix, suffix,
     assert info.tile_rows == rows and (rows > 16 or info.num_split_items == 0)
 
 
+@pytest.mark.parametrize("heads,prefix,suffix,pieces", [
+    ((32, 8, 128), [639] * 2, [1] * 2, {64: 80, 128: 48, 256: 32}), ((32, 8, 64), [511] * 3, [4] * 3, {64: 120, 128: 72, 256: 48}),
+    ((32, 8, 128), [1003], [37], {64: 240, 512: 160, 1024: 80})], ids=["decode", "few-rows-d64", "row-tiles"])
+def test_smallest_piece_of_the_caller_is_used_where_the_default_leaves_ranges_whole(lib, heads, prefix, suffix, pieces):
+    b = W.make_custom_batch("least", W.Geometry(*heads), prefix, suffix, seed=1)
+    whole = _check_cover(b, 0, 0)
+    assert whole.tile_rows == 16 and whole.num_split_items == 0
+    for least, want in pieces.items():
+        info = _check_cover(b, 0, 0, min_split_keys=least)
+        assert info.tile_rows == 16 and info.num_items == want and info.num_split_items in (0, want)
+
+
 @pytest.mark.parametrize("heads,prefix,suffix,groups,tile_rows", [
     ((8, 1, 64), [0], [4096], [-1], 0), ((8, 1, 64), [18612] * 3, [1648, 2400, 3297], [-1] * 3, 0), ((8, 2, 128), [373] * 3, [2685] * 3, [-1] * 3, 0),
     ((4, 1, 128), [512] * 5, [700, 300, 500, 600, 400], [0] * 5, 0), ((8, 1, 128), [0, 100], [400, 37], [-1] * 2, 64), ((4, 4, 64), [0, 100], [6200, 37], [-1] * 2, 0),
