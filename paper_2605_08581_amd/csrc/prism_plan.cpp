@@ -106,8 +106,8 @@ SplitRule coarser(const Costs &costs, int heads, const SplitRule &rule, int64_t 
   return with(lo);
 }
 
-// `sets` (cluster, kv head) sets, each of which runs on one die.  `asked`: min_chunk is the caller's.
-SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chunk, bool asked, bool stream, bool in_tiles, int d) {
+// `dies`: how many the row tiles go to.  `asked`: min_chunk is the caller's.
+SplitRule choose_split(const Costs &costs, int heads, int dies, int min_chunk, bool asked, bool stream, bool in_tiles, int d) {
   int64_t total = 0, n = 0;
   for (const auto &c : costs) {
     total += c.count * c.tiles * heads;
@@ -138,8 +138,8 @@ SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chun
     return SplitRule{chunk, chunk, min_chunk};
   }
   // For the others the least estimate decides, of no cuts and of those into at
-  // most one to four workgroups per CU, of the chip and of the dies that fewer than
-  // eight sets reach (a few more would wait for a round of their own).  In us: the
+  // most one to four workgroups per CU, of the chip and of the dies that the row tiles
+  // go to, where those are fewer (a few more would wait for a round of their own).  In us: the
   // longest piece takes `alone` per key tile, a CU that is never idle `busy`;
   // cutting adds the launch of the merge, the serial reads of the group with the
   // most pieces and, for 128 rows of partials, `partials` to write and read them.
@@ -149,9 +149,10 @@ SplitRule choose_split(const Costs &costs, int heads, int64_t sets, int min_chun
   // for both head dims without the terms for the merge, of 206 waves of 10 us and
   // more 18 take 3 to 25 % less and two 4 % more.  (34 rows x 15.9k keys, 8/1 heads,
   // d = 64: 50 pieces a group 38.8 us, 21 pieces 27.8, 4 pieces 44.8; 140 row tiles
-  // of 15 key tiles on two dies, d = 128: cut 58.1 us, uncut 45.5.)
+  // of 15 key tiles on two dies, d = 128: cut 58.1 us, uncut 45.5; dealt out to eight, cut
+  // 22.6, uncut 25.8.)
   const double alone = d == 64 ? 0.7 : 1.2, busy = d == 64 ? 0.47 : 0.95, partials = d == 64 ? 0.015 : 0.04;
-  const int64_t reached = std::min<int64_t>(sets, kNumXCD) * (kNumCU / kNumXCD);
+  const int64_t reached = (int64_t)dies * (kNumCU / kNumXCD);
   const int cus = d == 64 ? kNumCU : (int)reached;
   auto longest_piece = [&](const SplitRule &r) {
     int longest = 0;
@@ -459,8 +460,16 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     first_tile[r + 1] = (int)tile_keys.size();
   }
 
-  // Split-KV: no piece of the automatic cuts has fewer key tiles than a caller's
-  // min_split_keys; without one, all but the last of a range have four.
+  // Heaviest cluster first; inside a (cluster, kv head) set the requests, the
+  // longest first, and inside a request the row tiles, stay adjacent so that they
+  // run at the same time and find each other's K/V pages in cache.
+  std::sort(live.begin(), live.end(), [&](int a, int b) {
+    const int ca = cluster[a], cb = cluster[b];
+    if (ca != cb) return cluster_cost[ca] != cluster_cost[cb] ? cluster_cost[ca] > cluster_cost[cb] : ca < cb;
+    const int ka = key_tiles(prefix[a] + suffix[a]), kb = key_tiles(prefix[b] + suffix[b]);
+    return ka != kb ? ka > kb : a < b;
+  });
+
   // A (cluster, kv head) set of more row tiles than one and a half for each CU of a die
   // is dealt to as many dies as it takes to give each an eighth of the wave: with
   // fewer sets than dies, or a few more, most of the chip waited for those that had
@@ -472,15 +481,36 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // many (33 to 44 tiles would gain 1.05 to 1.5 where they are alone, 17 to 32 up to 1.7).
   const int64_t die_tiles = kNumCU / kNumXCD * 3 / 2;
   std::vector<int64_t> set_tiles(s.batch, 0);          // row tiles of a cluster, of one kv head
-  int64_t wave_cost = 0, sets = clusters * s.num_kv_heads;   // key tiles of all kv heads; sets, for the cuts
-  for (int r : live) {
-    const int tiles = first_tile[r + 1] - first_tile[r];
-    set_tiles[cluster[r]] += tiles;
-    if (!stream && tiles > die_tiles) sets = std::max<int64_t>(sets, kNumXCD);   // one request alone reaches every die
-  }
+  int64_t wave_cost = 0;                               // key tiles of all kv heads
+  for (int r : live) set_tiles[cluster[r]] += first_tile[r + 1] - first_tile[r];
   for (int c = 0; c < s.batch; ++c) wave_cost += cluster_cost[c] * s.num_kv_heads;
   auto dealt_out = [&](int c) { return !stream && set_tiles[c] > die_tiles; };
+  // The dies that the wave reaches, for the cuts: as many as it has sets, and those that
+  // the row tiles of sets dealt out go to, of one request or of several that share a
+  // prefix.  us per pass of the latter, cut as if each set had one die -> this: 8/1 heads,
+  // d = 128, 8 of 120 new over 16384 shared tokens 192.9 -> 69.1; 8/2 heads, 8 of 200 over 8192
+  // 103.0 -> 61.6, two of 1000 114.4 -> 91.7, 4 of 500 over 2000 36.1 -> 29.7, two of 1500 over
+  // 1000 38.4 -> 39.7.
+  auto dies_reached = [&]() -> int {
+    if (clusters * s.num_kv_heads >= kNumXCD) return kNumXCD;
+    Dealer to{wave_cost};
+    for (size_t i = 0, j; i < live.size(); i = j) {
+      for (j = i; j < live.size() && cluster[live[j]] == cluster[live[i]];) ++j;
+      for (int h = 0; h < s.num_kv_heads; ++h) {
+        to.open();
+        for (size_t m = i; m < j; ++m)
+          for (int tile = first_tile[live[m] + 1] - 1; tile >= first_tile[live[m]]; --tile) {
+            if (dealt_out(cluster[live[i]]) && to.full()) to.open();
+            ++to.run;
+            to.take(key_tiles(tile_keys[tile]));
+          }
+      }
+    }
+    return kNumXCD - (int)std::count(to.load, to.load + kNumXCD, 0);
+  };
 
+  // Split-KV: no piece of the automatic cuts has fewer key tiles than a caller's
+  // min_split_keys; without one, all but the last of a range have four.
   const int min_chunk = std::max(1, (opt.min_split_keys ? opt.min_split_keys : 256) / kTileKeys);
   SplitRule rule;
   Costs costs;
@@ -494,18 +524,8 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       }
     for (int c = most_cost; c > 0; --c)
       if (count[c]) costs.push_back({c, count[c], rows[c]});
-    rule = choose_split(costs, s.num_kv_heads, sets, min_chunk, opt.min_split_keys != 0, stream, in_tiles, d);
+    rule = choose_split(costs, s.num_kv_heads, dies_reached(), min_chunk, opt.min_split_keys != 0, stream, in_tiles, d);
   }
-
-  // Heaviest cluster first; inside a (cluster, kv head) set the requests, the
-  // longest first, and inside a request the row tiles, stay adjacent so that they
-  // run at the same time and find each other's K/V pages in cache.
-  std::sort(live.begin(), live.end(), [&](int a, int b) {
-    const int ca = cluster[a], cb = cluster[b];
-    if (ca != cb) return cluster_cost[ca] != cluster_cost[cb] ? cluster_cost[ca] > cluster_cost[cb] : ca < cb;
-    const int ka = key_tiles(prefix[a] + suffix[a]), kb = key_tiles(prefix[b] + suffix[b]);
-    return ka != kb ? ka > kb : a < b;
-  });
 
   // The key-splitting kernel reads every key of an item once: pages of one request
   // alone, whose rows are one tile, can pass the caches by, if the wave is more than those of the dies hold

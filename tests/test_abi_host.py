@@ -244,11 +244,13 @@ def test_sets_larger_than_a_die_are_dealt_out(lib, heads, prefix, suffix, groups
 
 
 @pytest.mark.parametrize("heads,prefix,suffix,least,most", [
-    ((8, 1, 64), [15838], [34], 8, 30), ((8, 2, 128), [224, 480], [1116] * 2, 1, 1), ((32, 8, 64), [2448] * 22, [12] * 22, 2, 5)],
-    ids=["deep-merge", "full-tiles", "few-rows-d64"])
+    ((8, 1, 64), [15838], [34], 8, 30), ((8, 2, 128), [224, 480], [750] * 2, 1, 1), ((8, 2, 128), [224, 480], [1116] * 2, 1, 3),
+    ((8, 1, 128), [16384] * 2, [480] * 2, 7, 9), ((8, 2, 128), [8192] * 2, [1000] * 2, 4, 4), ((32, 8, 64), [2448] * 22, [12] * 22, 2, 5)],
+    ids=["deep-merge", "full-tiles", "full-tiles-dealt-out", "sharers-dealt-out", "two-heads-dealt-out", "few-rows-d64"])
 def test_cuts_weigh_the_merge(lib, heads, prefix, suffix, least, most):
     """Pieces of a row tile where the estimate has to see how deep the merge gets, how many rows of partials
-    it moves, how many dies the wave reaches, and that a key tile takes half the time at d = 64."""
+    it moves, how many dies the wave reaches - two sets of 48 row tiles stay on theirs, sets of sharers with 60
+    and more are dealt out - and that a key tile takes half the time at d = 64."""
     b = W.make_custom_batch("merge", W.Geometry(*heads), prefix, suffix, seed=1,
                             share_groups=[-1 if len(prefix) > 2 else 0] * len(prefix))
     items = B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table)[2]
