@@ -112,7 +112,7 @@ __device__ __forceinline__ AttnItem load_item(const AttnItem *items, int i) {
   AttnItem it;
   it.req = w[0]; it.kv_head = w[1]; it.row0 = w[2]; it.kv_begin = w[3]; it.kv_end = w[4];
   it.part_slot = w[5]; it.prefix = w[6]; it.suffix = w[7]; it.q_off = w[8]; it.group = w[9];
-  it.read_once = w[10]; it.alone = w[11];
+  it.read_once = w[10];
   return it;
 }
 

@@ -32,8 +32,7 @@ struct AttnItem {
   int32_t q_off;       // token offset of the request in the packed q/out arrays
   int32_t group;       // part_slot >= 0: the ReduceGroup that merges it
   int32_t read_once;   // nothing else will ask for these cached pages soon: read them past the caches
-  int32_t alone;       // no other workgroup of the launch shares its compute unit
-  int32_t pad[4];
+  int32_t pad[5];
 };
 static_assert(sizeof(AttnItem) == 64, "AttnItem is 64 bytes");
 

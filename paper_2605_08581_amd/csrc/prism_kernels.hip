@@ -90,14 +90,16 @@ int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_po
 // accumulator rescale is skipped on almost every tile.
 // --------------------------------------------------------------------------
 
-constexpr bool q_by_lds(int d, int rb, int ns) { return d == 128 && rb == 1 && ns == 2; }
+constexpr bool q_by_lds(int d, int rb, int ns, bool direct) { return d == 128 && rb == 1 && ns == 2 && !direct; }
 // Bytes of LDS: the rings, and what of the Q rows finds no room in the last V slot.
-constexpr size_t attn_lds_bytes(int d, int rb, int nw, int ns) {
+constexpr size_t attn_lds_bytes(int d, int rb, int nw, int ns, bool direct) {
   const size_t tile = (size_t)kTileKeys * d * 2, q = (size_t)nw * 32 * d * 2;
-  return 2 * ns * tile + (q_by_lds(d, rb, ns) && q > tile ? q - tile : 0);
+  return 2 * ns * tile + (q_by_lds(d, rb, ns, direct) && q > tile ? q - tile : 0);
 }
 
-template <int D, int RB, int NW, int WPE, int NS>
+// DIRECT: for launches of no more workgroups than CUs, which load Q into registers and
+// store out straight from the accumulators (results do not depend on it).
+template <int D, int RB, int NW, int WPE, int NS, bool DIRECT>
 __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnArgs p) {
   constexpr int BN = kTileKeys;
   constexpr int NT = NW * 64;
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   constexpr int DB = D / 32;                     // 32-wide head-dim blocks of O^T
   constexpr int KB = BN / 32;                    // 32-key blocks per tile
   constexpr int KS = BN / 16;                    // 16-key MFMA k-steps of O^T per tile
-  constexpr bool Q_BY_LDS = q_by_lds(D, RB, NS);
+  constexpr bool Q_BY_LDS = q_by_lds(D, RB, NS, DIRECT);
 
   // LDS: a ring of NS tile slots for K followed by a ring of NS slots for V
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -186,7 +188,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 #pragma unroll
   for (int db = 0; db < DB; ++db) __asm__ volatile("" : "+v"(v_lane[db][0]), "+v"(v_lane[db][1]));
   pin_item(it);
-  __asm__ volatile("" : : "s"(it.alone));        // (its own load, later, cost 0.3 us a workgroup)
   if (it.req < 0) return;                        // idle padding entry
   const int P = it.prefix, S = it.suffix;
   const int rows_total = S * G.d;
@@ -224,14 +225,14 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   const int wrow0 = it.row0 + wave * (32 * RB);
   bf16x8 qf[RB][KK];
   // Few rows are few lines, and without a second workgroup there is nothing to make
-  // room for: such waves load Q, and store out, the short way.  us per pass, all
-  // turned through LDS -> these not: 29 requests of one new over 32 cached tokens x 40
-  // heads 13.1 -> 11.9, 27 of ten over up to 174 17.9 -> 17.2; 80 workgroups of one key
-  // tile 6.0 -> 5.5.
+  // room for: such waves store out the short way, straight from the accumulators.  us
+  // per pass, turned through LDS -> not: 29 requests of one new over 32 cached tokens x 40
+  // heads 13.1 -> 11.9, 64 of 2..6 over 50..120, 32/8 heads, 8.9 -> 8.5.
   // So do waves whose rows lie further apart than the 32-bit offsets of the copies
   // reach: a token's row of 2^18 heads and more (2^19 at d = 64).
   constexpr int kMostHeads = (int)((1u << 31) / (32 * ROW));
-  const bool few = it.alone || rows_total - wrow0 <= 16 || Hq > kMostHeads;
+  const bool wide = Hq > kMostHeads, one_wave = rows_total - it.row0 <= 32;
+  const bool few = DIRECT || rows_total - wrow0 <= 16 || one_wave || wide;
   int limit[RB];                                  // last visible key of the lane's row
   constexpr uint32_t Q_PART = UPW * 1024 < 32 * ROW ? UPW * 1024 : 32 * ROW;   // bytes of the wave's rows in the V slot
   const uint32_t q_slot = (uint32_t)((2 * NS - 1) * TILE_BYTES + wave * (UPW * 1024));
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     const int from = valid ? row : 0;             // rows past the end are cleared once they are here
     const int tok = G.quotient(from), g = from - tok * G.d;
     limit[rb] = valid ? P + tok : -1;
-    if (!Q_BY_LDS || few) {
+    if (!Q_BY_LDS) {
       const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D + 8 * hh;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
@@ -263,24 +264,45 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   auto copied_row = [&](int i, uint32_t own) __attribute__((always_inline)) -> uint32_t {
     return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (i * KPU + lane / CPR), (int)own) * (uint32_t)ROW;
   };
-  if (Q_BY_LDS && !few) {
+  // Where one wave has all the rows the copies have the operand's own layout, copy kk
+  // bringing each lane the 16 bytes that it will read back: the lines stay in L1, and
+  // no addresses have to change lanes (27 requests of ten new over up to 174 tokens x
+  // 40 heads 16.8 -> 16.5).  No load into registers may end in qf: the compiler, which
+  // does not see the copies, then waits for all that is under way, V of the first tile
+  // and K of the second, wherever qf is touched, on any way there.  us per pass, with
+  // such loads for few rows -> without: 43 requests of one new over 20..60 tokens x 40
+  // heads 18.2 -> 17.0, 40 of four over 60 20.0 -> 18.2, 10 of 65..150 over up to 100 14.3 ->
+  // 13.7, 28 of 33..50 over 50..300 x 8 heads 13.2 -> 13.5.  Launches that give every
+  // workgroup a CU are a kernel of their own (DIRECT), which has them: by copies 3
+  // requests of 100..200 over 50..300 x 40 heads took 12.9 -> 13.7.
+  const bool in_operand = one_wave || wide;
+  constexpr int QC = 32 / KPU;                    // 1 KB copies of a wave's rows
+  static_assert(QC == KK || !Q_BY_LDS, "a copy for each k-step, in either layout");
+  auto q_at = [&](int i) __attribute__((always_inline)) {   // where copy i goes
+    return lds_base + (i * 1024 < (int)Q_PART ? q_slot : q_rest) + (uint32_t)(i * 1024);
+  };
+  if (Q_BY_LDS && wrow0 < rows_total) {
     const uint32_t own = row_offset(l32);
-    uint32_t off[32 / KPU];
-#pragma unroll
-    for (int i = 0; i < 32 / KPU; ++i)
-      off[i] = copied_row(i, own) + (uint32_t)(((lane % CPR) ^ swz<D>(i * KPU + lane / CPR)) << 4);
     const unsigned char *q0 = (const unsigned char *)p.q + wave_rows;
-    auto to = [&](int i) __attribute__((always_inline)) {
-      return lds_base + (i * 1024 < (int)Q_PART ? q_slot : q_rest) + (uint32_t)(i * 1024);
-    };
-    if (((uintptr_t)p.q & 15) == 0) {
+    uint32_t off[QC];
+    if (in_operand) {
+#pragma unroll
+      for (int i = 0; i < QC; ++i) off[i] = own * (uint32_t)ROW + (uint32_t)(32 * i + 16 * hh);
+    } else {
+#pragma unroll
+      for (int i = 0; i < QC; ++i)
+        off[i] = copied_row(i, own) + (uint32_t)(((lane % CPR) ^ swz<D>(i * KPU + lane / CPR)) << 4);
+    }
+    if (((uintptr_t)p.q & 15) == 0 && !wide) {
       const i32x4 rows = block_resource(q0, (uint32_t)(__builtin_amdgcn_readlane((int)own, 31) + 1) * (uint32_t)ROW);
 #pragma unroll
-      for (int i = 0; i < 32 / KPU; ++i) copy16_to_lds(rows, off[i], to(i));
+      for (int i = 0; i < QC; ++i) copy16_to_lds(rows, off[i], q_at(i));
     } else {                                      // copies into LDS promise nothing for such rows
+      const int64_t beyond = (int64_t)own * ROW - (int64_t)(own * (uint32_t)ROW);   // of the offset's 32 bits: wide rows only
 #pragma unroll
-      for (int i = 0; i < 32 / KPU; ++i)
-        *(__attribute__((address_space(3))) u32x4 *)(uintptr_t)(to(i) + (uint32_t)(lane * 16)) = *reinterpret_cast<const u32x4 *>(q0 + off[i]);
+      for (int i = 0; i < QC; ++i)
+        *(__attribute__((address_space(3))) u32x4 *)(uintptr_t)(q_at(i) + (uint32_t)(lane * 16)) =
+            *reinterpret_cast<const u32x4 *>(q0 + off[i] + (wide ? beyond : 0));
     }
   }
 #pragma unroll
@@ -669,10 +691,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     }
     if (second) wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
     else wait_pending(std::integral_constant<int, 0>{});
-    if (Q_BY_LDS && wave_live && !few) {
+    if (Q_BY_LDS && wave_live) {
       const uint32_t at = l32 * ROW < (int)Q_PART ? q_slot : q_rest;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) qf[0][kk] = *(lds_b128_ptr)(uintptr_t)(k_lane[kk] + at);
+      for (int kk = 0; kk < KK; ++kk) qf[0][kk] = *(lds_b128_ptr)(uintptr_t)(in_operand ? q_at(kk) + (uint32_t)(lane * 16) : k_lane[kk] + at);
     }
     __syncthreads();
     if (wrow0 + 32 * RB > rows_total)
@@ -925,14 +947,19 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const AttnArgs p, int
                                   (blockIdx.y + 1) * ROWS);
 }
 
-template <int D, int RB, int NW, int WPE, int NS>
-static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
-  constexpr size_t lds_bytes = attn_lds_bytes(D, RB, NW, NS);
-  auto kernel = prefill_attn_kernel<D, RB, NW, WPE, NS>;
+template <int D, int RB, int NW, int WPE, int NS, bool DIRECT>
+static int launch_attn_direct(const LaunchParams &p, hipStream_t st) {
+  constexpr size_t lds_bytes = attn_lds_bytes(D, RB, NW, NS, DIRECT);
+  auto kernel = prefill_attn_kernel<D, RB, NW, WPE, NS, DIRECT>;
   static const hipError_t attr = hipFuncSetAttribute(
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (attr != hipSuccess) return (int)attr;
   return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st, p.args);
+}
+template <int D, int RB, int NW, int WPE, int NS>
+static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
+  return p.num_items <= kNumCU ? launch_attn_direct<D, RB, NW, WPE, NS, true>(p, st)
+                               : launch_attn_direct<D, RB, NW, WPE, NS, false>(p, st);
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot

@@ -696,8 +696,6 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
         sch.items.push_back(k < per_die[x].size() ? die_items[x][per_die[x][k]] : idle);
     // drop idle entries at the very end of the list
     while (!sch.items.empty() && sch.items.back().req < 0) sch.items.pop_back();
-    if (sch.items.size() <= (size_t)kNumCU)
-      for (AttnItem &it : sch.items) it.alone = 1;
     sch.num_slots = next_slot;
     sch.workspace_bytes = (size_t)next_slot * partial_slot_bytes(tile_rows, d);
   };

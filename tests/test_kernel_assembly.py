@@ -8,6 +8,9 @@ The kernels rely on properties that the source cannot enforce by itself:
   registers that only its own assembly statements name; the register
   allocator is free to use whatever a statement does not clobber at that
   point, so it must not have picked any of them;
+* where the 128-dim kernels with two-slot rings bring Q by copies, no wait of the
+  compiler's own may drain the copies that are under way when the first scores
+  begin: it would if any load into registers could end in the Q operands;
 * nothing spills to scratch memory, and no packed-fp32 vector instruction is
   emitted (the build switches them off).
 The device code is compiled to assembly with the flags of the build (no GPU
@@ -93,3 +96,18 @@ def test_no_spills_and_no_packed_fp32(assembly):
         for kernel, _, ins in _instructions(lines):
             assert not ins.startswith("scratch_"), f"{src}: {kernel}: {ins}"
             assert not re.match(r"v_pk_(add|mul|fma)_f32\b", ins), f"{src}: {kernel}: {ins}"
+
+
+def test_first_scores_leave_later_copies_under_way(assembly):
+    kernels = {}
+    for kernel, _, ins in _instructions(assembly["prism_kernels.hip"]):
+        m = kernel and re.search(r"prefill_attn_kernelILi128ELi1ELi([24])ELi2ELi2ELb0E", kernel)
+        if m:
+            kernels.setdefault(int(m.group(1)), []).append(ins)
+    assert set(kernels) == {2, 4}
+    for waves, code in kernels.items():
+        pending = 2 * 16 // waves                     # copies of V of tile 0 and K of tile 1
+        start = next(i for i, ins in enumerate(code) if re.match(rf"s_waitcnt vmcnt\({pending}\)", ins))
+        scores = [i for i, ins in enumerate(code) if i > start and ins.startswith("v_mfma")][15]
+        waits = [int(m.group(1)) for ins in code[start + 1:scores] for m in [re.search(r"vmcnt\((\d+)\)", ins)] if m]
+        assert waits in ([], [0]), f"{waves} waves: {waits}"   # 0: the way of a workgroup with one key tile
