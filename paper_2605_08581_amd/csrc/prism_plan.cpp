@@ -584,29 +584,35 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
       while (j < live.size() && cluster[live[j]] == cluster[live[i]]) ++j;
       for (int h = 0; h < s.num_kv_heads; ++h) {
         ItemSet set{};
-        auto open = [&]() {
+        std::vector<AttnItem> *items = nullptr;
+        // (calls of their own would make the plan of 32 requests x 40 heads 13 % longer)
+        auto open = [&]() __attribute__((always_inline)) {
           to.open();
-          set = ItemSet{0, die_items[to.die].size(), 0};
+          items = &die_items[to.die];
+          set = ItemSet{0, items->size(), 0};
         };
-        auto close = [&]() {
-          set.end = die_items[to.die].size();
+        auto close = [&]() __attribute__((always_inline)) {
+          set.end = items->size();
           die_sets[to.die].push_back(set);
         };
         const bool out = dealt_out(cluster[live[i]]);
-        auto add = [&](const AttnItem &it) {
-          if (out && to.full()) {
-            close();
-            open();
+        auto add = [&](const AttnItem &it) __attribute__((always_inline)) {
+          if (out) {
+            if (to.full()) {
+              close();
+              open();
+            }
+            to.run += it.kv_begin == 0;
+            to.take(key_tiles(it.kv_end - it.kv_begin));
           }
-          to.run += it.part_slot < 0 || it.kv_begin == 0;
-          to.take(key_tiles(it.kv_end - it.kv_begin));
           set.longest = std::max(set.longest, it.kv_end - it.kv_begin);
-          die_items[to.die].push_back(it);
+          items->push_back(it);
         };
         open();
         for (size_t m = i; m < j; ++m)
           for (int tile = first_tile[live[m] + 1] - 1; tile >= first_tile[live[m]]; --tile) {
             const int req = live[m], kv_len = tile_keys[tile], cost = key_tiles(kv_len);
+            if (!out) to.take(cost);
             int nsplit = 1;
             if (opt.split_kv > 1) nsplit = std::min(opt.split_kv, cost);
             else if (opt.split_kv == 0) nsplit = rule.pieces(cost);
