@@ -460,12 +460,18 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     first_tile[r + 1] = (int)tile_keys.size();
   }
 
-  // Heaviest cluster first; inside a (cluster, kv head) set the requests, the
+  // Heaviest cluster first, and of equal ones, where fits_in_row_tiles has counted on
+  // that, the one of more row tiles; inside a (cluster, kv head) set the requests, the
   // longest first, and inside a request the row tiles, stay adjacent so that they
   // run at the same time and find each other's K/V pages in cache.
+  std::vector<int64_t> set_tiles(s.batch, 0);          // row tiles of a cluster, of one kv head
+  for (int r : live) set_tiles[cluster[r]] += first_tile[r + 1] - first_tile[r];
   std::sort(live.begin(), live.end(), [&](int a, int b) {
     const int ca = cluster[a], cb = cluster[b];
-    if (ca != cb) return cluster_cost[ca] != cluster_cost[cb] ? cluster_cost[ca] > cluster_cost[cb] : ca < cb;
+    if (ca != cb) {
+      if (cluster_cost[ca] != cluster_cost[cb]) return cluster_cost[ca] > cluster_cost[cb];
+      return in_tiles && set_tiles[ca] != set_tiles[cb] ? set_tiles[ca] > set_tiles[cb] : ca < cb;
+    }
     const int ka = key_tiles(prefix[a] + suffix[a]), kb = key_tiles(prefix[b] + suffix[b]);
     return ka != kb ? ka > kb : a < b;
   });
@@ -480,9 +486,7 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
   // one of 1700 over 8000 228 -> 83.  Smaller sets keep their die, as most waves have
   // many (33 to 44 tiles would gain 1.05 to 1.5 where they are alone, 17 to 32 up to 1.7).
   const int64_t die_tiles = kNumCU / kNumXCD * 3 / 2;
-  std::vector<int64_t> set_tiles(s.batch, 0);          // row tiles of a cluster, of one kv head
   int64_t wave_cost = 0;                               // key tiles of all kv heads
-  for (int r : live) set_tiles[cluster[r]] += first_tile[r + 1] - first_tile[r];
   for (int c = 0; c < s.batch; ++c) wave_cost += cluster_cost[c] * s.num_kv_heads;
   auto dealt_out = [&](int c) { return !stream && set_tiles[c] > die_tiles; };
   // The dies that the wave reaches, for the cuts: as many as it has sets, and those that

@@ -202,6 +202,13 @@ def test_row_tiles_of_sixteen_while_they_find_places(lib, heads, prefix, suffix,
     assert info.tile_rows == rows and (rows > 16 or info.num_split_items == 0)
 
 
+def test_row_tiles_of_sixteen_are_dealt_as_they_were_counted(lib):
+    """Sets of as many key tiles, in 20 row tiles and in two, turn and turn about: 176 row tiles, 22 a die."""
+    b = W.make_custom_batch("ties", W.Geometry(8, 1, 128), [80, 1270] * 8, [40, 4] * 8, seed=1)
+    info, _, items = B.prism_plan_dry_run(B.shape_of(b), b.prefix_len, b.suffix_len, block_table=b.block_table)
+    assert info.tile_rows == 16 and np.bincount(np.flatnonzero(items[:, 0] >= 0) % 8, minlength=8).tolist() == [22] * 8
+
+
 @pytest.mark.parametrize("heads,prefix,suffix,pieces", [
     ((32, 8, 128), [639] * 2, [1] * 2, {64: 80, 128: 48, 256: 32}), ((32, 8, 64), [511] * 3, [4] * 3, {64: 120, 128: 72, 256: 48}),
     ((32, 8, 128), [1003], [37], {64: 240, 512: 160, 1024: 80})], ids=["decode", "few-rows-d64", "row-tiles"])
