@@ -281,29 +281,14 @@ __device__ __forceinline__ void merge_group(const AttnArgs &p, int group, const 
   }
 }
 
-// O^T += V^T P^T.  With 64 rows per wave the O^T accumulators (128 registers at
-// d = 128) live in accumulation registers for the whole kernel while the score
-// tiles, which the vector ALU works on, stay in ordinary registers; the
-// compiler picks one register kind for every MFMA of a function, so this one
-// is written out.  Only MFMAs and the (fenced) rescale and epilogue touch the
-// accumulators.
-template <bool ACC>
-__device__ __forceinline__ void pv_mfma(f32x16 &o, bf16x8 a, bf16x8 b) {
-  if constexpr (ACC) {
-    __asm__ volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(o) : "v"(a), "v"(b));
-  } else {
-    o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, o, 0, 0, 0);
-  }
-}
 // Wait until every MFMA issued so far has written its result (the longest one
-// here takes 8 passes of 4 cycles): needed before accumulators written by
-// pv_mfma<true> are read by anything but another MFMA.
+// here takes 8 passes of 4 cycles): needed before accumulators that inline
+// assembly names are read by anything but another MFMA.
 __device__ __forceinline__ void mfma_drain() {
   __builtin_amdgcn_sched_barrier(0);
   __asm__ volatile("s_nop 15\n\ts_nop 3");
   __builtin_amdgcn_sched_barrier(0);
 }
-
 
 // f(integral_constant<int, B>) ... f(integral_constant<int, E-1>), expanded at
 // compile time: the body sees its index as a constant expression.

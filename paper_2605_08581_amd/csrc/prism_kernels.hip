@@ -56,7 +56,7 @@ int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_po
 // --------------------------------------------------------------------------
 // Prefill attention.
 //
-// A workgroup of NW waves owns NW*32*RB packed query rows of one (request, kv
+// A workgroup of NW waves owns NW*32 packed query rows of one (request, kv
 // head) and walks the key range in tiles of 64 keys (four 16-token pages).
 // K and V rows are copied from the paged pool, or from the packed new rows when
 // the kernel appends them itself, straight into LDS (buffer_load ... lds, 16
@@ -90,20 +90,20 @@ int launch_append(const void *k_src, const void *v_src, void *k_pool, void *v_po
 // accumulator rescale is skipped on almost every tile.
 // --------------------------------------------------------------------------
 
-constexpr bool q_by_lds(int d, int rb, int ns, bool direct) { return d == 128 && rb == 1 && ns == 2 && !direct; }
+constexpr bool q_by_lds(int d, int ns, bool direct) { return d == 128 && ns == 2 && !direct; }
 // Bytes of LDS: the rings, and what of the Q rows finds no room in the last V slot.
-constexpr size_t attn_lds_bytes(int d, int rb, int nw, int ns, bool direct) {
+constexpr size_t attn_lds_bytes(int d, int nw, int ns, bool direct) {
   const size_t tile = (size_t)kTileKeys * d * 2, q = (size_t)nw * 32 * d * 2;
-  return 2 * ns * tile + (q_by_lds(d, rb, ns, direct) && q > tile ? q - tile : 0);
+  return 2 * ns * tile + (q_by_lds(d, ns, direct) && q > tile ? q - tile : 0);
 }
 
 // DIRECT: for launches of no more workgroups than CUs, which load Q into registers and
 // store out straight from the accumulators (results do not depend on it).
-template <int D, int RB, int NW, int WPE, int NS, bool DIRECT>
+template <int D, int NW, int WPE, int NS, bool DIRECT>
 __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnArgs p) {
   constexpr int BN = kTileKeys;
   constexpr int NT = NW * 64;
-  constexpr int BM = NW * 32 * RB;
+  constexpr int BM = NW * 32;
   constexpr int CPR = D / 8;                     // 16-byte chunks per key row
   constexpr int ROW = D * 2;                     // bytes per key row
   constexpr int TILE_BYTES = BN * D * 2;
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   constexpr int DB = D / 32;                     // 32-wide head-dim blocks of O^T
   constexpr int KB = BN / 32;                    // 32-key blocks per tile
   constexpr int KS = BN / 16;                    // 16-key MFMA k-steps of O^T per tile
-  constexpr bool Q_BY_LDS = q_by_lds(D, RB, NS, DIRECT);
+  constexpr bool Q_BY_LDS = q_by_lds(D, NS, DIRECT);
 
   // LDS: a ring of NS tile slots for K followed by a ring of NS slots for V
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -222,8 +222,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // behind the rings (16 KB at 128 rows: two workgroups then fill the CU's LDS).  us
   // per pass, loaded -> copied: 7 requests of 500..700 new tokens x 40 heads, 40
   // layers 2755 -> 2716, 32 full recomputes 3225 -> 3198; at d = 64 the same, so loaded.
-  const int wrow0 = it.row0 + wave * (32 * RB);
-  bf16x8 qf[RB][KK];
+  const int wrow0 = it.row0 + wave * 32;
+  bf16x8 qf[KK];
   // Few rows are few lines, and without a second workgroup there is nothing to make
   // room for: such waves store out the short way, straight from the accumulators.  us
   // per pass, turned through LDS -> not: 29 requests of one new over 32 cached tokens x 40
@@ -233,22 +233,17 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   constexpr int kMostHeads = (int)((1u << 31) / (32 * ROW));
   const bool wide = Hq > kMostHeads, one_wave = rows_total - it.row0 <= 32;
   const bool few = DIRECT || rows_total - wrow0 <= 16 || one_wave || wide;
-  int limit[RB];                                  // last visible key of the lane's row
   constexpr uint32_t Q_PART = UPW * 1024 < 32 * ROW ? UPW * 1024 : 32 * ROW;   // bytes of the wave's rows in the V slot
   const uint32_t q_slot = (uint32_t)((2 * NS - 1) * TILE_BYTES + wave * (UPW * 1024));
   const uint32_t q_rest = (uint32_t)(2 * NS * TILE_BYTES) + (uint32_t)wave * (32 * ROW - Q_PART) - Q_PART;
+  const bool valid = wrow0 + l32 < rows_total;
+  const int q_row = valid ? wrow0 + l32 : 0;      // rows past the end are cleared once they are here
+  const int q_tok = G.quotient(q_row);
+  const int limit = valid ? P + q_tok : -1;       // last visible key of the lane's row
+  if (!Q_BY_LDS) {
+    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + q_tok) * Hq + it.kv_head * G.d + q_row - q_tok * G.d) * D + 8 * hh;
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int row = wrow0 + rb * 32 + l32;
-    const bool valid = row < rows_total;
-    const int from = valid ? row : 0;             // rows past the end are cleared once they are here
-    const int tok = G.quotient(from), g = from - tok * G.d;
-    limit[rb] = valid ? P + tok : -1;
-    if (!Q_BY_LDS) {
-      const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(it.q_off + tok) * Hq + it.kv_head * G.d + g) * D + 8 * hh;
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) qf[rb][kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
-    }
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8 *>(qp + 16 * kk);
   }
   // How far from the wave's first row its row r lies in q and out, for the lanes of row
   // l32, in rows: row rho of a kv head lies at rho + token(rho) (Hq - G).
@@ -311,7 +306,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // Wave-uniform key bounds: at or below lo_limit no row of the wave is
   // masked, above hi_limit every row is.
   const int first_row = wrow0 < rows_total ? wrow0 : rows_total - 1;
-  int last_row = wrow0 + 32 * RB - 1;
+  int last_row = wrow0 + 31;
   if (last_row > rows_total - 1) last_row = rows_total - 1;
   const int lo_limit = P + G.quotient(first_row);
   const int hi_limit = P + G.quotient(last_row);
@@ -323,10 +318,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if (my_nt > nt) my_nt = nt;
   }
 
-  f32x16 oacc[DB][RB];
+  f32x16 oacc[DB];
   // m_run: running maximum (raw score units), l_run: running sum, bound: the
   // raw score above which the maximum has to be raised before exponentiating
-  float m_run[RB], l_run[RB], bound[RB];
+  float m_run, l_run, bound;
 
   // This wave's share of tile t into a ring slot, wherever its rows come from.
   auto copy_rows = [&](int which, int slot, int t, const PageIds &pg) __attribute__((always_inline)) {
@@ -428,17 +423,15 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     return a.v;
   };
   // (64 compares and selects per tile: only for 32-key blocks past the wave's first row)
-  auto mask_tile = [&](f32x16 (&sx)[KB][RB], int key0) __attribute__((always_inline)) {
+  auto mask_tile = [&](f32x16 (&sx)[KB], int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
       if (key0 + kb * 32 + 31 <= lo_limit) continue;
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = key0 + kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-          if (key > limit[rb]) sx[kb][rb][r] = -INFINITY;
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int key = key0 + kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
+        if (key > limit) sx[kb][r] = -INFINITY;
+      }
     }
   };
   // The lane's own maximum of a score tile against a precomputed bound (the
@@ -446,84 +439,64 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // Only when some score of the wave exceeds its bound do the two lanes of a
   // row exchange maxima, raise the running maximum and rescale what has been
   // accumulated.
-  auto raise_max = [&](const f32x16 (&sx)[KB][RB]) __attribute__((always_inline)) {
-    float mx[RB];
-    bool grow = false;
+  auto raise_max = [&](const f32x16 (&sx)[KB]) __attribute__((always_inline)) {
+    float mx = sx[0][0];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      mx[rb] = sx[0][rb][0];
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sx[kb][r]);
+    if (__builtin_amdgcn_ballot_w64(mx > bound) != 0) {
+      const float m_new = fmaxf(m_run, max_across_halves(mx));
+      bound = m_new + slack;
+      const float alpha = fast_exp2((m_run - m_new) * scale_log2e);
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx[rb] = fmaxf(mx[rb], sx[kb][rb][r]);
-      grow |= mx[rb] > bound[rb];
-    }
-    if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-      if constexpr (RB > 1) mfma_drain();
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const float m_new = fmaxf(m_run[rb], max_across_halves(mx[rb]));
-        bound[rb] = m_new + slack;
-        const float alpha = fast_exp2((m_run[rb] - m_new) * scale_log2e);
-        m_run[rb] = m_new;
-        l_run[rb] *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[db][rb][r] *= alpha;
-      }
-      if constexpr (RB > 1) __asm__ volatile("s_nop 1");
+        for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
     }
   };
   // P^T fragment of k-step ks from the scores (exp2, row sums, bf16 rounding)
-  auto p_frag = [&](const f32x16 (&sx)[KB][RB], int ks, int rb, float mc) __attribute__((always_inline)) -> bf16x8 {
+  auto p_frag = [&](const f32x16 (&sx)[KB], int ks, float mc) __attribute__((always_inline)) -> bf16x8 {
     bf16x8 pf;
     float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float p = fast_exp2(fmaf(sx[ks >> 1][rb][8 * (ks & 1) + e], scale_log2e, -mc));
+      const float p = fast_exp2(fmaf(sx[ks >> 1][8 * (ks & 1) + e], scale_log2e, -mc));
       sum += p;                                   // the fp32 exponentials, as in the overlapped step
       pf[e] = (__bf16)p;
     }
-    l_run[rb] += sum;
+    l_run += sum;
     return pf;
   };
 
   // Scores of the first tile, not overlapped with anything.
-  auto plain_scores = [&](f32x16 (&sx)[KB][RB], uint32_t k_lds, int key0) __attribute__((always_inline)) {
+  auto plain_scores = [&](f32x16 (&sx)[KB], uint32_t k_lds, int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sx[kb][rb][r] = 0.f;
+      for (int r = 0; r < 16; ++r) sx[kb][r] = 0.f;
 #pragma unroll
     for (int i = 0; i < KB * KK; ++i) {
       const bf16x8 a = k_frag(k_lds, i);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-        sx[i / KK][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[rb][i % KK], sx[i / KK][rb], 0, 0, 0);
+      sx[i / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[i % KK], sx[i / KK], 0, 0, 0);
     }
     mask_tile(sx, key0);
     raise_max(sx);
   };
   // Softmax and O^T update of the wave's last tile, nothing overlapped.  Where
   // its rows see none of the tile's upper 32 keys, those probabilities are zeros.
-  auto tail_step = [&](f32x16 (&sc)[KB][RB], uint32_t v_cur, bool lower_half) __attribute__((always_inline)) {
-    float mc[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) mc[rb] = m_run[rb] * scale_log2e;
+  auto tail_step = [&](f32x16 (&sc)[KB], uint32_t v_cur, bool lower_half) __attribute__((always_inline)) {
+    const float mc = m_run * scale_log2e;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       if (ks >= KS / 2 && lower_half) continue;
-      bf16x8 pf[RB];
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) pf[rb] = p_frag(sc, ks, rb, mc[rb]);
+      const bf16x8 pf = p_frag(sc, ks, mc);
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
         const bf16x8 a = v_frag(v_cur, ks * DB + db);
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) pv_mfma<(RB > 1)>(oacc[db][rb], a, pf[rb]);
+        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf, oacc[db], 0, 0, 0);
       }
     }
   };
@@ -539,38 +512,32 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // burst before the step: a copy instruction that finds the load queue full
   // then holds up one wave for a moment rather than every wave of the
   // workgroup at once, and the data still has most of an iteration to arrive.
-  constexpr int NQK = KB * KK;                    // K fragments per tile (one S^T MFMA each per row block)
-  constexpr int NPV = KS * DB;                    // V^T fragments per tile (one O^T MFMA each per row block)
-  constexpr int NEL = KB * 16;                    // score elements per lane per row block
+  constexpr int NQK = KB * KK;                    // K fragments per tile (one S^T MFMA each)
+  constexpr int NPV = KS * DB;                    // V^T fragments per tile (one O^T MFMA each)
+  constexpr int NEL = KB * 16;                    // score elements per lane
   constexpr int LA = 3;                           // fragment reads run this many fragments ahead
-  constexpr int NCH = (NQK + NPV) * RB;           // chunks (= MFMAs) per step
-  constexpr int CSPAN = (NQK + (KS - 1) * DB) * RB;   // chunks over which the exponentials spread
-  auto step = [&](f32x16 (&sc)[KB][RB], f32x16 (&sn)[KB][RB], uint32_t k_next, uint32_t v_cur, int t,
+  constexpr int NCH = NQK + NPV;                  // chunks (= MFMAs) per step
+  constexpr int CSPAN = NQK + (KS - 1) * DB;      // chunks over which the exponentials spread
+  auto step = [&](f32x16 (&sc)[KB], f32x16 (&sn)[KB], uint32_t k_next, uint32_t v_cur, int t,
                   auto mask_tag, auto vslot_tag, auto kslot_tag, auto new_tag) __attribute__((always_inline)) {
     constexpr int VSLOT = decltype(vslot_tag)::value, KSLOT = decltype(kslot_tag)::value;
     constexpr int NC = 2 * UPW;
     constexpr int STRIDE = 2 * NC <= NCH ? 2 : 1;   // every other chunk from the start of the step
-    float mc[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) mc[rb] = m_run[rb] * scale_log2e;
-    float sum_even[RB], sum_odd[RB];              // two chains per row: no add waits on the one before it
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) sum_even[rb] = sum_odd[rb] = 0.f;
+    const float mc = m_run * scale_log2e;
+    float sum_even = 0.f, sum_odd = 0.f;          // two chains: no add waits on the one before it
     bf16x8 frag[LA + 1];                          // ring of K / V^T fragments in flight
-    bf16x8 pf[KS][RB];                            // P^T fragments, one per 16-key k-step and row block
+    bf16x8 pf[KS];                                // P^T fragments, one per 16-key k-step
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sn[kb][rb][r] = 0.f;
+      for (int r = 0; r < 16; ++r) sn[kb][r] = 0.f;
     auto fetch = [&](int i) __attribute__((always_inline)) {                     // fragment i of the chain: K first, then V^T
       if (i < NQK) frag[i % (LA + 1)] = k_frag(k_next, i);
       else if (i < NQK + NPV) frag[i % (LA + 1)] = v_frag(v_cur, i - NQK);
     };
     // Softmax of the current tile, spread over the chunks as a three-stage
     // pipeline so that no chunk waits on its own results.  The elements are
-    // walked in the order the O^T MFMAs consume them (k-step, row block, key);
+    // walked in the order the O^T MFMAs consume them (k-step, key);
     // element x has its exponent argument formed in chunk home(x)-1, exp2
     // taken in chunk home(x), and is rounded to bf16 (two at a time) and added
     // to the row sum in chunk home(x)+1.  The row sum adds the fp32
@@ -578,23 +545,20 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     // measured 2 % faster over the whole kernel than a packed dot product of
     // the rounded pairs, and the difference to the rounded sum is far inside
     // the tolerance.
-    constexpr int NX = NEL * RB;
-    auto home = [](int x) { return 1 + (x * (CSPAN - 2)) / NX; };
+    auto home = [](int x) { return 1 + (x * (CSPAN - 2)) / NEL; };
     auto softmax_slice = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-      for (int x = 0; x < NX; ++x) {
-        const int ks = x / (8 * RB), rb = (x / 8) % RB, e8 = x % 8;
-        const int e = 8 * ks + e8;                // element of the row block's tile column
-        if (home(x) == c + 1) sc[e / 16][rb][e % 16] = fmaf(sc[e / 16][rb][e % 16], scale_log2e, -mc[rb]);
-        if (home(x) == c) sc[e / 16][rb][e % 16] = fast_exp2(sc[e / 16][rb][e % 16]);
+      for (int x = 0; x < NEL; ++x) {
+        if (home(x) == c + 1) sc[x / 16][x % 16] = fmaf(sc[x / 16][x % 16], scale_log2e, -mc);
+        if (home(x) == c) sc[x / 16][x % 16] = fast_exp2(sc[x / 16][x % 16]);
         if ((x & 1) && home(x) == c - 1) {
           bf16x2 pk;
-          pk[0] = (__bf16)sc[e / 16][rb][(e - 1) % 16];
-          pk[1] = (__bf16)sc[e / 16][rb][e % 16];
-          sum_even[rb] += sc[e / 16][rb][(e - 1) % 16];
-          sum_odd[rb] += sc[e / 16][rb][e % 16];
-          pf[ks][rb][e8 - 1] = pk[0];
-          pf[ks][rb][e8] = pk[1];
+          pk[0] = (__bf16)sc[x / 16][(x - 1) % 16];
+          pk[1] = (__bf16)sc[x / 16][x % 16];
+          sum_even += sc[x / 16][(x - 1) % 16];
+          sum_odd += sc[x / 16][x % 16];
+          pf[x / 8][(x - 1) % 8] = pk[0];
+          pf[x / 8][x % 8] = pk[1];
         }
       }
     };
@@ -612,22 +576,19 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     for (int i = 0; i < LA; ++i) fetch(i);
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NCH>([&](auto ct_) __attribute__((always_inline)) {
-      constexpr int c = decltype(ct_)::value;
-      constexpr int f = c / RB, rb = c % RB;      // fragment and row block of this chunk's MFMA
-      if constexpr (rb == 0) fetch(f + LA);
-      if constexpr (f < NQK) {
-        sn[f / KK][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f % (LA + 1)], qf[rb][f % KK],
-                                                                 sn[f / KK][rb], 0, 0, 0);
+      constexpr int c = decltype(ct_)::value;     // chunk, and fragment of its MFMA
+      fetch(c + LA);
+      if constexpr (c < NQK) {
+        sn[c / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[c % (LA + 1)], qf[c % KK], sn[c / KK], 0, 0, 0);
       } else {
-        constexpr int j = f - NQK;
-        pv_mfma<(RB > 1)>(oacc[j % DB][rb], frag[f % (LA + 1)], pf[j / DB][rb]);
+        constexpr int j = c - NQK;
+        oacc[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[c % (LA + 1)], pf[j / DB], oacc[j % DB], 0, 0, 0);
       }
       softmax_slice(c);
       mid_copy(c);
-      if (c < NCH - DB * RB) __builtin_amdgcn_sched_barrier(0);
+      if (c < NCH - DB) __builtin_amdgcn_sched_barrier(0);
     });
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) l_run[rb] += sum_even[rb] + sum_odd[rb];
+    l_run += sum_even + sum_odd;
     if (decltype(mask_tag)::value) mask_tile(sn, kv_begin + (t + 1) * BN);   // the next tile touches the diagonal
     raise_max(sn);
   };
@@ -650,7 +611,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));   // vmcnt(n) only
   };
   const bool wave_live = my_nt > 0;
-  f32x16 s_a[KB][RB], s_b[KB][RB];
+  f32x16 s_a[KB], s_b[KB];
   copy_rows(0, 0, 0, first_pages);
   if constexpr (NS > 2) {
     // With rings deeper than two slots copies stay in flight across
@@ -661,9 +622,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     // registers through an empty statement so that it knows.
     wait_pending(std::integral_constant<int, 0>{});
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) __asm__ volatile("" : "+v"(qf[rb][kk]));
+    for (int kk = 0; kk < KK; ++kk) __asm__ volatile("" : "+v"(qf[kk]));
   }
   {
     PageIds pg = first_pages;
@@ -680,29 +639,24 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     pg_v = pg;
     pg_k = pages_of(NS);
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[db][rb][r] = 0.f;
-      m_run[rb] = -1e30f;
-      l_run[rb] = 0.f;
-      bound[rb] = -1e30f;
-    }
+      for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
+    m_run = -1e30f;
+    l_run = 0.f;
+    bound = -1e30f;
     if (second) wait_pending(std::integral_constant<int, (2 * NS - 2) * UPW>{});   // K of tile 0 is in
     else wait_pending(std::integral_constant<int, 0>{});
     if (Q_BY_LDS && wave_live) {
       const uint32_t at = l32 * ROW < (int)Q_PART ? q_slot : q_rest;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) qf[0][kk] = *(lds_b128_ptr)(uintptr_t)(in_operand ? q_at(kk) + (uint32_t)(lane * 16) : k_lane[kk] + at);
+      for (int kk = 0; kk < KK; ++kk) qf[kk] = *(lds_b128_ptr)(uintptr_t)(in_operand ? q_at(kk) + (uint32_t)(lane * 16) : k_lane[kk] + at);
     }
     __syncthreads();
-    if (wrow0 + 32 * RB > rows_total)
+    if (wrow0 + 32 > rows_total)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-          if (limit[rb] < 0) qf[rb][kk] = bf16x8{};
+      for (int kk = 0; kk < KK; ++kk)
+        if (limit < 0) qf[kk] = bf16x8{};
     if (wave_live) plain_scores(s_a, k_slot(0), kv_begin);
   }
   // j is the tile index modulo NS, known at compile time in the fast loop so
@@ -827,9 +781,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     if (t < end) {
       any_iteration(t++, std::integral_constant<int, 0>{});
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) s_a[kb][rb] = s_b[kb][rb];
+      for (int kb = 0; kb < KB; ++kb) s_a[kb] = s_b[kb];
     }
     pass_on(t);
     tail_step(s_a, v_slot(t), hi_limit < kv_begin + t * BN + 32);
@@ -839,7 +791,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // The unused trailing copies of a deep ring drain.  With two slots none are left,
   // only the last tile's appended rows, and their stores take a microsecond.
   if constexpr (NS > 2) wait_pending(std::integral_constant<int, 0>{});
-  if constexpr (RB > 1) mfma_drain();
 
   // ---- epilogue.  A lane holds 4 dims here and 4 dims there of one row, so stores
   // straight from the accumulators touch 32 rows at once with 16 bytes of each, and
@@ -864,7 +815,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
     const uint32_t to = part + spread(l32 * ROW) + (swz<D>(l32) << 4);
     const uint32_t from = part + spread(from_row * ROW) + ((from_chunk ^ swz<D>(from_row)) << 4);
     // store(16 bytes, their offset) for every row of the block; offset(i): of the row of copy i
-    auto for_rows = [&](int rb, auto offset, auto store) __attribute__((always_inline)) {
+    auto for_rows = [&](auto offset, auto store) __attribute__((always_inline)) {
       uint32_t off[32 / KPU];
 #pragma unroll
       for (int i = 0; i < 32 / KPU; ++i) off[i] = offset(i) + 16u * from_chunk;
@@ -872,62 +823,59 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
 #pragma unroll
       for (int i = 0; i < 32 / KPU; ++i) {
         const uint32_t at = (from ^ (uint32_t)(swz<D>(i * KPU) << 4)) + spread(i * KPU * ROW);
-        if (wrow0 + rb * 32 + i * KPU + from_row < rows_total) store(*(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)at, off[i]);
+        if (wrow0 + i * KPU + from_row < rows_total) store(*(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)at, off[i]);
       }
       wait_lds_reads();                           // before the next block is written over it
     };
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const float l_tot = sum_across_halves(l_run[rb]);
-      if (it.part_slot < 0 && few) {
-        const float inv = 1.0f / l_tot;
-        unsigned char *op = (unsigned char *)p.out + wave_rows + (int64_t)row_offset(rb * 32 + l32) * ROW + 8 * hh;
-        if (wrow0 + rb * 32 + l32 < rows_total)
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              bf16x4 o4;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][rb][4 * g4 + e] * inv);
-              *reinterpret_cast<bf16x4 *>(op + (4 * db + g4) * 16) = o4;
-            }
-      } else if (it.part_slot < 0) {
-        const float inv = 1.0f / l_tot;
+    const float l_tot = sum_across_halves(l_run);
+    if (it.part_slot < 0 && few) {
+      const float inv = 1.0f / l_tot;
+      unsigned char *op = (unsigned char *)p.out + wave_rows + (int64_t)row_offset(l32) * ROW + 8 * hh;
+      if (wrow0 + l32 < rows_total)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
           for (int g4 = 0; g4 < 4; ++g4) {
             bf16x4 o4;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][rb][4 * g4 + e] * inv);
-            *(__attribute__((address_space(3))) bf16x4 *)(uintptr_t)((to ^ (uint32_t)((4 * db + g4) << 4)) + 8 * hh) = o4;
+            for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][4 * g4 + e] * inv);
+            *reinterpret_cast<bf16x4 *>(op + (4 * db + g4) * 16) = o4;
           }
-        unsigned char *out0 = (unsigned char *)p.out + wave_rows;
-        const uint32_t own = row_offset(rb * 32 + l32);
-        for_rows(rb, [&](int i) __attribute__((always_inline)) { return copied_row(i, own); },
-                 [&](u32x4 data, uint32_t off) __attribute__((always_inline)) { *reinterpret_cast<u32x4 *>(out0 + off) = data; });
-      } else {
-        float *slot = p.partials + (size_t)it.part_slot * ((size_t)BM * (D + 2));
-        unsigned char *po = (unsigned char *)(slot + (size_t)(wrow0 - it.row0) * D);
+    } else if (it.part_slot < 0) {
+      const float inv = 1.0f / l_tot;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {    // D/2 dims at a time: as wide as a row of bf16
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int db = 0; db < DB / 2; ++db)
+        for (int g4 = 0; g4 < 4; ++g4) {
+          bf16x4 o4;
 #pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              f32x4 o4;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o4[e] = oacc[half * (DB / 2) + db][rb][4 * g4 + e];
-              *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(to ^ (uint32_t)((8 * db + 2 * g4 + hh) << 4)) = o4;
-            }
-          for_rows(rb, [&](int i) __attribute__((always_inline)) { return (uint32_t)((rb * 32 + i * KPU + from_row) * 2 * ROW + half * ROW); },
-                   [&](u32x4 data, uint32_t off) __attribute__((always_inline)) { *reinterpret_cast<u32x4 *>(po + off) = data; });
+          for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][4 * g4 + e] * inv);
+          *(__attribute__((address_space(3))) bf16x4 *)(uintptr_t)((to ^ (uint32_t)((4 * db + g4) << 4)) + 8 * hh) = o4;
         }
-        const int row = wrow0 + rb * 32 + l32;
-        if (hh == 0 && row < rows_total)
-          *reinterpret_cast<float2 *>(slot + (size_t)BM * D + 2 * (row - it.row0)) = make_float2(m_run[rb], l_tot);
+      unsigned char *out0 = (unsigned char *)p.out + wave_rows;
+      const uint32_t own = row_offset(l32);
+      for_rows([&](int i) __attribute__((always_inline)) { return copied_row(i, own); },
+               [&](u32x4 data, uint32_t off) __attribute__((always_inline)) { *reinterpret_cast<u32x4 *>(out0 + off) = data; });
+    } else {
+      float *slot = p.partials + (size_t)it.part_slot * ((size_t)BM * (D + 2));
+      unsigned char *po = (unsigned char *)(slot + (size_t)(wrow0 - it.row0) * D);
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {    // D/2 dims at a time: as wide as a row of bf16
+#pragma unroll
+        for (int db = 0; db < DB / 2; ++db)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            f32x4 o4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o4[e] = oacc[half * (DB / 2) + db][4 * g4 + e];
+            *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(to ^ (uint32_t)((8 * db + 2 * g4 + hh) << 4)) = o4;
+          }
+        for_rows([&](int i) __attribute__((always_inline)) { return (uint32_t)((i * KPU + from_row) * 2 * ROW + half * ROW); },
+                 [&](u32x4 data, uint32_t off) __attribute__((always_inline)) { *reinterpret_cast<u32x4 *>(po + off) = data; });
       }
+      const int row = wrow0 + l32;
+      if (hh == 0 && row < rows_total)
+        *reinterpret_cast<float2 *>(slot + (size_t)BM * D + 2 * (row - it.row0)) = make_float2(m_run, l_tot);
     }
   }
 }
@@ -947,19 +895,19 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const AttnArgs p, int
                                   (blockIdx.y + 1) * ROWS);
 }
 
-template <int D, int RB, int NW, int WPE, int NS, bool DIRECT>
+template <int D, int NW, int WPE, int NS, bool DIRECT>
 static int launch_attn_direct(const LaunchParams &p, hipStream_t st) {
-  constexpr size_t lds_bytes = attn_lds_bytes(D, RB, NW, NS, DIRECT);
-  auto kernel = prefill_attn_kernel<D, RB, NW, WPE, NS, DIRECT>;
+  constexpr size_t lds_bytes = attn_lds_bytes(D, NW, NS, DIRECT);
+  auto kernel = prefill_attn_kernel<D, NW, WPE, NS, DIRECT>;
   static const hipError_t attr = hipFuncSetAttribute(
       (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (attr != hipSuccess) return (int)attr;
   return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st, p.args);
 }
-template <int D, int RB, int NW, int WPE, int NS>
+template <int D, int NW, int WPE, int NS>
 static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
-  return p.num_items <= kNumCU ? launch_attn_direct<D, RB, NW, WPE, NS, true>(p, st)
-                               : launch_attn_direct<D, RB, NW, WPE, NS, false>(p, st);
+  return p.num_items <= kNumCU ? launch_attn_direct<D, NW, WPE, NS, true>(p, st)
+                               : launch_attn_direct<D, NW, WPE, NS, false>(p, st);
 }
 
 // Tile shapes: 64 and 128 query rows run two workgroups per CU with two-slot
@@ -975,13 +923,13 @@ int launch_attention(const LaunchParams &p, void *stream) {
   if (p.num_items == 0) return 0;
   hipStream_t st = (hipStream_t)stream;
   if (p.d == 128) {
-    if (p.tile_rows == 64) return launch_attn_t<128, 1, 2, 2, 2>(p, st);
-    if (p.tile_rows == 128) return launch_attn_t<128, 1, 4, 2, 2>(p, st);
-    return launch_attn_t<128, 1, 8, 2, 4>(p, st);
+    if (p.tile_rows == 64) return launch_attn_t<128, 2, 2, 2>(p, st);
+    if (p.tile_rows == 128) return launch_attn_t<128, 4, 2, 2>(p, st);
+    return launch_attn_t<128, 8, 2, 4>(p, st);
   }
-  if (p.tile_rows == 64) return launch_attn_t<64, 1, 2, 2, 2>(p, st);
-  if (p.tile_rows == 128) return launch_attn_t<64, 1, 4, 3, 2>(p, st);
-  return launch_attn_t<64, 1, 8, 2, 4>(p, st);
+  if (p.tile_rows == 64) return launch_attn_t<64, 2, 2, 2>(p, st);
+  if (p.tile_rows == 128) return launch_attn_t<64, 4, 3, 2>(p, st);
+  return launch_attn_t<64, 8, 2, 4>(p, st);
 }
 
 int launch_reduce(const LaunchParams &p, void *stream) {

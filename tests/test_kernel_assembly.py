@@ -101,7 +101,7 @@ def test_no_spills_and_no_packed_fp32(assembly):
 def test_first_scores_leave_later_copies_under_way(assembly):
     kernels = {}
     for kernel, _, ins in _instructions(assembly["prism_kernels.hip"]):
-        m = kernel and re.search(r"prefill_attn_kernelILi128ELi1ELi([24])ELi2ELi2ELb0E", kernel)
+        m = kernel and re.search(r"prefill_attn_kernelILi128ELi([24])ELi2ELi2ELb0E", kernel)
         if m:
             kernels.setdefault(int(m.group(1)), []).append(ins)
     assert set(kernels) == {2, 4}
