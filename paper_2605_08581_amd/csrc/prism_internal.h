@@ -12,7 +12,7 @@ namespace prism {
 
 constexpr int kPage = 16;          // tokens per KV page
 constexpr int kTileKeys = 64;      // keys per inner iteration of the attention kernel
-constexpr int kStreamRows = 32;    // most packed rows per (request, kv head) of the key-splitting kernel
+constexpr int kStreamRows = 32;    // most packed rows of one row tile of the key-splitting kernel
 constexpr int kNumCU = 256;        // MI355X compute units
 constexpr int kNumXCD = 8;         // accelerator complex dies, each with its own L2
 constexpr int64_t kCacheBytes = (int64_t)kNumXCD * (4 << 20);   // of those L2s together
@@ -66,7 +66,7 @@ struct KernelTimes;    // defined in prism_api.cpp
 struct Schedule {
   int tile_rows = 128;
   int rows_per_wave = 32;
-  bool stream = false;         // few rows per kv head: the kernel whose waves split the keys
+  bool stream = false;         // few rows per kv head, or few row tiles: the kernel whose waves split the keys
   bool fused_append = false;   // attention may read new tokens from the packed arrays and append them itself
   bool read_once = false;      // some item has the flag of that name
   int most_pieces = 0;         // of any group

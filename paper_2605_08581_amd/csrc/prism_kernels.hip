@@ -362,6 +362,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void prefill_attn_kernel(const AttnAr
   // tiles still read: 7 requests of 500..700 new tokens x 40 heads, 40 layers 2940 ->
   // 2740 us, 3660 -> 3220 with a kernel after every layer that reads out; 32 full
   // recomputes 3213 -> 3187.  (out the same way saves here what that reader then pays.)
+  // Who reads them next, from memory then, is in these, plain stores -> with the hint: 40
+  // layers of 7 requests of 600 new x 40 heads, then a decode step through all of them
+  // 3070 -> 2813, 4 of 500 x 8 heads 1058 -> 1006, of 512 and then a second 512 2014 -> 1970;
+  // one layer alone, whose rows the caches would still hold, 24.8 -> 25.9 and 52.5 -> 50.5.
   int own_lo = 0x7fffffff, own_hi = 0x7fffffff;   // positions
   if (p.k_new) {
     own_lo = P + G.quotient(it.row0 + G.d - 1);
@@ -904,6 +908,10 @@ static int launch_attn_direct(const LaunchParams &p, hipStream_t st) {
   if (attr != hipSuccess) return (int)attr;
   return launch_kernel(kernel, dim3((unsigned)p.num_items), dim3(NW * 64), lds_bytes, st, p.args);
 }
+// A workgroup to a CU gains by the shorter way in and out, more of them by whole rows:
+// 3 requests of 100..200 new over 50..300 cached tokens x 40 heads (240 workgroups) 12.9 us,
+// with the other kernel 13.7; 5 of 130..250 over 100..400 (400 workgroups), by loads 18.0 us,
+// by copies 17.6.
 template <int D, int NW, int WPE, int NS>
 static int launch_attn_t(const LaunchParams &p, hipStream_t st) {
   return p.num_items <= kNumCU ? launch_attn_direct<D, NW, WPE, NS, true>(p, st)
@@ -939,7 +947,7 @@ int launch_reduce(const LaunchParams &p, void *stream) {
   // Merges of few rows are bound by their chain of reads: all partials at once, up
   // to sixteen, in twice the workgroups, as long as those find room together.  us per
   // pass, two rows and four partials -> one row and as many as there are, 32/8 heads:
-  // 37 new over 1003 cached tokens (3 pieces) 14.2 -> 13.6, over 8003 (14) 20.4 -> 18.3,
+  // 37 new over 1003 cached tokens (when that had 3 pieces) 14.2 -> 13.6, over 8003 (14) 20.4 -> 18.3,
   // 64 over 16001 at d = 64 (16) 22.1 -> 19.3; 100 over 4001, 40 heads (640 workgroups, 6 pieces) 26.8 -> 26.4, but
   // 1024 (four of 60 over 6001) 41.8 -> 42.1.  Asking for more than there are costs as
   // much as it gives: those 3 pieces 13.9 with eight, 14.5 with sixteen.

@@ -572,10 +572,10 @@ int build_schedule(const prism_shape_t &s, const int32_t *prefix, const int32_t 
     // Workgroup b runs on accelerator die b % 8, and each die has its own L2.
     // Row tiles (and key chunks) of one (request, kv head), and of requests with
     // a common cached prefix, read the same K/V pages, so each (cluster, kv
-    // head) set is dealt whole to one die - the least loaded so far, heaviest
-    // sets first - and the per-die lists are then interleaved so that list
-    // position k of die x becomes workgroup 8k + x.
-    struct ItemSet {                 // the workgroups of one (cluster, kv head)
+    // head) set is dealt to one die, or to several where it is larger than one -
+    // the least loaded so far, heaviest sets first - and the per-die lists are then
+    // interleaved so that list position k of die x becomes workgroup 8k + x.
+    struct ItemSet {                 // the workgroups of one (cluster, kv head) on one die
       int longest;                   // keys of the longest
       size_t begin, end;
     };

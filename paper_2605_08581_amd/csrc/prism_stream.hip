@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void stream_attn_kernel(const AttnArgs p) {
   // waiting for Q leaves the key copies in flight (loads into registers, which the
   // compiler waits for, would drain them: it does not see the copies).  The copy of
   // fragment (rb, kk) fetches for each lane the 16 bytes that the lane will read
-  // back: row c16, dims 32kk+8*g4..+7.  Row 0 stands in for rows past the end.
+  // back: row c16, dims 32kk+8*g4..+7.  The tile's first row stands in for rows past the end.
   // Q rows that do not lie on 16 bytes, which those copies do not promise to take,
   // go through registers, element by element.
   const uint32_t q_lds = lds_address(lds) + (uint32_t)(Shape::kRingBytes + wave * Shape::kQBytes);
